@@ -299,7 +299,8 @@ void launch_update(hipStream_t st, int grid, bool sr, bool kahan, const char* Gt
 // template so that the attribute call and the launch agree.
 template <int FMT, bool SR, bool KAHAN, bool DX, bool WD, bool DROP>
 int launch_dx_update_one(hipStream_t st, int grid, const char* Gt, const char* XT, char* Wc, uint16_t* Cc, float* dXacc, int n,
-                         int d, int Bp, float lr, float wd, uint64_t seed, uint64_t step, uint64_t elem0, int tpg, elmo::DropArgs dr) {
+                         int d, int Bp, float lr, float wd, uint64_t seed, uint64_t step, uint64_t elem0, int tpg, bool first,
+                         elmo::DropArgs dr) {
   constexpr int smem = elmo::dxu_smem_bytes<FMT, KAHAN, DROP>();
   if constexpr (smem > 160 * 1024) {
     return fail(-3, "internal: no single-pass kernel for this mode");      // the caller takes the separate kernels instead
@@ -313,17 +314,17 @@ int launch_dx_update_one(hipStream_t st, int grid, const char* Gt, const char* X
     });
     if (attr_rc != hipSuccess) return fail(-3, "hipFuncSetAttribute(k_dx_update) failed: %s", hipGetErrorString(attr_rc));
     elmo::k_dx_update<FMT, SR, KAHAN, DX, WD, DROP><<<grid, elmo::kGemmThreads, smem, st>>>(Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed,
-                                                                                            step, elem0, tpg, dr);
+                                                                                            step, elem0, tpg, first, dr);
     return 0;
   }
 }
 template <int FMT>
 int launch_dx_update(hipStream_t st, int grid, bool sr, bool kahan, bool dx, const char* Gt, const char* XT, char* Wc, uint16_t* Cc,
                      float* dXacc, int n, int d, int Bp, float lr, float wd, uint64_t seed, uint64_t step, uint64_t elem0, int tpg,
-                     elmo::DropArgs dr) {
+                     bool first, elmo::DropArgs dr) {
 #define ELMO_DXU3(SR_, KA_, DX_, WD_) \
-  return dr.thresh ? launch_dx_update_one<FMT, SR_, KA_, DX_, WD_, true>(st, grid, Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed, step, elem0, tpg, dr) \
-                   : launch_dx_update_one<FMT, SR_, KA_, DX_, WD_, false>(st, grid, Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed, step, elem0, tpg, dr)
+  return dr.thresh ? launch_dx_update_one<FMT, SR_, KA_, DX_, WD_, true>(st, grid, Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed, step, elem0, tpg, first, dr) \
+                   : launch_dx_update_one<FMT, SR_, KA_, DX_, WD_, false>(st, grid, Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed, step, elem0, tpg, first, dr)
 #define ELMO_DXU(SR_, KA_, DX_)                 \
   do {                                          \
     if (wd != 0.0f) ELMO_DXU3(SR_, KA_, DX_, true); \
@@ -432,8 +433,21 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   // whole grid is resident at once (256 CUs) and no second, nearly empty round of workgroups runs
   int S = std::max(1, 256 / (tiles_b * tiles_j));
   S = std::min(S, p.dx_rows / Bp256);
-  S = std::max(1, std::min(S, 64));
-  const int dx_slices = small_batch ? label_groups : S;
+  S = std::max(1, std::min({S, 64, (int)((std::min<int64_t>(p.chunk, p.L) + 63) / 64)}));
+  // planes of partial sums; the small-batch kernel uses as many as its largest launch has label groups
+  int dx_slices = S;
+  if (small_batch) {
+    dx_slices = 1;
+    auto groups = [&](int64_t n) {
+      const int64_t t = (n + 31) / 32, per = (t + label_groups - 1) / label_groups;
+      return n > 0 ? (int)((t + per - 1) / per) : 0;
+    };
+    const int64_t full = p.L / p.chunk, edge = p.kahan_rows % p.chunk;      // whole chunks; labels with compensation in the chunk where they end
+    const int64_t at_edge = std::min<int64_t>(p.chunk, p.L - p.kahan_rows / p.chunk * p.chunk);
+    for (int64_t n : {full ? p.chunk : (int64_t)0, p.L - full * p.chunk, edge, edge ? at_edge - edge : (int64_t)0})
+      dx_slices = std::max(dx_slices, groups(n));
+  }
+  bool dx_first = true;                                        // no launch has written the planes yet
   const int dx_plane_rows = small_batch ? 128 : Bp256;
 
   Profiler& prof = h->prof;
@@ -441,10 +455,8 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   // ---- step set-up: inputs, zeroed partial sums, label index
   {
     const size_t n = (size_t)Bp * d;
-    const size_t n_dx = dX_out ? (size_t)dx_slices * dx_plane_rows * d : 0;
-    const size_t work = std::max(n, n_dx);
-    elmo::k_step_setup<<<(int)std::min<size_t>((work + 255) / 256, 4096), elmo::kThreads, 0, st>>>(
-        (const uint16_t*)X, B, Bp, d, Xq, XT, (uint32_t*)dXacc, n_dx, (uint32_t*)cnt, (size_t)p.ntiles + 1, (uint32_t*)flag);
+    elmo::k_step_setup<<<(int)std::min<size_t>((n + 255) / 256, 4096), elmo::kThreads, 0, st>>>(
+        (const uint16_t*)X, B, Bp, d, Xq, XT, (uint32_t*)cnt, (size_t)p.ntiles + 1, (uint32_t*)flag);
     if (int rc = check_launch("k_step_setup")) return rc;
     const int row_grid = (B * elmo::kRowLanes + elmo::kThreads - 1) / elmo::kThreads;
     elmo::k_label_hist<<<row_grid, elmo::kThreads, 0, st>>>(indptr, indices, B, p.L, nnz, cnt, flag);
@@ -490,15 +502,17 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
         if (n_part == 0) continue;
         const bool kahan = part == 0;
         const int ntiles32 = (n_part + 31) / 32, tpg = (ntiles32 + label_groups - 1) / label_groups;
-        const int groups_used = (ntiles32 + tpg - 1) / tpg;
+        const bool first = dx_first;                         // the step's first launch writes every plane that is summed at the end
+        const int groups_used = first ? dx_slices : (ntiles32 + tpg - 1) / tpg;
         const uint64_t elem0 = (uint64_t)(c0 + l_off) * (uint64_t)d;
         const char* Gp = (const char*)(Gt + (size_t)l_off * Bp);
         char* Wp = Wc + (size_t)l_off * d * esz;
         uint16_t* Cp = kahan ? Cc + (size_t)l_off * d : nullptr;
         int rc;
-        if (fp8) rc = launch_dx_update<elmo::FMT_E4M3>(st, groups_used * col_blocks, sr, kahan, dX_out != nullptr, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, dr);
-        else rc = launch_dx_update<elmo::FMT_BF16>(st, groups_used * col_blocks, sr, kahan, dX_out != nullptr, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, dr);
+        if (fp8) rc = launch_dx_update<elmo::FMT_E4M3>(st, groups_used * col_blocks, sr, kahan, dX_out != nullptr, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, first, dr);
+        else rc = launch_dx_update<elmo::FMT_BF16>(st, groups_used * col_blocks, sr, kahan, dX_out != nullptr, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, first, dr);
         if (rc) return rc;
+        dx_first = false;
         if (int rc2 = check_launch("k_dx_update")) return rc2;
       }
       continue;
@@ -508,11 +522,12 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
       const int grid = tiles_b * tiles_j * S;
       const uint64_t celem0 = (uint64_t)c0 * (uint64_t)d;
 #define ELMO_DX(F, DR_) \
-  elmo::k_dx<F, DR_><<<grid, elmo::kGemmThreads, elmo::dx_smem_bytes<F>(), st>>>((const char*)Gt, Wc, dXacc, n, d, Bp, Bp256, S, seed, step, celem0, dr)
+  elmo::k_dx<F, DR_><<<grid, elmo::kGemmThreads, elmo::dx_smem_bytes<F>(), st>>>((const char*)Gt, Wc, dXacc, n, d, Bp, Bp256, S, dx_first, seed, step, celem0, dr)
       if (fp8) { if (dr.thresh) ELMO_DX(true, true); else ELMO_DX(true, false); }
       else { if (dr.thresh) ELMO_DX(false, true); else ELMO_DX(false, false); }
 #undef ELMO_DX
       if (int rc = check_launch("k_dx")) return rc;
+      dx_first = false;
     }
     prof.mark(st, CLS_UPDATE);
     for (int part = 0; part < 2; ++part) {
@@ -532,10 +547,9 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
 
   prof.mark(st, CLS_FINAL);
   if (dX_out || loss_out) {
-    const size_t n = (size_t)B * d;
-    const int grid = dX_out ? (int)std::min<size_t>((n + 255) / 256, 4096) : 1;
-    elmo::k_finalize<<<grid, elmo::kThreads, 0, st>>>(dXacc, dx_slices, dx_plane_rows, B, d, (uint16_t*)dX_out, loss_slots,
-                                                     p.ntiles * tiles_b, loss_out);
+    const int groups = dX_out ? (B + 31) / 32 * (d / 32) * 4 : 0;
+    elmo::k_finalize<<<groups + (loss_out ? 1 : 0), 64 * elmo::kFinalWaves, 0, st>>>(
+        dXacc, dx_slices, dx_plane_rows, B, d, groups, (uint16_t*)dX_out, loss_slots, p.ntiles * tiles_b, loss_out);
     if (int rc = check_launch("k_finalize")) return rc;
   }
   prof.mark(st, CLS_END);

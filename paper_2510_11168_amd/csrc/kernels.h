@@ -53,12 +53,10 @@ __global__ void __launch_bounds__(kThreads) k_prep_x(const uint16_t* __restrict_
   }
 }
 
-// k_prep_x plus the clearing of the step's scratch (input-gradient partial sums, bin counters,
-// validation flag) in one launch: the small heads are bound by the number of launches.
+// k_prep_x plus the clearing of the step's scratch (bin counters, validation flag) in one launch: the small heads are bound by the number of launches.
 __global__ void __launch_bounds__(kThreads) k_step_setup(const uint16_t* __restrict__ X, int B, int Bp, int d,
                                                          uint8_t* __restrict__ Xq, uint16_t* __restrict__ XT,
-                                                         uint32_t* __restrict__ dx_words, size_t n_dx, uint32_t* __restrict__ cnt,
-                                                         size_t n_cnt, uint32_t* __restrict__ flag) {
+                                                         uint32_t* __restrict__ cnt, size_t n_cnt, uint32_t* __restrict__ flag) {
   const size_t n = (size_t)Bp * d, stride = (size_t)gridDim.x * kThreads, t0 = (size_t)blockIdx.x * kThreads + threadIdx.x;
   for (size_t i = t0; i < n; i += stride) {
     const int b = (int)(i / d), j = (int)(i % d);
@@ -66,7 +64,6 @@ __global__ void __launch_bounds__(kThreads) k_step_setup(const uint16_t* __restr
     if (Xq) Xq[i] = (uint8_t)e4m3_rne(bf16_decode(bits));
     XT[(size_t)j * Bp + b] = (uint16_t)bits;
   }
-  for (size_t i = t0; i < n_dx; i += stride) dx_words[i] = 0u;
   for (size_t i = t0; i < n_cnt; i += stride) cnt[i] = 0u;
   if (flag && t0 == 0) *flag = 0u;
 }
@@ -485,14 +482,37 @@ k_logits(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wc, i
 // weight rows are re-reads of row n-1.  Columns beyond d in the last column tile re-read the
 // row's last 16 bytes and are not stored.
 // ---------------------------------------------------------------------------------------------
-// dst[32 x 32 block, row pitch d] += one 32x32 accumulator tile.  All sixteen loads are issued
-// before the first store, so the read-modify-write costs one memory round trip, not sixteen.
-__device__ inline void add_acc_to_global(float* __restrict__ dst, int d, int lane, const f32x16& acc) {
-  float old[16];
+// The FP32 partials live in the layout of the accumulators, not as matrix rows: a plane of R x d values
+// is a row-major array of 32 x 32 blocks, a block is four groups of 64 lanes x 16 bytes (group q, lane:
+// elements 4q .. 4q+3 of the lane's accumulator), so a wave moves 1 KiB per instruction.  What bounds this
+// read-modify-write is the number of memory instructions and their round trips (as rows of 4-byte accesses
+// it took 30 k of the input-gradient kernel's 364 k clocks); k_finalize turns the layout back.
+__device__ inline f32x4* dx_block(float* plane, int d, int row0, int col0) {
+  return reinterpret_cast<f32x4*>(plane + ((size_t)(row0 >> 5) * (d >> 5) + (col0 >> 5)) * 1024);
+}
+// NB blocks of a wave, at dst + b * 256: += acc[b], or = acc[b] in the step's first pass over the plane
+// (which is why the planes need no clearing).  The loads of one block are in flight while the block
+// before it is added and stored.
+template <int NB> __device__ __forceinline__ void add_acc_blocks(f32x4* __restrict__ dst, int lane, const f32x16 (&acc)[NB], bool first) {
+  auto quad = [&](int b, int q) { return f32x4{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]}; };
+  if (first) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) old[v] = dst[(size_t)acc_row(v, lane) * d + (lane & 31)];
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-  for (int v = 0; v < 16; ++v) dst[(size_t)acc_row(v, lane) * d + (lane & 31)] = old[v] + acc[v];
+      for (int q = 0; q < 4; ++q) dst[b * 256 + q * 64 + lane] = quad(b, q);
+    return;
+  }
+  f32x4 old[2][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) old[0][q] = dst[q * 64 + lane];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    if (b + 1 < NB)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) old[(b + 1) & 1][q] = dst[(b + 1) * 256 + q * 64 + lane];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) dst[b * 256 + q * 64 + lane] = old[b & 1][q] + quad(b, q);
+  }
 }
 
 // ring stage: [G^T slab 64 labels x 256 samples (512-byte rows) | W slab 64 labels x 256 columns]
@@ -502,7 +522,7 @@ template <bool FP8> constexpr int dx_smem_bytes() { return dx_stages<FP8>() * (6
 template <bool FP8, bool DROP>
 __global__ void __launch_bounds__(kGemmThreads, 1)
 k_dx(const char* __restrict__ Gt, const char* __restrict__ Wc, float* __restrict__ dXacc, int n, int d, int Bp,
-     int Bp256, int S, uint64_t seed, uint64_t step, uint64_t elem0, DropArgs dr) {
+     int Bp256, int S, bool first, uint64_t seed, uint64_t step, uint64_t elem0, DropArgs dr) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr int ESZ = FP8 ? 1 : 2, WROWB = 256 * ESZ;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
@@ -512,11 +532,19 @@ k_dx(const char* __restrict__ Gt, const char* __restrict__ Wc, float* __restrict
   const int b0 = bt << 8, j0 = jt << 8;
   const int ksteps = (n + 63) >> 6, per = (ksteps + S - 1) / S;
   const int ks0 = s * per, ks1 = min(ks0 + per, ksteps);
-  if (ks0 >= ks1) return;
+  if (ks0 >= ks1 && !first) return;
   const size_t strideA = (size_t)Bp * 2, strideB = (size_t)d * ESZ;
 
   f32x16 acc[2][4];
   zero_acc(acc);
+  float* out = dXacc + (size_t)s * Bp256 * d;
+  auto store = [&]() {
+    const int col = j0 + wn * 128;
+    if (col < d)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) add_acc_blocks<4>(dx_block(out, d, b0 + wm * 64 + 32 * i, col), lane, acc[i], first);
+  };
+  if (ks0 >= ks1) { store(); return; }                 // a slice without labels in the first chunk still owns its plane
   auto product = [&](const char* sa, const char* sb, int q0, int q1) {
 #pragma unroll
     for (int kk = q0; kk < q1; ++kk) {
@@ -557,35 +585,42 @@ k_dx(const char* __restrict__ Gt, const char* __restrict__ Wc, float* __restrict
         ga, strideA, va0, 64, 64 * strideA, 32, gb, strideB, n - ks0 * 64, 64, 64 * strideB, chunks_b, ks1 - ks0, smem, wave, lane,
         product);
   }
-  float* out = dXacc + (size_t)s * Bp256 * d;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = j0 + wn * 128 + 32 * j;
-      if (col < d) add_acc_to_global(out + (size_t)(b0 + wm * 64 + 32 * i) * d + col, d, lane, acc[i][j]);
-    }
+  store();
 }
 
-// dX_out = BF16(sum over label slices of the FP32 partials); loss_out = sum of the tile losses.
-__global__ void __launch_bounds__(kThreads) k_finalize(const float* __restrict__ dXacc, int S, int Bp256, int B, int d,
-                                                       uint16_t* __restrict__ dX_out, const float* __restrict__ loss_slots,
-                                                       int nslots, float* __restrict__ loss_out) {
-  __shared__ float red[4];
-  if (dX_out) {
-    const size_t n = (size_t)B * d, plane = (size_t)Bp256 * d;
-    for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads) {
-      float s = 0.0f;
-      for (int k = 0; k < S; ++k) s += dXacc[k * plane + i];
-      dX_out[i] = (uint16_t)bf16_rne(s);
-    }
-  }
-  if (loss_out && blockIdx.x == 0) {
+// dX_out = BF16(sum over the S planes of FP32 partials); loss_out = sum of the tile losses.
+// A workgroup turns one group of 64 lanes x 16 bytes (8 x 32 outputs) of the partials' layout into rows;
+// its eight waves share the planes, so that the chain of dependent loads is S / 8 long: with one thread per
+// output walking all S planes this kernel took 38 us at 64 outputs rows x 256 columns and 256 planes.
+// The last workgroup of the grid sums the losses.
+constexpr int kFinalWaves = 8;
+__global__ void __launch_bounds__(64 * kFinalWaves) k_finalize(const float* __restrict__ dXacc, int S, int plane_rows, int B, int d, int groups,
+                                                               uint16_t* __restrict__ dX_out, const float* __restrict__ loss_slots,
+                                                               int nslots, float* __restrict__ loss_out) {
+  __shared__ f32x4 part[kFinalWaves][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if ((int)blockIdx.x == groups) {
     float s = 0.0f;
-    for (int i = threadIdx.x; i < nslots; i += kThreads) s += loss_slots[i];
-    const float t = block_sum<4>(s, red);
-    if (threadIdx.x == 0) *loss_out = t;
+    for (int i = tid; i < nslots; i += 64 * kFinalWaves) s += loss_slots[i];
+    const float t = block_sum<kFinalWaves>(s, reinterpret_cast<float*>(part));
+    if (tid == 0) *loss_out = t;
+    return;
   }
+  const int u = blockIdx.x, blk = u >> 2, q = u & 3;
+  const size_t plane = (size_t)plane_rows * d / 4;
+  const f32x4* src = reinterpret_cast<const f32x4*>(dXacc) + (size_t)u * 64 + lane;
+  f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+  for (int k = wave; k < S; k += kFinalWaves) s += src[k * plane];
+  part[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int w = 1; w < kFinalWaves; ++w) s += part[w][lane];
+  const int row = (blk / (d >> 5)) * 32 + 8 * q + 4 * (lane >> 5), col = (blk % (d >> 5)) * 32 + (lane & 31);
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (row + e < B) dX_out[(size_t)(row + e) * d + col] = (uint16_t)bf16_rne(s[e]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -815,7 +850,7 @@ template <int FMT, bool SR, bool KAHAN, bool DX, bool WD, bool DROP>
 __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restrict__ Wc,
                                                uint16_t* __restrict__ Cc, float* __restrict__ dXacc, int n, int d, int Bp,
                                                float lr, float wd, uint64_t seed, uint64_t step, uint64_t elem0, int tiles_per_group,
-                                               DropArgs dr, char* smem) {
+                                               bool first, DropArgs dr, char* smem) {
   constexpr int ESZ = FMT == FMT_E4M3 ? 1 : 2;
   constexpr int WROWB = 256 * ESZ;
   constexpr int WBYTES = 32 * WROWB, GBYTES = 32 * 256, SBYTES = dxu_stage_bytes<FMT, KAHAN>();
@@ -826,7 +861,7 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
   const int g = wg / C, c = wg % C;
   const int ntiles = (n + 31) >> 5;
   const int t0 = g * tiles_per_group, t1 = min(t0 + tiles_per_group, ntiles);
-  if (t0 >= t1) return;
+  if (t0 >= t1 && !(DX && first)) return;                    // (in the first pass every group writes its dX plane)
   const int j0 = c << 8;
   const size_t gstride = (size_t)Bp * 2;
   const int KS = Bp >> 4;                                   // k16 steps over the batch: 4 or 8
@@ -858,7 +893,7 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
       dma_tile<32, 512, kGemmWaves>(reinterpret_cast<const char*>(Cc) + ((size_t)l0 * d + j0) * 2, (size_t)d * 2, valid,
                                     st + WBYTES + GBYTES, wave, lane);
   };
-  issue(t0);
+  if (t0 < t1) issue(t0);
   if (t0 + 1 < t1) issue(t0 + 1);
   for (int t = t0; t < t1; ++t) {
     // Tile t has landed once only younger operations are outstanding: tile t+1's loads and the
@@ -975,16 +1010,14 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
     }
   }
   if (DX) {
-    float* out = dXacc + (size_t)g * 128 * d;
     if (DROP) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int v = 0; v < 16; ++v) dxa[q][v] *= dr.scale;
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      add_acc_to_global(out + (size_t)(32 * bt) * d + j0 + 128 * jh + 32 * q, d, lane, dxa[q]);
+    // rows beyond the padded batch are never read
+    if (32 * bt < Bp) add_acc_blocks<4>(dx_block(dXacc + (size_t)g * 128 * d, d, 32 * bt, j0 + 128 * jh), lane, dxa, first);
   }
 }
 
@@ -992,9 +1025,9 @@ template <int FMT, bool SR, bool KAHAN, bool DX, bool WD, bool DROP>
 __global__ void __launch_bounds__(kGemmThreads, 1)
 k_dx_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restrict__ Wc, uint16_t* __restrict__ Cc,
             float* __restrict__ dXacc, int n, int d, int Bp, float lr, float wd, uint64_t seed, uint64_t step, uint64_t elem0,
-            int tiles_per_group, DropArgs dr) {
+            int tiles_per_group, bool first, DropArgs dr) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  dx_update_body<FMT, SR, KAHAN, DX, WD, DROP>(Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed, step, elem0, tiles_per_group, dr, smem);
+  dx_update_body<FMT, SR, KAHAN, DX, WD, DROP>(Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed, step, elem0, tiles_per_group, first, dr, smem);
 }
 
 // ---------------------------------------------------------------------------------------------

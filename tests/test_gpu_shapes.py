@@ -1,0 +1,37 @@
+"""GPU parity at the sizes where a kernel's split of the work can go wrong: edges of tiles, remainders, the
+smallest and largest of a range.  Oracle, inputs and bounds as in test_gpu_parity.py."""
+import numpy as np
+import pytest
+
+from oracle import elmo_oracle as o
+from paper_2510_11168_amd import synth
+from test_gpu_parity import Case, assert_dx_close, b, check_step, say  # noqa: F401  (b is the module's fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def batch(L, d, B, seed=5, rule="lognormal5"):
+    rng = np.random.default_rng(seed)
+    X = synth.make_x(rng, B, d)
+    indptr, indices = synth.ZipfLabels(L, 1.0).draw_csr(rng, B, rule)
+    return X, indptr, indices
+
+
+@pytest.mark.parametrize("B,d,L,chunk,kahan_rows", [
+    (40, 256, 9600 + 8192, 9600, 0),        # small batch: 150 label groups in the first chunk, 256 in the second
+    (40, 512, 3 * 128 + 5, 128, 0),         # fewer label tiles than groups; the last chunk has one ragged tile
+    (100, 256, 1024, 1024, 128),            # one chunk in two parts, the first with fewer groups than the second
+    (300, 256, 6400 + 4096, 6400, 0),       # 50 of 64 label slices used in the first chunk, all in the second
+    (130, 384, 70, 1000, 0),                # fewer label slabs than slices, half a column tile
+])
+def test_input_gradient_planes(b, B, d, L, chunk, kahan_rows):  # noqa: F811
+    """The first launch of a step writes every plane of partial sums that the end adds up, whether it has labels
+    for it or not; later launches add to them."""
+    fmt, flags = o.E4M3, o.FLAG_SR | (o.FLAG_KAHAN if kahan_rows else 0)
+    case = Case(b, L, d, fmt, chunk, flags, B, w_std=0.05, seed=8, kahan_rows=kahan_rows)
+    case.head.workspace.fill_(0x7F)         # whatever the planes held before must not matter
+    X, indptr, indices = batch(L, d, B)
+    dX, _ = case.step(X, indptr, indices, 0.05, 1, 2)
+    C = np.zeros((L, d), np.uint16) if kahan_rows else None
+    ref = o.head_step(case.W0, C, X, indptr, indices, 0.05, 1, 2, fmt, flags, **({"kahan_rows": kahan_rows} if kahan_rows else {}))
+    assert_dx_close(dX, ref["dX_partial"], 6e-2)
