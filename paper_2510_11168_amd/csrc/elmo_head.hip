@@ -366,6 +366,7 @@ int raise_lds_limits_once() {
   ELMO_ATTR_UPDATE(elmo::FMT_E4M3, false, true);
   ELMO_ATTR_UPDATE(elmo::FMT_E4M3, false, false);
 #undef ELMO_ATTR_UPDATE
+  ELMO_ATTR((elmo::k_step_setup), (int)elmo::setup_smem(elmo::kIndexMaxBins));
   ELMO_ATTR((elmo::k_dx<true, false>), elmo::dx_smem_bytes<true>());
   ELMO_ATTR((elmo::k_dx<true, true>), elmo::dx_smem_bytes<true>());
   ELMO_ATTR((elmo::k_dx<false, false>), elmo::dx_smem_bytes<false>());
@@ -454,17 +455,20 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   prof.mark(st, CLS_SETUP);
   // ---- step set-up: inputs, zeroed partial sums, label index
   {
-    const size_t n = (size_t)Bp * d;
-    elmo::k_step_setup<<<(int)std::min<size_t>((n + 255) / 256, 4096), elmo::kThreads, 0, st>>>(
-        (const uint16_t*)X, B, Bp, d, Xq, XT, (uint32_t*)cnt, (size_t)p.ntiles + 1, (uint32_t*)flag);
+    const bool one_wg = p.ntiles <= elmo::kIndexMaxBins && nnz <= elmo::kIndexMaxNnz;
+    const elmo::IndexArgs ia{indptr, indices, p.L, nnz, one_wg ? p.ntiles : 0, ptr, pos, flag};
+    elmo::k_step_setup<<<1 + Bp / 64 * (d / 128), elmo::kSetupThreads, elmo::setup_smem(ia.nb), st>>>(
+        (const uint16_t*)X, B, Bp, d, Xq, XT, ia, one_wg ? nullptr : cnt, (size_t)p.ntiles + 1);
     if (int rc = check_launch("k_step_setup")) return rc;
-    const int row_grid = (B * elmo::kRowLanes + elmo::kThreads - 1) / elmo::kThreads;
-    elmo::k_label_hist<<<row_grid, elmo::kThreads, 0, st>>>(indptr, indices, B, p.L, nnz, cnt, flag);
-    if (int rc = check_launch("k_label_hist")) return rc;
-    elmo::k_label_scan<<<1, 1024, 0, st>>>(cnt, p.ntiles, ptr, cur);
-    if (int rc = check_launch("k_label_scan")) return rc;
-    elmo::k_label_scatter<<<row_grid, elmo::kThreads, 0, st>>>(indptr, indices, B, p.L, nnz, cur, pos);
-    if (int rc = check_launch("k_label_scatter")) return rc;
+    if (!one_wg) {
+      const int row_grid = (B * elmo::kRowLanes + elmo::kThreads - 1) / elmo::kThreads;
+      elmo::k_label_hist<<<row_grid, elmo::kThreads, 0, st>>>(indptr, indices, B, p.L, nnz, cnt, flag);
+      if (int rc = check_launch("k_label_hist")) return rc;
+      elmo::k_label_scan<<<1, 1024, 0, st>>>(cnt, p.ntiles, ptr, cur);
+      if (int rc = check_launch("k_label_scan")) return rc;
+      elmo::k_label_scatter<<<row_grid, elmo::kThreads, 0, st>>>(indptr, indices, B, p.L, nnz, cur, pos);
+      if (int rc = check_launch("k_label_scatter")) return rc;
+    }
     if (flag) h->validated_step_pending = true;
   }
 
@@ -556,6 +560,15 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   return 0;
 }
 
+namespace {
+// Xq [Bp, d] <- E4M3(X), for the top-k paths (no transposed copy, no label index)
+int stage_queries(hipStream_t st, const void* X, int B, int Bp, int d, uint8_t* Xq) {
+  elmo::k_step_setup<<<1 + Bp / 64 * (d / 128), elmo::kSetupThreads, elmo::setup_smem(0), st>>>((const uint16_t*)X, B, Bp, d, Xq, nullptr,
+                                                                                              elmo::IndexArgs{}, nullptr, 0);
+  return check_launch("k_step_setup");
+}
+}  // namespace
+
 extern "C" int elmo_head_topk(elmo_head_t* h, const void* X, int32_t B, int32_t k, int32_t* idx_out, float* score_out,
                               void* hip_stream) {
   if (!h) return fail(-1, "NULL head");
@@ -569,12 +582,8 @@ extern "C" int elmo_head_topk(elmo_head_t* h, const void* X, int32_t B, int32_t 
   const bool fp8 = p.fmt == ELMO_FP8_E4M3;
   const int d = p.d, Bp = round_up(B, 64);
   uint8_t* Xq = fp8 ? (uint8_t*)(h->ws + p.off_xq) : nullptr;
-  uint16_t* XT = (uint16_t*)(h->ws + p.off_xt);
-  {
-    const size_t n = (size_t)Bp * d;
-    elmo::k_prep_x<<<(int)std::min<size_t>((n + 255) / 256, 4096), elmo::kThreads, 0, st>>>((const uint16_t*)X, B, Bp, d, Xq, XT);
-    if (int rc = check_launch("k_prep_x")) return rc;
-  }
+  if (fp8)      // E4M3 copy of X, rows B..Bp-1 zero (the BF16 product reads X itself and clamps its rows)
+    if (int rc = stage_queries(st, X, B, Bp, d, Xq)) return rc;
   const char* Xa = fp8 ? (const char*)Xq : (const char*)X;
   const int a_rows = fp8 ? Bp : B;
   h->prof.mark(st, CLS_TOPK);
@@ -638,11 +647,8 @@ extern "C" int elmo_topk_static(const void* W, int64_t L, int32_t d, int weight_
   if (int rc = static_scratch(&base)) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   uint8_t* Xq = (uint8_t*)base;
-  if (fp8) {   // E4M3 copy of X, rows B..Bp-1 zero (the BF16 product reads X itself and clamps its rows)
-    const size_t n = (size_t)Bp * d;
-    elmo::k_prep_x<<<(int)std::min<size_t>((n + 255) / 256, 4096), elmo::kThreads, 0, st>>>((const uint16_t*)X, B, Bp, d, Xq, nullptr);
-    if (int rc = check_launch("k_prep_x")) return rc;
-  }
+  if (fp8)
+    if (int rc = stage_queries(st, X, B, Bp, d, Xq)) return rc;
   // every call starts from the scratch the last call left: topk_run re-initialises the thresholds,
   // counters and overflow flags of all rows itself, and reads candidate slots only below the counters
   return elmo::topk_run(st, fp8, fp8 ? (const char*)Xq : (const char*)X, fp8 ? Bp : B, (const char*)W, L, d, 0, B, Bp, k,

@@ -39,35 +39,6 @@ __global__ void __launch_bounds__(kThreads) k_fill_u32(uint32_t* __restrict__ p,
   for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads) p[i] = v;
 }
 
-// Step set-up of the inputs (Algorithm 1: "X.t().to(float8_e4m3fn)"): the E4M3 cast Xq [Bp, d]
-// used by the logits product and the transposed BF16 copy XT [d, Bp] used by the weight-gradient
-// product; rows B..Bp-1 are zero padding.  Either output may be absent.
-__global__ void __launch_bounds__(kThreads) k_prep_x(const uint16_t* __restrict__ X, int B, int Bp, int d,
-                                                     uint8_t* __restrict__ Xq, uint16_t* __restrict__ XT) {
-  const size_t n = (size_t)Bp * d;
-  for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads) {
-    const int b = (int)(i / d), j = (int)(i % d);
-    const uint32_t bits = b < B ? X[i] : 0u;
-    if (Xq) Xq[i] = (uint8_t)e4m3_rne(bf16_decode(bits));
-    if (XT) XT[(size_t)j * Bp + b] = (uint16_t)bits;
-  }
-}
-
-// k_prep_x plus the clearing of the step's scratch (bin counters, validation flag) in one launch: the small heads are bound by the number of launches.
-__global__ void __launch_bounds__(kThreads) k_step_setup(const uint16_t* __restrict__ X, int B, int Bp, int d,
-                                                         uint8_t* __restrict__ Xq, uint16_t* __restrict__ XT,
-                                                         uint32_t* __restrict__ cnt, size_t n_cnt, uint32_t* __restrict__ flag) {
-  const size_t n = (size_t)Bp * d, stride = (size_t)gridDim.x * kThreads, t0 = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  for (size_t i = t0; i < n; i += stride) {
-    const int b = (int)(i / d), j = (int)(i % d);
-    const uint32_t bits = b < B ? X[i] : 0u;
-    if (Xq) Xq[i] = (uint8_t)e4m3_rne(bf16_decode(bits));
-    XT[(size_t)j * Bp + b] = (uint16_t)bits;
-  }
-  for (size_t i = t0; i < n_cnt; i += stride) cnt[i] = 0u;
-  if (flag && t0 == 0) *flag = 0u;
-}
-
 // ---------------------------------------------------------------------------------------------
 // Per-batch label index: the positives (CSR by sample) regrouped by 128-label tile, so that the
 // logits epilogue of a tile finds its few positives with two loads (Algorithm 1 filters the
@@ -197,6 +168,137 @@ __global__ void __launch_bounds__(kThreads) k_label_scatter(const int* __restric
       const int slot = hot[lab[k] >> 7] + rank[k];
       if (slot < nnz) pos[slot] = make_int2(lab[k], b);
     }
+}
+
+// The same index by one workgroup of 1024 threads with all bins in LDS: counts, exclusive prefix, positives
+// into their slots.  The three kernels above cost a launch each (4-5 us apart) and a single-workgroup scan of
+// all bins in memory (16 us at 23438 bins); this one runs beside the workgroups that stage the inputs, in the
+// same launch.  Its passes are chains of memory round trips, so the row pointers and first labels of
+// eight rows per thread are fetched at once.  Same treatment of malformed rows as above (skipped; flagged
+// when `flag` is given); positions never exceed nnz.
+constexpr int kSetupThreads = 1024;
+constexpr int kIndexMaxBins = 32768;                             // 128 KiB of LDS: labels 0 .. 4194303
+constexpr int kIndexMaxNnz = 65536;                              // above, one CU's share of the work takes longer than the launches
+struct IndexArgs {
+  const int* indptr; const int* indices;
+  int64_t L, nnz;
+  int nb;                                                        // bins; 0 = the index is built by the kernels above
+  int* ptr; int2* pos; int* flag;
+};
+template <class F>
+__device__ __forceinline__ void for_each_positive(const IndexArgs& ia, int B, int tid, F&& f) {
+  constexpr int NR = 8, RPP = kSetupThreads / kRowLanes;         // rows in flight per thread, rows per pass
+  const int sub = tid % kRowLanes;
+  for (int r0 = tid / kRowLanes; r0 < B; r0 += NR * RPP) {
+    int p0[NR], p1[NR], l[NR];
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const int r = r0 + k * RPP;
+      p0[k] = r < B ? ia.indptr[r] : 0;
+      p1[k] = r < B ? ia.indptr[r + 1] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      if (p0[k] < 0 || p1[k] < p0[k] || p1[k] > ia.nnz) { f(-1, -1, 0); p0[k] = p1[k] = 0; }
+      l[k] = p0[k] + sub < p1[k] ? ia.indices[p0[k] + sub] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < NR; ++k)
+      for (int p = p0[k] + sub; p < p1[k]; p += kRowLanes) f(p == p0[k] + sub ? l[k] : ia.indices[p], r0 + k * RPP, p > p0[k] ? p : 0);
+  }
+}
+__device__ inline void label_index(const IndexArgs& ia, int B, int* h) {
+  __shared__ int wsum[kSetupThreads / 64];
+  __shared__ int bad;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int i = tid; i < ia.nb; i += kSetupThreads) h[i] = 0;
+  if (tid == 0) bad = 0;
+  __syncthreads();
+  for_each_positive(ia, B, tid, [&](int l, int b, int p) {       // p: place in `indices` of a positive that has one before it in its row
+    if (b < 0) { if (ia.flag) atomicOr(&bad, 1); return; }
+    const bool in_range = l >= 0 && l < ia.L;
+    if (ia.flag && (!in_range || (p > 0 && l <= ia.indices[p - 1]))) atomicOr(&bad, 2);
+    if (in_range) atomicAdd(&h[l >> 7], 1);
+  });
+  __syncthreads();
+  const int run = ((ia.nb + kSetupThreads - 1) / kSetupThreads) | 1;      // odd: consecutive threads' runs start in different banks
+  const int i0 = min(tid * run, ia.nb), i1 = min(i0 + run, ia.nb);
+  int sum = 0;
+  for (int i = i0; i < i1; ++i) sum += h[i];
+  int scan = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(scan, o, 64);
+    scan += lane >= o ? t : 0;
+  }
+  if (lane == 63) wsum[wave] = scan;
+  __syncthreads();
+  int at = scan - sum, total = 0;
+#pragma unroll
+  for (int w = 0; w < kSetupThreads / 64; ++w) {
+    at += w < wave ? wsum[w] : 0;
+    total += wsum[w];
+  }
+  for (int i = i0; i < i1; ++i) {
+    const int v = h[i];
+    h[i] = at;
+    at += v;
+  }
+  __syncthreads();
+  const int most = (int)ia.nnz;
+  for (int i = tid; i < ia.nb; i += kSetupThreads) ia.ptr[i] = min(h[i], most);
+  if (tid == 0) {
+    ia.ptr[ia.nb] = min(total, most);
+    if (ia.flag) *ia.flag = bad;
+  }
+  __syncthreads();
+  for_each_positive(ia, B, tid, [&](int l, int b, int) {
+    if (b < 0 || l < 0 || l >= ia.L) return;
+    const int slot = atomicAdd(&h[l >> 7], 1);
+    if (slot < most) ia.pos[slot] = make_int2(l, b);
+  });
+}
+
+// Step set-up.  Workgroup 0 builds the label index (or nothing); the others stage the inputs (Algorithm 1:
+// "X.t().to(float8_e4m3fn)"), one tile of 64 samples x 128 columns each: the E4M3 cast Xq [Bp, d] used by the
+// logits product and the transposed BF16 copy XT [d, Bp] used by the weight-gradient product, turned in LDS so
+// that both sides are read and written 8 and 16 bytes at a time (2-byte stores at a stride of Bp took 46 us for
+// 4096 x 768).  Rows B..Bp-1 are zero padding.  Either output may be absent.  cnt: bin counters to clear for
+// the separate index kernels.
+constexpr int kXtPitch = 64 * 2 + 16;                             // bytes per staged column of 64 samples
+inline size_t setup_smem(int nb) { return (size_t)nb * 4 > 128 * kXtPitch ? (size_t)nb * 4 : 128 * kXtPitch; }
+__global__ void __launch_bounds__(kSetupThreads) k_step_setup(const uint16_t* __restrict__ X, int B, int Bp, int d,
+                                                              uint8_t* __restrict__ Xq, uint16_t* __restrict__ XT, IndexArgs ia,
+                                                              int* __restrict__ cnt, size_t n_cnt) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int tid = threadIdx.x;
+  if (cnt) {
+    const size_t t0 = (size_t)blockIdx.x * kSetupThreads + tid;
+    for (size_t i = t0; i < n_cnt; i += (size_t)gridDim.x * kSetupThreads) cnt[i] = 0;
+    if (ia.flag && t0 == 0) *ia.flag = 0;
+  }
+  if (blockIdx.x == 0) {
+    if (ia.nb) label_index(ia, B, reinterpret_cast<int*>(smem));
+    return;
+  }
+  const int tiles_c = d >> 7, tile = blockIdx.x - 1, b0 = tile / tiles_c * 64, c0 = tile % tiles_c * 128;
+  {
+    const int r = tid >> 4, c = (tid & 15) * 8;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (b0 + r < B) v = *reinterpret_cast<const u32x4*>(X + (size_t)(b0 + r) * d + c0 + c);
+    if (Xq) {
+      uint32_t q[2] = {0u, 0u};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) q[e >> 2] |= e4m3_rne(bf16_decode((v[e >> 1] >> (16 * (e & 1))) & 0xFFFFu)) << (8 * (e & 3));
+      *reinterpret_cast<uint2*>(Xq + (size_t)(b0 + r) * d + c0 + c) = make_uint2(q[0], q[1]);
+    }
+    if (!XT) return;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) *reinterpret_cast<uint16_t*>(smem + (c + e) * kXtPitch + r * 2) = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+  }
+  __syncthreads();
+  const int c = tid >> 3, sgm = tid & 7;
+  *reinterpret_cast<u32x4*>(XT + (size_t)(c0 + c) * Bp + b0 + sgm * 8) = *reinterpret_cast<const u32x4*>(smem + c * kXtPitch + sgm * 16);
 }
 
 // ---------------------------------------------------------------------------------------------

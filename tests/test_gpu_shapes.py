@@ -35,3 +35,29 @@ def test_input_gradient_planes(b, B, d, L, chunk, kahan_rows):  # noqa: F811
     C = np.zeros((L, d), np.uint16) if kahan_rows else None
     ref = o.head_step(case.W0, C, X, indptr, indices, 0.05, 1, 2, fmt, flags, **({"kahan_rows": kahan_rows} if kahan_rows else {}))
     assert_dx_close(dX, ref["dX_partial"], 6e-2)
+
+
+@pytest.mark.parametrize("B,per_row,L", [
+    (1, 1, 128),            # one positive, one bin
+    (129, 9, 128 * 3 + 1),  # one more row than a pass of the index covers, one more positive than the lanes of a row
+    (1030, 5, 300000),      # rows beyond one batch of passes, more bins than threads
+    (256, 256, 20000),      # 65536 positives: the largest batch one workgroup indexes
+    (257, 256, 20000),      # beyond it: the separate index kernels
+])
+def test_label_index_sizes(b, B, per_row, L):  # noqa: F811
+    """The positives of a batch reach their labels whatever the number of rows, positives and bins: the loss and dX
+    are the oracle's on the labels that have positives (and the first rows of the head)."""
+    d, fmt, flags = 128, o.E4M3, 0
+    case = Case(b, L, d, fmt, L, flags, B, max_nnz=B * per_row, w_std=0.05, seed=4)
+    rng = np.random.default_rng(6)
+    X = synth.make_x(rng, B, d)
+    indices = np.concatenate([np.sort(rng.choice(L, size=per_row, replace=False)) for _ in range(B)]).astype(np.int32)
+    indptr = (np.arange(B + 1) * per_row).astype(np.int32)
+    case.head.workspace.fill_(0x7F)
+    _, loss = case.step(X, indptr, indices, 0.05, 0, 0, want_dx=False)
+    rows = np.unique(np.concatenate([indices, np.arange(min(L, 256))]))[:4096]
+    ref = o.head_step(case.W0[rows], None, X, indptr, indices, 0.05, 0, 0, fmt, flags, label_ids=rows)
+    Wn = case.W()[rows]
+    assert np.mean(Wn == ref["W_new"]) >= 0.999
+    if len(rows) == L:
+        assert abs(loss - ref["loss"]) <= 2e-3 * abs(ref["loss"])
