@@ -234,13 +234,16 @@ int elmo_quantize(const float* src, int64_t n, int dtype, int mode, uint64_t see
   if (mode != 0 && mode != 1) return fail(-1, "mode must be 0 (nearest) or 1 (stochastic)");
   if (n == 0) return 0;
   hipStream_t st = (hipStream_t)hip_stream;
-  const int grid = (int)std::min<int64_t>((n + elmo::kThreads - 1) / elmo::kThreads, 256 * 16);
+  // eight elements per thread where both buffers are aligned to the accesses that move them
+  const bool wide = ((uintptr_t)src & 15) == 0 && ((uintptr_t)dst & (dtype == ELMO_BF16 ? 15 : 7)) == 0;
+  const int64_t groups = wide ? n / 8 : 0, work = wide ? groups + 8 : n;
+  const int grid = (int)std::min<int64_t>((work + elmo::kThreads - 1) / elmo::kThreads, 256 * 32);
   if (dtype == ELMO_BF16) {
-    if (mode) elmo::k_quantize<elmo::FMT_BF16, true><<<grid, elmo::kThreads, 0, st>>>(src, n, seed, step, first_elem, dst);
-    else elmo::k_quantize<elmo::FMT_BF16, false><<<grid, elmo::kThreads, 0, st>>>(src, n, seed, step, first_elem, dst);
+    if (mode) elmo::k_quantize<elmo::FMT_BF16, true><<<grid, elmo::kThreads, 0, st>>>(src, n, groups, seed, step, first_elem, dst);
+    else elmo::k_quantize<elmo::FMT_BF16, false><<<grid, elmo::kThreads, 0, st>>>(src, n, groups, seed, step, first_elem, dst);
   } else {
-    if (mode) elmo::k_quantize<elmo::FMT_E4M3, true><<<grid, elmo::kThreads, 0, st>>>(src, n, seed, step, first_elem, dst);
-    else elmo::k_quantize<elmo::FMT_E4M3, false><<<grid, elmo::kThreads, 0, st>>>(src, n, seed, step, first_elem, dst);
+    if (mode) elmo::k_quantize<elmo::FMT_E4M3, true><<<grid, elmo::kThreads, 0, st>>>(src, n, groups, seed, step, first_elem, dst);
+    else elmo::k_quantize<elmo::FMT_E4M3, false><<<grid, elmo::kThreads, 0, st>>>(src, n, groups, seed, step, first_elem, dst);
   }
   return check_launch("k_quantize");
 }

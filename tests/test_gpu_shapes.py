@@ -2,6 +2,7 @@
 smallest and largest of a range.  Oracle, inputs and bounds as in test_gpu_parity.py."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import elmo_oracle as o
 from paper_2510_11168_amd import synth
@@ -61,3 +62,27 @@ def test_label_index_sizes(b, B, per_row, L):  # noqa: F811
     assert np.mean(Wn == ref["W_new"]) >= 0.999
     if len(rows) == L:
         assert abs(loss - ref["loss"]) <= 2e-3 * abs(ref["loss"])
+
+
+@pytest.mark.parametrize("fmt", [o.BF16, o.E4M3])
+@pytest.mark.parametrize("n,first,shift", [
+    (1, 0, 0), (7, 3, 0), (8, 8, 0), (2049, 16, 0),     # fewer than a group, one group, a remainder
+    (4096 + 5, 13, 0),                                  # groups that span two blocks of fields
+    (4096 + 5, 13, 1), (2048, 0, 3),                    # buffers that are not aligned to the wide accesses
+    (256 * 32 * 256 * 8 + 24, 40, 0),                   # more groups than threads
+])
+def test_quantize_sizes_and_alignment(b, fmt, n, first, shift):  # noqa: F811
+    """Whatever the size, the first element and the alignment, the bits are the oracle's and nothing else is written."""
+    rng = np.random.default_rng(n)
+    x = (rng.standard_normal(n) * 0.05).astype(np.float32)
+    src = torch.zeros(n + 8, dtype=torch.float32, device="cuda:0")
+    src[shift:shift + n] = torch.from_numpy(x)
+    tdt, ndt = (torch.int16, np.uint16) if fmt == o.BF16 else (torch.uint8, np.uint8)
+    for mode in (0, 1):
+        dst = torch.full((n + 16,), 85, dtype=tdt, device="cuda:0")
+        b.elmo_quantize(src[shift:], n, fmt, mode, 77, 5, first, dst[shift:])
+        got = dst.cpu().numpy().view(ndt)
+        pick = np.arange(n) if n <= 1 << 16 else np.unique(np.concatenate([np.arange(4096), n - 1 - np.arange(4096), rng.integers(0, n, 4096)]))
+        r = o.sr_fields(77, 5, (first + pick).astype(np.uint64)) if mode else None
+        assert np.array_equal(got[shift + pick], o.quantize(x[pick], fmt, r))
+        assert (got[:shift] == 85).all() and (got[shift + n:] == 85).all()
