@@ -10,6 +10,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "kernels.h"
@@ -397,6 +398,49 @@ int raise_lds_limits() {
   return rc;
 }
 
+// Labels per pass of the step and where its logit gradients live.  The chunk bounds the memory that the
+// gradients take, not the work of a launch: a pass may take more labels where the workspace holds
+// their gradients anyway -- the chunk's own region when the batch is smaller than max_B, or the top-k
+// scratch, which is idle during a step.  Short launches cost most: L = 8192, B = 64 in chunks of 2048 spent
+// 54 of 61 us in eight kernels of 6-7 us each that leave most of the chip idle, one pass takes 26 us.
+// A larger batch has whole waves of 256 x 256 tiles to think of (one workgroup per CU): 677016 labels at
+// B = 2733 in passes of 16384 (192 update tiles) take 10.06 ms and in passes of 22656 (267, a second
+// wave of 11) 10.85 ms.  So every number of passes that the room allows is priced with the waves of
+// its launches (microseconds per tile and K slab as measured at d = 768: a tile's epilogue and its slabs,
+// and what three launches cost before and after their tiles) and the cheapest is taken, the chunk
+// itself included.  Passes are of equal size, never smaller than the chunk.  Results do not depend on the
+// split: every label's quantities depend on its own weight row only, and dX is summed in FP32.
+struct Pass { int64_t labels; size_t off_g; };
+Pass choose_pass(const Plan& p, int Bp, bool small_batch) {
+  Pass best{p.chunk, p.off_g};
+  if (p.chunk >= p.L) return best;
+  const int esz = p.fmt == ELMO_FP8_E4M3 ? 1 : 2;
+  const int64_t tiles_b = (Bp + 255) / 256, tiles_j = (p.d + 255) / 256, slices = std::max<int64_t>(1, 256 / (tiles_b * tiles_j));
+  auto launches = [&](int64_t n) {
+    const int64_t lt = (n + 255) / 256;
+    return (double)((lt * tiles_j + 255) / 256) * (10.0 + 1.4 * (Bp / 64)) + (double)((lt * tiles_b + 255) / 256) * (6.0 + 1.4 * (p.d * esz / 128)) +
+           1.4 * (double)((lt * 4 + slices - 1) / slices) + 15.0;
+  };
+  auto price = [&](int64_t n) { return (double)(p.L / n) * launches(n) + (p.L % n ? launches(p.L % n) : 0.0); };
+  double cheapest = small_batch ? 0.0 : price(p.chunk);
+  for (auto [off, end] : {std::pair<size_t, size_t>{p.off_g, p.off_dx}, {p.off_topk, p.total}}) {
+    if (end - off <= 4096) continue;
+    const int64_t room = (int64_t)((end - off - 4096) / ((size_t)Bp * 2)) / 128 * 128;   // the last rows are read 512 bytes wide
+    if (room <= p.chunk) continue;
+    const int64_t least = (p.L + room - 1) / room;
+    for (int64_t passes = least; passes < least + 64; ++passes) {
+      const int64_t labels = ((p.L + passes - 1) / passes + 127) / 128 * 128;
+      if (labels <= p.chunk) break;
+      if (small_batch) {                       // no tiles to fill: the fewer launches the better
+        if (labels > best.labels) best = {labels, off};
+        break;
+      }
+      if (const double t = price(labels); t < cheapest) { cheapest = t; best = {labels, off}; }
+    }
+  }
+  return best;
+}
+
 }  // namespace
 
 extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const int32_t* indptr, const int32_t* indices,
@@ -419,7 +463,6 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
 
   uint8_t* Xq = fp8 ? (uint8_t*)(h->ws + p.off_xq) : nullptr;
   uint16_t* XT = (uint16_t*)(h->ws + p.off_xt);
-  uint16_t* Gt = (uint16_t*)(h->ws + p.off_g);
   float* dXacc = (float*)(h->ws + p.off_dx);
   float* loss_slots = (float*)(h->ws + p.off_loss);
   int* cnt = (int*)(h->ws + p.off_cnt);
@@ -432,12 +475,14 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   // With dropout that kernel keeps a masked copy of the W tile in LDS, which does not fit next to
   // BF16 weights with compensation: that one mode takes the separate kernels.
   const bool small_batch = Bp <= 128 && d % 256 == 0 && !(p.drop_thresh && !fp8 && (p.flags & ELMO_KAHAN));
+  const Pass ps = choose_pass(p, Bp, small_batch);
+  uint16_t* Gt = (uint16_t*)(h->ws + ps.off_g);
   const int col_blocks = d / 256, label_groups = small_batch ? std::max(1, 256 / col_blocks) : 0;   // widths above 65536: one group
   // label slices of the input-gradient product: at most one 512-thread workgroup per CU, so the
   // whole grid is resident at once (256 CUs) and no second, nearly empty round of workgroups runs
   int S = std::max(1, 256 / (tiles_b * tiles_j));
   S = std::min(S, p.dx_rows / Bp256);
-  S = std::max(1, std::min({S, 64, (int)((std::min<int64_t>(p.chunk, p.L) + 63) / 64)}));
+  S = std::max(1, std::min({S, 64, (int)((std::min<int64_t>(ps.labels, p.L) + 63) / 64)}));
   // planes of partial sums; the small-batch kernel uses as many as its largest launch has label groups
   int dx_slices = S;
   if (small_batch) {
@@ -446,9 +491,9 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
       const int64_t t = (n + 31) / 32, per = (t + label_groups - 1) / label_groups;
       return n > 0 ? (int)((t + per - 1) / per) : 0;
     };
-    const int64_t full = p.L / p.chunk, edge = p.kahan_rows % p.chunk;      // whole chunks; labels with compensation in the chunk where they end
-    const int64_t at_edge = std::min<int64_t>(p.chunk, p.L - p.kahan_rows / p.chunk * p.chunk);
-    for (int64_t n : {full ? p.chunk : (int64_t)0, p.L - full * p.chunk, edge, edge ? at_edge - edge : (int64_t)0})
+    const int64_t full = p.L / ps.labels, edge = p.kahan_rows % ps.labels;      // whole chunks; labels with compensation in the chunk where they end
+    const int64_t at_edge = std::min<int64_t>(ps.labels, p.L - p.kahan_rows / ps.labels * ps.labels);
+    for (int64_t n : {full ? ps.labels : (int64_t)0, p.L - full * ps.labels, edge, edge ? at_edge - edge : (int64_t)0})
       dx_slices = std::max(dx_slices, groups(n));
   }
   bool dx_first = true;                                        // no launch has written the planes yet
@@ -479,8 +524,8 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   const size_t esz = fp8 ? 1 : 2;
   const char* Xa = fp8 ? (const char*)Xq : (const char*)X;
   const int a_rows = fp8 ? Bp : B;
-  for (int64_t c0 = 0; c0 < p.L; c0 += p.chunk) {
-    const int n = (int)std::min<int64_t>(p.chunk, p.L - c0);
+  for (int64_t c0 = 0; c0 < p.L; c0 += ps.labels) {
+    const int n = (int)std::min<int64_t>(ps.labels, p.L - c0);
     char* Wc = h->W + (size_t)c0 * d * esz;
     uint16_t* Cc = h->comp ? (uint16_t*)h->comp + (size_t)c0 * d : nullptr;
     const int tile0 = (int)(c0 / 128);

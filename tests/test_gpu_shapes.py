@@ -86,3 +86,33 @@ def test_quantize_sizes_and_alignment(b, fmt, n, first, shift):  # noqa: F811
         r = o.sr_fields(77, 5, (first + pick).astype(np.uint64)) if mode else None
         assert np.array_equal(got[shift + pick], o.quantize(x[pick], fmt, r))
         assert (got[:shift] == 85).all() and (got[shift + n:] == 85).all()
+
+
+@pytest.mark.parametrize("B,d,L,chunk,kahan_rows", [
+    (40, 256, 250000, 9600, 0),             # three passes of the small-batch kernel
+    (40, 256, 250000, 9600, 128 * 800),     # compensation ends inside a pass
+    (300, 384, 150000, 20000, 0),           # passes in the top-k scratch
+    (130, 640, 100003, 30000, 128 * 300),   # the last pass ragged
+    (5, 256, 5000, 128, 0),                 # everything in one pass
+])
+def test_passes_larger_than_the_chunk(b, B, d, L, chunk, kahan_rows):  # noqa: F811
+    """A head whose passes are made of several chunks computes what one with a single chunk does: the same weights and
+    compensation bit by bit, dX and loss to the order of FP32 sums (BF16 rounding of dX: one spacing, 2^-8 in norm), and
+    a top-k between two steps, whose scratch holds a pass's gradients, disturbs neither."""
+    fmt, flags = o.E4M3, o.FLAG_SR | (o.FLAG_KAHAN if kahan_rows else 0)
+    X, indptr, indices = batch(L, d, B)
+    got = []
+    for ch in (chunk, L):
+        case = Case(b, L, d, fmt, ch, flags, B, w_std=0.05, seed=8, kahan_rows=kahan_rows)
+        case.head.workspace.fill_(0x7F)
+        idx = torch.zeros((B, 7), dtype=torch.int32, device="cuda:0")
+        Xd = torch.from_numpy(X.view(np.int16)).to("cuda:0")
+        out = [case.step(X, indptr, indices, 0.05, 1, 2)]
+        case.head.topk(Xd, 7, idx, None)
+        out += [case.step(X, indptr, indices, 0.05, 1, 3), (idx.cpu().numpy(), 0.0), (case.W(), case.C())]
+        got.append(out)
+    (d0, d1, i, w), (e0, e1, j, v) = got
+    assert np.array_equal(w[0], v[0]) and np.array_equal(w[1], v[1]) and np.array_equal(i[0], j[0])
+    for (x, lx), (y, ly) in ((d0, e0), (d1, e1)):
+        assert_dx_close(x, y, 2.0 ** -8)
+        assert abs(lx - ly) <= 1e-5 * abs(ly)
