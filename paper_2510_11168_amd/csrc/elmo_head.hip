@@ -381,6 +381,13 @@ int raise_lds_limits_once() {
   ELMO_ATTR((elmo::k_topk_filter_run<true, false>), elmo::kTopkRunSmem);
   ELMO_ATTR((elmo::k_topk_filter_run<false, true>), elmo::kTopkRunSmem);
   ELMO_ATTR((elmo::k_topk_filter_run<false, false>), elmo::kTopkRunSmem);
+#define ELMO_ATTR_SMALL(F, TB) \
+  ELMO_ATTR((elmo::k_topk_small<F, TB, false>), elmo::topk_small_smem<TB>()); ELMO_ATTR((elmo::k_topk_small<F, TB, true>), elmo::topk_small_smem<TB>())
+  ELMO_ATTR_SMALL(true, 64);
+  ELMO_ATTR_SMALL(true, 128);
+  ELMO_ATTR_SMALL(false, 64);
+  ELMO_ATTR_SMALL(false, 128);
+#undef ELMO_ATTR_SMALL
   ELMO_ATTR((elmo::k_topk_chunk<true>), elmo::kTopkSmem);
   ELMO_ATTR((elmo::k_topk_chunk<false>), elmo::kTopkSmem);
 #undef ELMO_ATTR
@@ -711,10 +718,12 @@ extern "C" int elmo_precision_hits(const int32_t* idx, int32_t B, int32_t k, con
   if ((int64_t)B * k > INT32_MAX) return fail(-1, "B * k = %lld does not fit 31 bits", (long long)B * k);
   hipStream_t st = (hipStream_t)hip_stream;
   unsigned long long* hits = reinterpret_cast<unsigned long long*>(hits_out);
-  elmo::k_fill_u32<<<1, elmo::kThreads, 0, st>>>((uint32_t*)hits, (size_t)k * 2, 0u);
-  if (int rc = check_launch("k_fill_u32")) return rc;
-  const int64_t n = (int64_t)B * k;
-  elmo::k_hits_at<<<(int)((n + elmo::kThreads - 1) / elmo::kThreads), elmo::kThreads, 0, st>>>(idx, B, k, indptr, indices, hits);
+  const int row_groups = (B + elmo::kHitsRows - 1) / elmo::kHitsRows;
+  if (row_groups > 1) {
+    elmo::k_fill_u32<<<1, elmo::kThreads, 0, st>>>((uint32_t*)hits, (size_t)k * 2, 0u);
+    if (int rc = check_launch("k_fill_u32")) return rc;
+  }
+  elmo::k_hits_at<<<row_groups * k, elmo::kHitsRows, 0, st>>>(idx, B, k, indptr, indices, hits);
   if (int rc = check_launch("k_hits_at")) return rc;
   elmo::k_hits_scan<<<1, elmo::kThreads, 0, st>>>(hits, k);
   return check_launch("k_hits_scan");

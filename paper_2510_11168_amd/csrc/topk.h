@@ -1,20 +1,17 @@
 // Top-k scoring over all labels (the top_k of the paper's P@k definition) for gfx950.
 //
 // The [B, L] score matrix is never formed.  Main path: the labels are visited in levels of
-// geometrically growing size (the first 1024, then each level takes the labels seen so far from
-// N to 4 N).  A level computes its logits tile by tile on the matrix cores exactly as the
+// geometrically growing size (the first 4096, then each level multiplies the labels seen so far by up to
+// topk_growth).  A level computes its logits tile by tile on the matrix cores exactly as the
 // training step does (E4M3 x E4M3 or BF16 x BF16, FP32 accumulation) and appends every score that
 // beats the row's threshold -- the k-th best score over all earlier levels -- to the row's
-// candidate list; a select kernel then sorts the candidates, keeps the k best and raises the
+// candidate list; a select kernel then keeps the k best and raises the
 // threshold.  A later label that merely ties the threshold can never enter the top k (same score,
-// larger id), so the comparison is strict and the result exact.  With thresholds from a quarter
-// of the labels a level is expected to append about 3 x k scores per row (scores in no particular
-// order along the label axis); the lists hold 4096.  Every append is an atomic addition on the
-// row's counter, and those cost more than anything else besides the product: with levels growing
-// 17-fold (about 16 x k appends per row and level, 3600 per row in all at 3 M labels and k = 100) the two middle
-// levels took up to five times their product's time; growing 4-fold (1500 appends per row in all,
-// and selects over 400 instead of 1700 candidates) measured 9 % faster end to end, 3-fold the same,
-// 2-fold slower again (more launches).  In the large levels a pass is rare (a few per row and
+// larger id), so the comparison is strict and the result exact.  A level is expected to append about
+// k x (growth - 1) scores per row (scores in no particular order along the label axis); the lists hold
+// 4096.  An append is an atomic addition on the row's counter, and those cost more than anything else
+// besides the product in a large batch; a small one pays for the levels' launches.
+// In the large levels a pass is rare (a few per row and
 // million labels), so the filter first takes one wave-wide vote per sample on the largest of a
 // lane's four scores and skips the four compares when no lane passes (13 % end to end).
 // A row whose list overflows (scores rising steeply with
@@ -31,6 +28,7 @@
 #include <limits.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 
 #include "kernels.h"
@@ -41,8 +39,23 @@ constexpr int kTopkMaxK = 128;                     // entries selected per sweep
 constexpr int kTopkCand = 4096;                    // candidate list length per row (main path)
 constexpr int kTopkCntStride = 32;                 // ints between two rows' candidate counters: one 128-byte line each, so that the
                                                    // atomic additions of different rows do not queue up on the same few lines
-constexpr int kTopkGrowth = 4;                     // labels seen after a level / labels seen before it
-constexpr int kTopkLevel0 = 1024;                  // labels of the first level
+constexpr int kTopkLevel0 = 4096;                  // labels of the first level
+static_assert(kTopkLevel0 <= kTopkCand, "the first level writes one slot per label");
+// Labels seen after a level / labels seen before it, at most (the levels of a sweep grow by one factor, the
+// smallest that needs no more of them).  A level appends about k (growth - 1) scores per row; a level saved
+// is a launch that does not fill the chip and a select, 35-45 us at 256 rows.  131072 BF16 labels, B = 256,
+// k = 100: 175 us at most 4-fold, 150 us at 5.7; 20000 labels, B = 1024: 111 and 94 us.  Where the product is
+// everything, the appends (device-scope additions) weigh more: 3 M labels, B = 1024: 2.18 and 2.22 ms.
+// A small batch has few rows and pays for launches: up to 512 expected appends, an eighth of a list, and at
+// most 128-fold, because with k = 1 a level appends x scores or more with probability exp(-x / growth) (a full
+// list sends the row to the path for overflowed rows: exp(-32) here, but 3e-4 at 512-fold).
+inline double topk_growth(int64_t L, int Bp, int k) {
+  return Bp <= 128 ? std::min(128.0, 1.0 + 512.0 / k) : L * Bp >= (int64_t)1 << 31 ? 4.0 : 5.7;
+}
+// Launches of at most this many workgroups take the kernel with 128-row tiles at batches above 128 too: twice as
+// many workgroups, each with half the slab, and still a single wave (131072 BF16 labels, B = 256: 164 -> 150 us,
+// its first two levels 25 and 41 -> 16 and 25 us); with more than a wave the 256-row tiles win (1 M labels: 644 and 601 us).
+constexpr int kTopkSmallGrid = 256;
 constexpr int kTopkRows = 64;                       // query rows per workgroup
 constexpr int kTopkZP = 132;                        // floats per staged row
 constexpr int kTopkLP = 129;                        // list pitch (odd: one row per thread, no bank clash)
@@ -257,22 +270,14 @@ __global__ void __launch_bounds__(kThreads) k_topk_merge(const float* __restrict
 // ---------------------------------------------------------------------------------------------
 // Main path: threshold filter fused into the logits tile, and the per-row select.
 // ---------------------------------------------------------------------------------------------
-// cnt0: candidates per row that the first level writes without counting (all of its labels).
-// Rows at or beyond B (padding up to whole 256-row tiles) get an infinite threshold: they never emit.
-__global__ void __launch_bounds__(kThreads) k_topk_init(float* __restrict__ tau, int* __restrict__ cnt, int* __restrict__ ovf, int rows,
-                                                        int B, int cnt0) {
-  const int i = blockIdx.x * kThreads + threadIdx.x;
-  if (i < rows) { tau[i] = i < B ? -INFINITY : INFINITY; cnt[(size_t)i * kTopkCntStride] = cnt0; ovf[i] = 0; }
-}
-
 // Logits of labels [l_begin, l_begin + n) for all rows, 256 x 256 tiles as in the training step.
-// The first level has no threshold yet and at most kTopkCand labels: label l of the level goes to
-// slot l of every row, no counting (scores that could never be selected, NaN or -inf, are stored
-// as empty slots).
+// The first level has no threshold yet and at most kTopkCand labels: the score of label l goes to
+// slot l of every row, no ids, no counting (scores that could never be selected, NaN or not after the
+// row's cursor, are stored as empty slots, -inf).
 template <bool FP8>
 __global__ void __launch_bounds__(kGemmThreads, 1)
-k_topk_first(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wl, int n, int l_begin, int d, int Bp, int B,
-             float* __restrict__ cand_sc, int* __restrict__ cand_id, const float* __restrict__ cur_sc, const int* __restrict__ cur_id) {
+k_topk_first(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wl, int n, int d, int Bp, int B,
+             float* __restrict__ cand_sc, const float* __restrict__ cur_sc, const int* __restrict__ cur_id) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
   const int tiles_b = (Bp + 255) >> 8;
@@ -302,9 +307,8 @@ k_topk_first(const char* __restrict__ Xa, int a_rows, const char* __restrict__ W
         const int l = l0 + wn * 128 + 32 * j + (lane & 31);
         const float z = acc[i][j][v];
         if (l < n && row < B) {
-          const bool live = z > -INFINITY && (!paged || topk_after(z, l_begin + l, cs_s[b], ci_s[b]));
+          const bool live = z > -INFINITY && (!paged || topk_after(z, l, cs_s[b], ci_s[b]));
           cand_sc[(size_t)row * kTopkCand + l] = live ? z : -INFINITY;
-          cand_id[(size_t)row * kTopkCand + l] = live ? l_begin + l : INT_MAX;
         }
       }
     }
@@ -534,62 +538,329 @@ k_topk_filter_run(const char* __restrict__ Xa, int a_rows, const char* __restric
   }
 }
 
-// Per row: sort the candidates, keep the k best at the front of the list, raise the threshold.
-__global__ void __launch_bounds__(kThreads) k_topk_select(float* __restrict__ tau, int* __restrict__ cnt, float* __restrict__ cand_sc,
-                                                          int* __restrict__ cand_id, int k, int* __restrict__ idx_out,
-                                                          float* __restrict__ score_out, int out_ld, int out_off,
-                                                          float* __restrict__ next_sc, int* __restrict__ next_id) {
+// Levels of a small batch (padded batch <= 128): tiles of TB (64 or 128) samples x 256 labels.  Here the stream
+// of W is the work: a 256-row tile fills two thirds of its LDS traffic and half of the ring with
+// padding, and two stages of it keep 32 KiB of W in flight per CU.  With 64 or 128 rows a third stage fits
+// (64 KiB of W in flight), one batch tile covers the batch, so the thresholds are read once, and every pass goes
+// through the LDS lists.  Waves: 8 along the labels (TB = 64) or 2 x 4, 64 samples each.
+// FIRST: the first level, as k_topk_first.  One query against 670091 x 768 BF16
+// labels, all levels: 375 us on the 256-row tiles, 202 us here (5.1 TB/s).
+template <int TB> constexpr int topk_small_ring() { return 3 * (TB + 256) * 128; }
+template <int TB> constexpr int topk_small_cap() { return TB == 64 ? 32 : kTopkLdsCap; }
+template <int TB> constexpr int topk_small_smem() { return topk_small_ring<TB>() + TB * 16 + TB * topk_small_cap<TB>() * 8; }   // ring, [thresholds | cursors | counters], lists
+static_assert(topk_small_smem<64>() <= 160 * 1024 && topk_small_smem<128>() <= 160 * 1024, "LDS plan of the small-batch filter");
+template <bool FP8, int TB, bool FIRST>
+__global__ void __launch_bounds__(kGemmThreads, 1)
+k_topk_small(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wl, int n, int l_begin, int d, int B,
+             const float* __restrict__ tau, int* __restrict__ cnt, int* __restrict__ ovf, float* __restrict__ cand_sc,
+             int* __restrict__ cand_id, const float* __restrict__ cur_sc, const int* __restrict__ cur_id) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr int WGN = TB == 64 ? 8 : 4, FN = 8 / WGN, CAP = topk_small_cap<TB>();
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WGN, wn = wave % WGN;
+  const int b0 = (int)blockIdx.y * TB, rows = min(TB, B - b0);         // this workgroup's queries
+  const int ntiles = (n + 255) >> 8, G = (int)gridDim.x, w0 = xcd_logical_id((int)blockIdx.x, G);
+  const int mine = (ntiles - w0 + G - 1) / G;                          // this workgroup's tiles: w0, w0 + G, ... (the grid has no more workgroups than tiles)
+  const size_t rowb = (size_t)d * (FP8 ? 1 : 2);
+  const int nk = (int)(rowb >> 7);
+  const bool paged = cur_sc != nullptr;
+  float* tau_s = reinterpret_cast<float*>(smem + topk_small_ring<TB>());
+  float* cs_s = tau_s + TB;
+  int* ci_s = reinterpret_cast<int*>(cs_s + TB);
+  int* num = ci_s + TB;
+  int2* lists = reinterpret_cast<int2*>(num + TB);                     // [TB][CAP] (score, id)
+  if (tid < TB) {
+    tau_s[tid] = tid >= rows ? INFINITY : FIRST ? -INFINITY : tau[b0 + tid];
+    cs_s[tid] = paged && tid < rows ? cur_sc[b0 + tid] : INFINITY;
+    ci_s[tid] = paged && tid < rows ? cur_id[b0 + tid] : -1;
+    num[tid] = 0;
+  }
+  barrier_lds();
+  f32x16 acc[2][FN];
+  auto filter = [&](int l0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float th = tau_s[wm * 64 + 32 * i + acc_row(v, lane)];
+        float zmax = acc[i][0][v];
+#pragma unroll
+        for (int j = 1; j < FN; ++j) zmax = fmaxf(zmax, acc[i][j][v]);
+        if (!FIRST && __builtin_amdgcn_ballot_w64(zmax > th) == 0ull) continue;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));                                   // the rare branch forms its addresses from an opaque copy
+        const int row = wm * 64 + 32 * i + acc_row(v, ln);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const int l = l0 + wn * 32 * FN + 32 * j + (ln & 31);
+          const float z = acc[i][j][v];
+          if (FIRST) {
+            if (l < n && row < rows) {
+              const bool live = z > -INFINITY && (!paged || topk_after(z, l, cs_s[row], ci_s[row]));
+              cand_sc[(size_t)(b0 + row) * kTopkCand + l] = live ? z : -INFINITY;
+            }
+          } else if (l < n && z > th && (!paged || topk_after(z, l_begin + l, cs_s[row], ci_s[row]))) {
+            const int ls = atomicAdd(num + row, 1);
+            if (ls < CAP) {
+              lists[row * CAP + ls] = make_int2(__float_as_int(z), l_begin + l);
+              continue;
+            }
+            const int slot = atomicAdd(&cnt[(size_t)(b0 + row) * kTopkCntStride], 1);
+            if (slot < kTopkCand) {
+              cand_sc[(size_t)(b0 + row) * kTopkCand + slot] = z;
+              cand_id[(size_t)(b0 + row) * kTopkCand + slot] = l_begin + l;
+            } else {
+              ovf[b0 + row] = 1;
+            }
+          }
+        }
+      }
+  };
+  ring_stream_pp<TB, 128, 256, 128, 3, kGemmWaves, false>(
+      Xa, rowb, 8, Wl, rowb, 8, mine * nk, smem, wave, lane,
+      [&](int ks, size_t& off_a, int& va, size_t& off_b, int& vb) {
+        const int t = ks / nk, sl = ks - t * nk, l0 = (w0 + t * G) << 8;
+        off_a = (size_t)b0 * rowb + (size_t)sl * 128; va = a_rows - b0;
+        off_b = (size_t)l0 * rowb + (size_t)sl * 128; vb = n - l0;
+      },
+      [&](const char* sa, const char* sb, int q0, int q1, int ks) {
+        const int t = ks / nk, sl = ks - t * nk;
+        if (q0 == 0 && sl == 0) zero_acc(acc);
+        logits_slab_product<FP8, FN>(sa, sb, q0 >> 1, wm, wn, lane, acc);
+        if (q1 == 4 && sl == nk - 1) filter((w0 + t * G) << 8);
+      });
+  if (FIRST) return;
+  barrier_lds();                                                       // every wave's LDS appends are in
+  if (tid < rows) {
+    const int c = min(num[tid], CAP), row = b0 + tid;
+    if (c) {
+      const int base = atomicAdd(&cnt[(size_t)row * kTopkCntStride], c);
+      for (int e = 0; e < c; ++e) {
+        const int2 en = lists[tid * CAP + e];
+        if (base + e < kTopkCand) {
+          cand_sc[(size_t)row * kTopkCand + base + e] = __int_as_float(en.x);
+          cand_id[(size_t)row * kTopkCand + base + e] = en.y;
+        } else {
+          ovf[row] = 1;
+        }
+      }
+    }
+  }
+}
+
+// Per row: keep the k best candidates, best first, and raise the threshold.  One workgroup per row; what
+// bounds it is a chain of LDS round trips and barriers, not the few kilobytes it reads.  A bitonic sort of all
+// candidates walks 45 (512 candidates) to 78 (4096) barrier-separated passes.  Instead the candidates
+// are counted into 1024 buckets between the smallest and the largest score (order-preserving integer keys, so
+// any clustering costs at most three more such rounds over the range of one bucket), the buckets from the
+// top that hold the first k are kept, and of those at most 256 every thread counts how many stand
+// before its own (score descending, id ascending): its place in the result.  1024 rows of about 500
+// candidates: 18.5 -> 12 us; the first level's 4096 candidates per row 26 us, where the sort of 1024 took 28.
+// LDS is kept below 40 KiB so that four workgroups share a CU.
+// Where more than 256 candidates cannot be told apart from the k-th by score, all are sorted as before.
+// `seed` > 0: the first level, which wrote label l of its `seed` labels to slot l, without ids and counters;
+// workgroups of rows B and beyond (padding up to whole tiles) only set a threshold that nothing passes.
+constexpr int kSelBuckets = 1024, kSelMost = 256;
+static_assert(kTopkMaxK <= kSelMost && kSelMost == kThreads, "one survivor per thread");
+__device__ inline uint32_t score_key(float z) {      // larger score, larger key; both zeros alike
+  const uint32_t u = f2u(z + 0.0f);
+  return (u & 0x80000000u) ? ~u : u | 0x80000000u;
+}
+__global__ void __launch_bounds__(kThreads) k_topk_select(float* __restrict__ tau, int* __restrict__ cnt, int* __restrict__ ovf,
+                                                          float* __restrict__ cand_sc, int* __restrict__ cand_id, int B, int k, int seed,
+                                                          bool more_levels, int* __restrict__ idx_out, float* __restrict__ score_out,
+                                                          int out_ld, int out_off, float* __restrict__ next_sc, int* __restrict__ next_id) {
   __shared__ float sc[kTopkCand];
   __shared__ int id[kTopkCand];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int m = min(cnt[(size_t)b * kTopkCntStride], kTopkCand);
-  int N2 = 2;
-  while (N2 < max(m, k)) N2 <<= 1;                   // the first k sorted slots are read below even when fewer candidates exist
-  for (int i = tid; i < N2; i += kThreads) {
-    sc[i] = i < m ? cand_sc[(size_t)b * kTopkCand + i] : -INFINITY;
-    id[i] = i < m ? cand_id[(size_t)b * kTopkCand + i] : INT_MAX;
+  __shared__ uint32_t hist[kSelBuckets];
+  __shared__ __attribute__((aligned(16))) uint64_t kept[kSelMost];
+  __shared__ int kept_at[kSelMost];
+  __shared__ uint32_t red[2][kThreads / 64];
+  __shared__ int num[kThreads / 64], found[3], nkept;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (b >= B) {
+    if (tid == 0) tau[b] = INFINITY;
+    return;
   }
+  const int m = seed ? seed : min(cnt[(size_t)b * kTopkCntStride], kTopkCand);
+  const float* src_sc = cand_sc + (size_t)b * kTopkCand;
+  const int* src_id = cand_id + (size_t)b * kTopkCand;
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+  int live = 0;                                        // candidates that are not empty slots
+  for (int i = tid; i < m; i += kThreads) {
+    const float z = src_sc[i];
+    const bool ok = z > -INFINITY;
+    sc[i] = z;
+    id[i] = seed ? (ok ? i : INT_MAX) : src_id[i];
+    const uint32_t key = score_key(z);
+    if (ok) { lo = min(lo, key); hi = max(hi, key); ++live; }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, o, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
+    live += __shfl_xor(live, o, 64);
+  }
+  if (lane == 0) { red[0][wave] = lo; red[1][wave] = hi; num[wave] = live; }
+  if (tid == 0) nkept = 0;
   __syncthreads();
-  bitonic_sort_pairs(sc, id, N2, tid);
-  const int keep = min(m, k);
-  for (int i = tid; i < keep; i += kThreads) {
-    cand_sc[(size_t)b * kTopkCand + i] = sc[i];
-    cand_id[(size_t)b * kTopkCand + i] = id[i];
+  live = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) {
+    lo = min(lo, red[0][w]);
+    hi = max(hi, red[1][w]);
+    live += num[w];
+  }
+  const int keep = min(live, k);
+  bool sorted = false;
+  if (live > kSelMost) {                               // narrow the range of keys down to the k best and a few more
+    int above = 0;                                     // candidates above `hi`, all among the k best
+    for (;;) {
+      const int shift = max(0, 22 - __builtin_clz((hi - lo) | 1u));
+      for (int i = tid; i < kSelBuckets; i += kThreads) hist[i] = 0;
+      __syncthreads();
+      for (int i = tid; i < m; i += kThreads) {
+        const uint32_t key = score_key(sc[i]);
+        if (sc[i] > -INFINITY && key >= lo && key <= hi) atomicAdd(&hist[(key - lo) >> shift], 1u);
+      }
+      __syncthreads();
+      constexpr int RUN = kSelBuckets / kThreads;
+      const int top = kSelBuckets - 1 - tid * RUN;     // this thread's buckets: top, top - 1, ..., top - RUN + 1
+      int sum = 0;
+#pragma unroll
+      for (int q = 0; q < RUN; ++q) sum += (int)hist[top - q];
+      int scan = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(scan, o, 64);
+        scan += lane >= o ? t : 0;
+      }
+      if (lane == 63) num[wave] = scan;
+      __syncthreads();
+      int before = above + scan - sum;
+      for (int w = 0; w < wave; ++w) before += num[w];
+      if (before < k && before + sum >= k) {           // the k-th best is in one of this thread's buckets
+        int q = 0, c = (int)hist[top];
+        while (before + c < k) { before += c; ++q; c = (int)hist[top - q]; }
+        found[0] = top - q;
+        found[1] = before;
+        found[2] = c;
+      }
+      __syncthreads();
+      const uint32_t first = lo + ((uint32_t)found[0] << shift);
+      above = found[1];
+      if (above + found[2] <= kSelMost) { lo = first; break; }
+      if (shift == 0) { sorted = true; break; }        // more than kSelMost - k candidates with the k-th score itself
+      hi = min(hi, first + ((1u << shift) - 1u));
+      lo = first;
+      __syncthreads();                                 // `found` and `num` are read by all before the next round writes them
+    }
+  }
+  if (sorted) {
+    int N2 = 2;
+    while (N2 < m) N2 <<= 1;
+    for (int i = m + tid; i < N2; i += kThreads) { sc[i] = -INFINITY; id[i] = INT_MAX; }
+    __syncthreads();
+    bitonic_sort_pairs(sc, id, N2, tid);
+    if (tid < k) kept_at[tid] = tid;                   // (live > kSelMost >= k)
+    __syncthreads();
+  } else {
+    for (int i = tid; i < m; i += kThreads)
+      if (sc[i] > -INFINITY && score_key(sc[i]) >= lo) kept[atomicAdd(&nkept, 1)] = ((uint64_t)score_key(sc[i]) << 32) | (uint32_t)i;
+    __syncthreads();
+    const int n = nkept;                               // <= kSelMost
+    int at = 0;
+    uint64_t mine = 0;
+    if (tid < n) {
+      at = (int)(uint32_t)kept[tid];
+      mine = (kept[tid] & 0xFFFFFFFF00000000ull) | ~(uint32_t)id[at];   // the smaller id first
+    }
+    __syncthreads();
+    kept[tid] = mine;
+    __syncthreads();
+    int place = 0;
+    for (int i = 0; i < n; i += 2) {
+      place += kept[i] > mine;
+      place += kept[i + 1] > mine;
+    }
+    if (tid < n && place < k) kept_at[place] = at;
+    __syncthreads();
+  }
+  for (int i = tid; i < k; i += kThreads) {
+    const bool have = i < keep;
+    const float z = have ? sc[kept_at[i]] : -INFINITY;
+    const int l = have ? id[kept_at[i]] : INT_MAX;
+    if (more_levels && have) {
+      cand_sc[(size_t)b * kTopkCand + i] = z;
+      cand_id[(size_t)b * kTopkCand + i] = l;
+    }
+    if (idx_out) idx_out[(size_t)b * out_ld + out_off + i] = l;
+    if (score_out) score_out[(size_t)b * out_ld + out_off + i] = z;
+    if (i == k - 1) {
+      tau[b] = z;
+      if (next_sc) { next_sc[b] = z; next_id[b] = l; }
+    }
   }
   if (tid == 0) {
     cnt[(size_t)b * kTopkCntStride] = keep;
-    tau[b] = m >= k ? sc[k - 1] : -INFINITY;
+    if (seed) ovf[b] = 0;
   }
-  if (idx_out || score_out)
-    for (int i = tid; i < k; i += kThreads) {
-      if (idx_out) idx_out[(size_t)b * out_ld + out_off + i] = id[i];
-      if (score_out) score_out[(size_t)b * out_ld + out_off + i] = sc[i];
-    }
-  if (tid == 0 && next_sc) { next_sc[b] = sc[k - 1]; next_id[b] = id[k - 1]; }
 }
 
 // ---------------------------------------------------------------------------------------------
 // P@k numerators: per position j the number of rows whose j-th prediction is a true label, then
-// the running sum over positions.  Integer counts: the result does not depend on the order of the
-// atomic additions.
+// the running sum over positions.  Integer counts: the result does not depend on the order of additions.
+// One workgroup counts a position over up to 1024 rows; a batch of no more rows is written directly, with
+// nothing cleared before, a larger one is added up atomically.  The running sum of up to 2^20 positions is
+// a scan by one workgroup (a single thread's walk through memory took 14 us for k = 100).
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(kThreads) k_hits_at(const int* __restrict__ idx, int B, int k, const int* __restrict__ indptr,
-                                                      const int* __restrict__ indices, unsigned long long* __restrict__ hits) {
-  const int t = blockIdx.x * kThreads + threadIdx.x;
-  if (t >= B * k) return;
-  const int b = t / k, j = t - b * k;
-  const int l = idx[t];
-  int lo = indptr[b], hi = indptr[b + 1];          // binary search in the row's ascending ids
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (indices[mid] < l) lo = mid + 1; else hi = mid;
+constexpr int kHitsRows = 1024;
+__global__ void __launch_bounds__(kHitsRows) k_hits_at(const int* __restrict__ idx, int B, int k, const int* __restrict__ indptr,
+                                                       const int* __restrict__ indices, unsigned long long* __restrict__ hits) {
+  __shared__ int part[kHitsRows / 64];
+  const int j = blockIdx.x % k, tid = threadIdx.x, b = blockIdx.x / k * kHitsRows + tid;
+  bool hit = false;
+  if (b < B) {
+    const int l = idx[(size_t)b * k + j];
+    const int end = indptr[b + 1];
+    int lo = indptr[b], hi = end;                    // binary search in the row's ascending ids
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (indices[mid] < l) lo = mid + 1; else hi = mid;
+    }
+    hit = lo < end && indices[lo] == l;
   }
-  if (lo < indptr[b + 1] && indices[lo] == l) atomicAdd(&hits[j], 1ull);
+  const int count = __builtin_popcountll(__builtin_amdgcn_ballot_w64(hit));
+  if ((tid & 63) == 0) part[tid >> 6] = count;
+  __syncthreads();
+  if (tid != 0) return;
+  int sum = 0;
+#pragma unroll
+  for (int w = 0; w < kHitsRows / 64; ++w) sum += part[w];
+  if (B <= kHitsRows) hits[j] = (unsigned long long)sum;
+  else if (sum) atomicAdd(&hits[j], (unsigned long long)sum);
 }
 __global__ void __launch_bounds__(kThreads) k_hits_scan(unsigned long long* __restrict__ hits, int k) {
-  if (threadIdx.x == 0) {
-    unsigned long long run = 0;
-    for (int j = 0; j < k; ++j) { run += hits[j]; hits[j] = run; }
+  __shared__ unsigned long long part[kThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned long long carry = 0;
+  for (int base = 0; base < k; base += kThreads) {
+    unsigned long long v = base + tid < k ? hits[base + tid] : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned long long t = __shfl_up(v, o, 64);
+      v += lane >= o ? t : 0;
+    }
+    if (lane == 63) part[wave] = v;
+    __syncthreads();
+    unsigned long long all = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) {
+      if (w < wave) v += part[w];
+      all += part[w];
+    }
+    if (base + tid < k) hits[base + tid] = carry + v;
+    carry += all;
+    __syncthreads();
   }
 }
 
@@ -613,7 +884,6 @@ inline int topk_run(hipStream_t st, bool fp8, const char* Xa, int a_rows, const 
   int* cand_id = reinterpret_cast<int*>(scratch + lists0 + rows * (size_t)kTopkCand * 4);
   char* fb_scratch = scratch + topk_main_bytes(Bp);
   const size_t rowb = (size_t)d * (fp8 ? 1 : 2);
-  static_assert(kTopkLevel0 <= kTopkCand, "the first level writes one slot per label");
   const int tiles_b256 = (Bp + 255) / 256;
   // fallback geometry (rows whose candidate list overflowed)
   const int tiles_b = (B + kTopkRows - 1) / kTopkRows;
@@ -637,35 +907,48 @@ inline int topk_run(hipStream_t st, bool fp8, const char* Xa, int a_rows, const 
     const bool more = off + k < k_total;
     float* ns = more ? cursor_sc[(page + 1) & 1] : nullptr;
     int* ni = more ? cursor_id[(page + 1) & 1] : nullptr;
-    // ---- main path
-    k_topk_init<<<(int)((rows + kThreads - 1) / kThreads), kThreads, 0, st>>>(tau, cnt, ovf, (int)rows, B,
-                                                                               (int)std::min<int64_t>(L, kTopkLevel0));
-    if (int rc = topk_launch_error("k_topk_init", err, errsz)) return rc;
-    for (int64_t begin = 0, end = std::min<int64_t>(L, kTopkLevel0); begin < L; begin = end, end = std::min<int64_t>(L, end * kTopkGrowth)) {
-      const int n = (int)(end - begin);
-      const int grid = (n + 255) / 256 * tiles_b256;
-      const char* Wl = W + (size_t)begin * rowb;
-      const bool first = begin == 0;
-      // persistent levels: at most one workgroup per CU, a multiple of the batch tiles when there are enough of them
-      const int run_grid = grid <= 256 ? grid : (tiles_b256 <= 256 ? 256 - 256 % tiles_b256 : 256);
+    // ---- main path: a first level without thresholds, then levels that grow by one factor, as few as `growth` allows
+    const int64_t level0 = std::min<int64_t>(L, kTopkLevel0);
+    const double most = topk_growth(L, Bp, k);
+    const int levels = (int)std::ceil(std::log((double)L / (double)level0) / std::log(most) - 1e-9);
+    const double growth = levels > 0 ? std::pow((double)L / (double)level0, 1.0 / levels) : 1.0;
+    for (int lv = 0; lv <= levels; ++lv) {
+      const auto seen = [&](int n) { return n == levels ? L : std::min<int64_t>(L, (int64_t)((double)level0 * std::pow(growth, n) + 255.0) / 256 * 256); };
+      const int64_t begin = lv ? seen(lv - 1) : 0, end = lv ? seen(lv) : level0;
+      const bool first = lv == 0, last = lv == levels;
+      if (const int n = (int)(end - begin); n > 0) {
+        const int grid = (n + 255) / 256 * tiles_b256;
+        const char* Wl = W + (size_t)begin * rowb;
+        // persistent levels: at most one workgroup per CU, a multiple of the batch tiles when there are enough of them
+        const int run_grid = grid <= 256 ? grid : (tiles_b256 <= 256 ? 256 - 256 % tiles_b256 : 256);
+        // expected passes per row among a wave's 128 labels of this level: k (growth - 1) 128 / n
+        const bool dense = (double)k * (growth - 1.0) * 128.0 >= (double)n;
+        const int tb = Bp <= 64 ? 64 : 128, small_y = (Bp + tb - 1) / tb;
+        const bool small = small_y == 1 || 2 * grid <= kTopkSmallGrid;
 #define ELMO_TOPK_FIRST(F) \
-  k_topk_first<F><<<grid, kGemmThreads, logits_smem<256>(), st>>>(Xa, a_rows, Wl, n, (int)begin, d, Bp, B, cand_sc, cand_id, cs, ci)
+  k_topk_first<F><<<grid, kGemmThreads, logits_smem<256>(), st>>>(Xa, a_rows, Wl, n, d, Bp, B, cand_sc, cs, ci)
 #define ELMO_TOPK_FILTER_RUN(F, DE) \
   k_topk_filter_run<F, DE><<<run_grid, kGemmThreads, kTopkRunSmem, st>>>(Xa, a_rows, Wl, n, (int)begin, d, Bp, tau, cnt, ovf, cand_sc, cand_id, cs, ci)
-      // expected passes per row among a wave's 128 labels of this level: k (growth - 1) 128 / n
-      const bool dense = (int64_t)k * (kTopkGrowth - 1) * 128 >= n;
-      if (fp8 && first) ELMO_TOPK_FIRST(true);
-      else if (first) ELMO_TOPK_FIRST(false);
-      else if (fp8 && dense) ELMO_TOPK_FILTER_RUN(true, true);
-      else if (fp8) ELMO_TOPK_FILTER_RUN(true, false);
-      else if (dense) ELMO_TOPK_FILTER_RUN(false, true);
-      else ELMO_TOPK_FILTER_RUN(false, false);
+#define ELMO_TOPK_SMALL(F, TB, FI) \
+  k_topk_small<F, TB, FI><<<dim3(std::min((n + 255) / 256, 256 / small_y), small_y), kGemmThreads, topk_small_smem<TB>(), st>>>(Xa, a_rows, Wl, n, (int)begin, d, B, tau, cnt, ovf, cand_sc, cand_id, cs, ci)
+#define ELMO_TOPK_SMALL_TB(F, TB) do { if (first) ELMO_TOPK_SMALL(F, TB, true); else ELMO_TOPK_SMALL(F, TB, false); } while (0)
+        if (small && tb == 64) { if (fp8) ELMO_TOPK_SMALL_TB(true, 64); else ELMO_TOPK_SMALL_TB(false, 64); }
+        else if (small) { if (fp8) ELMO_TOPK_SMALL_TB(true, 128); else ELMO_TOPK_SMALL_TB(false, 128); }
+        else if (fp8 && first) ELMO_TOPK_FIRST(true);
+        else if (first) ELMO_TOPK_FIRST(false);
+        else if (fp8 && dense) ELMO_TOPK_FILTER_RUN(true, true);
+        else if (fp8) ELMO_TOPK_FILTER_RUN(true, false);
+        else if (dense) ELMO_TOPK_FILTER_RUN(false, true);
+        else ELMO_TOPK_FILTER_RUN(false, false);
 #undef ELMO_TOPK_FIRST
 #undef ELMO_TOPK_FILTER_RUN
-      if (int rc = topk_launch_error("top-k level kernel", err, errsz)) return rc;
-      const bool last = end == L;
-      k_topk_select<<<B, kThreads, 0, st>>>(tau, cnt, cand_sc, cand_id, k, last ? idx_out : nullptr, last ? score_out : nullptr,
-                                            k_total, off, last ? ns : nullptr, last ? ni : nullptr);
+#undef ELMO_TOPK_SMALL
+#undef ELMO_TOPK_SMALL_TB
+        if (int rc = topk_launch_error("top-k level kernel", err, errsz)) return rc;
+      }
+      k_topk_select<<<first ? (int)rows : B, kThreads, 0, st>>>(tau, cnt, ovf, cand_sc, cand_id, B, k, first ? (int)level0 : 0, !last,
+                                                               last ? idx_out : nullptr, last ? score_out : nullptr, k_total, off,
+                                                               last ? ns : nullptr, last ? ni : nullptr);
       if (int rc = topk_launch_error("k_topk_select", err, errsz)) return rc;
     }
     // ---- fallback for rows whose candidate list overflowed (does nothing when no row is flagged)

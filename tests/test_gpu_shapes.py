@@ -116,3 +116,61 @@ def test_passes_larger_than_the_chunk(b, B, d, L, chunk, kahan_rows):  # noqa: F
     for (x, lx), (y, ly) in ((d0, e0), (d1, e1)):
         assert_dx_close(x, y, 2.0 ** -8)
         assert abs(lx - ly) <= 1e-5 * abs(ly)
+
+
+@pytest.mark.parametrize("fmt", [o.BF16, o.E4M3])
+@pytest.mark.parametrize("B,L,d,levels", [
+    (1, 40, 128, 3),            # fewer labels than k allows, all in the first level
+    (1, 4096, 256, 5),          # exactly the first level
+    (64, 4097, 128, 9),         # one label more
+    (65, 30011, 384, 9),        # two more 64-row groups than one tile holds: the 128-row tile
+    (128, 21000, 128, 17),      # one slab per E4M3 tile
+    (129, 25000, 128, 9),       # the first batch on the 256-row tiles
+    (3, 70000, 128, 2),         # a handful of distinct scores: thousands of labels tie with the k-th
+])
+def test_topk_is_exact_with_ties(b, fmt, B, L, d, levels):  # noqa: F811
+    """Weights and inputs on a coarse grid make every score a small multiple of 2^-4, exact in FP32, so ids and scores
+    have one right answer, ties by smaller id included: across level and tile edges, through buckets that hold
+    more candidates than a workgroup can rank, and for signed zeros and negative scores."""
+    rng = np.random.default_rng(L + B)
+    W = (rng.integers(0, levels, (L, d)) - levels // 2).astype(np.float32) / 8
+    X = rng.integers(-1, 2, (B, d)).astype(np.float32) * (rng.random((B, d)) < 0.2) / 2
+    if B > 2:
+        X[0] = 0.0                                   # every score is zero
+        X[1] = -np.abs(X[1])
+    Wq = o.quantize(W, fmt)
+    assert np.array_equal(o.decode(Wq, fmt), W)
+    Wd = torch.from_numpy(Wq.view(np.int16) if fmt == o.BF16 else Wq).to("cuda:0")
+    Xd = torch.from_numpy(o.round_bf16(X).view(np.int16)).to("cuda:0")
+    head = b.Head(L, d, fmt, 4096, 0, B, B)
+    head.weights().copy_(Wd)
+    Z = torch.from_numpy(X) @ torch.from_numpy(W).T
+    for k in (1, 100, 128, 130):
+        k = min(k, L)
+        ref_sc, ref_idx = torch.sort(Z, dim=1, descending=True, stable=True)
+        ref_sc, ref_idx = ref_sc[:, :k].numpy(), ref_idx[:, :k].numpy()
+        outs = [lambda i, s: head.topk(Xd, k, i, s)]
+        if B <= 128:
+            outs.append(lambda i, s: b.elmo_topk_static(Wd, L, d, fmt, Xd, B, k, i, s))
+        for call in outs:
+            idx, sc = torch.full((B, k), -7, dtype=torch.int32, device="cuda:0"), torch.full((B, k), 7.0, device="cuda:0")
+            head.workspace.fill_(0x7F)
+            call(idx, sc)
+            assert np.array_equal(idx.cpu().numpy(), ref_idx)
+            assert np.array_equal(sc.cpu().numpy(), ref_sc)
+
+
+@pytest.mark.parametrize("B,k", [(1, 1), (1024, 3), (1025, 3), (3000, 300), (7, 1000)])
+def test_precision_hits_sizes(b, B, k):  # noqa: F811
+    """Row groups of 1024 and scans of 256 positions: the counts are the definition's."""
+    rng = np.random.default_rng(B)
+    n = 2000
+    idx = np.stack([rng.choice(n, k, replace=False) for _ in range(B)]).astype(np.int32)
+    rows = [np.sort(rng.choice(n, rng.integers(0, 12), replace=False)) for _ in range(B)]
+    indptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    indices = np.concatenate(rows + [np.zeros(1, np.int64)]).astype(np.int32)
+    want = np.cumsum(np.sum([np.isin(idx[i], rows[i]) for i in range(B)], axis=0))
+    hits = torch.full((k,), -1, dtype=torch.int64, device="cuda:0")
+    b.elmo_precision_hits(torch.from_numpy(idx).to("cuda:0"), B, k, torch.from_numpy(indptr).to("cuda:0"),
+                          torch.from_numpy(indices).to("cuda:0"), hits)
+    assert np.array_equal(hits.cpu().numpy(), want)
