@@ -174,3 +174,14 @@ def test_precision_hits_sizes(b, B, k):  # noqa: F811
     b.elmo_precision_hits(torch.from_numpy(idx).to("cuda:0"), B, k, torch.from_numpy(indptr).to("cuda:0"),
                           torch.from_numpy(indices).to("cuda:0"), hits)
     assert np.array_equal(hits.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("fmt,flags", [(o.BF16, o.FLAG_SR), (o.E4M3, o.FLAG_SR | o.FLAG_KAHAN)])
+@pytest.mark.parametrize("B,L", [
+    (129, 2000), (300, 257), (520, 130),    # 128-row tiles of a larger batch: the last one ragged, or with no rows of the padded batch
+    (200, 33000 + 7), (300, 16384 + 5),     # just too many tiles for them: the 256-row tiles, ragged both ways
+])
+def test_logits_tile_choice(b, fmt, flags, B, L):  # noqa: F811
+    case = Case(b, L, 128, fmt, L, flags, B, w_std=0.05, seed=9)
+    case.head.workspace.fill_(0x7F)
+    check_step(case, *batch(L, 128, B), 0.05, 1, 2, 6e-2)
