@@ -654,7 +654,7 @@ k_topk_small(const char* __restrict__ Xa, int a_rows, const char* __restrict__ W
 // any clustering costs at most three more such rounds over the range of one bucket), the buckets from the
 // top that hold the first k are kept, and of those at most 256 every thread counts how many stand
 // before its own (score descending, id ascending): its place in the result.  1024 rows of about 500
-// candidates: 18.5 -> 12 us; the first level's 4096 candidates per row 26 us, where the sort of 1024 took 28.
+// candidates: 18.5 -> 11 us; the first level's 4096 candidates per row 22 us, where the sort of 1024 took 28.
 // LDS is kept below 40 KiB so that four workgroups share a CU.
 // Where more than 256 candidates cannot be told apart from the k-th by score, all are sorted as before.
 // `seed` > 0: the first level, which wrote label l of its `seed` labels to slot l, without ids and counters;
@@ -686,13 +686,24 @@ __global__ void __launch_bounds__(kThreads) k_topk_select(float* __restrict__ ta
   const int* src_id = cand_id + (size_t)b * kTopkCand;
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
   int live = 0;                                        // candidates that are not empty slots
-  for (int i = tid; i < m; i += kThreads) {
-    const float z = src_sc[i];
-    const bool ok = z > -INFINITY;
-    sc[i] = z;
-    id[i] = seed ? (ok ? i : INT_MAX) : src_id[i];
-    const uint32_t key = score_key(z);
-    if (ok) { lo = min(lo, key); hi = max(hi, key); ++live; }
+  constexpr int NL = 8;                                // loads in flight per thread
+  for (int i0 = tid; i0 < m; i0 += NL * kThreads) {
+    float z[NL];
+    int l[NL];
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+      const int i = i0 + q * kThreads;
+      z[q] = i < m ? src_sc[i] : -INFINITY;
+      l[q] = i < m && !seed ? src_id[i] : i;
+    }
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+      const int i = i0 + q * kThreads;
+      const bool ok = z[q] > -INFINITY;
+      const uint32_t key = score_key(z[q]);
+      if (i < m) { sc[i] = z[q]; id[i] = ok ? l[q] : INT_MAX; }
+      if (ok) { lo = min(lo, key); hi = max(hi, key); ++live; }
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
