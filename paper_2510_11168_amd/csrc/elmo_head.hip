@@ -415,9 +415,18 @@ int raise_lds_limits() {
 // wave of 11) 10.85 ms.  So every number of passes that the room allows is priced with the waves of
 // its launches (microseconds per tile and K slab as measured at d = 768: a tile's epilogue and its slabs,
 // and what three launches cost before and after their tiles) and the cheapest is taken, the chunk
-// itself included.  Passes are of equal size, never smaller than the chunk.  Results do not depend on the
+// itself included: passes of equal size, and passes of whole waves of update tiles, the last of which takes
+// what is left if that fits (L = 131072, B = 256: 171 + 171 + 170 label tiles 442 us, 170 + 170 + 172 420 us).  No pass but the last is smaller than the chunk.  Results do not depend on the
 // split: every label's quantities depend on its own weight row only, and dX is summed in FP32.
-struct Pass { int64_t labels; size_t off_g; size_t slots; };
+struct Pass {
+  int64_t labels, most;      // labels of a pass; what is left at the end is one pass if it is no more than `most`
+  size_t off_g, slots;
+  int64_t take(int64_t left) const { return left <= most ? left : labels; }
+  int64_t largest(int64_t L) const {
+    const int64_t before = L > most ? (L - most + labels - 1) / labels : 0;
+    return std::max(before ? labels : 0, L - before * labels);
+  }
+};
 // Passes of at most this many 256 x 256 logits tiles take 128 x 128 tiles at batches above 128 too: half of the CUs
 // would have no tile, and four times the tiles, two on a CU at once, are one wave up to here.  32768 BF16 labels,
 // B = 256, d = 768: 30.4 -> 24.8 us; 60000 E4M3 labels, d = 512, B = 160, whole step: 134 -> 120 us; with a second wave
@@ -426,7 +435,7 @@ constexpr int kLogitsSmallGrid = 128;
 Pass choose_pass(const Plan& p, int Bp, bool small_batch) {
   // tile losses of 128 x 128 logits tiles at a batch above 128 go to the end of the top-k scratch (0: no room)
   const size_t slots = align256((size_t)p.ntiles * ((Bp + 127) / 128) * 4);
-  Pass best{p.chunk, p.off_g, p.total - p.off_topk >= slots ? p.total - slots : 0};
+  Pass best{p.chunk, p.chunk, p.off_g, p.total - p.off_topk >= slots ? p.total - slots : 0};
   if (p.chunk >= p.L) return best;
   const int esz = p.fmt == ELMO_FP8_E4M3 ? 1 : 2;
   const int64_t tiles_b = (Bp + 255) / 256, tiles_j = (p.d + 255) / 256, slices = std::max<int64_t>(1, 256 / (tiles_b * tiles_j));
@@ -435,23 +444,28 @@ Pass choose_pass(const Plan& p, int Bp, bool small_batch) {
     return (double)((lt * tiles_j + 255) / 256) * (10.0 + 1.4 * (Bp / 64)) + (double)((lt * tiles_b + 255) / 256) * (6.0 + 1.4 * (p.d * esz / 128)) +
            1.4 * (double)((lt * 4 + slices - 1) / slices) + 15.0;
   };
-  auto price = [&](int64_t n) { return (double)(p.L / n) * launches(n) + (p.L % n ? launches(p.L % n) : 0.0); };
-  double cheapest = small_batch ? 0.0 : price(p.chunk);
+  auto price = [&](int64_t n, int64_t most) {
+    const int64_t before = (p.L - most + n - 1) / n;           // (most < L, or one pass)
+    return p.L <= most ? launches(p.L) : (double)before * launches(n) + launches(p.L - before * n);
+  };
+  double cheapest = small_batch ? 0.0 : price(p.chunk, p.chunk);
   for (auto [off, end] : {std::pair<size_t, size_t>{p.off_g, p.off_dx}, {p.off_topk, best.slots}}) {
     if (end < off) continue;
     if (end - off <= 4096) continue;
     const int64_t room = (int64_t)((end - off - 4096) / ((size_t)Bp * 2)) / 128 * 128;   // the last rows are read 512 bytes wide
     if (room <= p.chunk) continue;
     const int64_t least = (p.L + room - 1) / room;
-    for (int64_t passes = least; passes < least + 64; ++passes) {
-      const int64_t labels = ((p.L + passes - 1) / passes + 127) / 128 * 128;
-      if (labels <= p.chunk) break;
-      if (small_batch) {                       // no tiles to fill: the fewer launches the better
-        if (labels > best.labels) best = {labels, off, best.slots};
-        break;
-      }
-      if (const double t = price(labels); t < cheapest) { cheapest = t; best = {labels, off, best.slots}; }
+    auto consider = [&](int64_t labels) {
+      if (labels <= p.chunk || labels > room) return;
+      if (const double t = price(labels, room); t < cheapest) { cheapest = t; best = {labels, room, off, best.slots}; }
+    };
+    if (small_batch) {                         // no tiles to fill: the fewer launches the better
+      const int64_t labels = ((p.L + least - 1) / least + 127) / 128 * 128;
+      if (labels > best.labels) best = {labels, labels, off, best.slots};
+      continue;
     }
+    for (int64_t passes = least; passes < least + 64; ++passes) consider(((p.L + passes - 1) / passes + 127) / 128 * 128);
+    for (int64_t waves = 1; waves <= 64; ++waves) consider(256 * waves / tiles_j * 256);
   }
   return best;
 }
@@ -536,7 +550,7 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   }
 
   // the logits kernel's tile is tb samples x tb labels
-  const int64_t pass_tiles = (std::min(ps.labels, p.L) + 255) / 256 * tiles_b;
+  const int64_t pass_tiles = (ps.largest(p.L) + 255) / 256 * tiles_b;
   const int tb = Bp <= 128 || (pass_tiles <= kLogitsSmallGrid && ps.slots) ? 128 : 256;
   const int loss_tiles = (Bp + tb - 1) / tb;
   if (tb == 128 && Bp > 128) loss_slots = (float*)(h->ws + ps.slots);
@@ -544,8 +558,8 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   const size_t esz = fp8 ? 1 : 2;
   const char* Xa = fp8 ? (const char*)Xq : (const char*)X;
   const int a_rows = fp8 ? Bp : B;
-  for (int64_t c0 = 0; c0 < p.L; c0 += ps.labels) {
-    const int n = (int)std::min<int64_t>(ps.labels, p.L - c0);
+  for (int64_t c0 = 0; c0 < p.L; c0 += ps.take(p.L - c0)) {
+    const int n = (int)ps.take(p.L - c0);
     char* Wc = h->W + (size_t)c0 * d * esz;
     uint16_t* Cc = h->comp ? (uint16_t*)h->comp + (size_t)c0 * d : nullptr;
     const int tile0 = (int)(c0 / 128);
