@@ -152,8 +152,9 @@ def measure(b, synth, torch, np, cfg, args, n_warm, n_steps, dev, profile_name, 
     per_step = [marks[i].elapsed_time(marks[i + 1]) for i in range(n_steps)]
     mem_peak = torch.cuda.max_memory_allocated() - mem_before
 
-    # ---------------- per-kernel algorithmic work (per launch = per chunk; averaged over the chunks)
-    n_chunks = -(-L // cfg.chunk)
+    # ---------------- per-kernel algorithmic work (per launch = per pass over labels; averaged over the passes, which
+    # take a chunk each, or more where the workspace holds it)
+    n_chunks = max(1, round(prof["logits"][1] / n_steps))
     n_avg = L / n_chunks                                   # labels per launch, averaged
     Bp = -(-B // 64) * 64
     # padded batches of at most 128 rows take the single-pass kernel: input gradient and update share

@@ -90,8 +90,9 @@ size_t elmo_logit_buffer_bytes(int64_t batch, int64_t labels);
 /* Create a head over caller-owned buffers.  Requirements: L >= 1; d a positive multiple of 128, at most 2^20;
  * chunk >= 1 (the labels processed per pass, Section 4.2 "chunking"; it need not divide L, the last
  * chunk is short.  The kernels work on whole 128-label tiles, so a pass takes round_up(chunk, 128)
- * labels; the updated weights do not depend on the chunk size at all and the input gradient only
- * through the order of its FP32 sums, so the rounding shows in the workspace size only); buffers at
+ * labels, or more where the workspace holds their gradients anyway; the updated weights do not
+ * depend on the chunk size at all and the input gradient only through the order of its FP32 sums, so
+ * the rounding shows in the workspace size only); buffers at
  * least as large as elmo_head_sizes says and 256-byte aligned.  Launches nothing.  *out receives the
  * handle.  Heads may be created and stepped from several host threads (one head per thread at a
  * time); the library's one-time set-up is guarded. */

@@ -416,8 +416,9 @@ int raise_lds_limits() {
 // its launches (microseconds per tile and K slab as measured at d = 768: a tile's epilogue and its slabs,
 // and what three launches cost before and after their tiles) and the cheapest is taken, the chunk
 // itself included: passes of equal size, and passes of whole waves of update tiles, the last of which takes
-// what is left if that fits (L = 131072, B = 256: 171 + 171 + 170 label tiles 442 us, 170 + 170 + 172 420 us).  No pass but the last is smaller than the chunk.  Results do not depend on the
-// split: every label's quantities depend on its own weight row only, and dX is summed in FP32.
+// what is left if that fits (L = 131072, B = 256: 171 + 171 + 170 label tiles 442 us, 170 + 170 + 172
+// 420 us).  No pass but the last is smaller than the chunk.  Results do not depend on the split: every label's
+// quantities depend on its own weight row only, and dX is summed in FP32.
 struct Pass {
   int64_t labels, most;      // labels of a pass; what is left at the end is one pass if it is no more than `most`
   size_t off_g, slots;
