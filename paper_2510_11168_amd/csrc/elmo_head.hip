@@ -388,6 +388,7 @@ int raise_lds_limits_once() {
   ELMO_ATTR_SMALL(false, 64);
   ELMO_ATTR_SMALL(false, 128);
 #undef ELMO_ATTR_SMALL
+  ELMO_ATTR((elmo::k_topk_select<2 * elmo::kTopkCand>), elmo::topk_select_smem<2 * elmo::kTopkCand>());
   ELMO_ATTR((elmo::k_topk_chunk<true>), elmo::kTopkSmem);
   ELMO_ATTR((elmo::k_topk_chunk<false>), elmo::kTopkSmem);
 #undef ELMO_ATTR

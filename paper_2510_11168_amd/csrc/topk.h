@@ -1,15 +1,15 @@
 // Top-k scoring over all labels (the top_k of the paper's P@k definition) for gfx950.
 //
 // The [B, L] score matrix is never formed.  Main path: the labels are visited in levels of
-// geometrically growing size (the first 4096, then each level multiplies the labels seen so far by up to
-// topk_growth).  A level computes its logits tile by tile on the matrix cores exactly as the
+// geometrically growing size (the first 4096, then each level multiplies the labels seen so far by one
+// factor, topk_levels.h).  A level computes its logits tile by tile on the matrix cores exactly as the
 // training step does (E4M3 x E4M3 or BF16 x BF16, FP32 accumulation) and appends every score that
 // beats the row's threshold -- the k-th best score over all earlier levels -- to the row's
 // candidate list; a select kernel then keeps the k best and raises the
 // threshold.  A later label that merely ties the threshold can never enter the top k (same score,
 // larger id), so the comparison is strict and the result exact.  A level is expected to append about
 // k x (growth - 1) scores per row (scores in no particular order along the label axis); the lists hold
-// 4096.  An append is an atomic addition on the row's counter, and those cost more than anything else
+// 4096, those of a batch of at most 128 rows 8192.  An append is an atomic addition on the row's counter, and those cost more than anything else
 // besides the product in a large batch; a small one pays for the levels' launches.
 // In the large levels a pass is rare (a few per row and
 // million labels), so the filter first takes one wave-wide vote per sample on the largest of a
@@ -28,30 +28,16 @@
 #include <limits.h>
 
 #include <algorithm>
-#include <cmath>
 #include <cstdio>
 
 #include "kernels.h"
+#include "topk_levels.h"
 
 namespace elmo {
 
 constexpr int kTopkMaxK = 128;                     // entries selected per sweep (one page)
-constexpr int kTopkCand = 4096;                    // candidate list length per row (main path)
 constexpr int kTopkCntStride = 32;                 // ints between two rows' candidate counters: one 128-byte line each, so that the
                                                    // atomic additions of different rows do not queue up on the same few lines
-constexpr int kTopkLevel0 = 4096;                  // labels of the first level
-static_assert(kTopkLevel0 <= kTopkCand, "the first level writes one slot per label");
-// Labels seen after a level / labels seen before it, at most (the levels of a sweep grow by one factor, the
-// smallest that needs no more of them).  A level appends about k (growth - 1) scores per row; a level saved
-// is a launch that does not fill the chip and a select, 35-45 us at 256 rows.  131072 BF16 labels, B = 256,
-// k = 100: 175 us at most 4-fold, 150 us at 5.7; 20000 labels, B = 1024: 111 and 94 us.  Where the product is
-// everything, the appends (device-scope additions) weigh more: 3 M labels, B = 1024: 2.18 and 2.22 ms.
-// A small batch has few rows and pays for launches: up to 512 expected appends, an eighth of a list, and at
-// most 128-fold, because with k = 1 a level appends x scores or more with probability exp(-x / growth) (a full
-// list sends the row to the path for overflowed rows: exp(-32) here, but 3e-4 at 512-fold).
-inline double topk_growth(int64_t L, int Bp, int k) {
-  return Bp <= 128 ? std::min(128.0, 1.0 + 512.0 / k) : L * Bp >= (int64_t)1 << 31 ? 4.0 : 5.7;
-}
 // Launches of at most this many workgroups take the kernel with 128-row tiles at batches above 128 too: twice as
 // many workgroups, each with half the slab, and still a single wave (131072 BF16 labels, B = 256: 164 -> 150 us,
 // its first two levels 25 and 41 -> 16 and 25 us); with more than a wave the 256-row tiles win (1 M labels: 644 and 601 us).
@@ -68,6 +54,7 @@ inline int topk_segments(int tiles_b) { return std::max(1, std::min(64, 512 / ti
 
 // Main-path scratch: thresholds, counters, overflow flags and candidate lists per (padded) row.
 inline size_t topk_main_rows(int Bp_max) { return (size_t)(Bp_max + 255) / 256 * 256; }
+static_assert(256 * kTopkCand >= 128 * 2 * kTopkCand, "the longer lists of at most 128 rows fit where those of 256 do");
 inline size_t topk_main_bytes(int Bp_max) { return topk_main_rows(Bp_max) * (24 + (size_t)kTopkCntStride * 4 + (size_t)kTopkCand * 8) + 1024; }
 
 // (score, id) strictly after the cursor (cs, ci) in the order score descending, id ascending.
@@ -543,7 +530,7 @@ k_topk_filter_run(const char* __restrict__ Xa, int a_rows, const char* __restric
 // padding, and two stages of it keep 32 KiB of W in flight per CU.  With 64 or 128 rows a third stage fits
 // (64 KiB of W in flight), one batch tile covers the batch, so the thresholds are read once, and every pass goes
 // through the LDS lists.  Waves: 8 along the labels (TB = 64) or 2 x 4, 64 samples each.
-// FIRST: the first level, as k_topk_first.  One query against 670091 x 768 BF16
+// FIRST: the first level, as k_topk_first.  `list`: slots of a row's candidate list.  One query against 670091 x 768 BF16
 // labels, all levels: 375 us on the 256-row tiles, 202 us here (5.1 TB/s).
 template <int TB> constexpr int topk_small_ring() { return 3 * (TB + 256) * 128; }
 template <int TB> constexpr int topk_small_cap() { return TB == 64 ? 32 : kTopkLdsCap; }
@@ -551,7 +538,7 @@ template <int TB> constexpr int topk_small_smem() { return topk_small_ring<TB>()
 static_assert(topk_small_smem<64>() <= 160 * 1024 && topk_small_smem<128>() <= 160 * 1024, "LDS plan of the small-batch filter");
 template <bool FP8, int TB, bool FIRST>
 __global__ void __launch_bounds__(kGemmThreads, 1)
-k_topk_small(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wl, int n, int l_begin, int d, int B,
+k_topk_small(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wl, int n, int l_begin, int d, int B, int list,
              const float* __restrict__ tau, int* __restrict__ cnt, int* __restrict__ ovf, float* __restrict__ cand_sc,
              int* __restrict__ cand_id, const float* __restrict__ cur_sc, const int* __restrict__ cur_id) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -596,7 +583,7 @@ k_topk_small(const char* __restrict__ Xa, int a_rows, const char* __restrict__ W
           if (FIRST) {
             if (l < n && row < rows) {
               const bool live = z > -INFINITY && (!paged || topk_after(z, l, cs_s[row], ci_s[row]));
-              cand_sc[(size_t)(b0 + row) * kTopkCand + l] = live ? z : -INFINITY;
+              cand_sc[(size_t)(b0 + row) * list + l] = live ? z : -INFINITY;
             }
           } else if (l < n && z > th && (!paged || topk_after(z, l_begin + l, cs_s[row], ci_s[row]))) {
             const int ls = atomicAdd(num + row, 1);
@@ -605,9 +592,9 @@ k_topk_small(const char* __restrict__ Xa, int a_rows, const char* __restrict__ W
               continue;
             }
             const int slot = atomicAdd(&cnt[(size_t)(b0 + row) * kTopkCntStride], 1);
-            if (slot < kTopkCand) {
-              cand_sc[(size_t)(b0 + row) * kTopkCand + slot] = z;
-              cand_id[(size_t)(b0 + row) * kTopkCand + slot] = l_begin + l;
+            if (slot < list) {
+              cand_sc[(size_t)(b0 + row) * list + slot] = z;
+              cand_id[(size_t)(b0 + row) * list + slot] = l_begin + l;
             } else {
               ovf[b0 + row] = 1;
             }
@@ -636,9 +623,9 @@ k_topk_small(const char* __restrict__ Xa, int a_rows, const char* __restrict__ W
       const int base = atomicAdd(&cnt[(size_t)row * kTopkCntStride], c);
       for (int e = 0; e < c; ++e) {
         const int2 en = lists[tid * CAP + e];
-        if (base + e < kTopkCand) {
-          cand_sc[(size_t)row * kTopkCand + base + e] = __int_as_float(en.x);
-          cand_id[(size_t)row * kTopkCand + base + e] = en.y;
+        if (base + e < list) {
+          cand_sc[(size_t)row * list + base + e] = __int_as_float(en.x);
+          cand_id[(size_t)row * list + base + e] = en.y;
         } else {
           ovf[row] = 1;
         }
@@ -655,22 +642,25 @@ k_topk_small(const char* __restrict__ Xa, int a_rows, const char* __restrict__ W
 // top that hold the first k are kept, and of those at most 256 every thread counts how many stand
 // before its own (score descending, id ascending): its place in the result.  1024 rows of about 500
 // candidates: 18.5 -> 11 us; the first level's 4096 candidates per row 22 us, where the sort of 1024 took 28.
-// LDS is kept below 40 KiB so that four workgroups share a CU.
+// LDS is kept below 40 KiB so that four workgroups share a CU (lists of 4096; there are few rows with longer ones).
 // Where more than 256 candidates cannot be told apart from the k-th by score, all are sorted as before.
 // `seed` > 0: the first level, which wrote label l of its `seed` labels to slot l, without ids and counters;
 // workgroups of rows B and beyond (padding up to whole tiles) only set a threshold that nothing passes.
 constexpr int kSelBuckets = 1024, kSelMost = 256;
+template <int LIST> constexpr int topk_select_smem() { return LIST * 8; }
 static_assert(kTopkMaxK <= kSelMost && kSelMost == kThreads, "one survivor per thread");
 __device__ inline uint32_t score_key(float z) {      // larger score, larger key; both zeros alike
   const uint32_t u = f2u(z + 0.0f);
   return (u & 0x80000000u) ? ~u : u | 0x80000000u;
 }
+template <int LIST>
 __global__ void __launch_bounds__(kThreads) k_topk_select(float* __restrict__ tau, int* __restrict__ cnt, int* __restrict__ ovf,
                                                           float* __restrict__ cand_sc, int* __restrict__ cand_id, int B, int k, int seed,
                                                           bool more_levels, int* __restrict__ idx_out, float* __restrict__ score_out,
                                                           int out_ld, int out_off, float* __restrict__ next_sc, int* __restrict__ next_id) {
-  __shared__ float sc[kTopkCand];
-  __shared__ int id[kTopkCand];
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  float* sc = reinterpret_cast<float*>(smem);          // [LIST] scores, [LIST] ids
+  int* id = reinterpret_cast<int*>(smem) + LIST;
   __shared__ uint32_t hist[kSelBuckets];
   __shared__ __attribute__((aligned(16))) uint64_t kept[kSelMost];
   __shared__ int kept_at[kSelMost];
@@ -681,9 +671,9 @@ __global__ void __launch_bounds__(kThreads) k_topk_select(float* __restrict__ ta
     if (tid == 0) tau[b] = INFINITY;
     return;
   }
-  const int m = seed ? seed : min(cnt[(size_t)b * kTopkCntStride], kTopkCand);
-  const float* src_sc = cand_sc + (size_t)b * kTopkCand;
-  const int* src_id = cand_id + (size_t)b * kTopkCand;
+  const int m = seed ? seed : min(cnt[(size_t)b * kTopkCntStride], LIST);
+  const float* src_sc = cand_sc + (size_t)b * LIST;
+  const int* src_id = cand_id + (size_t)b * LIST;
   uint32_t lo = 0xFFFFFFFFu, hi = 0u;
   int live = 0;                                        // candidates that are not empty slots
   constexpr int NL = 8;                                // loads in flight per thread
@@ -801,8 +791,8 @@ __global__ void __launch_bounds__(kThreads) k_topk_select(float* __restrict__ ta
     const float z = have ? sc[kept_at[i]] : -INFINITY;
     const int l = have ? id[kept_at[i]] : INT_MAX;
     if (more_levels && have) {
-      cand_sc[(size_t)b * kTopkCand + i] = z;
-      cand_id[(size_t)b * kTopkCand + i] = l;
+      cand_sc[(size_t)b * LIST + i] = z;
+      cand_id[(size_t)b * LIST + i] = l;
     }
     if (idx_out) idx_out[(size_t)b * out_ld + out_off + i] = l;
     if (score_out) score_out[(size_t)b * out_ld + out_off + i] = z;
@@ -895,7 +885,7 @@ inline int topk_run(hipStream_t st, bool fp8, const char* Xa, int a_rows, const 
   int* cand_id = reinterpret_cast<int*>(scratch + lists0 + rows * (size_t)kTopkCand * 4);
   char* fb_scratch = scratch + topk_main_bytes(Bp);
   const size_t rowb = (size_t)d * (fp8 ? 1 : 2);
-  const int tiles_b256 = (Bp + 255) / 256;
+  const int tiles_b256 = (Bp + 255) / 256, list = topk_list(Bp);
   // fallback geometry (rows whose candidate list overflowed)
   const int tiles_b = (B + kTopkRows - 1) / kTopkRows;
   const int tiles_l = (int)((L + 127) / 128);
@@ -918,22 +908,18 @@ inline int topk_run(hipStream_t st, bool fp8, const char* Xa, int a_rows, const 
     const bool more = off + k < k_total;
     float* ns = more ? cursor_sc[(page + 1) & 1] : nullptr;
     int* ni = more ? cursor_id[(page + 1) & 1] : nullptr;
-    // ---- main path: a first level without thresholds, then levels that grow by one factor, as few as `growth` allows
-    const int64_t level0 = std::min<int64_t>(L, kTopkLevel0);
-    const double most = topk_growth(L, Bp, k);
-    const int levels = (int)std::ceil(std::log((double)L / (double)level0) / std::log(most) - 1e-9);
-    const double growth = levels > 0 ? std::pow((double)L / (double)level0, 1.0 / levels) : 1.0;
-    for (int lv = 0; lv <= levels; ++lv) {
-      const auto seen = [&](int n) { return n == levels ? L : std::min<int64_t>(L, (int64_t)((double)level0 * std::pow(growth, n) + 255.0) / 256 * 256); };
-      const int64_t begin = lv ? seen(lv - 1) : 0, end = lv ? seen(lv) : level0;
-      const bool first = lv == 0, last = lv == levels;
+    // ---- main path: a first level without thresholds, then levels that grow by one factor
+    const TopkLevels levels = topk_levels(L, Bp, k);
+    for (int lv = 0; lv <= levels.n; ++lv) {
+      const int64_t begin = lv ? levels.end(lv - 1) : 0, end = lv ? levels.end(lv) : levels.level0;
+      const bool first = lv == 0, last = lv == levels.n;
       if (const int n = (int)(end - begin); n > 0) {
         const int grid = (n + 255) / 256 * tiles_b256;
         const char* Wl = W + (size_t)begin * rowb;
         // persistent levels: at most one workgroup per CU, a multiple of the batch tiles when there are enough of them
         const int run_grid = grid <= 256 ? grid : (tiles_b256 <= 256 ? 256 - 256 % tiles_b256 : 256);
         // expected passes per row among a wave's 128 labels of this level: k (growth - 1) 128 / n
-        const bool dense = (double)k * (growth - 1.0) * 128.0 >= (double)n;
+        const bool dense = (double)k * (levels.growth - 1.0) * 128.0 >= (double)n;
         const int tb = Bp <= 64 ? 64 : 128, small_y = (Bp + tb - 1) / tb;
         const bool small = small_y == 1 || 2 * grid <= kTopkSmallGrid;
 #define ELMO_TOPK_FIRST(F) \
@@ -941,7 +927,7 @@ inline int topk_run(hipStream_t st, bool fp8, const char* Xa, int a_rows, const 
 #define ELMO_TOPK_FILTER_RUN(F, DE) \
   k_topk_filter_run<F, DE><<<run_grid, kGemmThreads, kTopkRunSmem, st>>>(Xa, a_rows, Wl, n, (int)begin, d, Bp, tau, cnt, ovf, cand_sc, cand_id, cs, ci)
 #define ELMO_TOPK_SMALL(F, TB, FI) \
-  k_topk_small<F, TB, FI><<<dim3(std::min((n + 255) / 256, 256 / small_y), small_y), kGemmThreads, topk_small_smem<TB>(), st>>>(Xa, a_rows, Wl, n, (int)begin, d, B, tau, cnt, ovf, cand_sc, cand_id, cs, ci)
+  k_topk_small<F, TB, FI><<<dim3(std::min((n + 255) / 256, 256 / small_y), small_y), kGemmThreads, topk_small_smem<TB>(), st>>>(Xa, a_rows, Wl, n, (int)begin, d, B, list, tau, cnt, ovf, cand_sc, cand_id, cs, ci)
 #define ELMO_TOPK_SMALL_TB(F, TB) do { if (first) ELMO_TOPK_SMALL(F, TB, true); else ELMO_TOPK_SMALL(F, TB, false); } while (0)
         if (small && tb == 64) { if (fp8) ELMO_TOPK_SMALL_TB(true, 64); else ELMO_TOPK_SMALL_TB(false, 64); }
         else if (small) { if (fp8) ELMO_TOPK_SMALL_TB(true, 128); else ELMO_TOPK_SMALL_TB(false, 128); }
@@ -957,9 +943,13 @@ inline int topk_run(hipStream_t st, bool fp8, const char* Xa, int a_rows, const 
 #undef ELMO_TOPK_SMALL_TB
         if (int rc = topk_launch_error("top-k level kernel", err, errsz)) return rc;
       }
-      k_topk_select<<<first ? (int)rows : B, kThreads, 0, st>>>(tau, cnt, ovf, cand_sc, cand_id, B, k, first ? (int)level0 : 0, !last,
-                                                               last ? idx_out : nullptr, last ? score_out : nullptr, k_total, off,
-                                                               last ? ns : nullptr, last ? ni : nullptr);
+#define ELMO_TOPK_SELECT(LIST) \
+  k_topk_select<LIST><<<first ? (int)rows : B, kThreads, topk_select_smem<LIST>(), st>>>(tau, cnt, ovf, cand_sc, cand_id, B, k, first ? (int)levels.level0 : 0, !last, \
+                                                                                       last ? idx_out : nullptr, last ? score_out : nullptr, k_total, off, \
+                                                                                       last ? ns : nullptr, last ? ni : nullptr)
+      if (list > kTopkCand) ELMO_TOPK_SELECT(2 * kTopkCand);
+      else ELMO_TOPK_SELECT(kTopkCand);
+#undef ELMO_TOPK_SELECT
       if (int rc = topk_launch_error("k_topk_select", err, errsz)) return rc;
     }
     // ---- fallback for rows whose candidate list overflowed (does nothing when no row is flagged)

@@ -160,6 +160,33 @@ def test_topk_is_exact_with_ties(b, fmt, B, L, d, levels):  # noqa: F811
             assert np.array_equal(sc.cpu().numpy(), ref_sc)
 
 
+@pytest.mark.parametrize("fmt", [o.BF16, o.E4M3])
+@pytest.mark.parametrize("B", [3, 100, 200])        # lists of 8192 on 64-row and on 128-row tiles, lists of 4096
+@pytest.mark.parametrize("above", [4096 - 5, 4097, 8192 - 5, 8192 - 4, 9000])
+def test_topk_list_lengths(b, fmt, B, above):  # noqa: F811
+    """`above` labels after the first 4096 beat every label of the first level: with the five that are kept as many as a list of
+    4096 (where one level takes them all) or 8192 holds, one more (the overflow path), or well beyond.  Scores are small
+    multiples of 1/16, so thousands tie, and ids and scores have one right answer."""
+    L, d, k = 60000, 128, 5
+    rng = np.random.default_rng(above)
+    W = np.zeros((L, d), np.float32)
+    W[:, 0] = rng.integers(-8, 9, L) / 8
+    W[rng.choice(np.arange(4096, 20000), above, replace=False), 0] = rng.integers(9, 17, above) / 8
+    X = np.zeros((B, d), np.float32)
+    X[:, 0] = 0.5
+    Wq = o.quantize(W, fmt)
+    assert np.array_equal(o.decode(Wq, fmt), W)
+    Xd = torch.from_numpy(o.round_bf16(X).view(np.int16)).to("cuda:0")
+    head = b.Head(L, d, fmt, 4096, 0, B, B)
+    head.weights().copy_(torch.from_numpy(Wq.view(np.int16) if fmt == o.BF16 else Wq).to("cuda:0"))
+    head.workspace.fill_(0x7F)
+    idx, sc = torch.full((B, k), -7, dtype=torch.int32, device="cuda:0"), torch.full((B, k), 7.0, device="cuda:0")
+    head.topk(Xd, k, idx, sc)
+    ref_sc, ref_idx = torch.sort(torch.from_numpy(W[:, 0] / 2), descending=True, stable=True)
+    assert np.array_equal(idx.cpu().numpy(), np.tile(ref_idx[:k].numpy(), (B, 1)))
+    assert np.array_equal(sc.cpu().numpy(), np.tile(ref_sc[:k].numpy(), (B, 1)))
+
+
 @pytest.mark.parametrize("B,k", [(1, 1), (1024, 3), (1025, 3), (3000, 300), (7, 1000)])
 def test_precision_hits_sizes(b, B, k):  # noqa: F811
     """Row groups of 1024 and scans of 256 positions: the counts are the definition's."""
