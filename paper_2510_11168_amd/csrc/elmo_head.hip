@@ -370,7 +370,7 @@ int raise_lds_limits_once() {
   ELMO_ATTR_UPDATE(elmo::FMT_E4M3, false, true);
   ELMO_ATTR_UPDATE(elmo::FMT_E4M3, false, false);
 #undef ELMO_ATTR_UPDATE
-  ELMO_ATTR((elmo::k_step_setup), (int)elmo::setup_smem(elmo::kIndexMaxBins));
+  ELMO_ATTR((elmo::k_step_setup), elmo::kSetupMaxSmem);
   ELMO_ATTR((elmo::k_dx<true, false>), elmo::dx_smem_bytes<true>());
   ELMO_ATTR((elmo::k_dx<true, true>), elmo::dx_smem_bytes<true>());
   ELMO_ATTR((elmo::k_dx<false, false>), elmo::dx_smem_bytes<false>());
@@ -534,9 +534,9 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   prof.mark(st, CLS_SETUP);
   // ---- step set-up: inputs, zeroed partial sums, label index
   {
-    const bool one_wg = p.ntiles <= elmo::kIndexMaxBins && nnz <= elmo::kIndexMaxNnz;
+    const bool one_wg = elmo::index_in_one_workgroup(p.ntiles, B, nnz);
     const elmo::IndexArgs ia{indptr, indices, p.L, nnz, one_wg ? p.ntiles : 0, ptr, pos, flag};
-    elmo::k_step_setup<<<1 + Bp / 64 * (d / 128), elmo::kSetupThreads, elmo::setup_smem(ia.nb), st>>>(
+    elmo::k_step_setup<<<1 + Bp / 64 * (d / 128), elmo::kSetupThreads, elmo::setup_smem(ia.nb, B), st>>>(
         (const uint16_t*)X, B, Bp, d, Xq, XT, ia, one_wg ? nullptr : cnt, (size_t)p.ntiles + 1);
     if (int rc = check_launch("k_step_setup")) return rc;
     if (!one_wg) {
@@ -646,7 +646,7 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
 namespace {
 // Xq [Bp, d] <- E4M3(X), for the top-k paths (no transposed copy, no label index)
 int stage_queries(hipStream_t st, const void* X, int B, int Bp, int d, uint8_t* Xq) {
-  elmo::k_step_setup<<<1 + Bp / 64 * (d / 128), elmo::kSetupThreads, elmo::setup_smem(0), st>>>((const uint16_t*)X, B, Bp, d, Xq, nullptr,
+  elmo::k_step_setup<<<1 + Bp / 64 * (d / 128), elmo::kSetupThreads, elmo::setup_smem(0, 0), st>>>((const uint16_t*)X, B, Bp, d, Xq, nullptr,
                                                                                               elmo::IndexArgs{}, nullptr, 0);
   return check_launch("k_step_setup");
 }

@@ -174,23 +174,38 @@ __global__ void __launch_bounds__(kThreads) k_label_scatter(const int* __restric
 // into their slots.  The three kernels above cost a launch each (4-5 us apart) and a single-workgroup scan of
 // all bins in memory (16 us at 23438 bins); this one runs beside the workgroups that stage the inputs, in the
 // same launch.  Its passes are chains of memory round trips, so the row pointers and first labels of
-// eight rows per thread are fetched at once.  Same treatment of malformed rows as above (skipped; flagged
+// eight rows per thread are fetched at once, and what a row has beyond kRowWalk positives is left to whole waves at the
+// end of a pass: eight rows of 3000 positives 128 apart among 1024 rows, 3 M labels, whose chains all fell to the same
+// eight threads, took 1277 us (the kernels above 333), now 80.  Same treatment of malformed rows as above (skipped; flagged
 // when `flag` is given); positions never exceed nnz.
 constexpr int kSetupThreads = 1024;
 constexpr int kIndexMaxBins = 32768;                             // 128 KiB of LDS: labels 0 .. 4194303
-constexpr int kIndexMaxNnz = 65536;                              // above, one CU's share of the work takes longer than the launches
+constexpr int kIndexMaxNnz = 65536;
+constexpr int kRowWalk = 64;
+constexpr int kSetupMaxSmem = 159 * 1024;                        // beside the static part
+// One CU places 64 positives in about the time of 64 scattered stores and takes a round of latencies per 1024 rows, the kernels
+// above pay launches and their scan of the bins: where the lines cross (set-up of a step, one workgroup / kernels):
+//   782 bins:    1024 rows of 7 13 / 18 us, of 16 20 / 18; 2048 rows of 4 20 / 20; 4096 rows of 1 32 / 22
+//   23438 bins:  512 rows of 64 43 / 42; 2048 rows of 7 26 / 32, of 16 41 / 35; 3072 rows of 4 30 / 32, of 16 58 / 35
+// With at most one row per group of lanes the walk is never longer than the kernels' (64 rows of 1000: 64 / 240 us).
+inline bool index_in_one_workgroup(int64_t nb, int B, int64_t nnz) {
+  if (nb > kIndexMaxBins || nnz > kIndexMaxNnz || (nb + B) * 4 > kSetupMaxSmem) return false;
+  return B <= kSetupThreads / kRowLanes || nnz + 4 * (int64_t)B + 10 * std::max<int64_t>(B - 1024, 0) <= 17500 + nb * 3 / 4;
+}
 struct IndexArgs {
   const int* indptr; const int* indices;
   int64_t L, nnz;
   int nb;                                                        // bins; 0 = the index is built by the kernels above
   int* ptr; int2* pos; int* flag;
 };
+// f(label, row, place in `indices` of a positive that has one before it in its row, or 0) for the first kRowWalk positives of
+// every row; the rows that have more are collected in long_rows if it is given.
 template <class F>
-__device__ __forceinline__ void for_each_positive(const IndexArgs& ia, int B, int tid, F&& f) {
+__device__ __forceinline__ void for_each_positive(const IndexArgs& ia, int B, int tid, int* long_rows, int* n_long, F&& f) {
   constexpr int NR = 8, RPP = kSetupThreads / kRowLanes;         // rows in flight per thread, rows per pass
   const int sub = tid % kRowLanes;
   for (int r0 = tid / kRowLanes; r0 < B; r0 += NR * RPP) {
-    int p0[NR], p1[NR], l[NR];
+    int p0[NR], p1[NR], l[NR], most = 0;
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       const int r = r0 + k * RPP;
@@ -201,26 +216,50 @@ __device__ __forceinline__ void for_each_positive(const IndexArgs& ia, int B, in
     for (int k = 0; k < NR; ++k) {
       if (p0[k] < 0 || p1[k] < p0[k] || p1[k] > ia.nnz) { f(-1, -1, 0); p0[k] = p1[k] = 0; }
       l[k] = p0[k] + sub < p1[k] ? ia.indices[p0[k] + sub] : 0;
+      most = max(most, p1[k] - p0[k]);
     }
+    if (most > kRowWalk)
+#pragma unroll
+      for (int k = 0; k < NR; ++k)
+        if (p1[k] - p0[k] > kRowWalk) {
+          if (long_rows && sub == 0) long_rows[atomicAdd(n_long, 1)] = r0 + k * RPP;
+          p1[k] = p0[k] + kRowWalk;
+        }
 #pragma unroll
     for (int k = 0; k < NR; ++k)
       for (int p = p0[k] + sub; p < p1[k]; p += kRowLanes) f(p == p0[k] + sub ? l[k] : ia.indices[p], r0 + k * RPP, p > p0[k] ? p : 0);
   }
 }
+// The rest of the collected rows, a wave each.
+template <class F>
+__device__ __forceinline__ void for_each_left_positive(const IndexArgs& ia, int tid, const int* long_rows, int n, F&& f) {
+  const int lane = tid & 63;
+  for (int i = tid >> 6; i < n; i += kSetupThreads / 64) {
+    const int r = long_rows[i], end = ia.indptr[r + 1];
+    for (int p = ia.indptr[r] + kRowWalk + lane; p < end; p += 64) f(ia.indices[p], r, p);
+  }
+}
 __device__ inline void label_index(const IndexArgs& ia, int B, int* h) {
   __shared__ int wsum[kSetupThreads / 64];
-  __shared__ int bad;
+  __shared__ int bad, n_long;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int* long_rows = h + ia.nb;                                    // [B]
   for (int i = tid; i < ia.nb; i += kSetupThreads) h[i] = 0;
-  if (tid == 0) bad = 0;
+  if (tid == 0) bad = n_long = 0;
   __syncthreads();
-  for_each_positive(ia, B, tid, [&](int l, int b, int p) {       // p: place in `indices` of a positive that has one before it in its row
+  const auto count = [&](int l, int b, int p) {
     if (b < 0) { if (ia.flag) atomicOr(&bad, 1); return; }
     const bool in_range = l >= 0 && l < ia.L;
     if (ia.flag && (!in_range || (p > 0 && l <= ia.indices[p - 1]))) atomicOr(&bad, 2);
     if (in_range) atomicAdd(&h[l >> 7], 1);
-  });
+  };
+  for_each_positive(ia, B, tid, long_rows, &n_long, count);
   __syncthreads();
+  const int n = n_long;
+  if (n) {
+    for_each_left_positive(ia, tid, long_rows, n, count);
+    __syncthreads();
+  }
   const int run = ((ia.nb + kSetupThreads - 1) / kSetupThreads) | 1;      // odd: consecutive threads' runs start in different banks
   const int i0 = min(tid * run, ia.nb), i1 = min(i0 + run, ia.nb);
   int sum = 0;
@@ -252,11 +291,13 @@ __device__ inline void label_index(const IndexArgs& ia, int B, int* h) {
     if (ia.flag) *ia.flag = bad;
   }
   __syncthreads();
-  for_each_positive(ia, B, tid, [&](int l, int b, int) {
+  const auto place = [&](int l, int b, int) {
     if (b < 0 || l < 0 || l >= ia.L) return;
     const int slot = atomicAdd(&h[l >> 7], 1);
     if (slot < most) ia.pos[slot] = make_int2(l, b);
-  });
+  };
+  for_each_positive(ia, B, tid, nullptr, nullptr, place);
+  for_each_left_positive(ia, tid, long_rows, n, place);
 }
 
 // Step set-up.  Workgroup 0 builds the label index (or nothing); the others stage the inputs (Algorithm 1:
@@ -266,7 +307,11 @@ __device__ inline void label_index(const IndexArgs& ia, int B, int* h) {
 // 4096 x 768).  Rows B..Bp-1 are zero padding.  Either output may be absent.  cnt: bin counters to clear for
 // the separate index kernels.
 constexpr int kXtPitch = 64 * 2 + 16;                             // bytes per staged column of 64 samples
-inline size_t setup_smem(int nb) { return (size_t)nb * 4 > 128 * kXtPitch ? (size_t)nb * 4 : 128 * kXtPitch; }
+// LDS of a launch that indexes nb bins and B rows, or that only stages (nb = 0)
+inline size_t setup_smem(int nb, int B) {
+  const size_t index = nb ? (size_t)(nb + B) * 4 : 0;
+  return index > 128 * kXtPitch ? index : 128 * kXtPitch;
+}
 __global__ void __launch_bounds__(kSetupThreads) k_step_setup(const uint16_t* __restrict__ X, int B, int Bp, int d,
                                                               uint8_t* __restrict__ Xq, uint16_t* __restrict__ XT, IndexArgs ia,
                                                               int* __restrict__ cnt, size_t n_cnt) {

@@ -64,6 +64,92 @@ def test_label_index_sizes(b, B, per_row, L):  # noqa: F811
         assert abs(loss - ref["loss"]) <= 2e-3 * abs(ref["loss"])
 
 
+def uneven(B, lens, L, seed=3):
+    """CSR of rows of the given lengths, ids spread over the whole head, the first and the last label in every long row."""
+    rng = np.random.default_rng(seed)
+    rows = []
+    for n in lens:
+        r = np.sort(rng.choice(L, size=n, replace=False))
+        if n > 1:
+            r[0], r[-1] = 0, L - 1
+        rows.append(r)
+    assert len(rows) == B
+    return np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), np.concatenate(rows + [np.zeros(0, np.int64)]).astype(np.int32)
+
+
+def index_case(B, what, L):
+    rng = np.random.default_rng(9)
+    lens = {"none": np.zeros(B, int), "one": np.ones(B, int), "five": np.full(B, 5), "eight": np.full(B, 8),
+            "eight and one more": np.full(B, 8) + (np.arange(B) == B // 2), "every third": np.arange(B) % 3 // 2 * 7,
+            "most": np.full(B, 65536 // B), "long": np.where(np.arange(B) % 128 == 5, 1000, 1), "longer": np.where(np.arange(B) % 128 == 5, 3000, 1), "mixed": rng.integers(0, 40, B)}[what]
+    return uneven(B, lens, L)
+
+
+@pytest.mark.parametrize("B,what,L", [
+    (1, "one", 128), (1, "most", 70000), (2, "none", 300), (7, "mixed", 5000), (128, "most", 20000), (129, "five", 385),
+    (300, "every third", 70000),                                    # empty rows
+    (1024, "long", 100000), (1024, "longer", 100000),               # rows of 1000 positives among rows of one; 3000: the separate kernels
+    (400, "mixed", 300000), (1030, "five", 300000),                 # more rows than one round of the workgroup
+    (1500, "one", 9000), (1700, "one", 9000), (2000, "eight", 9000),    # on both sides of the line to the separate kernels
+    (16, "mixed", 4194304), (3000, "one", 4194304), (16, "mixed", 4194305),   # the most bins, and one more
+])
+def test_every_positive_reaches_its_label(b, B, what, L):  # noqa: F811
+    """Zero weights make every logit zero and G = 1/2 - Y exactly; with inputs of +-1/8 that cancel in pairs the new weights
+    lr (Y^T X - sum(X) / 2) are exact, so each of the L x d shows exactly the positives of its label."""
+    d, lr = 128, 0.5
+    indptr, indices = index_case(B, what, L)
+    rng = np.random.default_rng(2)
+    X = rng.choice([-0.125, 0.125], (B, d)).astype(np.float32)
+    X[1::2] = -X[:B // 2 * 2:2]
+    head = b.Head(L, d, o.BF16, 131072, 0, B, max(len(indices), 1))
+    head.workspace.fill_(0x7F)
+    Xd, ip, ix = (torch.from_numpy(v).to("cuda:0") for v in (o.round_bf16(X).view(np.int16), indptr, indices))
+    head.step(Xd, ip, ix, lr, 0, 0)
+    Xf = torch.from_numpy(X).to("cuda:0")
+    want = (-lr / 2 * Xf.double().sum(0)).float().expand(L, d).clone()
+    want.index_add_(0, ix.long(), lr * Xf[torch.repeat_interleave(torch.arange(B, device="cuda:0"), ip.diff().long())])
+    assert torch.equal(head.weights().view(torch.bfloat16).float(), want.bfloat16().float())
+
+
+def test_malformed_rows_are_skipped_and_reported(b):  # noqa: F811
+    """Rows whose pointers fall, leave the list or name ids out of order: skipped or taken as they stand, and the next call says so."""
+    L, d, B = 1000, 128, 6
+    X = torch.from_numpy(o.round_bf16(np.full((B, d), 0.125, np.float32)).view(np.int16)).to("cuda:0")
+    for indptr, indices in (([0, 2, 1, 2, 3, 4, 5], [1, 2, 3, 4, 5, 6]), ([0, 1, 2, 3, 4, 5, 9], [1, 2, 3, 4, 5, 6]), ([0, 2, 3, 4, 5, 6, 6], [7, 7, 1, 2, 3, 4]),
+                            ([0, 1, 2, 3, 4, 5, 6], [1, 2, -1, 4, 5, 6])):
+        head = b.Head(L, d, o.BF16, L, b.ELMO_VALIDATE, B, 6)
+        head.step(X, torch.tensor(indptr, dtype=torch.int32, device="cuda:0"), torch.tensor(indices, dtype=torch.int32, device="cuda:0"), 0.5, 0, 0)
+        rows = [(r, indices[p]) for r in range(B) if indptr[r] <= indptr[r + 1] <= len(indices) for p in range(indptr[r], indptr[r + 1])]
+        G = np.full((B, L), 0.5)
+        for r, l in rows:
+            if l >= 0:
+                G[r, l] = -0.5
+        assert np.array_equal(head.weights().view(torch.bfloat16).float().cpu().numpy()[:, 0], -0.5 * 0.125 * G.sum(0).astype(np.float32))
+        with pytest.raises(b.ElmoError) as e:
+            head.step(X, torch.zeros(B + 1, dtype=torch.int32, device="cuda:0"), torch.zeros(0, dtype=torch.int32, device="cuda:0"), 0.5, 0, 1)
+        assert e.value.code == -4
+
+
+def test_set_up_does_not_wait_for_uneven_rows(b):  # noqa: F811
+    """Eight rows of 1000 positives 128 rows apart among rows of one: the set-up takes about what the same number of positives
+    in even rows takes (thirty times that where a few threads walk them one after another)."""
+    B, L, d = 1024, 100000, 128
+    us = []
+    for lens in (np.where(np.arange(B) % 128 == 5, 1000, 1), np.full(B, 9)):
+        indptr, indices = uneven(B, lens, L)
+        head = b.Head(L, d, o.E4M3, L, 0, B, len(indices))
+        args = [torch.from_numpy(v).to("cuda:0") for v in (synth.make_x(np.random.default_rng(1), B, d).view(np.int16), indptr, indices)]
+        b.elmo_head_profile(head.h, True)
+        for _ in range(3):
+            head.step(*args, 0.0, 0, 0)
+        b.elmo_head_profile_read(head.h)
+        for _ in range(10):
+            head.step(*args, 0.0, 0, 0)
+        us.append(100 * b.elmo_head_profile_read(head.h)["setup"][0])
+    say(f"   set-up: uneven rows {us[0]:.1f} us, even rows {us[1]:.1f} us")
+    assert us[0] <= 4 * us[1]
+
+
 @pytest.mark.parametrize("fmt", [o.BF16, o.E4M3])
 @pytest.mark.parametrize("n,first,shift", [
     (1, 0, 0), (7, 3, 0), (8, 8, 0), (2049, 16, 0),     # fewer than a group, one group, a remainder
