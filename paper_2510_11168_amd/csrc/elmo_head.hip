@@ -235,17 +235,18 @@ int elmo_quantize(const float* src, int64_t n, int dtype, int mode, uint64_t see
   if (mode != 0 && mode != 1) return fail(-1, "mode must be 0 (nearest) or 1 (stochastic)");
   if (n == 0) return 0;
   hipStream_t st = (hipStream_t)hip_stream;
-  // eight elements per thread where both buffers are aligned to the accesses that move them
-  const bool wide = ((uintptr_t)src & 15) == 0 && ((uintptr_t)dst & (dtype == ELMO_BF16 ? 15 : 7)) == 0;
+  // eight elements per thread where both buffers are aligned to the accesses that move them and the work fills the chip that way
+  const bool wide = ((uintptr_t)src & 15) == 0 && ((uintptr_t)dst & (dtype == ELMO_BF16 ? 15 : 7)) == 0 && (mode == 0 || n >= elmo::kQuantWideSr);
   const int64_t groups = wide ? n / 8 : 0, work = wide ? groups + 8 : n;
-  const int grid = (int)std::min<int64_t>((work + elmo::kThreads - 1) / elmo::kThreads, 256 * 32);
-  if (dtype == ELMO_BF16) {
-    if (mode) elmo::k_quantize<elmo::FMT_BF16, true><<<grid, elmo::kThreads, 0, st>>>(src, n, groups, seed, step, first_elem, dst);
-    else elmo::k_quantize<elmo::FMT_BF16, false><<<grid, elmo::kThreads, 0, st>>>(src, n, groups, seed, step, first_elem, dst);
-  } else {
-    if (mode) elmo::k_quantize<elmo::FMT_E4M3, true><<<grid, elmo::kThreads, 0, st>>>(src, n, groups, seed, step, first_elem, dst);
-    else elmo::k_quantize<elmo::FMT_E4M3, false><<<grid, elmo::kThreads, 0, st>>>(src, n, groups, seed, step, first_elem, dst);
-  }
+  const int grid = (int)std::min<int64_t>((work + elmo::kThreads - 1) / elmo::kThreads, 256 * (wide ? 32 : 16));
+#define ELMO_QUANT(F, SR_)                                                                                                      \
+  do {                                                                                                                          \
+    if (wide) elmo::k_quantize<F, SR_, true><<<grid, elmo::kThreads, 0, st>>>(src, n, groups, seed, step, first_elem, dst);     \
+    else elmo::k_quantize<F, SR_, false><<<grid, elmo::kThreads, 0, st>>>(src, n, 0, seed, step, first_elem, dst);              \
+  } while (0)
+  if (dtype == ELMO_BF16) { if (mode) ELMO_QUANT(elmo::FMT_BF16, true); else ELMO_QUANT(elmo::FMT_BF16, false); }
+  else { if (mode) ELMO_QUANT(elmo::FMT_E4M3, true); else ELMO_QUANT(elmo::FMT_E4M3, false); }
+#undef ELMO_QUANT
   return check_launch("k_quantize");
 }
 

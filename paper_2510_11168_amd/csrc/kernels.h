@@ -1184,38 +1184,44 @@ k_dx_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __re
 // block (two where `first` is not a multiple of 8) that holds their fields.  One element per thread
 // moved a byte per store and drew a whole block per element: 50 M elements to
 // E4M3 took 69.7 us (3.6 TB/s), now 46.0 us (5.5 TB/s).
-// `groups` whole groups of eight are taken this way (0 where a buffer is not aligned to the wide
-// accesses), the rest element by element.
+// WIDE: `groups` whole groups of eight are taken this way and the rest element by element.  Otherwise everything is, one
+// element per thread: buffers that are not aligned to the wide accesses, and short stochastic calls, where the Philox rounds
+// of one element are all there is to wait for and the two blocks and eight roundings of a group only lengthen the chain.
 // ---------------------------------------------------------------------------------------------
-template <int FMT, bool SR>
+// Elements from which a stochastic call takes the wide form; E4M3, one element / eight per thread: 0.1 M 2.4 / 3.1 us,
+// 1.5 M 4.7 / 5.0, 2 M 5.5 / 5.5, 3 M 7.4 / 6.5.
+constexpr int64_t kQuantWideSr = 2 << 20;
+template <int FMT, bool SR, bool WIDE>
 __global__ void __launch_bounds__(kThreads) k_quantize(const float* __restrict__ src, int64_t n, int64_t groups, uint64_t seed, uint64_t step,
                                                        uint64_t first, void* __restrict__ dst) {
   const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x, nt = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = t0; i < groups; i += nt) {
-    const f32x4 a = reinterpret_cast<const f32x4*>(src)[2 * i], b = reinterpret_cast<const f32x4*>(src)[2 * i + 1];
-    uint32_t r[8];
-    if (SR) {
-      const uint64_t e = first + 8 * (uint64_t)i;
-      const int o = (int)(e & 7);
-      const U4 lo = sr_block(e >> 3, seed, step);
-      U4 hi = lo;
-      if (o) hi = sr_block((e >> 3) + 1, seed, step);
+  if constexpr (WIDE) {
+    for (int64_t i = t0; i < groups; i += nt) {
+      const f32x4 a = reinterpret_cast<const f32x4*>(src)[2 * i], b = reinterpret_cast<const f32x4*>(src)[2 * i + 1];
+      uint32_t r[8];
+      if (SR) {
+        const uint64_t e = first + 8 * (uint64_t)i;
+        const int o = (int)(e & 7);
+        const U4 lo = sr_block(e >> 3, seed, step);
+        U4 hi = lo;
+        if (o) hi = sr_block((e >> 3) + 1, seed, step);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) r[k] = sr_field(o + k < 8 ? lo : hi, (o + k) & 7);
-    }
-    uint32_t q[8];
+        for (int k = 0; k < 8; ++k) r[k] = sr_field(o + k < 8 ? lo : hi, (o + k) & 7);
+      }
+      uint32_t q[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float t = k < 4 ? a[k & 3] : b[k & 3];
-      q[k] = SR ? quant_sr<FMT>(t, r[k]) : quant_rne<FMT>(t);
-    }
-    if (FMT == FMT_E4M3) {
-      reinterpret_cast<uint2*>(dst)[i] = make_uint2(q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24), q[4] | (q[5] << 8) | (q[6] << 16) | (q[7] << 24));
-    } else {
-      reinterpret_cast<u32x4*>(dst)[i] = u32x4{q[0] | (q[1] << 16), q[2] | (q[3] << 16), q[4] | (q[5] << 16), q[6] | (q[7] << 16)};
+      for (int k = 0; k < 8; ++k) {
+        const float t = k < 4 ? a[k & 3] : b[k & 3];
+        q[k] = SR ? quant_sr<FMT>(t, r[k]) : quant_rne<FMT>(t);
+      }
+      if (FMT == FMT_E4M3) {
+        reinterpret_cast<uint2*>(dst)[i] = make_uint2(q[0] | (q[1] << 8) | (q[2] << 16) | (q[3] << 24), q[4] | (q[5] << 8) | (q[6] << 16) | (q[7] << 24));
+      } else {
+        reinterpret_cast<u32x4*>(dst)[i] = u32x4{q[0] | (q[1] << 16), q[2] | (q[3] << 16), q[4] | (q[5] << 16), q[6] | (q[7] << 16)};
+      }
     }
   }
-  for (int64_t i = 8 * groups + t0; i < n; i += nt) {
+  for (int64_t i = (WIDE ? 8 * groups : 0) + t0; i < n; i += nt) {
     const float t = src[i];
     uint32_t q;
     if (SR) {

@@ -156,6 +156,7 @@ def test_set_up_does_not_wait_for_uneven_rows(b):  # noqa: F811
     (4096 + 5, 13, 0),                                  # groups that span two blocks of fields
     (4096 + 5, 13, 1), (2048, 0, 3),                    # buffers that are not aligned to the wide accesses
     (256 * 32 * 256 * 8 + 24, 40, 0),                   # more groups than threads
+    ((2 << 20) - 1, 13, 0), ((2 << 20) + 5, 13, 0),     # on both sides of the line between the two forms of stochastic rounding
 ])
 def test_quantize_sizes_and_alignment(b, fmt, n, first, shift):  # noqa: F811
     """Whatever the size, the first element and the alignment, the bits are the oracle's and nothing else is written."""
