@@ -103,7 +103,9 @@ int elmo_head_create(int64_t L, int32_t d, int weight_dtype, int64_t chunk,
  *   for each chunk c of labels:  Z = Xq W_c^T ; G = sigmoid(Z) - Y_c ; dX += G W_c (old W_c);
  *                                W_c <- Q(W_c - lr * G^T X)   (fused, FP32 arithmetic)
  * X      [B, d] BF16 inputs (the encoder's output).  With FP8 weights the logits use X rounded
- *        to E4M3 (nearest even); the weight gradient always uses the BF16 X.
+ *        to E4M3 (nearest even); the weight gradient always uses the BF16 X.  With BF16 weights X
+ *        is 16-byte aligned (the logits product reads it as it is, 16 bytes at a time); with FP8
+ *        weights it may begin at any BF16 element.
  * indptr [B+1], indices [nnz] int32: CSR of the positive label ids of each sample; within a row
  *        ids are distinct, ascending, in [0, L); nnz == indptr[B] <= max_nnz.
  * lr     learning rate; the gradient is summed over the batch (no 1/B).
@@ -121,6 +123,7 @@ int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const int32_t* indp
 
 /* Top-k scoring (the top_k of the P@k definition): for each of the B rows of X the k labels with
  * the largest logit over all L labels, ordered by (logit descending, label id ascending).
+ * X is aligned as for elmo_head_step.
  * idx_out [B, k] int32, score_out [B, k] float (either may be NULL).  1 <= k <= L.
  * Up to k = 128 the labels are swept once; larger k is produced in pages of 128 entries, one more
  * sweep per page (each page admits only what ranks strictly after the last entry of the page

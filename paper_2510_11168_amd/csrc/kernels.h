@@ -307,6 +307,8 @@ __device__ inline void label_index(const IndexArgs& ia, int B, int* h) {
 // 4096 x 768).  Rows B..Bp-1 are zero padding.  Either output may be absent.  cnt: bin counters to clear for
 // the separate index kernels.
 constexpr int kXtPitch = 64 * 2 + 16;                             // bytes per staged column of 64 samples
+// X is the caller's and may begin at any of its elements (one 16-byte load all the same: global loads need no alignment)
+typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
 // LDS of a launch that indexes nb bins and B rows, or that only stages (nb = 0)
 inline size_t setup_smem(int nb, int B) {
   const size_t index = nb ? (size_t)(nb + B) * 4 : 0;
@@ -330,7 +332,7 @@ __global__ void __launch_bounds__(kSetupThreads) k_step_setup(const uint16_t* __
   {
     const int r = tid >> 4, c = (tid & 15) * 8;
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (b0 + r < B) v = *reinterpret_cast<const u32x4*>(X + (size_t)(b0 + r) * d + c0 + c);
+    if (b0 + r < B) v = *reinterpret_cast<const u32x4_at2*>(X + (size_t)(b0 + r) * d + c0 + c);
     if (Xq) {
       uint32_t q[2] = {0u, 0u};
 #pragma unroll

@@ -299,3 +299,25 @@ def test_logits_tile_choice(b, fmt, flags, B, L):  # noqa: F811
     case = Case(b, L, 128, fmt, L, flags, B, w_std=0.05, seed=9)
     case.head.workspace.fill_(0x7F)
     check_step(case, *batch(L, 128, B), 0.05, 1, 2, 6e-2)
+
+
+@pytest.mark.parametrize("B,d", [(40, 256), (300, 384)])
+@pytest.mark.parametrize("shift", [1, 3, 4])
+def test_inputs_of_an_fp8_head_may_begin_at_any_element(b, B, d, shift):  # noqa: F811
+    """X is staged before use: the same step and the same top-k, bit for bit, whatever its first element's address."""
+    L, fmt, flags = 3000, o.E4M3, o.FLAG_SR | o.FLAG_KAHAN
+    X, indptr, indices = batch(L, d, B)
+    Xh = torch.from_numpy(X.view(np.int16))
+    out = []
+    for s in (0, shift):
+        case = Case(b, L, d, fmt, L, flags, B, w_std=0.05, seed=8)
+        buf = torch.zeros(B * d + 8, dtype=torch.int16, device="cuda:0")
+        Xd = buf[s:s + B * d].view(B, d)
+        Xd.copy_(Xh)
+        dX = torch.zeros((B, d), dtype=torch.int16, device="cuda:0")
+        idx, sc = torch.zeros((B, 9), dtype=torch.int32, device="cuda:0"), torch.zeros((B, 9), device="cuda:0")
+        case.head.topk(Xd, 9, idx, sc)
+        case.head.step(Xd, torch.from_numpy(indptr).to("cuda:0"), torch.from_numpy(indices).to("cuda:0"), 0.05, 1, 2, dX, None)
+        out.append((case.W(), case.C(), dX.cpu().numpy(), idx.cpu().numpy(), sc.cpu().numpy()))
+    for p, q in zip(*out):
+        assert np.array_equal(p, q)
