@@ -7,7 +7,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libelmo_head.so")
 SOURCES = [os.path.join(HERE, "csrc", "elmo_head.hip")]
-HEADERS = [os.path.join(HERE, "csrc", h) for h in ("numerics.h", "tiles.h", "kernels.h", "topk_levels.h", "topk.h")] + [
+HEADERS = [os.path.join(HERE, "csrc", h) for h in ("numerics.h", "tiles.h", "kernels.h", "topk_levels.h", "plan.h", "topk.h")] + [
     os.path.join(os.path.dirname(HERE), "include", "elmo_head.h")]
 
 HIPCC_FLAGS = [

@@ -10,13 +10,20 @@
 #include <cstring>
 #include <mutex>
 #include <new>
-#include <utility>
 #include <vector>
 
 #include "kernels.h"
+#include "plan.h"
 #include "topk.h"
 
 namespace {
+
+using elmo::Plan;
+using elmo::Pass;
+using elmo::align256;
+using elmo::round_up;
+using elmo::lay_out;
+using elmo::choose_pass;
 
 thread_local char g_err[512] = "";
 
@@ -33,22 +40,6 @@ int fail(int code, const char* fmt, ...) {
     hipError_t e_ = (call);                                                                  \
     if (e_ != hipSuccess) return fail(-3, "%s failed: %s", #call, hipGetErrorString(e_));    \
   } while (0)
-
-inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
-
-// Workspace plan: byte offsets of every region (Section 4.2/4.4: only one chunk's logit-gradient
-// buffer is ever alive; everything else is O(max_B * d) or O(L / 128) integers).
-struct Plan {
-  int64_t L; int d; int fmt; int64_t chunk; int maxB; int64_t max_nnz; uint32_t flags;
-  int64_t kahan_rows;                   // leading label rows that carry compensation (0 without ELMO_KAHAN)
-  float weight_decay;                   // L2 term of the update, 0 = none
-  uint32_t drop_thresh;                 // classifier dropout: weights dropped with probability drop_thresh / 256, 0 = none
-  int Bp_max, tiles_b_max, ntiles;      // padded batch, batch tiles, 128-label tiles of the whole head
-  int dx_rows;                          // rows of FP32 input-gradient partials (slices x padded batch)
-  size_t off_xq, off_xt, off_g, off_dx, off_loss, off_cnt, off_ptr, off_cur, off_pos, off_flag, off_topk, total;
-  size_t W_bytes, comp_bytes;
-};
 
 int make_plan(int64_t L, int d, int fmt, int64_t chunk, int maxB, int64_t max_nnz, uint32_t flags, int64_t kahan_rows, Plan& p) {
   if (L < 1) return fail(-1, "L must be >= 1 (got %lld)", (long long)L);
@@ -73,29 +64,7 @@ int make_plan(int64_t L, int d, int fmt, int64_t chunk, int maxB, int64_t max_nn
   p.kahan_rows = (flags & ELMO_KAHAN) ? (kahan_rows ? kahan_rows : L) : 0;
   p.weight_decay = 0.0f;
   p.drop_thresh = 0;
-  p.Bp_max = round_up(maxB, 64);
-  p.tiles_b_max = (p.Bp_max + 255) / 256;      // 256-sample tiles of the matrix products
-  p.ntiles = (int)((L + 127) / 128);
-  const int tiles_j = (d + 255) / 256;           // 256-column tiles of the input-gradient product
-  // slices x padded batch of the input-gradient partials: about one workgroup per CU
-  p.dx_rows = std::min(65536 / tiles_j + 256 * p.tiles_b_max + 256, 64 * 256 * p.tiles_b_max);
-  if (d % 256 == 0) p.dx_rows = std::max(p.dx_rows, std::max(1, 256 / (d / 256)) * 128);   // small-batch path: one 128-row slice per label group
-  const int64_t chunk_eff = std::min<int64_t>(chunk, (L + 127) / 128 * 128);
-  size_t o = 0;
-  p.off_xq = o;  o += align256(fmt == ELMO_FP8_E4M3 ? (size_t)p.Bp_max * d : 0);
-  p.off_xt = o;  o += align256((size_t)d * p.Bp_max * 2);
-  p.off_g = o;   o += align256((size_t)chunk_eff * p.Bp_max * 2 + 4096);   // + slack: the last rows are read 512 bytes wide
-  p.off_dx = o;  o += align256((size_t)p.dx_rows * d * 4);
-  p.off_loss = o; o += align256((size_t)p.ntiles * p.tiles_b_max * 4);
-  p.off_cnt = o; o += align256((size_t)(p.ntiles + 1) * 4);
-  p.off_ptr = o; o += align256((size_t)(p.ntiles + 1) * 4);
-  p.off_cur = o; o += align256((size_t)(p.ntiles + 1) * 4);
-  p.off_pos = o; o += align256((size_t)max_nnz * 8);
-  p.off_flag = o; o += 256;
-  p.off_topk = o; o += align256(elmo::topk_scratch_bytes(p.Bp_max, chunk_eff));
-  p.total = o;
-  p.W_bytes = (size_t)L * d * (fmt == ELMO_FP8_E4M3 ? 1 : 2);
-  p.comp_bytes = (size_t)p.kahan_rows * d * 2;
+  lay_out(p);
   return 0;
 }
 
@@ -407,71 +376,11 @@ int raise_lds_limits() {
   return rc;
 }
 
-// Labels per pass of the step and where its logit gradients live.  The chunk bounds the memory that the
-// gradients take, not the work of a launch: a pass may take more labels where the workspace holds
-// their gradients anyway -- the chunk's own region when the batch is smaller than max_B, or the top-k
-// scratch, which is idle during a step.  Short launches cost most: L = 8192, B = 64 in chunks of 2048 spent
-// 54 of 61 us in eight kernels of 6-7 us each that leave most of the chip idle, one pass takes 26 us.
-// A larger batch has whole waves of 256 x 256 tiles to think of (one workgroup per CU): 677016 labels at
-// B = 2733 in passes of 16384 (192 update tiles) take 10.06 ms and in passes of 22656 (267, a second
-// wave of 11) 10.85 ms.  So every number of passes that the room allows is priced with the waves of
-// its launches (microseconds per tile and K slab as measured at d = 768: a tile's epilogue and its slabs,
-// and what three launches cost before and after their tiles) and the cheapest is taken, the chunk
-// itself included: passes of equal size, and passes of whole waves of update tiles, the last of which takes
-// what is left if that fits (L = 131072, B = 256: 171 + 171 + 170 label tiles 442 us, 170 + 170 + 172
-// 420 us).  No pass but the last is smaller than the chunk.  Results do not depend on the split: every label's
-// quantities depend on its own weight row only, and dX is summed in FP32.
-struct Pass {
-  int64_t labels, most;      // labels of a pass; what is left at the end is one pass if it is no more than `most`
-  size_t off_g, slots;
-  int64_t take(int64_t left) const { return left <= most ? left : labels; }
-  int64_t largest(int64_t L) const {
-    const int64_t before = L > most ? (L - most + labels - 1) / labels : 0;
-    return std::max(before ? labels : 0, L - before * labels);
-  }
-};
 // Passes of at most this many 256 x 256 logits tiles take 128 x 128 tiles at batches above 128 too: half of the CUs
 // would have no tile, and four times the tiles, two on a CU at once, are one wave up to here.  32768 BF16 labels,
 // B = 256, d = 768: 30.4 -> 24.8 us; 60000 E4M3 labels, d = 512, B = 160, whole step: 134 -> 120 us; with a second wave
 // of the small tiles the large ones win (43776 labels: 34 us against 43 us).
 constexpr int kLogitsSmallGrid = 128;
-Pass choose_pass(const Plan& p, int Bp, bool small_batch) {
-  // tile losses of 128 x 128 logits tiles at a batch above 128 go to the end of the top-k scratch (0: no room)
-  const size_t slots = align256((size_t)p.ntiles * ((Bp + 127) / 128) * 4);
-  Pass best{p.chunk, p.chunk, p.off_g, p.total - p.off_topk >= slots ? p.total - slots : 0};
-  if (p.chunk >= p.L) return best;
-  const int esz = p.fmt == ELMO_FP8_E4M3 ? 1 : 2;
-  const int64_t tiles_b = (Bp + 255) / 256, tiles_j = (p.d + 255) / 256, slices = std::max<int64_t>(1, 256 / (tiles_b * tiles_j));
-  auto launches = [&](int64_t n) {
-    const int64_t lt = (n + 255) / 256;
-    return (double)((lt * tiles_j + 255) / 256) * (10.0 + 1.4 * (Bp / 64)) + (double)((lt * tiles_b + 255) / 256) * (6.0 + 1.4 * (p.d * esz / 128)) +
-           1.4 * (double)((lt * 4 + slices - 1) / slices) + 15.0;
-  };
-  auto price = [&](int64_t n, int64_t most) {
-    const int64_t before = (p.L - most + n - 1) / n;           // (most < L, or one pass)
-    return p.L <= most ? launches(p.L) : (double)before * launches(n) + launches(p.L - before * n);
-  };
-  double cheapest = small_batch ? 0.0 : price(p.chunk, p.chunk);
-  for (auto [off, end] : {std::pair<size_t, size_t>{p.off_g, p.off_dx}, {p.off_topk, best.slots}}) {
-    if (end < off) continue;
-    if (end - off <= 4096) continue;
-    const int64_t room = (int64_t)((end - off - 4096) / ((size_t)Bp * 2)) / 128 * 128;   // the last rows are read 512 bytes wide
-    if (room <= p.chunk) continue;
-    const int64_t least = (p.L + room - 1) / room;
-    auto consider = [&](int64_t labels) {
-      if (labels <= p.chunk || labels > room) return;
-      if (const double t = price(labels, room); t < cheapest) { cheapest = t; best = {labels, room, off, best.slots}; }
-    };
-    if (small_batch) {                         // no tiles to fill: the fewer launches the better
-      const int64_t labels = ((p.L + least - 1) / least + 127) / 128 * 128;
-      if (labels > best.labels) best = {labels, labels, off, best.slots};
-      continue;
-    }
-    for (int64_t passes = least; passes < least + 64; ++passes) consider(((p.L + passes - 1) / passes + 127) / 128 * 128);
-    for (int64_t waves = 1; waves <= 64; ++waves) consider(256 * waves / tiles_j * 256);
-  }
-  return best;
-}
 
 }  // namespace
 
@@ -507,7 +416,7 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   // With dropout that kernel keeps a masked copy of the W tile in LDS, which does not fit next to
   // BF16 weights with compensation: that one mode takes the separate kernels.
   const bool small_batch = Bp <= 128 && d % 256 == 0 && !(p.drop_thresh && !fp8 && (p.flags & ELMO_KAHAN));
-  const Pass ps = choose_pass(p, Bp, small_batch);
+  const Pass ps = choose_pass(p, Bp, small_batch, dX_out != nullptr);
   uint16_t* Gt = (uint16_t*)(h->ws + ps.off_g);
   const int col_blocks = d / 256, label_groups = small_batch ? std::max(1, 256 / col_blocks) : 0;   // widths above 65536: one group
   // label slices of the input-gradient product: at most one 512-thread workgroup per CU, so the

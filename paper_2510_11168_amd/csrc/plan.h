@@ -1,0 +1,120 @@
+// Host side of a head: its workspace and the passes of a step.  Arithmetic only, no HIP.
+#pragma once
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+#include <utility>
+
+#include "../../include/elmo_head.h"
+#include "topk_levels.h"
+
+namespace elmo {
+
+inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
+
+// Workspace plan: byte offsets of every region (Section 4.2/4.4: only one chunk's logit-gradient
+// buffer is ever alive; everything else is O(max_B * d) or O(L / 128) integers).
+struct Plan {
+  int64_t L; int d; int fmt; int64_t chunk; int maxB; int64_t max_nnz; uint32_t flags;
+  int64_t kahan_rows;                   // leading label rows that carry compensation (0 without ELMO_KAHAN)
+  float weight_decay;                   // L2 term of the update, 0 = none
+  uint32_t drop_thresh;                 // classifier dropout: weights dropped with probability drop_thresh / 256, 0 = none
+  int Bp_max, tiles_b_max, ntiles;      // padded batch, batch tiles, 128-label tiles of the whole head
+  int dx_rows;                          // rows of FP32 input-gradient partials (slices x padded batch)
+  size_t off_xq, off_xt, off_g, off_dx, off_loss, off_cnt, off_ptr, off_cur, off_pos, off_flag, off_topk, total;
+  size_t W_bytes, comp_bytes;
+};
+
+// Sizes and offsets from the first two lines of a plan.
+inline void lay_out(Plan& p) {
+  p.Bp_max = round_up(p.maxB, 64);
+  p.tiles_b_max = (p.Bp_max + 255) / 256;      // 256-sample tiles of the matrix products
+  p.ntiles = (int)((p.L + 127) / 128);
+  const int tiles_j = (p.d + 255) / 256;           // 256-column tiles of the input-gradient product
+  // slices x padded batch of the input-gradient partials: about one workgroup per CU
+  p.dx_rows = std::min(65536 / tiles_j + 256 * p.tiles_b_max + 256, 64 * 256 * p.tiles_b_max);
+  if (p.d % 256 == 0) p.dx_rows = std::max(p.dx_rows, std::max(1, 256 / (p.d / 256)) * 128);   // small-batch path: one 128-row slice per label group
+  const int64_t chunk_eff = std::min<int64_t>(p.chunk, (p.L + 127) / 128 * 128);
+  size_t o = 0;
+  p.off_xq = o;  o += align256(p.fmt == ELMO_FP8_E4M3 ? (size_t)p.Bp_max * p.d : 0);
+  p.off_xt = o;  o += align256((size_t)p.d * p.Bp_max * 2);
+  p.off_g = o;   o += align256((size_t)chunk_eff * p.Bp_max * 2 + 4096);   // + slack: the last rows are read 512 bytes wide
+  p.off_dx = o;  o += align256((size_t)p.dx_rows * p.d * 4);
+  p.off_loss = o; o += align256((size_t)p.ntiles * p.tiles_b_max * 4);
+  p.off_cnt = o; o += align256((size_t)(p.ntiles + 1) * 4);
+  p.off_ptr = o; o += align256((size_t)(p.ntiles + 1) * 4);
+  p.off_cur = o; o += align256((size_t)(p.ntiles + 1) * 4);
+  p.off_pos = o; o += align256((size_t)p.max_nnz * 8);
+  p.off_flag = o; o += 256;
+  p.off_topk = o; o += align256(topk_scratch_bytes(p.Bp_max, chunk_eff));
+  p.total = o;
+  p.W_bytes = (size_t)p.L * p.d * (p.fmt == ELMO_FP8_E4M3 ? 1 : 2);
+  p.comp_bytes = (size_t)p.kahan_rows * p.d * 2;
+}
+
+// Labels per pass of the step and where its logit gradients live.  The chunk bounds the memory that the
+// gradients take, not the work of a launch: a pass may take more labels where the workspace holds
+// their gradients anyway -- the chunk's own region when the batch is smaller than max_B, or the top-k
+// scratch, which is idle during a step.  Short launches cost most: L = 8192, B = 64 in chunks of 2048 spent
+// 54 of 61 us in eight kernels of 6-7 us each that leave most of the chip idle, one pass takes 26 us.
+// A larger batch has whole waves of 256 x 256 tiles to think of (one workgroup per CU): 677016 labels at
+// B = 2733 in passes of 16384 (192 update tiles) take 10.06 ms and in passes of 22656 (267, a second
+// wave of 11) 10.85 ms.  So every number of passes that the room allows is priced with the waves of
+// its launches (microseconds per tile and K slab as measured at d = 768: a tile's epilogue and its slabs,
+// and what the launches cost before and after their tiles, 15 us, 13 without the input gradient where dX is not asked
+// for: 60000 E4M3 labels at B = 3000 506 us in the passes that are cheapest with it, 480 without) and the cheapest is
+// taken, the chunk itself included.  The prices only rank the splits of one head, and coarsely: they give
+// 258 us for the step of 131072 BF16 labels with compensation at B = 256 that takes 424, whose update is bound by
+// memory.  Offered are passes of equal size, and passes of whole waves of update tiles, the last of which takes what is
+// left if that fits (L = 131072, B = 256: 171 + 171 + 170 label tiles 442 us, 170 + 170 + 172 420 us).  No pass but the
+// last is smaller than the chunk.  Results do not depend on the split: every label's quantities depend on its own
+// weight row only, and dX is summed in FP32.
+struct Pass {
+  int64_t labels, most;      // labels of a pass; what is left at the end is one pass if it is no more than `most`
+  size_t off_g, slots;
+  int64_t take(int64_t left) const { return left <= most ? left : labels; }
+  int64_t largest(int64_t L) const {
+    const int64_t before = L > most ? (L - most + labels - 1) / labels : 0;
+    return std::max(before ? labels : 0, L - before * labels);
+  }
+};
+inline Pass choose_pass(const Plan& p, int Bp, bool small_batch, bool want_dx) {
+  // tile losses of 128 x 128 logits tiles at a batch above 128 go to the end of the top-k scratch (0: no room)
+  const size_t slots = align256((size_t)p.ntiles * ((Bp + 127) / 128) * 4);
+  Pass best{p.chunk, p.chunk, p.off_g, p.total - p.off_topk >= slots ? p.total - slots : 0};
+  if (p.chunk >= p.L) return best;
+  const int esz = p.fmt == ELMO_FP8_E4M3 ? 1 : 2;
+  const int64_t tiles_b = (Bp + 255) / 256, tiles_j = (p.d + 255) / 256, slices = std::max<int64_t>(1, 256 / (tiles_b * tiles_j));
+  auto launches = [&](int64_t n) {
+    const int64_t lt = (n + 255) / 256;
+    return (double)((lt * tiles_j + 255) / 256) * (10.0 + 1.4 * (Bp / 64)) + (double)((lt * tiles_b + 255) / 256) * (6.0 + 1.4 * (p.d * esz / 128)) +
+           (want_dx ? 1.4 * (double)((lt * 4 + slices - 1) / slices) + 15.0 : 13.0);
+  };
+  auto price = [&](int64_t n, int64_t most) {
+    const int64_t before = (p.L - most + n - 1) / n;           // (most < L, or one pass)
+    return p.L <= most ? launches(p.L) : (double)before * launches(n) + launches(p.L - before * n);
+  };
+  double cheapest = small_batch ? 0.0 : price(p.chunk, p.chunk);
+  for (auto [off, end] : {std::pair<size_t, size_t>{p.off_g, p.off_dx}, {p.off_topk, best.slots}}) {
+    if (end < off) continue;
+    if (end - off <= 4096) continue;
+    const int64_t room = (int64_t)((end - off - 4096) / ((size_t)Bp * 2)) / 128 * 128;   // the last rows are read 512 bytes wide
+    if (room <= p.chunk) continue;
+    const int64_t least = (p.L + room - 1) / room;
+    auto consider = [&](int64_t labels) {
+      if (labels <= p.chunk || labels > room) return;
+      if (const double t = price(labels, room); t < cheapest) { cheapest = t; best = {labels, room, off, best.slots}; }
+    };
+    if (small_batch) {                         // no tiles to fill: the fewer launches the better
+      const int64_t labels = ((p.L + least - 1) / least + 127) / 128 * 128;
+      if (labels > best.labels) best = {labels, labels, off, best.slots};
+      continue;
+    }
+    for (int64_t passes = least; passes < least + 64; ++passes) consider(((p.L + passes - 1) / passes + 127) / 128 * 128);
+    for (int64_t waves = 1; waves <= 64; ++waves) consider(256 * waves / tiles_j * 256);
+  }
+  return best;
+}
+
+}  // namespace elmo

@@ -35,38 +35,18 @@
 
 namespace elmo {
 
-constexpr int kTopkMaxK = 128;                     // entries selected per sweep (one page)
-constexpr int kTopkCntStride = 32;                 // ints between two rows' candidate counters: one 128-byte line each, so that the
-                                                   // atomic additions of different rows do not queue up on the same few lines
 // Launches of at most this many workgroups take the kernel with 128-row tiles at batches above 128 too: twice as
 // many workgroups, each with half the slab, and still a single wave (131072 BF16 labels, B = 256: 164 -> 150 us,
 // its first two levels 25 and 41 -> 16 and 25 us); with more than a wave the 256-row tiles win (1 M labels: 644 and 601 us).
 constexpr int kTopkSmallGrid = 256;
-constexpr int kTopkRows = 64;                       // query rows per workgroup
 constexpr int kTopkZP = 132;                        // floats per staged row
 constexpr int kTopkLP = 129;                        // list pitch (odd: one row per thread, no bank clash)
 constexpr int kTopkStage = 49152;                   // operand double buffer (2 x (8 + 16) KiB); aliases the stage
 constexpr int kTopkSmem = kTopkStage + 2 * kTopkRows * kTopkLP * 4 + kTopkRows * 16;
 static_assert(kTopkRows * kTopkZP * 4 <= kTopkStage, "staged tile must fit the operand buffers");
 
-// Label segments per 64-row group: enough workgroups to fill the chip, at most 64 lists to merge.
-inline int topk_segments(int tiles_b) { return std::max(1, std::min(64, 512 / tiles_b)); }
-
-// Main-path scratch: thresholds, counters, overflow flags and candidate lists per (padded) row.
-inline size_t topk_main_rows(int Bp_max) { return (size_t)(Bp_max + 255) / 256 * 256; }
-static_assert(256 * kTopkCand >= 128 * 2 * kTopkCand, "the longer lists of at most 128 rows fit where those of 256 do");
-inline size_t topk_main_bytes(int Bp_max) { return topk_main_rows(Bp_max) * (24 + (size_t)kTopkCntStride * 4 + (size_t)kTopkCand * 8) + 1024; }
-
 // (score, id) strictly after the cursor (cs, ci) in the order score descending, id ascending.
 __device__ inline bool topk_after(float z, int l, float cs, int ci) { return z < cs || (z == cs && l > ci); }
-
-// Bytes of per-segment partial lists for any batch of at most Bp_max rows, plus the main path's.
-inline size_t topk_scratch_bytes(int Bp_max, int64_t /*chunk*/) {
-  const int tb_max = (Bp_max + kTopkRows - 1) / kTopkRows;
-  size_t lists = 0;
-  for (int tb = 1; tb <= tb_max; ++tb) lists = std::max(lists, (size_t)tb * kTopkRows * topk_segments(tb));
-  return lists * kTopkMaxK * 8 + topk_main_bytes(Bp_max);
-}
 
 template <bool FP8>
 __global__ void __launch_bounds__(kThreads, 1)

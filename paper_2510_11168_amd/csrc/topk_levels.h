@@ -1,11 +1,16 @@
-// Levels of a top-k sweep: which labels each level takes.  Host arithmetic only, no HIP.
+// Levels of a top-k sweep, which labels each level takes, and the scratch of a call.  Host arithmetic only, no HIP.
 #pragma once
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 
 namespace elmo {
 
+constexpr int kTopkMaxK = 128;                     // entries selected per sweep (one page)
+constexpr int kTopkCntStride = 32;                 // ints between two rows' candidate counters: one 128-byte line each, so that the
+                                                   // atomic additions of different rows do not queue up on the same few lines
+constexpr int kTopkRows = 64;                       // query rows per workgroup
 constexpr int kTopkCand = 4096;                    // candidate list length per row of a batch padded to whole 256-row tiles
 constexpr int kTopkLevel0 = 4096;                  // labels of the first level
 static_assert(kTopkLevel0 <= kTopkCand, "the first level writes one slot per label");
@@ -45,6 +50,22 @@ inline TopkLevels topk_levels(int64_t L, int Bp, int k) {
   t.n = (int)std::ceil(std::log(ratio) / std::log(most) - 1e-9);
   if (t.n > 0) t.growth = std::pow(ratio, 1.0 / t.n);
   return t;
+}
+
+// Label segments per 64-row group: enough workgroups to fill the chip, at most 64 lists to merge.
+inline int topk_segments(int tiles_b) { return std::max(1, std::min(64, 512 / tiles_b)); }
+
+// Main-path scratch: thresholds, counters, overflow flags and candidate lists per (padded) row.
+inline size_t topk_main_rows(int Bp_max) { return (size_t)(Bp_max + 255) / 256 * 256; }
+static_assert(256 * kTopkCand >= 128 * 2 * kTopkCand, "the longer lists of at most 128 rows fit where those of 256 do");
+inline size_t topk_main_bytes(int Bp_max) { return topk_main_rows(Bp_max) * (24 + (size_t)kTopkCntStride * 4 + (size_t)kTopkCand * 8) + 1024; }
+
+// Bytes of per-segment partial lists for any batch of at most Bp_max rows, plus the main path's.
+inline size_t topk_scratch_bytes(int Bp_max, int64_t /*chunk*/) {
+  const int tb_max = (Bp_max + kTopkRows - 1) / kTopkRows;
+  size_t lists = 0;
+  for (int tb = 1; tb <= tb_max; ++tb) lists = std::max(lists, (size_t)tb * kTopkRows * topk_segments(tb));
+  return lists * kTopkMaxK * 8 + topk_main_bytes(Bp_max);
 }
 
 }  // namespace elmo
