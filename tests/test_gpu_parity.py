@@ -191,12 +191,12 @@ class Case:
     """A head on the device initialised from host bits, plus the host copies the oracle needs."""
 
     def __init__(self, b, L, d, fmt, chunk, flags, B, max_nnz=None, seed=0, w_std=0.02, comp_std=0.0, kahan_rows=0,
-                 weight_decay=0.0, dropout_p=0.0):
+                 weight_decay=0.0, dropout_p=0.0, like=None):
         rng = np.random.default_rng([seed, L, d])
         self.b, self.L, self.d, self.fmt, self.flags = b, L, d, fmt, flags
-        self.W0 = o.quantize(synth.make_w0_f32(rng, L, d, w_std), fmt)
-        self.C0 = None
-        if flags & o.FLAG_KAHAN:
+        self.W0 = o.quantize(synth.make_w0_f32(rng, L, d, w_std), fmt) if like is None else like.W0
+        self.C0 = None if like is None else like.C0
+        if flags & o.FLAG_KAHAN and like is None:
             self.C0 = o.round_bf16((rng.standard_normal((kahan_rows or L, d)) * comp_std).astype(np.float32))
         self.head = b.Head(L, d, fmt, chunk, flags, B, max_nnz or 64 * B, kahan_rows=kahan_rows, weight_decay=weight_decay,
                            dropout_p=dropout_p)
@@ -218,8 +218,11 @@ class Case:
         Xd, ip, ix = dev(X), dev(indptr), dev(indices)
         dX = torch.zeros(X.shape, dtype=torch.int16, device=DEV) if want_dx else None
         loss = torch.zeros(1, dtype=torch.float32, device=DEV) if want_loss else None
+        self.b.elmo_head_profile(self.head.h, True)
         self.head.step(Xd, ip, ix, lr, seed, step, dX, loss)
         torch.cuda.synchronize()
+        self.passes = self.b.elmo_head_profile_read(self.head.h)["logits"][1]     # one logits launch per pass
+        self.b.elmo_head_profile(self.head.h, False)
         return (None if dX is None else o.decode_bf16(host_u16(dX)),
                 None if loss is None else float(loss.item()))
 
@@ -270,8 +273,8 @@ def test_tiny_config_three_steps(b):
     (o.BF16, 0, 2e-2),
 ])
 def test_ragged_shapes_all_modes(b, fmt, flags, tol):
-    """Labels and batch that are no multiple of any tile, several chunks with a short last one,
-    non-zero compensation on entry."""
+    """Labels and batch that are no multiple of any tile, non-zero compensation on entry.  (A head this small goes in one pass
+    whatever its chunk.)"""
     L, d, B, chunk = 5 * 128 + 77, 256, 70, 256
     case = Case(b, L, d, fmt, chunk, flags, B, w_std=0.05, comp_std=2e-4, seed=3)
     rng = np.random.default_rng(5)
@@ -291,7 +294,7 @@ def test_large_batch_kernels_on_ragged_tiles(b, fmt, flags, d, tol):
     """Batches above 128 rows take the three separate 256 x 256-tile kernels.  Element-by-element
     parity where nothing is a multiple of a tile: 300 samples (two batch tiles, the second one
     mostly padding), widths with a half column tile (384, 128), three label tiles with a ragged
-    tail, two chunks of different length, non-zero compensation on entry."""
+    tail, non-zero compensation on entry."""
     L, B, chunk = 3 * 256 + 77, 300, 512
     case = Case(b, L, d, fmt, chunk, flags, B, w_std=0.05, comp_std=2e-4, seed=6)
     rng = np.random.default_rng(11)
@@ -317,8 +320,7 @@ def test_wider_embeddings(b, d, B):
 
 @pytest.mark.parametrize("B", [70, 300])
 def test_kahan_for_head_labels_only(b, B):
-    """Compensation on the first 256 labels only, boundary inside the second chunk (384 labels per
-    chunk), for the single-pass small-batch kernel (B = 70) and the separate kernels (B = 300):
+    """Compensation on the first 256 labels only, boundary inside a pass, for the single-pass small-batch kernel (B = 70) and the separate kernels (B = 300):
     head rows against the oracle's Kahan update with their compensation, the other rows against
     its plain update."""
     L, d, chunk, k = 5 * 128 + 77, 256, 384, 256
@@ -391,7 +393,7 @@ def test_weight_decay(b, fmt, flags, B):
 def test_classifier_dropout(b, fmt, flags, B, d, T):
     """Dropout on the weights inside the three products: the library regenerates the oracle's mask
     from (seed, step, element) in the logits, the input-gradient and the update kernel, for both
-    logits tile sizes, a width with a half column tile, ragged label tails and several chunks.
+    logits tile sizes, a width with a half column tile and ragged label tails.
     A mask that differed in one kernel, or a missing scale, would miss every bar here: the logits
     feed the loss and G, the input gradient sums masked weights, and the weight gradient of a
     dropped element is zero, so without rounding noise and compensation it must not move at all."""
@@ -418,7 +420,7 @@ def test_classifier_dropout(b, fmt, flags, B, d, T):
         keep = o.dropout_keep(77, 4, np.arange(L * d, dtype=np.int64).reshape(L, d), T)
         assert np.array_equal(Wn[~keep], case.W0[~keep])
         assert np.any(Wn[keep] != case.W0[keep])
-    # the mask is a function of the element, not of the chunking
+    # the same again in a head of its own (its passes do not change with the chunk; masks of later passes: test_gpu_shapes.py)
     other = Case(b, L, d, fmt, 256, flags, B, w_std=0.05, comp_std=2e-4, seed=23, dropout_p=T / 256)
     other.step(X, indptr, indices, lr, 77, 4)
     assert np.array_equal(other.W(), Wn)
@@ -509,24 +511,26 @@ def test_which_logit_gradient_the_kernels_compute(b, fmt, flags, B):
 def test_weights_do_not_depend_on_chunk_and_steps_repeat(b):
     """Chunk invariance: identical updated weights for any chunk size at fixed (seed, step);
     same call twice from the same state gives the same bits; another step index does not."""
-    L, d, B = 1000, 256, 96
+    L, d, B = 140000, 256, 96
     rng = np.random.default_rng(2)
     X = synth.make_x(rng, B, d)
     indptr, indices = synth.ZipfLabels(L, 1.0).draw_csr(rng, B, "fixed5")
     flags = o.FLAG_SR | o.FLAG_KAHAN
-    outs = []
-    for chunk in (128, 384, 1024, 100, 1, 777):         # any positive chunk: a pass takes the next multiple of 128 labels
-        case = Case(b, L, d, o.E4M3, chunk, flags, B, w_std=0.05, seed=1)
-        say(f"[chunk-invariance] chunk={chunk}")
+    outs, case = [], None
+    # any positive chunk; passes: 3 x 46720, 50048 + 50048 + 39904, 70016 + 69984, one
+    for chunk, passes in ((128, 3), (777, 3), (1, 3), (50000, 3), (70000, 2), (140000, 1)):
+        case = Case(b, L, d, o.E4M3, chunk, flags, B, w_std=0.05, seed=1, like=case)
         dX, _ = case.step(X, indptr, indices, 0.05, 9, 4)
+        say(f"[chunk-invariance] chunk={chunk} passes={case.passes}")
+        assert case.passes == passes
         outs.append((case.W(), case.C(), dX))
     for W, C, dX in outs[1:]:
         assert np.array_equal(W, outs[0][0]) and np.array_equal(C, outs[0][1])
         assert rel_fro(dX, outs[0][2]) < 1e-2
-    case = Case(b, L, d, o.E4M3, 384, flags, B, w_std=0.05, seed=1)
+    case.load(case.W0, case.C0)
     case.step(X, indptr, indices, 0.05, 9, 4)
     assert np.array_equal(case.W(), outs[0][0])
-    case = Case(b, L, d, o.E4M3, 384, flags, B, w_std=0.05, seed=1)
+    case.load(case.W0, case.C0)
     case.step(X, indptr, indices, 0.05, 9, 5)
     assert not np.array_equal(case.W(), outs[0][0])
 
@@ -536,7 +540,7 @@ def test_step_replays_bit_identically_from_a_hip_graph(b):
     no host synchronisation without ELMO_VALIDATE), so it can be captured: three replays of a
     captured step, with eager work and synchronisations between them, leave the same weights,
     compensation, input gradient and loss as three eager calls with the same arguments."""
-    L, d, B, chunk = 3 * 256 + 77, 256, 300, 512
+    L, d, B, chunk = 60000 + 77, 256, 300, 512           # two passes
     fmt, flags = o.E4M3, o.FLAG_SR | o.FLAG_KAHAN
     rng = np.random.default_rng(51)
     X = synth.make_x(rng, B, d)
@@ -547,8 +551,8 @@ def test_step_replays_bit_identically_from_a_hip_graph(b):
         case = Case(b, L, d, fmt, chunk, flags, B, w_std=0.05, comp_std=2e-4, seed=33)
         dX = torch.zeros(X.shape, dtype=torch.int16, device=DEV)
         loss = torch.zeros(1, dtype=torch.float32, device=DEV)
-        case.head.step(Xd, ip, ix, 0.1, 9, 0, dX, loss)            # warm-up: one-time kernel attributes
-        torch.cuda.synchronize()
+        case.step(X, indptr, indices, 0.1, 9, 0)                   # warm-up: one-time kernel attributes
+        assert case.passes == 2
         case.load(case.W0, case.C0)
         side = torch.cuda.Stream()
         graph = None

@@ -6,7 +6,7 @@ import torch
 
 from oracle import elmo_oracle as o
 from paper_2510_11168_amd import synth
-from test_gpu_parity import Case, assert_dx_close, b, check_step, say  # noqa: F401  (b is the module's fixture)
+from test_gpu_parity import Case, assert_dx_close, assert_far_misses_are_tiny, b, check_step, ordered, say  # noqa: F401  (b is the module's fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -18,14 +18,18 @@ def batch(L, d, B, seed=5, rule="lognormal5"):
     return X, indptr, indices
 
 
-@pytest.mark.parametrize("B,d,L,chunk,kahan_rows", [
-    (40, 256, 9600 + 8192, 9600, 0),        # small batch: 150 label groups in the first chunk, 256 in the second
-    (40, 512, 3 * 128 + 5, 128, 0),         # fewer label tiles than groups; the last chunk has one ragged tile
-    (100, 256, 1024, 1024, 128),            # one chunk in two parts, the first with fewer groups than the second
-    (300, 256, 6400 + 4096, 6400, 0),       # 50 of 64 label slices used in the first chunk, all in the second
-    (130, 384, 70, 1000, 0),                # fewer label slabs than slices, half a column tile
-])
-def test_input_gradient_planes(b, B, d, L, chunk, kahan_rows):  # noqa: F811
+# (B, d, L, chunk, kahan_rows, passes of the step, planes of its first pass, of its last): test_step_passes.py holds the library to the last three
+PLANES = [
+    (40, 256, 246016, 9600, 0, 3, 234, 256),        # small batch: a later pass has more label groups than the first
+    (40, 512, 128 * 3 + 5, 128, 0, 1, 13, 13),      # fewer label tiles than groups; a ragged last tile
+    (100, 256, 1024, 1024, 128, 1, 28, 28),         # one pass in two parts, the first with fewer groups than the second
+    (300, 128, 65624, 6400, 0, 2, 58, 64),          # more label slices in the second pass
+    (130, 384, 70, 1000, 0, 1, 2, 2),               # fewer label slabs than slices, half a column tile
+]
+
+
+@pytest.mark.parametrize("B,d,L,chunk,kahan_rows,passes", [row[:6] for row in PLANES])
+def test_input_gradient_planes(b, B, d, L, chunk, kahan_rows, passes):  # noqa: F811
     """The first launch of a step writes every plane of partial sums that the end adds up, whether it has labels
     for it or not; later launches add to them."""
     fmt, flags = o.E4M3, o.FLAG_SR | (o.FLAG_KAHAN if kahan_rows else 0)
@@ -33,21 +37,22 @@ def test_input_gradient_planes(b, B, d, L, chunk, kahan_rows):  # noqa: F811
     case.head.workspace.fill_(0x7F)         # whatever the planes held before must not matter
     X, indptr, indices = batch(L, d, B)
     dX, _ = case.step(X, indptr, indices, 0.05, 1, 2)
-    C = np.zeros((L, d), np.uint16) if kahan_rows else None
-    ref = o.head_step(case.W0, C, X, indptr, indices, 0.05, 1, 2, fmt, flags, **({"kahan_rows": kahan_rows} if kahan_rows else {}))
-    assert_dx_close(dX, ref["dX_partial"], 6e-2)
+    assert case.passes == passes
+    ref, _ = o.input_gradient_rows(case.W0, X, indptr, indices, fmt, np.arange(B))
+    assert_dx_close(dX, ref, 6e-2)
 
 
 @pytest.mark.parametrize("B,per_row,L", [
     (1, 1, 128),            # one positive, one bin
     (129, 9, 128 * 3 + 1),  # one more row than a pass of the index covers, one more positive than the lanes of a row
     (1030, 5, 300000),      # rows beyond one batch of passes, more bins than threads
-    (256, 256, 20000),      # 65536 positives: the largest batch one workgroup indexes
-    (257, 256, 20000),      # beyond it: the separate index kernels
+    (128, 256, 20000),      # 32768 positives by one workgroup
+    (256, 256, 20000),      # 65536: the separate index kernels
 ])
 def test_label_index_sizes(b, B, per_row, L):  # noqa: F811
-    """The positives of a batch reach their labels whatever the number of rows, positives and bins: the loss and dX
-    are the oracle's on the labels that have positives (and the first rows of the head)."""
+    """The positives of a batch reach their labels whatever the number of rows, positives and bins: the weights are the
+    oracle's on labels drawn from the whole head, most of them with positives, and the loss where that is all labels
+    (every positive of larger heads: test_every_positive_reaches_its_label)."""
     d, fmt, flags = 128, o.E4M3, 0
     case = Case(b, L, d, fmt, L, flags, B, max_nnz=B * per_row, w_std=0.05, seed=4)
     rng = np.random.default_rng(6)
@@ -56,7 +61,9 @@ def test_label_index_sizes(b, B, per_row, L):  # noqa: F811
     indptr = (np.arange(B + 1) * per_row).astype(np.int32)
     case.head.workspace.fill_(0x7F)
     _, loss = case.step(X, indptr, indices, 0.05, 0, 0, want_dx=False)
-    rows = np.unique(np.concatenate([indices, np.arange(min(L, 256))]))[:4096]
+    hot = np.unique(indices)
+    rows = np.unique(np.concatenate([rng.choice(hot, min(len(hot), 3500), replace=False), rng.integers(0, L, 300), np.arange(min(L, 128)), np.arange(max(0, L - 128), L)]))
+    rows = np.arange(L) if L <= 4096 else rows
     ref = o.head_step(case.W0[rows], None, X, indptr, indices, 0.05, 0, 0, fmt, flags, label_ids=rows)
     Wn = case.W()[rows]
     assert np.mean(Wn == ref["W_new"]) >= 0.999
@@ -175,34 +182,64 @@ def test_quantize_sizes_and_alignment(b, fmt, n, first, shift):  # noqa: F811
         assert (got[:shift] == 85).all() and (got[shift + n:] == 85).all()
 
 
-@pytest.mark.parametrize("B,d,L,chunk,kahan_rows", [
-    (40, 256, 250000, 9600, 0),             # three passes of the small-batch kernel
-    (40, 256, 250000, 9600, 128 * 800),     # compensation ends inside a pass
-    (300, 384, 150000, 20000, 0),           # passes in the top-k scratch
-    (130, 640, 100003, 30000, 128 * 300),   # the last pass ragged
-    (5, 256, 5000, 128, 0),                 # everything in one pass
-])
-def test_passes_larger_than_the_chunk(b, B, d, L, chunk, kahan_rows):  # noqa: F811
+SR, KA = o.FLAG_SR, o.FLAG_KAHAN
+# (fmt, flags, B, d, L, chunk, kahan_rows, dropout threshold, weight decay, passes)
+SEVERAL = [
+    (o.E4M3, SR, 40, 256, 250000, 9600, 0, 0, 0.0, 3),              # the small-batch kernel
+    (o.E4M3, SR | KA, 40, 256, 250000, 9600, 128 * 800, 0, 0.0, 3), # compensation ends inside a pass
+    (o.E4M3, SR | KA, 70, 256, 100000, 512, 0, 77, 0.01, 2),        # masked tile copy
+    (o.BF16, SR, 100, 256, 100000, 512, 0, 128, 0.0, 2),
+    (o.BF16, KA, 70, 256, 100000, 512, 128 * 500, 0, 0.01, 2),
+    (o.BF16, KA, 70, 256, 100000, 512, 0, 26, 0.0, 2),              # no room for the masked copy: the separate kernels at a small batch
+    (o.E4M3, SR, 300, 384, 150000, 20000, 0, 0, 0.0, 4),            # the separate kernels, passes in the top-k scratch
+    (o.E4M3, SR | KA, 130, 640, 100003, 30000, 128 * 300, 0, 0.0, 2),   # the last pass ragged
+    (o.E4M3, SR | KA, 300, 128, 100000, 512, 128 * 500, 64, 0.01, 2),
+    (o.BF16, SR, 300, 128, 60000, 512, 0, 128, 0.0, 2),
+    (o.BF16, KA, 600, 256, 60000, 512, 0, 26, 0.01, 2),             # the last pass larger than the first
+    (o.E4M3, SR, 5, 256, 5000, 128, 0, 0, 0.0, 1),                  # everything in one pass
+]
+
+
+@pytest.mark.parametrize("fmt,flags,B,d,L,chunk,kahan_rows,T,wd,passes", SEVERAL)
+def test_passes_larger_than_the_chunk(b, fmt, flags, B, d, L, chunk, kahan_rows, T, wd, passes):  # noqa: F811
     """A head whose passes are made of several chunks computes what one with a single chunk does: the same weights and
     compensation bit by bit, dX and loss to the order of FP32 sums (BF16 rounding of dX: one spacing, 2^-8 in norm), and
-    a top-k between two steps, whose scratch holds a pass's gradients, disturbs neither."""
-    fmt, flags = o.E4M3, o.FLAG_SR | (o.FLAG_KAHAN if kahan_rows else 0)
+    a top-k between two steps, whose scratch holds a pass's gradients, disturbs neither.  Labels of every pass against
+    the oracle too, so that an offset lost in both -- the masks, the rounding fields -- shows."""
     X, indptr, indices = batch(L, d, B)
-    got = []
+    got, like = [], None
     for ch in (chunk, L):
-        case = Case(b, L, d, fmt, ch, flags, B, w_std=0.05, seed=8, kahan_rows=kahan_rows)
+        case = Case(b, L, d, fmt, ch, flags, B, w_std=0.05, seed=8, kahan_rows=kahan_rows, dropout_p=T / 256, weight_decay=wd, like=like)
+        like = case
         case.head.workspace.fill_(0x7F)
         idx = torch.zeros((B, 7), dtype=torch.int32, device="cuda:0")
         Xd = torch.from_numpy(X.view(np.int16)).to("cuda:0")
         out = [case.step(X, indptr, indices, 0.05, 1, 2)]
+        assert case.passes == (passes if ch == chunk else 1)
+        first = case.W()
         case.head.topk(Xd, 7, idx, None)
         out += [case.step(X, indptr, indices, 0.05, 1, 3), (idx.cpu().numpy(), 0.0), (case.W(), case.C())]
         got.append(out)
+        case.head.close()
     (d0, d1, i, w), (e0, e1, j, v) = got
-    assert np.array_equal(w[0], v[0]) and np.array_equal(w[1], v[1]) and np.array_equal(i[0], j[0])
+    assert np.array_equal(w[0], v[0]) and np.array_equal(i[0], j[0])
+    assert w[1] is None or np.array_equal(w[1], v[1])
     for (x, lx), (y, ly) in ((d0, e0), (d1, e1)):
         assert_dx_close(x, y, 2.0 ** -8)
         assert abs(lx - ly) <= 1e-5 * abs(ly)
+    rows = np.unique(np.concatenate([np.arange(l, min(l + 64, L)) for l in range(0, L, max(L // 24, 1))] + [np.arange(L - 64, L)]))
+    C = None
+    if flags & KA:
+        C = np.zeros((len(rows), d), np.uint16)
+        held = rows < (kahan_rows or L)
+        C[held] = case.C0[rows[held]]
+    ref = o.head_step(case.W0[rows], C, X, indptr, indices, 0.05, 1, 2, fmt, flags, label_ids=rows, weight_decay=wd, dropout=T,
+                      **({"kahan_rows": kahan_rows} if kahan_rows else {}))
+    dist = np.abs(ordered(first[rows], fmt) - ordered(ref["W_new"], fmt))
+    assert np.mean(dist <= 1) >= 0.999
+    assert_far_misses_are_tiny(first[rows], ref["W_new"], dist, fmt, 0.05)
+    ref, _ = o.input_gradient_rows(case.W0, X, indptr, indices, fmt, np.arange(min(B, 8)), dropout=T, seed=1, step=2)
+    assert_dx_close(d0[0][:8], ref, 6e-2)
 
 
 @pytest.mark.parametrize("fmt", [o.BF16, o.E4M3])

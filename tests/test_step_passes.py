@@ -77,3 +77,30 @@ def test_an_input_gradient_that_is_not_asked_for_is_not_priced(passes, B, fmt):
     that are left without dX equal ones (2 to 5 % faster)."""
     assert passes(60000, 768, fmt, 16384, B)["labels"] == [21760, 21760, 16480]
     assert passes(60000, 768, fmt, 16384, B, want_dx=False)["labels"] == [20096, 20096, 19808]
+
+
+def planes(labels, B, d, kahan_rows=0):
+    """Planes of input-gradient partials that a pass over `labels` labels fills: label groups of 32-label tiles for a small
+    batch, slices of 64-label slabs otherwise."""
+    Bp = (B + 63) // 64 * 64
+    if Bp <= 128 and d % 256 == 0:
+        def groups(n):
+            t = -(-n // 32)
+            return -(-t // -(-t // max(1, 256 // (d // 256))))
+        parts = [n for n in (min(kahan_rows, labels), labels - min(kahan_rows, labels)) if n]
+        return max(groups(n) for n in parts)
+    slabs = -(-labels // 64)
+    S = min(max(1, 256 // (-(-Bp // 256) * -(-d // 256))), 64, slabs)
+    return -(-slabs // -(-slabs // S))
+
+
+def test_heads_of_the_gpu_tests_split_as_they_say(passes):
+    """The GPU tests of later passes are worth something only while their heads really go in several."""
+    gpu = pytest.importorskip("test_gpu_shapes")
+    for B, d, L, chunk, kahan_rows, n, first, last in gpu.PLANES:
+        labels = passes(L, d, gpu.o.E4M3, chunk, B)["labels"]
+        assert len(labels) == n and planes(labels[0], B, d, kahan_rows) == first and planes(labels[-1], B, d, kahan_rows) == last, (labels, B, d, L)
+    for fmt, flags, B, d, L, chunk, kahan_rows, T, wd, n in gpu.SEVERAL:
+        separate = T and fmt == gpu.o.BF16 and flags & gpu.KA
+        assert len(passes(L, d, fmt, chunk, B, separate=bool(separate))["labels"]) == n, (fmt, flags, B, d, L)
+        assert len(passes(L, d, fmt, L, B, separate=bool(separate))["labels"]) == 1
