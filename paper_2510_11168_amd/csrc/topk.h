@@ -889,9 +889,9 @@ inline int topk_run(hipStream_t st, bool fp8, const char* Xa, int a_rows, const 
     float* ns = more ? cursor_sc[(page + 1) & 1] : nullptr;
     int* ni = more ? cursor_id[(page + 1) & 1] : nullptr;
     // ---- main path: a first level without thresholds, then levels that grow by one factor
-    const TopkLevels levels = topk_levels(L, Bp, k);
+    const TopkLevels levels = topk_levels(L, Bp, k, (int)(rowb >> 7));
     for (int lv = 0; lv <= levels.n; ++lv) {
-      const int64_t begin = lv ? levels.end(lv - 1) : 0, end = lv ? levels.end(lv) : levels.level0;
+      const int64_t begin = lv ? levels.end(lv - 1) : 0, end = levels.end(lv);
       const bool first = lv == 0, last = lv == levels.n;
       if (const int n = (int)(end - begin); n > 0) {
         const int grid = (n + 255) / 256 * tiles_b256;

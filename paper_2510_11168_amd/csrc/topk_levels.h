@@ -36,19 +36,31 @@ struct TopkLevels {
   // labels seen when `level` (0: the first) has been taken
   int64_t end(int level) const {
     if (level == n) return L;
+    if (level == 0) return level0;
     return std::min<int64_t>(L, (int64_t)((double)level0 * std::pow(growth, level) + 255.0) / 256 * 256);
   }
 };
-inline TopkLevels topk_levels(int64_t L, int Bp, int k) {
+// As few levels as the lists allow for a batch of at most 128 rows, which pays for launches (one query or 128, 20000 .. 1.5 M BF16
+// labels: a level more is 5 .. 24 us).  A larger batch also pays for appends, device-scope additions, and a level of it
+// may end just above a whole wave of 256 x 256 tiles.  So every number of levels is priced, in us: launch and select of a
+// level, its waves of tiles of `slabs` K slabs (as the step's logits), and its appends, which a wave hands over together the
+// more of them there are.  575 shapes (160 .. 2048 rows, 20000 .. 3 M labels, k = 1 .. 100, both types, d = 768): 0.15 % above
+// the best number of levels on average, 6 % at most; with a fixed limit of 5.7 2.6 % and 38 %.  BF16, 140000 labels (two
+// levels / three): 256 rows, k = 10 113 / 138 us; 1024 rows, k = 34 328 / 293; 131072 labels, 1024 rows, k = 100 381 / 356.
+inline TopkLevels topk_levels(int64_t L, int Bp, int k, int slabs) {
   TopkLevels t{L, std::min<int64_t>(L, kTopkLevel0), 0, 1.0};
   const double ratio = (double)L / (double)t.level0;
-  double most = topk_most_growth(Bp, k);
-  // A level saved is a launch that does not fill the chip and a select, 35-45 us at 256 rows.  131072 BF16 labels, B = 256,
-  // k = 100: 175 us at most 4-fold, 150 us at 5.7; 20000 labels, B = 1024: 111 and 94 us.  Where the product is
-  // everything, the appends (device-scope additions) weigh more: 3 M labels, B = 1024: 2.18 and 2.22 ms.
-  if (Bp > 128) most = std::min(most, L * Bp >= (int64_t)1 << 31 ? 4.0 : 5.7);
-  t.n = (int)std::ceil(std::log(ratio) / std::log(most) - 1e-9);
-  if (t.n > 0) t.growth = std::pow(ratio, 1.0 / t.n);
+  const int least = (int)std::ceil(std::log(ratio) / std::log(topk_most_growth(Bp, k)) - 1e-9);
+  if (least <= 0) return t;
+  const int64_t tiles_b = (Bp + 255) / 256;
+  double cheapest = 0.0;
+  for (int n = least; n <= (Bp <= 128 ? least : least + 6); ++n) {
+    TopkLevels c{L, t.level0, n, std::pow(ratio, 1.0 / n)};
+    if (n > least && c.growth < 2.25) break;                   // (beyond what was measured)
+    double price = n * (16.0 + 0.001 * Bp * std::sqrt((double)k) * (c.growth - 1.0));
+    for (int lv = 1; lv <= n; ++lv) price += (double)((((c.end(lv) - c.end(lv - 1) + 255) / 256) * tiles_b + 255) / 256) * (6.0 + 1.4 * slabs);
+    if (n == least || price < cheapest) { cheapest = price; t = c; }
+  }
   return t;
 }
 

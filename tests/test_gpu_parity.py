@@ -857,13 +857,14 @@ def test_topk_small_brute_force(b, fmt):
 
 
 @pytest.mark.parametrize("fmt", [o.E4M3, o.BF16])
-def test_topk_one_slab_per_tile_and_several_batch_tiles(b, fmt):
-    """d = 128: an E4M3 tile is a single 128-byte K slab, so the kernel that keeps its ring running from
-    tile to tile changes tile at every slab (thresholds of the next tile's rows fetched a tile ahead);
-    300 queries are two batch tiles, the second ragged; 9000 + 5 labels are the first level, two
-    more levels (both in the form for levels where many scores pass) and a ragged last label tile;
-    k = 100 and a second page (k = 130)."""
-    L, d, B = 9000 + 5, 128, 300
+@pytest.mark.parametrize("L,B", [(9000 + 5, 300), (21000 + 5, 1030)])
+def test_topk_one_slab_per_tile_and_several_batch_tiles(b, fmt, L, B):
+    """d = 128: an E4M3 tile is a single 128-byte K slab, so the kernels that keep their ring running from
+    tile to tile change tile at every slab; a first level, one more (in which a large share of the scores passes) and a
+    ragged last label tile; k = 100 and a second page (k = 130).  300 queries are three 128-row tiles, the last ragged
+    (the kernel for launches that fill no wave); 1030 are five 256-row tiles with more tiles than workgroups (thresholds
+    of the next tile's rows fetched a tile ahead, slots reserved for all of a wave's passes at once)."""
+    d = 128
     case = Case(b, L, d, fmt, 4096, 0, B, w_std=0.05, seed=23)
     X = synth.make_x(np.random.default_rng(5), B, d)
     for k in (100, 130):
@@ -872,12 +873,11 @@ def test_topk_one_slab_per_tile_and_several_batch_tiles(b, fmt):
 
 
 def test_topk_passes_collected_per_workgroup_over_several_label_tiles(b):
-    """Three batch tiles (600 queries) and a last level of 93 label tiles: more tiles than one workgroup
+    """Three batch tiles (600 queries) and a last level of about a hundred label tiles: more tiles than one workgroup
     per CU, so the workgroups of that level walk one or two label tiles of one batch tile (a grid of 255,
-    the multiple of three below 256) and hands the passes it collected in LDS to the rows' lists at its
-    end; with k = 20 few scores pass per row, with k = 60 (the largest k for which that level still
-    takes the sparse form) a few rows fill their eight LDS entries and append the rest directly.  Both
-    against the oracle's full sort."""
+    the multiple of three below 256) and hand the passes they collected in LDS to the rows' lists at their
+    end; with k = 20 few scores pass per row, with k = 60 a few rows fill their eight LDS entries and append the rest
+    directly.  Both against the oracle's full sort."""
     L, d, B = 40000 + 3, 128, 600
     case = Case(b, L, d, o.E4M3, 8192, 0, B, w_std=0.05, seed=29)
     X = synth.make_x(np.random.default_rng(6), B, d)

@@ -11,9 +11,9 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = r"""
 #include "topk_levels.h"
-extern "C" int topk_level_ends(int64_t L, int Bp, int k, int64_t* ends, int* list) {
-  const elmo::TopkLevels t = elmo::topk_levels(L, Bp, k);
-  for (int i = 0; i <= t.n; ++i) ends[i] = i ? t.end(i) : t.level0;
+extern "C" int topk_level_ends(int64_t L, int Bp, int k, int slabs, int64_t* ends, int* list) {
+  const elmo::TopkLevels t = elmo::topk_levels(L, Bp, k, slabs);
+  for (int i = 0; i <= t.n; ++i) ends[i] = t.end(i);
   *list = elmo::topk_list(Bp);
   return t.n + 1;
 }
@@ -28,11 +28,11 @@ def level_ends(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
                     os.path.join(ROOT, "paper_2510_11168_amd", "csrc"), "-o", lib, str(d / "shim.cpp")], check=True)
     f = ctypes.CDLL(lib).topk_level_ends
-    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int)]
+    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int)]
 
-    def ends(L, Bp, k):
+    def ends(L, Bp, k, slabs=6):
         e, n = (ctypes.c_int64 * 256)(), ctypes.c_int()
-        m = f(L, Bp, k, e, ctypes.byref(n))
+        m = f(L, Bp, k, slabs, e, ctypes.byref(n))
         return list(e[:m]), n.value
     return ends
 
@@ -43,7 +43,7 @@ def test_levels_cover_the_labels(level_ends):
             for k in (1, 2, 7, 10, 100, 128):
                 if k > L:
                     continue
-                ends, n = level_ends(L, Bp, k)
+                ends, n = level_ends(L, Bp, k, 1 + (L + k) % 64)
                 assert n == (8192 if Bp <= 128 else 4096)
                 assert ends[0] == min(L, 4096) and ends[-1] == L and len(ends) <= 24
                 assert all(a < b for a, b in zip(ends, ends[1:])) or ends == [L]      # no level is empty
@@ -69,3 +69,12 @@ def test_lists_hold_what_a_level_appends(level_ends, Bp, spread):
                     worst[L, k] = max(worst.get((L, k), 0), (k + len(passed)) / n)
                     top = np.partition(np.concatenate([top, passed]), -k)[-k:]
     assert max(worst.values()) <= 1.0, {c: round(w, 2) for c, w in worst.items() if w > 1.0}
+
+
+@pytest.mark.parametrize("slabs,L,rows,k,levels", [
+    # d = 768 (12 slabs: BF16, 6: E4M3); levels after the first, the fastest measured
+    (12, 50000, 256, 1, 1), (6, 50000, 512, 1, 1), (12, 131072, 256, 100, 2), (12, 140000, 256, 10, 2), (6, 140000, 256, 5, 2), (12, 140000, 1024, 34, 3),
+    (12, 131072, 1024, 100, 3), (6, 131072, 2048, 100, 4), (6, 3000000, 1024, 100, 5), (12, 670091, 64, 10, 2),
+])
+def test_number_of_levels_follows_the_measured_times(level_ends, slabs, L, rows, k, levels):
+    assert len(level_ends(L, rows, k, slabs)[0]) == levels + 1
