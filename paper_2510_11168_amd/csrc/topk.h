@@ -9,8 +9,8 @@
 // threshold.  A later label that merely ties the threshold can never enter the top k (same score,
 // larger id), so the comparison is strict and the result exact.  A level is expected to append about
 // k x (growth - 1) scores per row (scores in no particular order along the label axis); the lists hold
-// 4096, those of a batch of at most 128 rows 8192.  An append is an atomic addition on the row's counter, and those cost more than anything else
-// besides the product in a large batch; a small one pays for the levels' launches.
+// 4096, those of a batch of at most 128 rows 8192.  An append is an atomic addition on the row's counter, and
+// those cost more than anything else besides the product in a large batch; a small one pays for the levels' launches.
 // In the large levels a pass is rare (a few per row and
 // million labels), so the filter first takes one wave-wide vote per sample on the largest of a
 // lane's four scores and skips the four compares when no lane passes (13 % end to end).
