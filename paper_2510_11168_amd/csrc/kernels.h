@@ -344,24 +344,17 @@ __global__ void __launch_bounds__(kSetupThreads) k_step_setup(const uint16_t* __
     for (int e = 0; e < 8; ++e) *reinterpret_cast<uint16_t*>(smem + (c + e) * kXtPitch + r * 2) = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
   }
   __syncthreads();
-  const int c = tid >> 3, sgm = tid & 7;
-  *reinterpret_cast<u32x4*>(XT + (size_t)(c0 + c) * Bp + b0 + sgm * 8) = *reinterpret_cast<const u32x4*>(smem + c * kXtPitch + sgm * 16);
+  const int cb = tid >> 8, o = (tid >> 5) & 7, c = tid & 31;
+  *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(XT) + (size_t)((c0 >> 5) + cb) * blk_strip(Bp) + blk_off((b0 >> 3) + o, c)) =
+      *reinterpret_cast<const u32x4*>(smem + (cb * 32 + c) * kXtPitch + o * 16);
 }
 
 // ---------------------------------------------------------------------------------------------
-// The three matrix products share one shape: 512-thread workgroups (8 waves as 4 x 2, each wave a
-// 64 x 128 block of 32x32 MFMA tiles) computing a 256 x 256 output tile, operands streamed by
-// asynchronous global->LDS loads through a ring of LDS stages (tiles.h, ring_pipeline_pp).  One
-// workgroup per CU.  On this part the matrix cores and the L2->LDS fill do not overlap for free:
-// a tile of this size halves the fill traffic per flop of a 256 x 128 tile, and the ping-pong
-// issue order of the ring hides most of what is left.
+// The three matrix products share one shape: 512-thread workgroups (8 waves) computing a 256 x 256 output tile,
+// operands streamed by asynchronous global->LDS loads through a ring of LDS stages (tiles.h: ring_pipeline_pp for
+// the logits, ring_alternate for the other two).  One workgroup per CU.  On this part the matrix cores and the L2->LDS
+// fill do not overlap for free: a tile of this size halves the fill traffic per flop of a 256 x 128 tile.
 // ---------------------------------------------------------------------------------------------
-// How the input-gradient product splits a slab's loads between the early and the late waves
-// (tiles.h, ring_stream_pp): uneven = three quarters early; late issue after this many quarters of
-// the slab's MFMAs (issuing after one or three quarters was never better than after two).  The
-// update product uses the paced ring instead (ring_pipeline_paced).
-constexpr bool kDxUneven = true;
-constexpr int kDxLateAfter = 2;
 constexpr int kGemmThreads = 512;
 constexpr int kGemmWaves = 8;
 constexpr int kStages = 3;                                       // ring depth of the small-batch kernel
@@ -426,28 +419,45 @@ __device__ __forceinline__ void drop_slab(char* tile, uint64_t blk0, uint32_t bl
   }
 }
 
+// The same for the four rows of a 32-row slab of 256 columns that a wave has loaded itself (dma_tile<32, ROWB, 8>): a lane draws one mask
+// block, of row 4 wave + lane / 16, columns 16 (lane % 16) .. +15.
+template <int ROWB, bool FP8>
+__device__ __forceinline__ void drop_own_rows(char* tile, int wave, int lane, uint64_t blk0, uint32_t blk_stride, uint64_t seed, uint64_t step,
+                                              uint32_t thresh) {
+  static_assert(ROWB == (FP8 ? 256 : 512), "256 columns");
+  const int r = 4 * wave + (lane >> 4), k = lane & 15;
+  const U4 rb = drop_block(blk0 + (uint64_t)r * blk_stride + k, seed, step);
+  const uint32_t tb = thresh * 0x01010101u;
+  const uint32_t m[4] = {keep_bytes(rb.x, tb), keep_bytes(rb.y, tb), keep_bytes(rb.z, tb), keep_bytes(rb.w, tb)};
+  if (FP8) {
+    u32x4* p = reinterpret_cast<u32x4*>(tile + tile_off<ROWB>(r, k));
+    *p = *p & u32x4{m[0], m[1], m[2], m[3]};
+  } else {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {                                // byte mask -> one 16-bit mask per element
+      u32x4* p = reinterpret_cast<u32x4*>(tile + tile_off<ROWB>(r, 2 * k + h));
+      *p = *p & u32x4{__builtin_amdgcn_perm(m[2 * h], m[2 * h], 0x01010000u), __builtin_amdgcn_perm(m[2 * h], m[2 * h], 0x03030202u),
+                      __builtin_amdgcn_perm(m[2 * h + 1], m[2 * h + 1], 0x01010000u), __builtin_amdgcn_perm(m[2 * h + 1], m[2 * h + 1], 0x03030202u)};
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Logits + fused epilogue (Algorithm 1: matmul_fp8, sigmoid_, "-= 1" at the positives).
 // One workgroup computes a 256 (samples) x 256 (labels) tile of Z = Xq W_c^T with FP32
-// accumulation over the full embedding width, then G = sigmoid(Z) - Y, and stores G^T[l][b] as
-// BF16 (labels x batch, the layout the paper's logits buffer has).  Z never reaches memory.
+// accumulation over the full embedding width, then G = sigmoid(Z) - Y, and stores G^T as
+// BF16 in blocks of 32 labels (tiles.h, blk_off), the order in which the other two products take it.  Z never reaches memory.
 // FP8: both operands E4M3, v_mfma_f32_32x32x64_f8f6f4.  BF16: v_mfma_f32_32x32x16_bf16.
 // The positives of the tile's two 128-label bins are turned into a bit mask in LDS before the K
 // loop; afterwards every wave finishes its accumulators in registers (sigmoid, minus the mask
-// bit, BF16), transposes its block through a private LDS area and stores 128-byte segments of
-// G^T rows, without a workgroup barrier.
+// bit, BF16) and stores them a KiB at a time, without LDS and without a workgroup barrier.
 // Rows of G^T between n and the next multiple of 128 are written as zeros (the input-gradient
-// product reads whole 64-label slabs).
+// product reads whole 32-label blocks).
 // ---------------------------------------------------------------------------------------------
 // TB x TB output tiles: TB = 256, or 128 for padded batches of at most 128 rows, where half of a
 // 256-row tile would be padding and the kernel is bound by the stream of W: 128 x 128 tiles need
 // 66 KiB of LDS, so two workgroups share a CU and one's epilogue overlaps the other's loads.
-constexpr int kGtPitch = 136;                                                        // bytes per staged G^T row segment of 64 samples (odd multiple of 8)
-template <int TB> constexpr int logits_ring_bytes() { return 2 * (TB + TB) * 128; }
-template <int TB> constexpr int logits_stage_bytes() { return TB * (TB / 64) * kGtPitch; }   // 8 waves x (their label rows) x pitch
-template <int TB> constexpr int logits_mask_offset() {                              // positives mask: behind ring and G^T stages
-  return logits_stage_bytes<TB>() > logits_ring_bytes<TB>() ? logits_stage_bytes<TB>() : logits_ring_bytes<TB>();
-}
+template <int TB> constexpr int logits_mask_offset() { return 2 * (TB + TB) * 128; }   // positives mask: behind the ring
 template <int TB> constexpr int logits_smem() { return logits_mask_offset<TB>() + TB * (TB / 32) * 4 + 32; }
 
 // One half (0 or 1) of the product of a 128-byte K slab of the logits tile: A = TB sample rows,
@@ -551,66 +561,61 @@ k_logits(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wc, i
   }
 
 
-  // ---- G = sigmoid(Z) - Y in registers, BF16, transposed through LDS, stored as row segments.
-  // Each wave finishes its own 64-sample x (32 FN)-label block on its own: it stages the block in
-  // a private LDS area ((32 FN) rows of 128 bytes, 4 samples = 8 bytes per write) and stores
-  // 128-byte segments of G^T rows (8 lanes each).  No workgroup barrier: one wave's stores overlap
-  // another's arithmetic, and this phase is bound by the vector ALU (two transcendental
-  // instructions per value).
+  // ---- G = sigmoid(Z) - Y in registers, BF16, stored as two octets of a label block (1 KiB) per instruction.
+  // Each wave finishes its own 64-sample x (32 FN)-label block on its own: one wave's stores overlap another's
+  // arithmetic, and this phase is bound by the vector ALU (two transcendental instructions per value).
+  // Turned through LDS into 128-byte segments of label rows the launch took 147 us per 131072 E4M3 labels (d = 768,
+  // 1024 samples), now 133.
   // Positives are a handful per sample among millions of labels: a 32 x 32 block whose mask words
   // are all zero, in a tile without ragged rows, takes the short form (sigmoid only); the wave
   // votes, so the choice is uniform.
   constexpr int WROWS = 32 * FN;
-  char* gts = smem + wave * (WROWS * kGtPitch);
   float loss = 0.0f;
-  const bool tile_full = n - l0 >= TB;
+  const bool tile_full = n - l0 >= TB, in_batch = b0 + wm * 64 < Bp;
+  const size_t strip = blk_strip(Bp);
+  char* gt = reinterpret_cast<char*>(Gt) + (size_t)((l0 + wn * WROWS) >> 5) * strip + (size_t)((b0 >> 3) + wm * 8) * 512;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < FN; ++j)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int lw = 32 * j + (lane & 31), l = wn * WROWS + lw;
+    for (int i = 0; i < 2; ++i) {
+      const int l = wn * WROWS + 32 * j + (lane & 31);
       const bool row_ok = l0 + l < n;
       const uint32_t ybits = (ym[l * MW + 2 * wm + i] >> (4 * (lane >> 5))) & 0x0F0F0F0Fu;
       const bool plain = !LOSS && tile_full && __builtin_amdgcn_ballot_w64(ybits != 0u) == 0ull;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int bw = 32 * i + 8 * q + 4 * (lane >> 5), b = wm * 64 + bw;
-        float g[4];
-        if (plain) {
+      for (int qp = 0; qp < 2; ++qp) {                               // 16 samples: two octets
+        uint32_t o[2][2];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) g[e] = sigmoidf_fast(DROP ? acc[i][j][4 * q + e] * dr.scale : acc[i][j][4 * q + e]);
-        } else {
+        for (int h = 0; h < 2; ++h) {
+          const int q = 2 * qp + h, b = wm * 64 + 32 * i + 8 * q + 4 * (lane >> 5);
+          float g[4];
+          if (plain) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float z = DROP ? acc[i][j][4 * q + e] * dr.scale : acc[i][j][4 * q + e];
-            const float y = (float)((ybits >> (8 * q + e)) & 1u);
-            g[e] = row_ok ? sigmoidf_fast(z) - y : 0.0f;
-            if (LOSS) loss += (row_ok && b0 + b + e < B) ? softplusf_fast(z) - y * z : 0.0f;
+            for (int e = 0; e < 4; ++e) g[e] = sigmoidf_fast(DROP ? acc[i][j][4 * q + e] * dr.scale : acc[i][j][4 * q + e]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float z = DROP ? acc[i][j][4 * q + e] * dr.scale : acc[i][j][4 * q + e];
+              const float y = (float)((ybits >> (8 * q + e)) & 1u);
+              g[e] = row_ok ? sigmoidf_fast(z) - y : 0.0f;
+              if (LOSS) loss += (row_ok && b0 + b + e < B) ? softplusf_fast(z) - y * z : 0.0f;
+            }
           }
+          o[h][0] = pack2_bf16(g[0], g[1]);
+          o[h][1] = pack2_bf16(g[2], g[3]);
         }
-        uint2 o;
-        o.x = pack2_bf16(g[0], g[1]);
-        o.y = pack2_bf16(g[2], g[3]);
-        *reinterpret_cast<uint2*>(gts + lw * kGtPitch + bw * 2) = o;
-      }
-    }
-  __builtin_amdgcn_s_waitcnt(0xC07F);              // this wave's LDS writes have completed (its lanes read each other's)
-  asm volatile("" ::: "memory");
-  if (b0 + wm * 64 < Bp) {
-#pragma unroll
-    for (int it = 0; it < WROWS * 8 / 64; ++it) {
-      const int id = it * 64 + lane, r = id >> 3, sgm = id & 7;
-      const int row = wn * WROWS + r;
-      if (row < rows_out) {
-        const uint2 lo = *reinterpret_cast<const uint2*>(gts + r * kGtPitch + sgm * 16);
-        const uint2 hi = *reinterpret_cast<const uint2*>(gts + r * kGtPitch + sgm * 16 + 8);
-        // streaming store: G^T is written once here and read by other kernels later (measured 157 -> 150 us
+        // a lane holds half of each octet, the lane 32 further the other half: after the exchange the lower lanes hold the first
+        // octet and the upper ones the second
+        const auto s0 = __builtin_amdgcn_permlane32_swap(o[0][0], o[1][0], false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(o[0][1], o[1][1], false, false);
+        // streaming store: the gradients are written once here and read by other kernels later (measured 157 -> 150 us
         // per chunk against a plain store; the same hint on the weight stores of the update kernels and on
         // the asynchronous loads changed nothing or made them slower)
-        __builtin_nontemporal_store(u32x4{lo.x, lo.y, hi.x, hi.y}, reinterpret_cast<u32x4*>(Gt + (size_t)(l0 + row) * Bp + b0 + wm * 64 + sgm * 8));
+        if (in_batch && wn * WROWS + 32 * j < rows_out)
+          __builtin_nontemporal_store(u32x4{s0[0], s1[0], s0[1], s1[1]},
+                                      reinterpret_cast<u32x4*>(gt + j * strip + blk_off(4 * i + 2 * qp + (lane >> 5), lane & 31)));
       }
     }
-  }
   if (LOSS) {
     const float s = block_sum<kGemmWaves>(loss, red);
     if (tid == 0) {
@@ -627,7 +632,7 @@ k_logits(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wc, i
 // weights are widened to BF16 in registers (no up-cast copy of W in memory).
 // Workgroup = 256 samples x 256 embedding columns x one slice s of the chunk's labels; the FP32
 // partial goes to dXacc[s] (owned by exactly this workgroup, so plain read-modify-write).
-// Label rows beyond n inside the last 64-label slab are harmless: G^T holds zeros there and the
+// Label rows beyond n inside the last 32-label slab are harmless: G^T holds zeros there and the
 // weight rows are re-reads of row n-1.  Columns beyond d in the last column tile re-read the
 // row's last 16 bytes and are not stored.
 // ---------------------------------------------------------------------------------------------
@@ -664,75 +669,93 @@ template <int NB> __device__ __forceinline__ void add_acc_blocks(f32x4* __restri
   }
 }
 
-// ring stage: [G^T slab 64 labels x 256 samples (512-byte rows) | W slab 64 labels x 256 columns]
-template <bool FP8> constexpr int dx_stages() { return FP8 ? 3 : 2; }
-template <bool FP8> constexpr int dx_smem_bytes() { return dx_stages<FP8>() * (64 * 512 + 64 * (FP8 ? 256 : 512)); }
+// Ring stage: [32 labels x 256 samples of the gradients (one block's octets, as in memory) | W slab 32 labels x 256 columns].
+constexpr int kDxStages = 4;
+template <bool FP8> constexpr int dx_stage_bytes() { return 32 * 512 + 32 * (FP8 ? 256 : 512); }
+template <bool FP8> constexpr int dx_smem_bytes() { return kDxStages * dx_stage_bytes<FP8>(); }
 
+// Fragments of one step of 16 labels: four blocks of 32 samples, two of 32 columns (E4M3: as stored).
+template <bool FP8> struct FragDx { bf16x8 a[4]; typename std::conditional<FP8, i32x2, bf16x8>::type b[2]; };
+
+// The waves stand 2 x 4, 128 samples x 64 columns each: a weight fragment then feeds four MFMAs and is widened in two waves (64 x 128
+// each: two MFMAs, four waves), and it is widened between the MFMAs, where the vector ALU is free, not before them.
+// Alone, 131072 E4M3 labels x 768, 1024 samples: 156 us, 164 us as 64 x 128, 167 us widened ahead of the product.
 template <bool FP8, bool DROP>
 __global__ void __launch_bounds__(kGemmThreads, 1)
 k_dx(const char* __restrict__ Gt, const char* __restrict__ Wc, float* __restrict__ dXacc, int n, int d, int Bp,
      int Bp256, int S, bool first, uint64_t seed, uint64_t step, uint64_t elem0, DropArgs dr) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr int ESZ = FP8 ? 1 : 2, WROWB = 256 * ESZ;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  constexpr int ESZ = FP8 ? 1 : 2, WROWB = 256 * ESZ, GBYTES = 32 * 512;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 2, wn = wave & 3;
   const int tiles_b = Bp256 >> 8, tiles_j = (d + 255) >> 8;
   const int wg = xcd_logical_id(blockIdx.x, gridDim.x);
   const int jt = wg % tiles_j, bt = (wg / tiles_j) % tiles_b, s = wg / (tiles_j * tiles_b);
   const int b0 = bt << 8, j0 = jt << 8;
-  const int ksteps = (n + 63) >> 6, per = (ksteps + S - 1) / S;
+  const int ksteps = (n + 31) >> 5, per = (ksteps + S - 1) / S;
   const int ks0 = s * per, ks1 = min(ks0 + per, ksteps);
   if (ks0 >= ks1 && !first) return;
-  const size_t strideA = (size_t)Bp * 2, strideB = (size_t)d * ESZ;
+  const size_t strip = blk_strip(Bp), strideB = (size_t)d * ESZ;
 
-  f32x16 acc[2][4];
-  zero_acc(acc);
+  f32x16 acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
   float* out = dXacc + (size_t)s * Bp256 * d;
   auto store = [&]() {
-    const int col = j0 + wn * 128;
+    const int col = j0 + wn * 64;
     if (col < d)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) add_acc_blocks<4>(dx_block(out, d, b0 + wm * 64 + 32 * i, col), lane, acc[i], first);
+      for (int i = 0; i < 4; ++i) add_acc_blocks<2>(dx_block(out, d, b0 + wm * 128 + 32 * i, col), lane, acc[i], first);
   };
   if (ks0 >= ks1) { store(); return; }                 // a slice without labels in the first chunk still owns its plane
-  auto product = [&](const char* sa, const char* sb, int q0, int q1) {
+  const char* ga = Gt + (size_t)ks0 * strip;
+  const char* gb = Wc + (size_t)ks0 * 32 * strideB + (size_t)j0 * ESZ;
+  const int kibs = Bp >> 4, kib0 = (b0 >> 4) + 2 * wave;   // KiB of a strip; this wave's two of every slab (beyond the batch: the last one again)
+  const int chunks_b = min(256, d - j0) * ESZ / 16;
+  auto issue = [&](int ks, int to) {
+    const char* g = ga + (size_t)ks * strip;
+    char* st = smem + to;
+    dma_kib(g + (size_t)min(kib0, kibs - 1) * 1024, st + 2 * wave * 1024, lane);
+    dma_kib(g + (size_t)min(kib0 + 1, kibs - 1) * 1024, st + (2 * wave + 1) * 1024, lane);
+    dma_tile<32, WROWB, kGemmWaves>(gb + (size_t)ks * 32 * strideB, strideB, n - (ks0 + ks) * 32, st + GBYTES, wave, lane, chunks_b);
+  };
+  auto ld = [&](FragDx<FP8>& f, const char* st, int kk) {
 #pragma unroll
-    for (int kk = q0; kk < q1; ++kk) {
-      bf16x8 a[2], b[4];
+    for (int i = 0; i < 4; ++i) f.a[i] = frag_tr_blk(st, 16 * kk, wm * 128 + 32 * i, lane);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = frag_tr_bf16<512>(sa, 16 * kk, wm * 64 + 32 * i, lane);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        b[j] = FP8 ? frag_tr_fp8<WROWB>(sb, 16 * kk, wn * 128 + 32 * j, lane)
-                   : frag_tr_bf16<WROWB>(sb, 16 * kk, wn * 128 + 32 * j, lane);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    for (int j = 0; j < 2; ++j) {
+      if constexpr (FP8) f.b[j] = frag_tr_raw8<WROWB>(st + GBYTES, 16 * kk, wn * 64 + 32 * j, lane);
+      else f.b[j] = frag_tr_bf16<WROWB>(st + GBYTES, 16 * kk, wn * 64 + 32 * j, lane);
     }
   };
-  const char* ga = Gt + (size_t)ks0 * 64 * strideA + (size_t)b0 * 2;
-  const char* gb = Wc + (size_t)ks0 * 64 * strideB + (size_t)j0 * ESZ;
-  const int va0 = (ksteps - ks0) * 64;                 // zero rows of G^T past n are real
-  const int chunks_b = min(256, d - j0) * ESZ / 16;
+  auto mm = [&](const FragDx<FP8>& f) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      bf16x8 b;
+      if constexpr (FP8) b = widen8(f.b[j]);
+      else b = f.b[j];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], b, acc[i][j], 0, 0, 0);
+    }
+  };
+  constexpr int LPS = 2 + dma_loads_per_wave<32, WROWB, kGemmWaves>();
   if constexpr (DROP) {
     // the same masked weights as in the logits product (appendix "Low-Memory Dropout for Classifier")
-    const uint64_t blk_first = (elem0 + (uint64_t)ks0 * 64 * d + j0) >> 4;
-    ring_pipeline_pp<64, 512, 64, WROWB, dx_stages<FP8>(), kGemmWaves, kDxUneven, kDxLateAfter>(
-        ga, strideA, va0, 64, 64 * strideA, 32, gb, strideB, n - ks0 * 64, 64, 64 * strideB, chunks_b, ks1 - ks0, smem, wave, lane,
-        product, [&](char* sb, int ks) {
-          drop_slab<64, WROWB, FP8>(sb, blk_first + (uint64_t)ks * 4 * d, (uint32_t)d >> 4, seed, step, dr.thresh, tid);
-        });
+    const uint64_t blk_first = (elem0 + (uint64_t)ks0 * 32 * d + j0) >> 4;
+    ring_alternate<kDxStages, dx_stage_bytes<FP8>(), LPS, FragDx<FP8>>(ks1 - ks0, smem, wave >= 4, issue, ld, mm, [&](char* st, int ks) {
+      drop_own_rows<WROWB, FP8>(st + GBYTES, wave, lane, blk_first + (uint64_t)ks * 2 * d, (uint32_t)d >> 4, seed, step, dr.thresh);
+    });
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] *= dr.scale;
   } else {
-    ring_pipeline_pp<64, 512, 64, WROWB, dx_stages<FP8>(), kGemmWaves, kDxUneven, kDxLateAfter>(
-        ga, strideA, va0, 64, 64 * strideA, 32, gb, strideB, n - ks0 * 64, 64, 64 * strideB, chunks_b, ks1 - ks0, smem, wave, lane,
-        product);
+    ring_alternate<kDxStages, dx_stage_bytes<FP8>(), LPS, FragDx<FP8>>(ks1 - ks0, smem, wave >= 4, issue, ld, mm);
   }
   store();
 }
@@ -782,7 +805,8 @@ __global__ void __launch_bounds__(64 * kFinalWaves) k_finalize(const float* __re
 // ---------------------------------------------------------------------------------------------
 constexpr int kGPitch = 132;                                     // floats per staged gradient row of 128 columns
 constexpr int kUpdateEpiBytes = kGemmWaves * 32 * kGPitch * 4;   // one 32 x 128 FP32 half-block per wave
-constexpr int kUpdateSmem = kUpdateEpiBytes > kWideRingBytes ? kUpdateEpiBytes : kWideRingBytes;
+constexpr int kUpdateStages = 4, kUpdateStageBytes = (256 + 256) * 64;    // [8 blocks of gradients | 8 blocks of inputs] x 32 samples
+constexpr int kUpdateSmem = kUpdateEpiBytes > kUpdateStages * kUpdateStageBytes ? kUpdateEpiBytes : kUpdateStages * kUpdateStageBytes;
 
 // Sixteen consecutive elements of one weight row: storage bits in, storage bits out.
 // E4M3: w[0..3] hold 4 codes each; BF16: w[0..7] hold 2 patterns each.  c[0..7]: BF16 compensation.
@@ -860,7 +884,6 @@ k_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restr
   const int wg = xcd_logical_id(blockIdx.x, gridDim.x);
   const int lt = wg / tiles_j, jt = wg % tiles_j;
   const int l0 = lt << 8, j0 = jt << 8;
-  const size_t stride = (size_t)Bp * 2;
   // Every wave finishes its own 64 (labels) x 128 (columns) block of the tile on its own, in two
   // halves of 32 labels: per half the lane handles 4 passes x 16 consecutive columns of one row
   // (row = 8 pass + lane / 8; eight lanes cover the 128 columns of a row, i.e. whole 128-byte
@@ -891,19 +914,32 @@ k_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restr
 
   f32x16 acc[2][4];
   zero_acc(acc);
-  // K loop over the batch in slabs of 64 samples
-  ring_pipeline_paced<256, 128, 256, 128, kGemmWaves, 4, 6, 8, FragBF16<2, 4>>(
-      Gt + (size_t)l0 * stride, stride, n - l0, 0, 128, 8, XT + (size_t)j0 * stride, stride, d - j0, 0, 128, 8, Bp >> 6, smem, wave,
-      lane,
-      [&](FragBF16<2, 4>& f, const char* sa, const char* sb, int kk) {
+  // K loop over the batch in slabs of 32 samples; a wave loads one 32-row block of each operand (beyond the last: that one again)
+  const int uw = __builtin_amdgcn_readfirstlane(wave);
+  const size_t strip = blk_strip(Bp);
+  const char* ga = Gt + (size_t)((l0 >> 5) + min(uw, ((n - l0 + 31) >> 5) - 1)) * strip;
+  const char* gb = XT + (size_t)((j0 >> 5) + min(uw, ((d - j0) >> 5) - 1)) * strip;
+  ring_alternate<kUpdateStages, kUpdateStageBytes, 4, FragBF16<2, 4>>(
+      Bp >> 5, smem, uw >= 4,
+      [&](int ks, int to) {
+        char* st = smem + to + uw * 2048;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) f.a[i] = frag_bf16(sa, wm * 64 + 32 * i, kk, lane);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) f.b[j] = frag_bf16(sb, wn * 128 + 32 * j, kk, lane);
+        for (int i = 0; i < 2; ++i) {
+          dma_kib(ga + (size_t)ks * 2048 + 1024 * i, st + 1024 * i, lane);
+          dma_kib(gb + (size_t)ks * 2048 + 1024 * i, st + 16384 + 1024 * i, lane);
+        }
       },
-      [&](const FragBF16<2, 4>& f, int i) {
+      [&](FragBF16<2, 4>& f, const char* st, int kk) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < 2; ++i) f.a[i] = frag_blk(st + (wm * 2 + i) * 2048, kk, lane);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f.b[j] = frag_blk(st + 16384 + (wn * 4 + j) * 2048, kk, lane);
+      },
+      [&](const FragBF16<2, 4>& f) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
       });
   if (!has_cols) return;                             // after the ring's last barrier: no barrier follows
 #pragma unroll
@@ -1012,7 +1048,7 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
   const int t0 = g * tiles_per_group, t1 = min(t0 + tiles_per_group, ntiles);
   if (t0 >= t1 && !(DX && first)) return;                    // (in the first pass every group writes its dX plane)
   const int j0 = c << 8;
-  const size_t gstride = (size_t)Bp * 2;
+  const size_t strip = blk_strip(Bp);
   const int KS = Bp >> 4;                                   // k16 steps over the batch: 4 or 8
   char* ring = smem;
   float* gs = reinterpret_cast<float*>(smem + kStages * SBYTES);
@@ -1022,8 +1058,8 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
   bf16x8 xt[8];
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) {
-    const int b = min(16 * ks + 8 * (lane >> 5), Bp - 8);
-    xt[ks] = *reinterpret_cast<const bf16x8*>(XT + ((size_t)(j0 + 32 * wave + (lane & 31)) * Bp + b) * 2);
+    const int o = min(2 * ks + (lane >> 5), (Bp >> 3) - 1);
+    xt[ks] = *reinterpret_cast<const bf16x8*>(XT + (size_t)((j0 >> 5) + wave) * strip + blk_off(o, lane & 31));
   }
   const int bt = wave & 3, jh = wave >> 2;                  // dX block of this wave: rows 32*bt.., columns 128*jh..
   f32x16 dxa[4];
@@ -1037,7 +1073,7 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
     const int l0 = t << 5, valid = n - l0;
     dma_tile<32, WROWB, kGemmWaves>(Wc + ((size_t)l0 * d + j0) * ESZ, (size_t)d * ESZ, valid, st, wave, lane);
     // rows of G^T past n exist and hold zeros (written by the logits kernel): no clamping, so they add nothing to dX
-    dma_tile<32, 256, kGemmWaves>(Gt + (size_t)l0 * gstride, gstride, 32, st + WBYTES, wave, lane, Bp >> 3);
+    dma_kib(Gt + (size_t)t * strip + (size_t)min(wave, (Bp >> 4) - 1) * 1024, st + WBYTES + wave * 1024, lane);
     if (KAHAN)
       dma_tile<32, 512, kGemmWaves>(reinterpret_cast<const char*>(Cc) + ((size_t)l0 * d + j0) * 2, (size_t)d * 2, valid,
                                     st + WBYTES + GBYTES, wave, lane);
@@ -1105,12 +1141,12 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
     for (int v = 0; v < 16; ++v) wa[v] = 0.0f;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks)
-      if (ks < KS) wa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_bf16<256>(gsl, 0, ks, lane), xt[ks], wa, 0, 0, 0);
+      if (ks < KS) wa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_blk(gsl, ks, lane), xt[ks], wa, 0, 0, 0);
     // dX[32 samples x 128 columns of this wave] += G W_tile (weights as stored before the update)
     if (DX) {
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        const bf16x8 a = frag_tr_bf16<256>(gsl, 16 * kk, 32 * bt, lane);
+        const bf16x8 a = frag_tr_blk(gsl, 16 * kk, 32 * bt, lane);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const bf16x8 b = FMT == FMT_E4M3 ? frag_tr_fp8<WROWB>(wdx, 16 * kk, 128 * jh + 32 * q, lane)

@@ -251,95 +251,79 @@ __device__ inline void ring_pipeline_pp(const char* __restrict__ ga, size_t stri
       [&](const char* sa, const char* sb, int q0, int q1, int) { mma(sa, sb, q0, q1); }, static_cast<Prep&&>(prep));
 }
 
-// Software-pipelined, paced form of the two-stage ring for one output tile.  The product of a slab
-// is KSTEPS fragment steps; ld(f, stageA, stageB, kk) reads the fragments of step kk into registers
-// and mm(f, h) issues half h (0 / 1) of that step's MFMAs.  Two fragment sets alternate: the LDS
-// reads of step kk + 1 are issued before the MFMAs of step kk, and the last step of a slab is
-// multiplied after the next slab's barrier, behind the first fragment reads of that slab, so a
-// wave meets one wait per slab (the barrier) instead of an LDS round trip with idle matrix cores
-// at every half slab (what the compiler makes of ring_pipeline_pp: read, wait, 8 MFMAs per step).
-// Every wave issues its equal share of the next slab's asynchronous loads in four quarters,
-// between the MFMA groups of the first two steps after the barrier, instead of half of the waves
-// issuing everything at once.  Fragments of the stage being left are all in registers
-// (lgkmcnt(0)) before a wave arrives at the barrier that lets other waves overwrite that stage.
-// NRD / NMM: LDS reads per ld() and MFMAs per step; the scheduler is told to issue a step's reads
-// ahead of the MFMAs they overlap with (it otherwise sinks them behind the MFMAs to save registers).
-// Measured on the update product (per chunk of the 3M-label FP8 head, B = 1024): 282 us with
-// ring_pipeline_pp, 274 us software-pipelined with the early / late split, 267 us paced.  What
-// bounds the loop is the round trip of a slab's loads (about 3 k clocks for 64 KiB whether or not
-// the lines are already in L2; the same loop without MFMAs and fragment reads takes 0.8 of the
-// full loop's time, without loads 0.65), and 160 KiB of LDS do not hold a third 64 KiB stage.
-template <int NRD, int NMM> __device__ __forceinline__ void sched_reads_then_mfma() {
-  __builtin_amdgcn_sched_group_barrier(0x100, NRD, 0);
-  __builtin_amdgcn_sched_group_barrier(0x008, NMM, 0);
+// Alternating ring: the K loop of one output tile in slabs of two fragment steps.  Waves w and w + NW / 2 share a SIMD; the
+// lower half of the waves multiplies a slab (16 MFMAs, 512 clocks) while the upper half reads the fragments of its own and
+// issues its loads, then they change places, with a barrier at each change.  So neither the LDS round trip nor the issue of
+// asynchronous loads (some 77 clocks a KiB, in which a wave can do nothing else) ever stands between two MFMAs of a SIMD.
+// issue(ks, to): this wave's LPS loads of slab ks into the stage at byte `to`; ld(f, stage, kk): fragments of step kk (0 / 1);
+// mm(f): a step's MFMAs; prep(stage, ks): may rewrite in LDS what this wave itself has loaded of a slab that has landed.
+// NST stages: the loads of slab ks + NST - 1 go out while slab ks is read, into the stage whose last fragments the other half of the
+// waves had in registers (lgkmcnt(0)) one barrier earlier; the younger slabs stay in flight over a wait (vmcnt counts in issue order).
+// The update's K loop alone (131072 x 768 outputs, 1024 samples, values as in training, random): 1381 TFLOP/s, 1168 clocks a
+// slab of 32 samples (1024 are MFMAs).  Free-running waves with the same loads and two fragment sets ahead: 1266 TFLOP/s, 1450
+// clocks, with 3 stages or with 5 (so it is not the latency of the loads).  The rest is power: on zeros the same loop
+// runs 1774 TFLOP/s at 2.2 GHz, on random values the clock falls to 1.6 GHz.
+template <int LPS, int N> __device__ inline void wait_slabs(int left) {   // at most min(left, N) slabs of LPS loads outstanding
+  if constexpr (N == 0) wait_vmcnt<0>();
+  else if (left >= N) wait_vmcnt<N * LPS>();
+  else wait_slabs<LPS, N - 1>(left);
 }
-template <int AROWS, int AROWB, int BROWS, int BROWB, int NW, int KSTEPS, int NRD, int NMM, class F, class Ld, class Mm>
-__device__ inline void ring_pipeline_paced(const char* __restrict__ ga, size_t stride_a, int va0, int dva, size_t adv_a, int chunks_a,
-                                           const char* __restrict__ gb, size_t stride_b, int vb0, int dvb, size_t adv_b, int chunks_b,
-                                           int nk, char* smem, int wave, int lane, Ld&& ld, Mm&& mm) {
-  static_assert(KSTEPS >= 2 && KSTEPS % 2 == 0, "fragment steps come in pairs");
-  constexpr int ABYTES = AROWS * AROWB, SBYTES = ABYTES + BROWS * BROWB;
-  constexpr int NA = dma_loads_per_wave<AROWS, AROWB, NW>(), NB = dma_loads_per_wave<BROWS, BROWB, NW>();
-  static_assert(NA % 2 == 0 && NB % 2 == 0, "loads are issued in four quarters");
-  auto issue_a = [&](int ks, auto half) {
-    constexpr int H = decltype(half)::value;
-    dma_tile<AROWS, AROWB, NW, H * NA / 2, (H + 1) * NA / 2>(ga + (size_t)ks * adv_a, stride_a, va0 - ks * dva, smem + (ks & 1) * SBYTES, wave, lane, chunks_a);
-  };
-  auto issue_b = [&](int ks, auto half) {
-    constexpr int H = decltype(half)::value;
-    dma_tile<BROWS, BROWB, NW, H * NB / 2, (H + 1) * NB / 2>(gb + (size_t)ks * adv_b, stride_b, vb0 - ks * dvb, smem + (ks & 1) * SBYTES + ABYTES, wave, lane, chunks_b);
-  };
-  using H0 = std::integral_constant<int, 0>;
-  using H1 = std::integral_constant<int, 1>;
-  issue_a(0, H0{}); issue_a(0, H1{}); issue_b(0, H0{}); issue_b(0, H1{});
-  F f0, f1;
+template <int NST, int SBYTES, int LPS, class F, class Issue, class Ld, class Mm, class Prep = NoPrep>
+__device__ __forceinline__ void ring_alternate(int nk, char* __restrict__ smem, bool upper, Issue&& issue, Ld&& ld, Mm&& mm, Prep&& prep = Prep{}) {
+  constexpr bool HAS_PREP = !std::is_same<std::remove_cv_t<std::remove_reference_t<Prep>>, NoPrep>::value;
+  static_assert(NST >= 3 && (NST - 1) * LPS <= 63, "ring depth");
+  for (int s = 0; s < NST - 1; ++s)
+    if (s < nk) issue(s, s * SBYTES);
+  wait_slabs<LPS, NST - 2>(nk - 1);
+  if constexpr (HAS_PREP) prep(smem, 0);
+  barrier_lds();
+  if (upper) barrier_nofence();
+  int at = 0, to = (NST - 1) * SBYTES;                   // stage of slab ks and of slab ks + NST - 1
   for (int ks = 0; ks < nk; ++ks) {
-    wait_vmcnt<0>();
-    barrier_nofence();
-    const bool more = ks + 1 < nk;
-    const char* sa = smem + (ks & 1) * SBYTES;
-    const char* sb = sa + ABYTES;
+    const int next = at == (NST - 1) * SBYTES ? 0 : at + SBYTES;
+    F f0, f1;
     __builtin_amdgcn_sched_barrier(0);
-    ld(f0, sa, sb, 0);
-    if (ks > 0) {                          // last step of the slab before, behind this slab's first reads
-      mm(f1, 0);
-      sched_reads_then_mfma<NRD, NMM / 2>();
-      __builtin_amdgcn_sched_barrier(0);
-      if (more) issue_a(ks + 1, H0{});
-      __builtin_amdgcn_sched_barrier(0);
-      mm(f1, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (more) issue_a(ks + 1, H1{});
-    } else if (more) {
-      issue_a(ks + 1, H0{});
-      issue_a(ks + 1, H1{});
+    ld(f0, smem + at, 0);
+    ld(f1, smem + at, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (ks + NST - 1 < nk) issue(ks + NST - 1, to);
+    if (ks + 1 < nk) {
+      wait_slabs<LPS, NST - 2>(nk - 2 - ks);
+      if constexpr (HAS_PREP) prep(smem + next, ks + 1);
     }
+    barrier_lds();                                       // this wave's fragments are in registers, its part of the next slab in LDS
     __builtin_amdgcn_sched_barrier(0);
-    ld(f1, sa, sb, 1);
-    mm(f0, 0);
-    sched_reads_then_mfma<NRD, NMM / 2>();
+    mm(f0);
+    mm(f1);
     __builtin_amdgcn_sched_barrier(0);
-    if (more) issue_b(ks + 1, H0{});
-    __builtin_amdgcn_sched_barrier(0);
-    mm(f0, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    if (more) issue_b(ks + 1, H1{});
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kk = 2; kk < KSTEPS; kk += 2) {
-      ld(f0, sa, sb, kk);
-      mm(f1, 0); mm(f1, 1);
-      sched_reads_then_mfma<NRD, NMM>();
-      __builtin_amdgcn_sched_barrier(0);
-      ld(f1, sa, sb, kk + 1);
-      mm(f0, 0); mm(f0, 1);
-      sched_reads_then_mfma<NRD, NMM>();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0): every fragment of this stage is in registers
+    if (ks + 1 < nk || !upper) barrier_nofence();        // (the lower half's last barrier is the one between the upper half's last reads and products)
+    to = at;
+    at = next;
   }
-  mm(f1, 0); mm(f1, 1);
-  barrier_nofence();   // every wave is done with the ring: the caller may reuse the memory
+  // every wave has read its last fragments: the caller may reuse the memory, and the lower half goes on while the upper one multiplies its last slab
+}
+
+// ---------------------------------------------------------------------------------------------
+// Blocked BF16 matrices (the logit gradients and the transposed inputs): rows in blocks of 32, samples in octets, a
+// 16-byte chunk holds one row's eight samples, and a block is a strip of octets of 32 chunks:
+// chunk (row r, octet o) of a block is at blk_off(o, r).  That is the order in which the lanes of an MFMA fragment take the chunks, so
+// loads, LDS copies and fragment reads move whole consecutive KiB (two octets) with no address arithmetic per lane; the XOR
+// spreads four neighbouring octets over the LDS banks for the transposing reads of the input gradient.
+// ---------------------------------------------------------------------------------------------
+__device__ inline int blk_off(int o, int r) { return (o << 9) + ((r ^ ((o & 3) << 2)) << 4); }
+// Bytes of a block's strip for Bp samples.
+__device__ inline size_t blk_strip(int Bp) { return (size_t)Bp * 64; }
+// One KiB (consecutive in memory and in LDS) by one wave.
+__device__ inline void dma_kib(const char* __restrict__ g, char* lds, int lane) {
+  uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)g), hi = __builtin_amdgcn_readfirstlane((uint32_t)((uintptr_t)g >> 32));
+  asm volatile("" : "+s"(lo), "+s"(hi));
+  g = reinterpret_cast<const char*>(((uintptr_t)hi << 32) | lo);
+  const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"((uint32_t)(lane * 16)), "s"(g) : "memory", "m0");
+}
+// Fragment of v_mfma_f32_32x32x16_bf16 from a block at `strip`, samples 16 kk .. +15: lane i holds row i%32, samples 8*(i/32) .. +7.
+__device__ inline bf16x8 frag_blk(const char* strip, int kk, int lane) {
+  return *reinterpret_cast<const bf16x8*>(strip + blk_off(2 * kk + (lane >> 5), lane & 31));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -382,18 +366,35 @@ template <int ROWB> __device__ inline bf16x8 frag_tr_bf16(const char* lds, int k
   u.s[0] = a; u.s[1] = b;
   return u.v;
 }
-// Same fragment from an FP8 (E4M3) tile; the eight values are widened to BF16 (exact).
-template <int ROWB> __device__ inline bf16x8 frag_tr_fp8(const char* lds, int k0, int col0, int lane) {
+// Same fragment with the samples of a blocked strip as columns (col0 a multiple of 32) and rows k0 .. k0+15 of the block as K.
+__device__ inline bf16x8 frag_tr_blk(const char* strip, int k0, int col0, int lane) {
+  const int g = lane >> 4, q = lane & 15;
+  const int col = col0 + 16 * (g & 1) + 4 * (q & 3);
+  const int kr = k0 + 8 * (g >> 1) + (q >> 2);
+  const int h = (col & 4) << 1;
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16(ELMO_LDS_PTR(s16x4, strip + blk_off(col >> 3, kr) + h));
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16(ELMO_LDS_PTR(s16x4, strip + blk_off(col >> 3, kr + 4) + h));
+  union { s16x4 s[2]; bf16x8 v; } u;
+  u.s[0] = a; u.s[1] = b;
+  return u.v;
+}
+// Same fragment from an FP8 (E4M3) tile, and its eight values widened to BF16 (exact).
+template <int ROWB> __device__ inline i32x2 frag_tr_raw8(const char* lds, int k0, int col0, int lane) {
   const int g = lane >> 4, q = lane & 15;
   const int col = col0 + 16 * (g & 1) + 8 * (q & 1);     // byte column of this lane's 8 bytes
   const int kr = k0 + 8 * (g >> 1) + (q >> 1);
-  const i32x2 w = __builtin_amdgcn_ds_read_tr8_b64_v2i32(ELMO_LDS_PTR(i32x2, lds + tile_off<ROWB>(kr, col >> 4) + (col & 8)));
+  return __builtin_amdgcn_ds_read_tr8_b64_v2i32(ELMO_LDS_PTR(i32x2, lds + tile_off<ROWB>(kr, col >> 4) + (col & 8)));
+}
+__device__ inline bf16x8 widen8(i32x2 w) {
   union { bf16x2 p[4]; bf16x8 v; } u;
   u.p[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((unsigned)w[0], 1.0f, false);
   u.p[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((unsigned)w[0], 1.0f, true);
   u.p[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((unsigned)w[1], 1.0f, false);
   u.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((unsigned)w[1], 1.0f, true);
   return u.v;
+}
+template <int ROWB> __device__ inline bf16x8 frag_tr_fp8(const char* lds, int k0, int col0, int lane) {
+  return widen8(frag_tr_raw8<ROWB>(lds, k0, col0, lane));
 }
 
 // Accumulator element v (0..15) of a 32x32 MFMA tile sits at row 8*(v/4) + 4*(lane/32) + v%4,

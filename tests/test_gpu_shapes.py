@@ -358,3 +358,26 @@ def test_inputs_of_an_fp8_head_may_begin_at_any_element(b, B, d, shift):  # noqa
         out.append((case.W(), case.C(), dX.cpu().numpy(), idx.cpu().numpy(), sc.cpu().numpy()))
     for p, q in zip(*out):
         assert np.array_equal(p, q)
+
+
+@pytest.mark.parametrize("B,d,L", [
+    (1, 384, 33),       # two slabs of samples, fewer than the ring's stages; one label slab and one row per slice
+    (128, 128, 31),     # four, as many as stages; less than one label block
+    (300, 640, 257),    # ten; half a column tile, one row beyond a label tile
+    (321, 256, 1025),   # the last samples in a slab of their own
+])
+@pytest.mark.parametrize("fmt,flags,T", [(o.BF16, o.FLAG_SR, 0), (o.E4M3, o.FLAG_SR | o.FLAG_KAHAN, 0), (o.E4M3, o.FLAG_SR, 64), (o.BF16, o.FLAG_SR, 64)])
+def test_short_rings_and_cut_blocks(b, fmt, flags, T, B, d, L):  # noqa: F811
+    """Products over fewer slabs than the rings have stages, and gradients whose label blocks and octets of samples are cut."""
+    case = Case(b, L, d, fmt, L, flags, B, w_std=0.05, seed=11, **({"dropout_p": T / 256} if T else {}))
+    case.head.workspace.fill_(0x7F)
+    X, indptr, indices = batch(L, d, B, rule="fixed5")
+    tol = 6e-2 if fmt == o.E4M3 else 2e-2
+    if not T:
+        check_step(case, X, indptr, indices, 0.05, 3, 1, tol)
+        return
+    ref = o.head_step(case.W0, None, X, indptr, indices, 0.05, 3, 1, fmt, flags, dropout=T)
+    dX, _ = case.step(X, indptr, indices, 0.05, 3, 1)
+    dist = np.abs(ordered(case.W(), fmt) - ordered(ref["W_new"], fmt))
+    assert np.mean(dist <= 1) >= 0.999
+    assert_dx_close(dX, ref["dX_partial"], tol)
