@@ -907,10 +907,6 @@ k_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restr
       creg[it][1] = *reinterpret_cast<const u32x4*>(Cc + eoff + 8);
     }
   };
-  if (has_cols) {   // passes 0 and 1 of the first half before the product, passes 2 and 3 right after it
-#pragma unroll
-    for (int it = 0; it < 2; ++it) fetch(it, 0);
-  }
 
   f32x16 acc[2][4];
   zero_acc(acc);
@@ -940,6 +936,10 @@ k_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restr
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+      },
+      NoPrep{},
+      [&]() {       // passes 0 and 1 of the first half before the product, passes 2 and 3 right after it
+        if (has_cols) { fetch(0, 0); fetch(1, 0); }
       });
   if (!has_cols) return;                             // after the ring's last barrier: no barrier follows
 #pragma unroll

@@ -268,12 +268,17 @@ template <int LPS, int N> __device__ inline void wait_slabs(int left) {   // at 
   else if (left >= N) wait_vmcnt<N * LPS>();
   else wait_slabs<LPS, N - 1>(left);
 }
-template <int NST, int SBYTES, int LPS, class F, class Issue, class Ld, class Mm, class Prep = NoPrep>
-__device__ __forceinline__ void ring_alternate(int nk, char* __restrict__ smem, bool upper, Issue&& issue, Ld&& ld, Mm&& mm, Prep&& prep = Prep{}) {
+// extra(), if given, may issue loads of the caller's own, behind those of the first slabs (ahead of them the first slab would be
+// waited for as long as they).
+template <int NST, int SBYTES, int LPS, class F, class Issue, class Ld, class Mm, class Prep = NoPrep, class Extra = NoPrep>
+__device__ __forceinline__ void ring_alternate(int nk, char* __restrict__ smem, bool upper, Issue&& issue, Ld&& ld, Mm&& mm, Prep&& prep = Prep{},
+                                               Extra&& extra = Extra{}) {
   constexpr bool HAS_PREP = !std::is_same<std::remove_cv_t<std::remove_reference_t<Prep>>, NoPrep>::value;
+  constexpr bool HAS_EXTRA = !std::is_same<std::remove_cv_t<std::remove_reference_t<Extra>>, NoPrep>::value;
   static_assert(NST >= 3 && (NST - 1) * LPS <= 63, "ring depth");
   for (int s = 0; s < NST - 1; ++s)
     if (s < nk) issue(s, s * SBYTES);
+  if constexpr (HAS_EXTRA) extra();
   wait_slabs<LPS, NST - 2>(nk - 1);
   if constexpr (HAS_PREP) prep(smem, 0);
   barrier_lds();
