@@ -316,6 +316,33 @@ int launch_dx_update(hipStream_t st, int grid, bool sr, bool kahan, bool dx, con
 #undef ELMO_DXU3
 }
 
+// The same for padded batches of 129 to 256 rows.
+template <int FMT, bool SR, bool KAHAN, bool WD, bool DROP>
+int launch_dx_update_wide_one(hipStream_t st, int grid, const char* Gt, const char* XT, char* Wc, uint16_t* Cc, float* dXacc, int n, int d, int Bp,
+                              float lr, float wd, uint64_t seed, uint64_t step, uint64_t elem0, int tpg, bool first, elmo::DropArgs dr) {
+  constexpr int smem = elmo::dxw_smem_bytes<FMT, KAHAN, DROP>();
+  static_assert(smem <= 160 * 1024, "LDS plan of the wide one-pass kernel");
+  static std::once_flag once;
+  static hipError_t attr_rc = hipSuccess;
+  std::call_once(once, [] {
+    attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(&elmo::k_dx_update_wide<FMT, SR, KAHAN, WD, DROP>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  });
+  if (attr_rc != hipSuccess) return fail(-3, "hipFuncSetAttribute(k_dx_update_wide) failed: %s", hipGetErrorString(attr_rc));
+  elmo::k_dx_update_wide<FMT, SR, KAHAN, WD, DROP><<<grid, elmo::kGemmThreads, smem, st>>>(Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed, step,
+                                                                                          elem0, tpg, first, dr);
+  return 0;
+}
+template <int FMT, bool SR, bool KAHAN>
+int launch_dx_update_wide(hipStream_t st, int grid, const char* Gt, const char* XT, char* Wc, uint16_t* Cc, float* dXacc, int n, int d, int Bp,
+                          float lr, float wd, uint64_t seed, uint64_t step, uint64_t elem0, int tpg, bool first, elmo::DropArgs dr) {
+#define ELMO_DXW(WD_, DR_) return launch_dx_update_wide_one<FMT, SR, KAHAN, WD_, DR_>(st, grid, Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed, step, elem0, tpg, first, dr)
+  if (dr.thresh) { if (wd != 0.0f) ELMO_DXW(true, true); ELMO_DXW(false, true); }
+  if (wd != 0.0f) ELMO_DXW(true, false);
+  ELMO_DXW(false, false);
+#undef ELMO_DXW
+}
+
 // Opt in to more than 64 KiB of dynamic LDS for the tile kernels: once per process, whichever
 // host thread comes first (std::call_once below); every caller sees the same outcome.
 int raise_lds_limits_once() {
@@ -418,27 +445,33 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   const bool small_batch = Bp <= 128 && d % 256 == 0 && !(p.drop_thresh && !fp8 && (p.flags & ELMO_KAHAN));
   const Pass ps = choose_pass(p, Bp, small_batch, dX_out != nullptr);
   uint16_t* Gt = (uint16_t*)(h->ws + ps.off_g);
-  const int col_blocks = d / 256, label_groups = small_batch ? std::max(1, 256 / col_blocks) : 0;   // widths above 65536: one group
+  // The same kernel in tiles of 128 columns up to 256 rows, as far as the planes of partial sums have room for groups that
+  // fill the chip (d = 384: 64 groups of 3 workgroups; d = 128, 64 workgroups, takes the separate kernels), and where an input
+  // gradient is asked for: the update alone has no second read of W to save (21293 E4M3 labels, B = 134: 39 us, 45 us here).
+  const int wide_groups = std::max(1, std::min(256 / (d / 128), p.dx_rows / 256));
+  const bool wide_batch = dX_out && Bp > 128 && Bp <= 256 && wide_groups * (d / 128) >= 192;
+  const bool fused = small_batch || wide_batch;
+  const int col_blocks = wide_batch ? d / 128 : d / 256, label_groups = wide_batch ? wide_groups : small_batch ? std::max(1, 256 / col_blocks) : 0;   // widths above 65536: one group
   // label slices of the input-gradient product: at most one 512-thread workgroup per CU, so the
   // whole grid is resident at once (256 CUs) and no second, nearly empty round of workgroups runs
   int S = std::max(1, 256 / (tiles_b * tiles_j));
   S = std::min(S, p.dx_rows / Bp256);
   S = std::max(1, std::min({S, 64, (int)((std::min<int64_t>(ps.labels, p.L) + 63) / 64)}));
-  // planes of partial sums; the small-batch kernel uses as many as its largest launch has label groups
+  // planes of partial sums; the fused kernel uses as many as its largest launch has label groups
   int dx_slices = S;
-  if (small_batch) {
+  if (fused) {
     dx_slices = 1;
     auto groups = [&](int64_t n) {
       const int64_t t = (n + 31) / 32, per = (t + label_groups - 1) / label_groups;
       return n > 0 ? (int)((t + per - 1) / per) : 0;
     };
-    const int64_t full = p.L / ps.labels, edge = p.kahan_rows % ps.labels;      // whole chunks; labels with compensation in the chunk where they end
-    const int64_t at_edge = std::min<int64_t>(ps.labels, p.L - p.kahan_rows / ps.labels * ps.labels);
-    for (int64_t n : {full ? ps.labels : (int64_t)0, p.L - full * ps.labels, edge, edge ? at_edge - edge : (int64_t)0})
-      dx_slices = std::max(dx_slices, groups(n));
+    for (int64_t c0 = 0; c0 < p.L; c0 += ps.take(p.L - c0)) {
+      const int64_t n = ps.take(p.L - c0), head = std::max<int64_t>(0, std::min(n, p.kahan_rows - c0));
+      dx_slices = std::max({dx_slices, groups(head), groups(n - head)});
+    }
   }
   bool dx_first = true;                                        // no launch has written the planes yet
-  const int dx_plane_rows = small_batch ? 128 : Bp256;
+  const int dx_plane_rows = small_batch ? 128 : Bp256;       // (256 for the fused kernel's wide batches)
 
   Profiler& prof = h->prof;
   prof.mark(st, CLS_SETUP);
@@ -492,7 +525,7 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
     // (Kahan summation for head labels), the others are updated without it.
     const bool sr = p.flags & ELMO_SR;
     const int n_head = (int)std::max<int64_t>(0, std::min<int64_t>(n, p.kahan_rows - c0));
-    if (small_batch) {
+    if (fused) {
       prof.mark(st, CLS_UPDATE);
       for (int part = 0; part < 2; ++part) {
         const int l_off = part ? n_head : 0, n_part = part ? n - n_head : n_head;   // n_head is a multiple of 32 or all of n
@@ -505,9 +538,19 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
         const char* Gp = (const char*)(Gt + (size_t)l_off * Bp);
         char* Wp = Wc + (size_t)l_off * d * esz;
         uint16_t* Cp = kahan ? Cc + (size_t)l_off * d : nullptr;
+        const int grid = groups_used * col_blocks;
         int rc;
-        if (fp8) rc = launch_dx_update<elmo::FMT_E4M3>(st, groups_used * col_blocks, sr, kahan, dX_out != nullptr, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, first, dr);
-        else rc = launch_dx_update<elmo::FMT_BF16>(st, groups_used * col_blocks, sr, kahan, dX_out != nullptr, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, first, dr);
+#define ELMO_WIDE(F, SR_, KA_) rc = launch_dx_update_wide<F, SR_, KA_>(st, grid, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, first, dr)
+#define ELMO_WIDE_F(F)                                                                          \
+  do {                                                                                          \
+    if (sr) { if (kahan) ELMO_WIDE(F, true, true); else ELMO_WIDE(F, true, false); }            \
+    else { if (kahan) ELMO_WIDE(F, false, true); else ELMO_WIDE(F, false, false); }             \
+  } while (0)
+        if (wide_batch) { if (fp8) ELMO_WIDE_F(elmo::FMT_E4M3); else ELMO_WIDE_F(elmo::FMT_BF16); }
+        else if (fp8) rc = launch_dx_update<elmo::FMT_E4M3>(st, grid, sr, kahan, dX_out != nullptr, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, first, dr);
+        else rc = launch_dx_update<elmo::FMT_BF16>(st, grid, sr, kahan, dX_out != nullptr, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, first, dr);
+#undef ELMO_WIDE_F
+#undef ELMO_WIDE
         if (rc) return rc;
         dx_first = false;
         if (int rc2 = check_launch("k_dx_update")) return rc2;
@@ -546,7 +589,7 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   if (dX_out || loss_out) {
     const int groups = dX_out ? (B + 31) / 32 * (d / 32) * 4 : 0;
     elmo::k_finalize<<<groups + (loss_out ? 1 : 0), 64 * elmo::kFinalWaves, 0, st>>>(
-        dXacc, dx_slices, dx_plane_rows, B, d, groups, (uint16_t*)dX_out, loss_slots, p.ntiles * loss_tiles, loss_out);
+        dXacc, dx_slices, dx_plane_rows, B, d, groups, wide_batch ? dr.scale : 1.0f, (uint16_t*)dX_out, loss_slots, p.ntiles * loss_tiles, loss_out);
     if (int rc = check_launch("k_finalize")) return rc;
   }
   prof.mark(st, CLS_END);

@@ -357,7 +357,7 @@ __global__ void __launch_bounds__(kSetupThreads) k_step_setup(const uint16_t* __
 // ---------------------------------------------------------------------------------------------
 constexpr int kGemmThreads = 512;
 constexpr int kGemmWaves = 8;
-constexpr int kStages = 3;                                       // ring depth of the small-batch kernel
+constexpr int kStages = 3;                                       // ring depth of the one-pass kernels
 constexpr int kWideRingBytes = 2 * (256 + 256) * 128;            // K-contiguous operands, 128-byte slabs, 2 stages
 
 // Register fragments of one step of a product: FM x FN blocks of 32 x 32 outputs.
@@ -644,6 +644,17 @@ k_logits(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wc, i
 __device__ inline f32x4* dx_block(float* plane, int d, int row0, int col0) {
   return reinterpret_cast<f32x4*>(plane + ((size_t)(row0 >> 5) * (d >> 5) + (col0 >> 5)) * 1024);
 }
+// NB blocks of a wave at src + b * 256.
+template <int NB> __device__ __forceinline__ void load_acc_blocks(const f32x4* __restrict__ src, int lane, f32x16 (&acc)[NB]) {
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 v = src[b * 256 + q * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[b][4 * q + e] = v[e];
+    }
+}
 // NB blocks of a wave, at dst + b * 256: += acc[b], or = acc[b] in the step's first pass over the plane
 // (which is why the planes need no clearing).  The loads of one block are in flight while the block
 // before it is added and stored.
@@ -767,7 +778,7 @@ k_dx(const char* __restrict__ Gt, const char* __restrict__ Wc, float* __restrict
 // The last workgroup of the grid sums the losses.
 constexpr int kFinalWaves = 8;
 __global__ void __launch_bounds__(64 * kFinalWaves) k_finalize(const float* __restrict__ dXacc, int S, int plane_rows, int B, int d, int groups,
-                                                               uint16_t* __restrict__ dX_out, const float* __restrict__ loss_slots,
+                                                               float scale, uint16_t* __restrict__ dX_out, const float* __restrict__ loss_slots,
                                                                int nslots, float* __restrict__ loss_out) {
   __shared__ f32x4 part[kFinalWaves][64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -792,7 +803,7 @@ __global__ void __launch_bounds__(64 * kFinalWaves) k_finalize(const float* __re
   const int row = (blk / (d >> 5)) * 32 + 8 * q + 4 * (lane >> 5), col = (blk % (d >> 5)) * 32 + (lane & 31);
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    if (row + e < B) dX_out[(size_t)(row + e) * d + col] = (uint16_t)bf16_rne(s[e]);
+    if (row + e < B) dX_out[(size_t)(row + e) * d + col] = (uint16_t)bf16_rne(s[e] * scale);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -808,16 +819,20 @@ constexpr int kUpdateEpiBytes = kGemmWaves * 32 * kGPitch * 4;   // one 32 x 128
 constexpr int kUpdateStages = 4, kUpdateStageBytes = (256 + 256) * 64;    // [8 blocks of gradients | 8 blocks of inputs] x 32 samples
 constexpr int kUpdateSmem = kUpdateEpiBytes > kUpdateStages * kUpdateStageBytes ? kUpdateEpiBytes : kUpdateStages * kUpdateStageBytes;
 
-// Sixteen consecutive elements of one weight row: storage bits in, storage bits out.
-// E4M3: w[0..3] hold 4 codes each; BF16: w[0..7] hold 2 patterns each.  c[0..7]: BF16 compensation.
+// N (8 or 16) consecutive elements of one weight row: storage bits in, storage bits out.
+// E4M3: w[0 .. N/4-1] hold 4 codes each; BF16: w[0 .. N/2-1] hold 2 patterns each.  c[0 .. N/2-1]: BF16 compensation.
 // WD = false ignores wd (the two extra operations of the decay are not even selected away).
-template <int FMT, bool SR, bool KAHAN, bool WD>
-__device__ inline void update16_wd(uint32_t (&w)[8], uint32_t (&c)[8], const float (&g)[16], float lr, float wd_, const U4 (&rb)[2]) {
+template <int FMT, bool SR, bool KAHAN, bool WD, int N>
+__device__ inline void update_wd(uint32_t (&w)[8], uint32_t (&c)[8], const float (&g)[N], float lr, float wd_, const U4 (&rb)[N / 8]) {
   const float wd = WD ? wd_ : 0.0f;
-  const uint32_t rw[8] = {rb[0].x, rb[0].y, rb[0].z, rb[0].w, rb[1].x, rb[1].y, rb[1].z, rb[1].w};
+  uint32_t rw[N / 2];
+#pragma unroll
+  for (int i = 0; i < N / 8; ++i) {
+    rw[4 * i] = rb[i].x; rw[4 * i + 1] = rb[i].y; rw[4 * i + 2] = rb[i].z; rw[4 * i + 3] = rb[i].w;
+  }
   if (FMT == FMT_E4M3) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < N / 4; ++q) {
       // four codes at a time: the packed conversion decodes two E4M3 bytes per instruction (exact)
       const f32x2 wlo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[q], 1.0f, false);
       const f32x2 whi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[q], 1.0f, true);
@@ -855,7 +870,7 @@ __device__ inline void update16_wd(uint32_t (&w)[8], uint32_t (&c)[8], const flo
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < N; ++i) {
       uint32_t wb = (w[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu;
       uint32_t cb = KAHAN ? (c[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu : 0u;
       const uint32_t r16 = SR ? ((rw[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu) : 0u;
@@ -992,7 +1007,7 @@ k_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restr
         rb[0] = sr_block(blk, seed, step);
         rb[1] = sr_block(blk + 1, seed, step);
       }
-      update16_wd<FMT, SR, KAHAN, WD>(w, c, g, lr, wd, rb);
+      update_wd<FMT, SR, KAHAN, WD, 16>(w, c, g, lr, wd, rb);
       char* wp = Wc + eoff * ESZ;
       *reinterpret_cast<u32x4*>(wp) = u32x4{w[0], w[1], w[2], w[3]};
       if (WQ == 2) *reinterpret_cast<u32x4*>(wp + 16) = u32x4{w[4], w[5], w[6], w[7]};
@@ -1184,7 +1199,7 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
         rb[0] = sr_block(blk, seed, step);
         rb[1] = sr_block(blk + 1, seed, step);
       }
-      update16_wd<FMT, SR, KAHAN, WD>(w, cc, gr, lr, wd, rb);
+      update_wd<FMT, SR, KAHAN, WD, 16>(w, cc, gr, lr, wd, rb);
       char* wp = Wc + eoff * ESZ;
       *reinterpret_cast<u32x4*>(wp) = u32x4{w[0], w[1], w[2], w[3]};
       if (ESZ == 2) *reinterpret_cast<u32x4*>(wp + 16) = u32x4{w[4], w[5], w[6], w[7]};
@@ -1213,6 +1228,207 @@ k_dx_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __re
             int tiles_per_group, bool first, DropArgs dr) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   dx_update_body<FMT, SR, KAHAN, DX, WD, DROP>(Gt, XT, Wc, Cc, dXacc, n, d, Bp, lr, wd, seed, step, elem0, tiles_per_group, first, dr, smem);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same for padded batches of 129 to 256 rows, in tiles of 32 labels x 128 columns.  With twice the samples the X operand of the
+// gradient product (64 registers a lane) and the slice of dX (128) no longer fit into one wave, so the waves have a role each: waves
+// 0-3 form the gradient of 32 columns over all samples, waves 4-7 the dX of 64 samples x 128 columns, 16 MFMAs a tile either way, and a
+// SIMD holds one of each.  The update of a tile, by all eight, comes one tile late: while the upper waves update tile t - 1 the
+// lower ones multiply tile t, then they change places, so the matrix cores work behind the vector ALU (a tile's update is some
+// 1.5 k clocks of it on a SIMD, its products 1 k) and a tile costs one barrier.  The new weights are read
+// from the tile into registers an iteration before they are updated, which is what lets three stages do.
+// 131072 BF16 labels with compensation, B = 256, d = 768, per pass of 43520 labels: input gradient 36 us and update 71 us as separate
+// kernels, 83 us here, and a launch and a third of the partial sums less; all waves in the same role, products and update in
+// turn (two waves to a gradient sum, 128 samples each): 95 us; the sums of earlier passes added at the end, not loaded at the start: 88 us.
+// ---------------------------------------------------------------------------------------------
+template <int FMT, bool KAHAN> constexpr int dxw_stage_bytes() {
+  return 32 * 128 * (FMT == FMT_E4M3 ? 1 : 2) + 32 * 512 + (KAHAN ? 32 * 256 : 0);
+}
+constexpr int kDxwGsPitch = 132;
+// three stages, two gradient tiles, and with dropout the masked copy of the W tile that the input gradient reads and its keep bits
+template <int FMT, bool KAHAN, bool DROP> constexpr int dxw_smem_bytes() {
+  return kStages * dxw_stage_bytes<FMT, KAHAN>() + 2 * 32 * kDxwGsPitch * 4 + (DROP ? 32 * 128 * (FMT == FMT_E4M3 ? 1 : 2) + 512 : 0);
+}
+template <int FMT, bool SR, bool KAHAN, bool WD, bool DROP, bool LOWER>
+__device__ __forceinline__ void dx_update_wide_role(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restrict__ Wc,
+                                                    uint16_t* __restrict__ Cc, float* __restrict__ plane, int n, int d, int Bp, float lr,
+                                                    float wd, uint64_t seed, uint64_t step, uint64_t elem0, int t0, int t1, int j0, bool first,
+                                                    DropArgs dr, char* __restrict__ smem) {
+  constexpr int ESZ = FMT == FMT_E4M3 ? 1 : 2, WROWB = 128 * ESZ;
+  constexpr int WBYTES = 32 * WROWB, GBYTES = 32 * 512, SBYTES = dxw_stage_bytes<FMT, KAHAN>();
+  constexpr bool LOADS_W = ESZ == 2 || LOWER;                // 4 KiB of E4M3 weights: by the lower waves alone
+  constexpr int LPS = (LOADS_W ? 1 : 0) + 2 + (KAHAN ? 1 : 0), NSTORE = 1 + (KAHAN ? 1 : 0);   // loads and stores per wave and tile
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), rw = wave & 3;
+  const size_t strip = blk_strip(Bp);
+  char* gs0 = smem + kStages * SBYTES;
+  char* wmk = gs0 + 2 * 32 * kDxwGsPitch * 4;
+  uint16_t* keep = reinterpret_cast<uint16_t*>(wmk + WBYTES);
+
+  const int xoct = (Bp >> 3) - 1, KS = Bp >> 4;              // last octet of the samples; k16 steps over them: 12 or 16
+  bf16x8 xt[LOWER ? 16 : 1];                                 // lower: X^T fragments of columns 32 rw ..
+  f32x16 dxa[LOWER ? 1 : 2][4];                              // upper: dX of samples 64 rw .., all columns
+  if constexpr (LOWER) {
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks)
+      xt[ks] = *reinterpret_cast<const bf16x8*>(XT + (size_t)((j0 >> 5) + rw) * strip + blk_off(min(2 * ks + (lane >> 5), xoct), lane & 31));
+  } else {
+    // the sums of the passes before are where this one's begin: their loads are all in flight at once, beside the first tiles'
+    zero_acc(dxa);
+    if (!first)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        if (64 * rw + 32 * s < Bp) load_acc_blocks<4>(dx_block(plane, d, 64 * rw + 32 * s, j0), lane, dxa[s]);
+  }
+  auto issue = [&](int t) {
+    char* st = smem + (t % kStages) * SBYTES;
+    const int l0 = t << 5, valid = n - l0;
+    if constexpr (LOADS_W) dma_tile<32, WROWB, ESZ == 2 ? 8 : 4>(Wc + ((size_t)l0 * d + j0) * ESZ, (size_t)d * ESZ, valid, st, wave, lane);
+    // rows of G^T past n exist and hold zeros (written by the logits kernel): no clamping, so they add nothing to dX
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      dma_kib(Gt + (size_t)t * strip + (size_t)min(2 * wave + i, KS - 1) * 1024, st + WBYTES + (2 * wave + i) * 1024, lane);
+    if constexpr (KAHAN)
+      dma_tile<32, 256, kGemmWaves>(reinterpret_cast<const char*>(Cc) + ((size_t)l0 * d + j0) * 2, (size_t)d * 2, valid, st + WBYTES + GBYTES, wave, lane);
+  };
+  // this thread's part of a tile: one label row, eight consecutive columns; its weights and compensation, an iteration ahead of their update
+  const int l = tid >> 4, seg = tid & 15;
+  uint32_t w[8], cc[8];
+  auto fetch = [&](const char* st) {
+    if constexpr (ESZ == 1) {
+      const uint2 v = *reinterpret_cast<const uint2*>(st + tile_off<WROWB>(l, seg >> 1) + (seg & 1) * 8);
+      w[0] = v.x; w[1] = v.y;
+    } else {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(st + tile_off<WROWB>(l, seg));
+      w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
+    }
+    if constexpr (KAHAN) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(st + WBYTES + GBYTES + tile_off<256>(l, seg));
+      cc[0] = v[0]; cc[1] = v[1]; cc[2] = v[2]; cc[3] = v[3];
+    }
+  };
+  uint32_t kept = 0;                                         // DROP: keep bits of the eight weights
+  // DROP, lower: this thread's part of the step's keep mask (appendix "Low-Memory Dropout for Classifier"), a row's 16 elements, drawn a
+  // tile ahead; the input gradient reads a masked copy of the tile, the update masks the gradient
+  const int mr = (tid & 255) >> 3, mb = tid & 7;
+  uint32_t m[4];
+  auto draw = [&](int t) {
+    const U4 b = drop_block((elem0 + (size_t)((t << 5) + mr) * d + j0 + mb * 16) >> 4, seed, step);
+    const uint32_t tb = dr.thresh * 0x01010101u;
+    m[0] = keep_bytes(b.x, tb); m[1] = keep_bytes(b.y, tb); m[2] = keep_bytes(b.z, tb); m[3] = keep_bytes(b.w, tb);
+  };
+  if constexpr (DROP && LOWER) draw(t0);
+  auto update = [&](int t, int rows) {                       // rows: n, or 0 where there is nothing to store
+    const float* gs = reinterpret_cast<const float*>(gs0) + (t & 1) * 32 * kDxwGsPitch + l * kDxwGsPitch + seg * 8;
+    const f32x4 ga = *reinterpret_cast<const f32x4*>(gs), gb = *reinterpret_cast<const f32x4*>(gs + 4);
+    float g[8] = {ga[0], ga[1], ga[2], ga[3], gb[0], gb[1], gb[2], gb[3]};
+    if (DROP) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) g[i] = ((kept >> i) & 1u) ? g[i] * dr.scale : 0.0f;
+    }
+    const int row = (t << 5) + l;
+    const size_t eoff = (size_t)row * d + j0 + seg * 8;
+    U4 rb[1];
+    if (SR) rb[0] = sr_block((elem0 + eoff) >> 3, seed, step);
+    update_wd<FMT, SR, KAHAN, WD, 8>(w, cc, g, lr, wd, rb);
+    if ((uint32_t)row < (uint32_t)rows) {                    // (before the first tile the row may be negative)
+      char* wp = Wc + eoff * ESZ;
+      if constexpr (ESZ == 1) *reinterpret_cast<uint2*>(wp) = make_uint2(w[0], w[1]);
+      else *reinterpret_cast<u32x4*>(wp) = u32x4{w[0], w[1], w[2], w[3]};
+      if constexpr (KAHAN) *reinterpret_cast<u32x4*>(Cc + eoff) = u32x4{cc[0], cc[1], cc[2], cc[3]};
+    }
+  };
+  if (t0 < t1) issue(t0);
+  if (t0 + 1 < t1) issue(t0 + 1);
+  for (int t = t0; t < t1; ++t) {
+    // Tile t's loads were issued two iterations ago; younger are the loads of tile t + 1 and the stores of the two updates since, of
+    // which one may be waited for (loads and stores retire in issue order and share vmcnt).  Every wave issues its
+    // stores in every tile but a ragged last one, after which nothing is waited for.
+    if (t + 1 >= t1) wait_vmcnt<0>();
+    else if (t < t0 + 2) wait_vmcnt<LPS>();
+    else wait_vmcnt<LPS + NSTORE>();
+    barrier_lds();                                           // tile t, and the gradient of tile t - 1
+    if (t + 2 < t1) issue(t + 2);
+    const char* st = smem + (t % kStages) * SBYTES;
+    const char* gsl = st + WBYTES;
+    if constexpr (LOWER) {
+      if constexpr (DROP) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bits |= (((m[i] & 0x01010101u) * 0x01020408u) >> 24 & 15u) << (4 * i);
+        keep[mr * 8 + mb] = (uint16_t)bits;
+        if constexpr (ESZ == 1) {
+          const int o = tile_off<WROWB>(mr, mb);
+          *reinterpret_cast<u32x4*>(wmk + o) = *reinterpret_cast<const u32x4*>(st + o) & u32x4{m[0], m[1], m[2], m[3]};
+        } else {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int o = tile_off<WROWB>(mr, 2 * mb + h);
+            *reinterpret_cast<u32x4*>(wmk + o) = *reinterpret_cast<const u32x4*>(st + o) &
+                u32x4{__builtin_amdgcn_perm(m[2 * h], m[2 * h], 0x01010000u), __builtin_amdgcn_perm(m[2 * h], m[2 * h], 0x03030202u),
+                      __builtin_amdgcn_perm(m[2 * h + 1], m[2 * h + 1], 0x01010000u), __builtin_amdgcn_perm(m[2 * h + 1], m[2 * h + 1], 0x03030202u)};
+          }
+        }
+        barrier_lds();
+      }
+      f32x16 wa;                                             // grad[32 labels x 32 columns] = G^T X
+#pragma unroll
+      for (int v = 0; v < 16; ++v) wa[v] = 0.0f;
+#pragma unroll
+      for (int ks = 0; ks < 16; ++ks)
+        if (ks < KS) wa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_blk(gsl, ks, lane), xt[ks], wa, 0, 0, 0);
+      if constexpr (DROP) draw(t + 1);
+      update(t - 1, t > t0 ? n : 0);
+      float* gs = reinterpret_cast<float*>(gs0) + (t & 1) * 32 * kDxwGsPitch;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) gs[acc_row(v, lane) * kDxwGsPitch + 32 * rw + (lane & 31)] = wa[v];
+    } else {
+      if constexpr (DROP) barrier_lds();
+      update(t - 1, t > t0 ? n : 0);
+      const char* wdx = DROP ? wmk : st;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {                       // dX += G W_tile (weights as stored before the update)
+        bf16x8 a[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) a[s] = frag_tr_blk(gsl, 16 * kk, 64 * rw + 32 * s, lane);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          bf16x8 b;
+          if constexpr (ESZ == 1) b = frag_tr_fp8<WROWB>(wdx, 16 * kk, 32 * q, lane);
+          else b = frag_tr_bf16<WROWB>(wdx, 16 * kk, 32 * q, lane);
+#pragma unroll
+          for (int s = 0; s < 2; ++s) dxa[s][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], b, dxa[s][q], 0, 0, 0);
+        }
+      }
+    }
+    fetch(st);
+    if constexpr (DROP) kept = keep[l * 8 + (seg >> 1)] >> (8 * (seg & 1));
+  }
+  if (t0 < t1) {
+    barrier_lds();
+    update(t1 - 1, n);
+  }
+  if constexpr (!LOWER) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)            // rows beyond the padded batch are never read; with dropout 1 / (1 - p) comes with the final sum
+      if (64 * rw + 32 * s < Bp) add_acc_blocks<4>(dx_block(plane, d, 64 * rw + 32 * s, j0), lane, dxa[s], true);
+  }
+}
+
+template <int FMT, bool SR, bool KAHAN, bool WD, bool DROP>
+__global__ void __launch_bounds__(kGemmThreads, 1)
+k_dx_update_wide(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restrict__ Wc, uint16_t* __restrict__ Cc,
+                 float* __restrict__ dXacc, int n, int d, int Bp, float lr, float wd, uint64_t seed, uint64_t step, uint64_t elem0,
+                 int tiles_per_group, bool first, DropArgs dr) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int C = d >> 7, wg = xcd_logical_id(blockIdx.x, gridDim.x), g = wg / C, c = wg % C;
+  const int t0 = g * tiles_per_group, t1 = min(t0 + tiles_per_group, (n + 31) >> 5);
+  if (t0 >= t1 && !first) return;                            // (in the first pass every group writes its dX plane)
+  float* plane = dXacc + (size_t)g * 256 * d;
+  if (threadIdx.x < 256)
+    dx_update_wide_role<FMT, SR, KAHAN, WD, DROP, true>(Gt, XT, Wc, Cc, plane, n, d, Bp, lr, wd, seed, step, elem0, t0, t1, c << 7, first, dr, smem);
+  else
+    dx_update_wide_role<FMT, SR, KAHAN, WD, DROP, false>(Gt, XT, Wc, Cc, plane, n, d, Bp, lr, wd, seed, step, elem0, t0, t1, c << 7, first, dr, smem);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -381,3 +381,34 @@ def test_short_rings_and_cut_blocks(b, fmt, flags, T, B, d, L):  # noqa: F811
     dist = np.abs(ordered(case.W(), fmt) - ordered(ref["W_new"], fmt))
     assert np.mean(dist <= 1) >= 0.999
     assert_dx_close(dX, ref["dX_partial"], tol)
+
+
+@pytest.mark.parametrize("B,d,L,kahan_rows", [
+    (129, 256, 31, 0),      # the fewest rows, less than a label tile
+    (192, 640, 97, 0),      # the second half of the samples half empty
+    (193, 384, 4133, 128),  # one row beyond 192; compensation for the first tiles, a launch each
+    (256, 768, 3000, 0),    # the most rows; groups of three label tiles, the last with fewer
+])
+@pytest.mark.parametrize("fmt,flags,T,wd", [(o.E4M3, o.FLAG_SR | o.FLAG_KAHAN, 0, 0.0), (o.E4M3, o.FLAG_SR, 64, 0.01), (o.BF16, o.FLAG_KAHAN, 64, 0.0), (o.BF16, o.FLAG_SR, 0, 0.0)])
+def test_one_pass_kernel_of_129_to_256_rows(b, fmt, flags, T, wd, B, d, L, kahan_rows):  # noqa: F811
+    """Input gradient and update in one pass over 128-column tiles, two waves to a gradient sum."""
+    kr = kahan_rows if flags & o.FLAG_KAHAN else 0
+    case = Case(b, L, d, fmt, L, flags, B, w_std=0.05, comp_std=2e-4 if flags & o.FLAG_KAHAN else 0.0, seed=12, kahan_rows=kr, weight_decay=wd, dropout_p=T / 256)
+    case.head.workspace.fill_(0x7F)
+    X, indptr, indices = batch(L, d, B, rule="fixed5")
+    C0 = case.C0
+    if kr:
+        C0 = np.zeros((L, d), np.uint16)
+        C0[:kr] = case.C0
+    ref = o.head_step(case.W0, C0, X, indptr, indices, 0.05, 3, 1, fmt, flags, kahan_rows=kr or None, weight_decay=wd, dropout=T)
+    dX, loss = case.step(X, indptr, indices, 0.05, 3, 1)
+    dist = np.abs(ordered(case.W(), fmt) - ordered(ref["W_new"], fmt))
+    assert np.mean(dist <= 1) >= 0.999
+    assert_far_misses_are_tiny(case.W(), ref["W_new"], dist, fmt, 0.05)
+    assert_dx_close(dX, ref["dX_partial"], 6e-2 if fmt == o.E4M3 else 2e-2)
+    assert abs(loss - ref["loss"]) <= 2e-3 * abs(ref["loss"])
+    if flags & o.FLAG_KAHAN:
+        n = kr or L
+        same = dist[:n] == 0
+        err = np.abs(o.decode_bf16(case.C()[:n]) - o.decode_bf16(ref["comp_new"][:n]))[same] / np.maximum(np.abs(o.decode(ref["W_new"][:n], fmt)), 2.0**-9)[same]
+        assert np.quantile(err, 0.999) <= 2.0**-8
