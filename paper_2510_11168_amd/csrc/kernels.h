@@ -497,10 +497,10 @@ __device__ __forceinline__ void logits_slab_product(const char* sa, const char* 
 // Z tile = Xa[TB rows] . Wc[TB rows]^T over the full embedding width (rowb bytes per row), FP32
 // accumulators.  Waves as (8 / WGN) x WGN with WGN = 2 (TB = 256, 64 x 128 per wave) or 4
 // (TB = 128, 64 x 32 per wave).
-template <bool FP8, int TB, int FN, class Prep = NoPrep>
+template <bool FP8, int TB, int FN, class Prep = NoPrep, class Extra = NoPrep>
 __device__ __forceinline__ void logits_tile_product(const char* __restrict__ Xa, int a_valid, const char* __restrict__ Wc, int w_valid,
                                                     size_t rowb, char* smem, int wave, int lane, f32x16 (&acc)[2][FN],
-                                                    Prep&& prep = Prep{}) {
+                                                    Prep&& prep = Prep{}, Extra&& extra = Extra{}) {
   constexpr int WGN = TB / 32 / FN;
   static_assert(WGN == (TB == 256 ? 2 : 4), "wave layout");
   const int wm = wave / WGN, wn = wave % WGN;
@@ -508,7 +508,7 @@ __device__ __forceinline__ void logits_tile_product(const char* __restrict__ Xa,
   ring_pipeline_pp<TB, 128, TB, 128, 2, kGemmWaves, true>(
       Xa, rowb, a_valid, 0, 128, 8, Wc, rowb, w_valid, 0, 128, 8, (int)(rowb >> 7), smem, wave, lane,
       [&](const char* sa, const char* sb, int q0, int) { logits_slab_product<FP8, FN>(sa, sb, q0 >> 1, wm, wn, lane, acc); },
-      static_cast<Prep&&>(prep));
+      static_cast<Prep&&>(prep), static_cast<Extra&&>(extra));
 }
 
 // DROP: the W slabs are masked in LDS as they land (drop_slab) and Z is scaled by 1 / (1 - p);
@@ -534,32 +534,34 @@ k_logits(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wc, i
   const int gt0 = tile0 + lt * (TB / 128);                               // first of the tile's one or two bins
 
   // ---- positives of this tile's bins that fall into this batch tile -> bit mask.  The mask lives
-  // behind the ring, so it is built first: its loads overlap the first slabs' way in, and the K
-  // loop's barriers publish it.
-  for (int i = tid; i < TB * MW; i += kGemmThreads) ym[i] = 0u;
-  barrier_lds();
-  {
+  // behind the ring and is built behind the loads of the first slab, which its own two round trips overlap; the K
+  // loop's first barrier publishes it.
+  auto build_mask = [&]() {
+    for (int i = tid; i < TB * MW; i += kGemmThreads) ym[i] = 0u;
     const int p0 = binptr[gt0], p1 = binptr[gt0 + (rows_out >> 7)];
+    barrier_lds();
     for (int p = p0 + tid; p < p1; p += kGemmThreads) {
       const int2 e = pos[p];
       const int lr_ = e.x - (gt0 << 7), br = e.y - b0;
       if (br >= 0 && br < TB && lr_ >= 0 && lr_ < TB) atomicOr(&ym[lr_ * MW + (br >> 5)], 1u << (br & 31));
     }
-  }
-  barrier_lds();
+    __builtin_amdgcn_s_waitcnt(0xC07F);                                  // in LDS ahead of that barrier
+  };
 
   f32x16 acc[2][FN];
+  const char* xa = Xa + (size_t)b0 * rowb;
+  const char* wc = Wc + (size_t)l0 * rowb;
   if constexpr (DROP) {
     const uint64_t blk_tile = (elem0 + (uint64_t)l0 * d) >> 4;     // mask block of the tile's first element
-    logits_tile_product<FP8, TB, FN>(Xa + (size_t)b0 * rowb, a_rows - b0, Wc + (size_t)l0 * rowb, n - l0, rowb, smem, wave, lane, acc,
-                                     [&](char* sb, int ks) {
-                                       drop_slab<TB, 128, FP8>(sb, blk_tile + (uint64_t)ks * (FP8 ? 8 : 4), (uint32_t)d >> 4, seed,
-                                                               step, dr.thresh, tid);
-                                     });
+    logits_tile_product<FP8, TB, FN>(
+        xa, a_rows - b0, wc, n - l0, rowb, smem, wave, lane, acc,
+        [&](char* sb, int ks) {
+          drop_slab<TB, 128, FP8>(sb, blk_tile + (uint64_t)ks * (FP8 ? 8 : 4), (uint32_t)d >> 4, seed, step, dr.thresh, tid);
+        },
+        build_mask);
   } else {
-    logits_tile_product<FP8, TB, FN>(Xa + (size_t)b0 * rowb, a_rows - b0, Wc + (size_t)l0 * rowb, n - l0, rowb, smem, wave, lane, acc);
+    logits_tile_product<FP8, TB, FN>(xa, a_rows - b0, wc, n - l0, rowb, smem, wave, lane, acc, NoPrep{}, build_mask);
   }
-
 
   // ---- G = sigmoid(Z) - Y in registers, BF16, stored as two octets of a label block (1 KiB) per instruction.
   // Each wave finishes its own 64-sample x (32 FN)-label block on its own: one wave's stores overlap another's

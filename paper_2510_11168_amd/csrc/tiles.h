@@ -184,11 +184,13 @@ template <int ROWS, int ROWB> struct TileLoader {
 struct NoPrep {};
 // LATE_AFTER (1..3): the product of a slab is four quarters, mma(stageA, stageB, q0, q1, ks) runs
 // quarters [q0, q1); the late waves issue after LATE_AFTER of them (2 = between the two halves).
+// extra(), if given, runs once, behind the loads of the first slabs.
 template <int AROWS, int AROWB, int BROWS, int BROWB, int NST, int NW, bool UNEVEN, int LATE_AFTER = 2, class Src, class Mma,
-          class Prep = NoPrep>
+          class Prep = NoPrep, class Extra = NoPrep>
 __device__ inline void ring_stream_pp(const char* __restrict__ ga, size_t stride_a, int chunks_a, const char* __restrict__ gb,
                                       size_t stride_b, int chunks_b, int nk, char* smem, int wave, int lane, Src&& src, Mma&& mma,
-                                      Prep&& prep = Prep{}) {
+                                      Prep&& prep = Prep{}, Extra&& extra = Extra{}) {
+  constexpr bool HAS_EXTRA = !std::is_same<std::remove_cv_t<std::remove_reference_t<Extra>>, NoPrep>::value;
   constexpr bool HAS_PREP = !std::is_same<std::remove_cv_t<std::remove_reference_t<Prep>>, NoPrep>::value;
   constexpr int ABYTES = AROWS * AROWB, SBYTES = ABYTES + BROWS * BROWB, NH = NW / 2, BH = BROWS / 2;
   constexpr int LPS_ALL = dma_loads_per_wave<AROWS, AROWB, NW>() + dma_loads_per_wave<BROWS, BROWB, NW>();
@@ -215,6 +217,7 @@ __device__ inline void ring_stream_pp(const char* __restrict__ ga, size_t stride
   };
   for (int s = 0; s < NST - 1; ++s)
     if (s < nk) issue(s);
+  if constexpr (HAS_EXTRA) extra();
   for (int ks = 0; ks < nk; ++ks) {
     if (NST == 2 || ks + 1 >= nk) wait_vmcnt<0>();
     else if (late) wait_vmcnt<LPS_LATE>();
@@ -238,17 +241,18 @@ __device__ inline void ring_stream_pp(const char* __restrict__ ga, size_t stride
 }
 
 // One output tile: slab ks of an operand starts at g + ks*adv and has v0 - ks*dv valid rows.
-template <int AROWS, int AROWB, int BROWS, int BROWB, int NST, int NW, bool UNEVEN, int LATE_AFTER = 2, class Mma, class Prep = NoPrep>
+template <int AROWS, int AROWB, int BROWS, int BROWB, int NST, int NW, bool UNEVEN, int LATE_AFTER = 2, class Mma, class Prep = NoPrep,
+          class Extra = NoPrep>
 __device__ inline void ring_pipeline_pp(const char* __restrict__ ga, size_t stride_a, int va0, int dva, size_t adv_a, int chunks_a,
                                         const char* __restrict__ gb, size_t stride_b, int vb0, int dvb, size_t adv_b, int chunks_b,
-                                        int nk, char* smem, int wave, int lane, Mma&& mma, Prep&& prep = Prep{}) {
+                                        int nk, char* smem, int wave, int lane, Mma&& mma, Prep&& prep = Prep{}, Extra&& extra = Extra{}) {
   ring_stream_pp<AROWS, AROWB, BROWS, BROWB, NST, NW, UNEVEN, LATE_AFTER>(
       ga, stride_a, chunks_a, gb, stride_b, chunks_b, nk, smem, wave, lane,
       [&](int ks, size_t& off_a, int& va, size_t& off_b, int& vb) {
         off_a = (size_t)ks * adv_a; va = va0 - ks * dva;
         off_b = (size_t)ks * adv_b; vb = vb0 - ks * dvb;
       },
-      [&](const char* sa, const char* sb, int q0, int q1, int) { mma(sa, sb, q0, q1); }, static_cast<Prep&&>(prep));
+      [&](const char* sa, const char* sb, int q0, int q1, int) { mma(sa, sb, q0, q1); }, static_cast<Prep&&>(prep), static_cast<Extra&&>(extra));
 }
 
 // Alternating ring: the K loop of one output tile in slabs of two fragment steps.  Waves w and w + NW / 2 share a SIMD; the
