@@ -235,17 +235,17 @@ int poll_validation(elmo_head* h) {
 template <bool FP8, bool LOSS, int TB, bool DROP>
 void launch_logits_tb(hipStream_t st, int grid, const char* Xa, int a_rows, const char* Wc, int n, int d, int Bp, int B,
                       uint16_t* Gt, const int* binptr, const int2* pos, int tile0, float* loss_slots, uint64_t seed, uint64_t step,
-                      uint64_t elem0, elmo::DropArgs dr) {
+                      uint64_t elem0, elmo::DropArgs dr, elmo::DirectArgs da) {
   elmo::k_logits<FP8, LOSS, TB, DROP><<<grid, elmo::kGemmThreads, elmo::logits_smem<TB>(), st>>>(
-      Xa, a_rows, Wc, n, d, Bp, B, Gt, binptr, pos, tile0, loss_slots, seed, step, elem0, dr);
+      Xa, a_rows, Wc, n, d, Bp, B, Gt, binptr, pos, tile0, loss_slots, seed, step, elem0, dr, da);
 }
 // tb = rows of the batch tile (256, or 128 when the whole padded batch fits in 128 rows)
 template <bool FP8, bool LOSS>
 void launch_logits(hipStream_t st, int tb, int grid, const char* Xa, int a_rows, const char* Wc, int n, int d, int Bp, int B,
                    uint16_t* Gt, const int* binptr, const int2* pos, int tile0, float* loss_slots, uint64_t seed, uint64_t step,
-                   uint64_t elem0, elmo::DropArgs dr) {
+                   uint64_t elem0, elmo::DropArgs dr, elmo::DirectArgs da) {
 #define ELMO_LOGITS(TB_, DR_) \
-  launch_logits_tb<FP8, LOSS, TB_, DR_>(st, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, binptr, pos, tile0, loss_slots, seed, step, elem0, dr)
+  launch_logits_tb<FP8, LOSS, TB_, DR_>(st, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, binptr, pos, tile0, loss_slots, seed, step, elem0, dr, da)
   if (tb == 128) { if (dr.thresh) ELMO_LOGITS(128, true); else ELMO_LOGITS(128, false); }
   else { if (dr.thresh) ELMO_LOGITS(256, true); else ELMO_LOGITS(256, false); }
 #undef ELMO_LOGITS
@@ -316,7 +316,7 @@ int launch_dx_update(hipStream_t st, int grid, bool sr, bool kahan, bool dx, con
 #undef ELMO_DXU3
 }
 
-// The same for padded batches of 129 to 256 rows.
+// The same in tiles of 128 columns, up to 256 rows.
 template <int FMT, bool SR, bool KAHAN, bool WD, bool DROP>
 int launch_dx_update_wide_one(hipStream_t st, int grid, const char* Gt, const char* XT, char* Wc, uint16_t* Cc, float* dXacc, int n, int d, int Bp,
                               float lr, float wd, uint64_t seed, uint64_t step, uint64_t elem0, int tpg, bool first, elmo::DropArgs dr) {
@@ -445,11 +445,15 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   const bool small_batch = Bp <= 128 && d % 256 == 0 && !(p.drop_thresh && !fp8 && (p.flags & ELMO_KAHAN));
   const Pass ps = choose_pass(p, Bp, small_batch, dX_out != nullptr);
   uint16_t* Gt = (uint16_t*)(h->ws + ps.off_g);
-  // The same kernel in tiles of 128 columns up to 256 rows, as far as the planes of partial sums have room for groups that
+  // In tiles of 128 columns (k_dx_update_wide) up to 256 rows, as far as the planes of partial sums have room for groups that
   // fill the chip (d = 384: 64 groups of 3 workgroups; d = 128, 64 workgroups, takes the separate kernels), and where an input
-  // gradient is asked for: the update alone has no second read of W to save (21293 E4M3 labels, B = 134: 39 us, 45 us here).
+  // gradient is asked for: the update alone has no second read of W to save (21293 E4M3 labels, B = 134: 39 us, 45 us there).
+  // At most 128 rows take it where 256 does not divide d (300000 E4M3 labels, d = 640, B = 128: separate kernels 409 us, 283 us there) and where
+  // a workgroup has no more than four of its tiles (16384 E4M3 labels, d = 256, B = 64: 256 columns 29.5, 128 columns 25.7 us;
+  // 16384 x 768, twelve tiles: 35.7 and 36.1; 1 M labels, B = 128, with compensation: 1406 and 1472).
   const int wide_groups = std::max(1, std::min(256 / (d / 128), p.dx_rows / 256));
-  const bool wide_batch = dX_out && Bp > 128 && Bp <= 256 && wide_groups * (d / 128) >= 192;
+  const int64_t wide_tiles = (std::min<int64_t>(ps.labels, p.L) + 31) / 32 * (d / 128);
+  const bool wide_batch = dX_out && Bp <= 256 && (!small_batch || wide_tiles <= 4 * 256) && wide_groups * (d / 128) >= 192;
   const bool fused = small_batch || wide_batch;
   const int col_blocks = wide_batch ? d / 128 : d / 256, label_groups = wide_batch ? wide_groups : small_batch ? std::max(1, 256 / col_blocks) : 0;   // widths above 65536: one group
   // label slices of the input-gradient product: at most one 512-thread workgroup per CU, so the
@@ -457,12 +461,15 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   int S = std::max(1, 256 / (tiles_b * tiles_j));
   S = std::min(S, p.dx_rows / Bp256);
   S = std::max(1, std::min({S, 64, (int)((std::min<int64_t>(ps.labels, p.L) + 63) / 64)}));
+  // Label tiles per group.  Not one: a group's plane is as much work as a tile, here and in the final sum (8192 labels, d = 256, 256
+  // groups of one tile / 128 of two / 64 of four: B = 64 28.9 / 25.6 / 26.9 us, B = 128 35.7 / 31.3 / 30.6); below 129 tiles there are CUs to spare.
+  auto tiles_per_group = [&](int64_t tiles) { return std::max<int64_t>((tiles + label_groups - 1) / label_groups, !wide_batch && tiles > 128 ? 2 : 1); };
   // planes of partial sums; the fused kernel uses as many as its largest launch has label groups
   int dx_slices = S;
   if (fused) {
     dx_slices = 1;
     auto groups = [&](int64_t n) {
-      const int64_t t = (n + 31) / 32, per = (t + label_groups - 1) / label_groups;
+      const int64_t t = (n + 31) / 32, per = tiles_per_group(t);
       return n > 0 ? (int)((t + per - 1) / per) : 0;
     };
     for (int64_t c0 = 0; c0 < p.L; c0 += ps.take(p.L - c0)) {
@@ -471,12 +478,13 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
     }
   }
   bool dx_first = true;                                        // no launch has written the planes yet
-  const int dx_plane_rows = small_batch ? 128 : Bp256;       // (256 for the fused kernel's wide batches)
+  const int dx_plane_rows = fused && !wide_batch ? 128 : Bp256;
 
   Profiler& prof = h->prof;
   prof.mark(st, CLS_SETUP);
-  // ---- step set-up: inputs, zeroed partial sums, label index
-  {
+  // ---- step set-up: inputs, label index; a small BF16 step has none (the logits kernel finds its positives itself and makes X^T)
+  const bool direct = Bp <= 128 && !fp8 && !flag && nnz <= elmo::kDirectMaxNnz;
+  if (!direct) {
     const bool one_wg = elmo::index_in_one_workgroup(p.ntiles, B, nnz);
     const elmo::IndexArgs ia{indptr, indices, p.L, nnz, one_wg ? p.ntiles : 0, ptr, pos, flag};
     elmo::k_step_setup<<<1 + Bp / 64 * (d / 128), elmo::kSetupThreads, elmo::setup_smem(ia.nb, B), st>>>(
@@ -510,14 +518,16 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
     const int tile0 = (int)(c0 / 128);
     prof.mark(st, CLS_LOGITS);
     {
-      const int grid = ((n + tb - 1) / tb) * ((Bp + tb - 1) / tb);
+      const int tiles = ((n + tb - 1) / tb) * ((Bp + tb - 1) / tb), staging = direct && c0 == 0 ? Bp / 64 * (d / 128) : 0;
+      const int grid = tiles + staging;
+      const elmo::DirectArgs da = direct ? elmo::DirectArgs{indptr, indices, (int)nnz, staging ? tiles : 0, XT} : elmo::DirectArgs{};
       const uint64_t celem0 = (uint64_t)c0 * (uint64_t)d;
       if (fp8) {
-        if (loss_out) launch_logits<true, true>(st, tb, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, ptr, pos, tile0, loss_slots, seed, step, celem0, dr);
-        else launch_logits<true, false>(st, tb, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, ptr, pos, tile0, loss_slots, seed, step, celem0, dr);
+        if (loss_out) launch_logits<true, true>(st, tb, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, ptr, pos, tile0, loss_slots, seed, step, celem0, dr, da);
+        else launch_logits<true, false>(st, tb, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, ptr, pos, tile0, loss_slots, seed, step, celem0, dr, da);
       } else {
-        if (loss_out) launch_logits<false, true>(st, tb, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, ptr, pos, tile0, loss_slots, seed, step, celem0, dr);
-        else launch_logits<false, false>(st, tb, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, ptr, pos, tile0, loss_slots, seed, step, celem0, dr);
+        if (loss_out) launch_logits<false, true>(st, tb, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, ptr, pos, tile0, loss_slots, seed, step, celem0, dr, da);
+        else launch_logits<false, false>(st, tb, grid, Xa, a_rows, Wc, n, d, Bp, B, Gt, ptr, pos, tile0, loss_slots, seed, step, celem0, dr, da);
       }
       if (int rc = check_launch("k_logits")) return rc;
     }
@@ -531,7 +541,7 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
         const int l_off = part ? n_head : 0, n_part = part ? n - n_head : n_head;   // n_head is a multiple of 32 or all of n
         if (n_part == 0) continue;
         const bool kahan = part == 0;
-        const int ntiles32 = (n_part + 31) / 32, tpg = (ntiles32 + label_groups - 1) / label_groups;
+        const int ntiles32 = (n_part + 31) / 32, tpg = (int)tiles_per_group(ntiles32);
         const bool first = dx_first;                         // the step's first launch writes every plane that is summed at the end
         const int groups_used = first ? dx_slices : (ntiles32 + tpg - 1) / tpg;
         const uint64_t elem0 = (uint64_t)(c0 + l_off) * (uint64_t)d;

@@ -309,6 +309,34 @@ __device__ inline void label_index(const IndexArgs& ia, int B, int* h) {
 constexpr int kXtPitch = 64 * 2 + 16;                             // bytes per staged column of 64 samples
 // X is the caller's and may begin at any of its elements (one 16-byte load all the same: global loads need no alignment)
 typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
+template <int NT>
+__device__ __forceinline__ void stage_inputs(const uint16_t* __restrict__ X, int B, int Bp, int d, uint8_t* __restrict__ Xq, uint16_t* __restrict__ XT,
+                                             int tile, char* smem) {
+  const int tiles_c = d >> 7, b0 = tile / tiles_c * 64, c0 = tile % tiles_c * 128, tid = threadIdx.x;
+#pragma unroll
+  for (int t = tid; t < 1024; t += NT) {
+    const int r = t >> 4, c = (t & 15) * 8;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (b0 + r < B) v = *reinterpret_cast<const u32x4_at2*>(X + (size_t)(b0 + r) * d + c0 + c);
+    if (Xq) {
+      uint32_t q[2] = {0u, 0u};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) q[e >> 2] |= e4m3_rne(bf16_decode((v[e >> 1] >> (16 * (e & 1))) & 0xFFFFu)) << (8 * (e & 3));
+      *reinterpret_cast<uint2*>(Xq + (size_t)(b0 + r) * d + c0 + c) = make_uint2(q[0], q[1]);
+    }
+    if (XT)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) *reinterpret_cast<uint16_t*>(smem + (c + e) * kXtPitch + r * 2) = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+  }
+  if (!XT) return;
+  __syncthreads();
+#pragma unroll
+  for (int t = tid; t < 1024; t += NT) {
+    const int cb = t >> 8, o = (t >> 5) & 7, c = t & 31;
+    *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(XT) + (size_t)((c0 >> 5) + cb) * blk_strip(Bp) + blk_off((b0 >> 3) + o, c)) =
+        *reinterpret_cast<const u32x4*>(smem + (cb * 32 + c) * kXtPitch + o * 16);
+  }
+}
 // LDS of a launch that indexes nb bins and B rows, or that only stages (nb = 0)
 inline size_t setup_smem(int nb, int B) {
   const size_t index = nb ? (size_t)(nb + B) * 4 : 0;
@@ -328,25 +356,7 @@ __global__ void __launch_bounds__(kSetupThreads) k_step_setup(const uint16_t* __
     if (ia.nb) label_index(ia, B, reinterpret_cast<int*>(smem));
     return;
   }
-  const int tiles_c = d >> 7, tile = blockIdx.x - 1, b0 = tile / tiles_c * 64, c0 = tile % tiles_c * 128;
-  {
-    const int r = tid >> 4, c = (tid & 15) * 8;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (b0 + r < B) v = *reinterpret_cast<const u32x4_at2*>(X + (size_t)(b0 + r) * d + c0 + c);
-    if (Xq) {
-      uint32_t q[2] = {0u, 0u};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) q[e >> 2] |= e4m3_rne(bf16_decode((v[e >> 1] >> (16 * (e & 1))) & 0xFFFFu)) << (8 * (e & 3));
-      *reinterpret_cast<uint2*>(Xq + (size_t)(b0 + r) * d + c0 + c) = make_uint2(q[0], q[1]);
-    }
-    if (!XT) return;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) *reinterpret_cast<uint16_t*>(smem + (c + e) * kXtPitch + r * 2) = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
-  }
-  __syncthreads();
-  const int cb = tid >> 8, o = (tid >> 5) & 7, c = tid & 31;
-  *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(XT) + (size_t)((c0 >> 5) + cb) * blk_strip(Bp) + blk_off((b0 >> 3) + o, c)) =
-      *reinterpret_cast<const u32x4*>(smem + (cb * 32 + c) * kXtPitch + o * 16);
+  stage_inputs<kSetupThreads>(X, B, Bp, d, Xq, XT, blockIdx.x - 1, smem);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -357,7 +367,6 @@ __global__ void __launch_bounds__(kSetupThreads) k_step_setup(const uint16_t* __
 // ---------------------------------------------------------------------------------------------
 constexpr int kGemmThreads = 512;
 constexpr int kGemmWaves = 8;
-constexpr int kStages = 3;                                       // ring depth of the one-pass kernels
 constexpr int kWideRingBytes = 2 * (256 + 256) * 128;            // K-contiguous operands, 128-byte slabs, 2 stages
 
 // Register fragments of one step of a product: FM x FN blocks of 32 x 32 outputs.
@@ -511,19 +520,31 @@ __device__ __forceinline__ void logits_tile_product(const char* __restrict__ Xa,
       static_cast<Prep&&>(prep), static_cast<Extra&&>(extra));
 }
 
+// A small BF16 step needs neither an E4M3 cast of X nor, with this few positives, an index of them: every workgroup finds
+// its tile's in the CSR rows themselves (two dependent loads, as through the index), and the transposed copy of X, which only the
+// next kernel reads, is made by workgroups of the same launch behind the `tiles` that have logits to compute.  That takes the set-up launch out of the
+// chain of a step that is all launches (8192 labels, d = 256, B = 64: 25.6 -> 21.0 us).
+struct DirectArgs { const int* indptr; const int* indices; int nnz; int tiles; uint16_t* XT; };
+// Positives that every tile walks: at 128 rows of 16, four threads to a row, four round trips, hidden behind the first slab's.
+constexpr int kDirectMaxNnz = 2048;
 // DROP: the W slabs are masked in LDS as they land (drop_slab) and Z is scaled by 1 / (1 - p);
 // elem0 = flat index of the chunk's first weight element.
 template <bool FP8, bool LOSS, int TB, bool DROP>
 __global__ void __launch_bounds__(kGemmThreads, TB == 256 ? 1 : 2)
 k_logits(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wc, int n, int d, int Bp, int B,
          uint16_t* __restrict__ Gt, const int* __restrict__ binptr, const int2* __restrict__ pos, int tile0,
-         float* __restrict__ loss_slots, uint64_t seed, uint64_t step, uint64_t elem0, DropArgs dr) {
+         float* __restrict__ loss_slots, uint64_t seed, uint64_t step, uint64_t elem0, DropArgs dr, DirectArgs da) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr int WGN = TB == 256 ? 2 : 4, FN = TB / 32 / WGN;   // waves along the labels, 32-label blocks per wave
+  constexpr bool MAY_DIRECT = !FP8 && TB == 128;
+  if (MAY_DIRECT && da.tiles && (int)blockIdx.x >= da.tiles) {           // X^T for the kernels after this one
+    stage_inputs<kGemmThreads>(reinterpret_cast<const uint16_t*>(Xa), B, Bp, d, nullptr, da.XT, blockIdx.x - da.tiles, smem);
+    return;
+  }
   constexpr int MW = TB / 32;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WGN, wn = wave % WGN;
   const int tiles_b = (Bp + TB - 1) / TB;
-  const int wg = xcd_logical_id(blockIdx.x, gridDim.x);
+  const int wg = xcd_logical_id(blockIdx.x, MAY_DIRECT && da.tiles ? da.tiles : gridDim.x);
   const int lt = wg / tiles_b, bt = wg % tiles_b;
   const int b0 = bt * TB, l0 = lt * TB;
   const size_t rowb = (size_t)d * (FP8 ? 1 : 2);
@@ -538,6 +559,18 @@ k_logits(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wc, i
   // loop's first barrier publishes it.
   auto build_mask = [&]() {
     for (int i = tid; i < TB * MW; i += kGemmThreads) ym[i] = 0u;
+    if (MAY_DIRECT && da.indptr) {                                       // four threads to a row of the (one) batch tile
+      const int r = tid >> 2;
+      const int p0 = r < B ? da.indptr[r] : 0, p1 = r < B ? da.indptr[r + 1] : 0;
+      barrier_lds();
+      if (p0 >= 0 && p1 <= da.nnz)
+        for (int p = p0 + (tid & 3); p < p1; p += 4) {
+          const int lr_ = da.indices[p] - (gt0 << 7);
+          if (lr_ >= 0 && lr_ < TB && l0 + lr_ < n) atomicOr(&ym[lr_ * MW + (r >> 5)], 1u << (r & 31));
+        }
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      return;
+    }
     const int p0 = binptr[gt0], p1 = binptr[gt0 + (rows_out >> 7)];
     barrier_lds();
     for (int p = p0 + tid; p < p1; p += kGemmThreads) {
@@ -731,8 +764,8 @@ k_dx(const char* __restrict__ Gt, const char* __restrict__ Wc, float* __restrict
   auto issue = [&](int ks, int to) {
     const char* g = ga + (size_t)ks * strip;
     char* st = smem + to;
-    dma_kib(g + (size_t)min(kib0, kibs - 1) * 1024, st + 2 * wave * 1024, lane);
-    dma_kib(g + (size_t)min(kib0 + 1, kibs - 1) * 1024, st + (2 * wave + 1) * 1024, lane);
+    dma_kib_of(g, kib0, kibs, st + 2 * wave * 1024, lane);
+    dma_kib_of(g, kib0 + 1, kibs, st + (2 * wave + 1) * 1024, lane);
     dma_tile<32, WROWB, kGemmWaves>(gb + (size_t)ks * 32 * strideB, strideB, n - (ks0 + ks) * 32, st + GBYTES, wave, lane, chunks_b);
   };
   auto ld = [&](FragDx<FP8>& f, const char* st, int kk) {
@@ -1039,8 +1072,11 @@ template <int FMT, bool KAHAN> constexpr int dxu_stage_bytes() {
 constexpr int kDxuGsBytes = 32 * 260 * 4;
 // With dropout one more W tile: the masked copy the input-gradient product reads (the update
 // needs the stored weights, so the tile cannot be masked in place).
+// Three stages, also where the LDS holds more: with six of 16 KiB 1 M E4M3 labels without compensation, B = 128, take 1177 us a step, with
+// three 1052.
+constexpr int kDxuStages = 3;
 template <int FMT, bool KAHAN, bool DROP = false> constexpr int dxu_smem_bytes() {
-  return kStages * dxu_stage_bytes<FMT, KAHAN>() + kDxuGsBytes + (DROP ? 32 * 256 * (FMT == FMT_E4M3 ? 1 : 2) : 0);
+  return kDxuStages * dxu_stage_bytes<FMT, KAHAN>() + kDxuGsBytes + (DROP ? 32 * 256 * (FMT == FMT_E4M3 ? 1 : 2) : 0);
 }
 
 // The body is a separate inlined function with restrict-qualified parameters on purpose: inlining
@@ -1057,6 +1093,7 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
   constexpr int WROWB = 256 * ESZ;
   constexpr int WBYTES = 32 * WROWB, GBYTES = 32 * 256, SBYTES = dxu_stage_bytes<FMT, KAHAN>();
   constexpr int LPS = WROWB / 256 + 1 + (KAHAN ? 2 : 0);     // asynchronous loads per wave and tile
+  constexpr int NST = kDxuStages;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int C = d >> 8;
   const int wg = xcd_logical_id(blockIdx.x, gridDim.x);
@@ -1066,10 +1103,9 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
   if (t0 >= t1 && !(DX && first)) return;                    // (in the first pass every group writes its dX plane)
   const int j0 = c << 8;
   const size_t strip = blk_strip(Bp);
-  const int KS = Bp >> 4;                                   // k16 steps over the batch: 4 or 8
   char* ring = smem;
-  float* gs = reinterpret_cast<float*>(smem + kStages * SBYTES);
-  char* wmk = smem + kStages * SBYTES + kDxuGsBytes;          // DROP: masked copy of the current W tile
+  float* gs = reinterpret_cast<float*>(smem + NST * SBYTES);
+  char* wmk = smem + NST * SBYTES + kDxuGsBytes;          // DROP: masked copy of the current W tile
 
   // X^T fragments of this wave's 32 columns (B operand of grad = G^T X), resident for the kernel
   bf16x8 xt[8];
@@ -1086,29 +1122,28 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
     for (int v = 0; v < 16; ++v) dxa[t][v] = 0.0f;
 
   auto issue = [&](int t) {
-    char* st = ring + (t % kStages) * SBYTES;
+    char* st = ring + (t % NST) * SBYTES;
     const int l0 = t << 5, valid = n - l0;
     dma_tile<32, WROWB, kGemmWaves>(Wc + ((size_t)l0 * d + j0) * ESZ, (size_t)d * ESZ, valid, st, wave, lane);
     // rows of G^T past n exist and hold zeros (written by the logits kernel): no clamping, so they add nothing to dX
-    dma_kib(Gt + (size_t)t * strip + (size_t)min(wave, (Bp >> 4) - 1) * 1024, st + WBYTES + wave * 1024, lane);
+    dma_kib_of(Gt + (size_t)t * strip, wave, Bp >> 4, st + WBYTES + wave * 1024, lane);
     if (KAHAN)
       dma_tile<32, 512, kGemmWaves>(reinterpret_cast<const char*>(Cc) + ((size_t)l0 * d + j0) * 2, (size_t)d * 2, valid,
                                     st + WBYTES + GBYTES, wave, lane);
   };
-  if (t0 < t1) issue(t0);
-  if (t0 + 1 < t1) issue(t0 + 1);
+  for (int s = 0; s < NST - 1; ++s)
+    if (t0 + s < t1) issue(t0 + s);
   for (int t = t0; t < t1; ++t) {
-    // Tile t has landed once only younger operations are outstanding: tile t+1's loads and the
+    // Tile t has landed once only younger operations are outstanding: the loads of the tiles after it and, at least, the
     // stores of tile t-1's update (vector loads and stores retire in issue order on gfx9-family
     // parts and share vmcnt).  Every wave issues NSTORE stores per full tile; the only tile that
     // can be ragged is the last one of the chunk, after which nothing is waited for.
     constexpr int NSTORE = ESZ + (KAHAN ? 2 : 0);
-    if (t + 1 >= t1) wait_vmcnt<0>();
-    else if (t == t0) wait_vmcnt<LPS>();
-    else wait_vmcnt<LPS + NSTORE>();
+    if (t == t0 || t + NST - 1 > t1) wait_slabs<LPS, NST - 2>(t1 - 1 - t);
+    else wait_vmcnt<(NST - 2) * LPS + NSTORE>();
     barrier_nofence();
-    if (t + 2 < t1) issue(t + 2);
-    const char* ws = ring + (t % kStages) * SBYTES;
+    if (t + NST - 1 < t1) issue(t + NST - 1);
+    const char* ws = ring + (t % NST) * SBYTES;
     const char* gsl = ws + WBYTES;
     const char* cs = gsl + GBYTES;
     const int l0 = t << 5;
@@ -1152,22 +1187,37 @@ __device__ __forceinline__ void dx_update_body(const char* __restrict__ Gt, cons
     }
     const char* wdx = DROP ? wmk : ws;                      // what the input-gradient product reads
 
-    // grad[32 labels x 32 columns of this wave] = G^T X
+    // grad[32 labels x 32 columns of this wave] = G^T X, four reads in flight (behind a test each, every MFMA waited for its own)
     f32x16 wa;
 #pragma unroll
     for (int v = 0; v < 16; ++v) wa[v] = 0.0f;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-      if (ks < KS) wa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_blk(gsl, ks, lane), xt[ks], wa, 0, 0, 0);
+    for (int k0 = 0; k0 < 8; k0 += 4)
+      if (16 * k0 < Bp) {
+        bf16x8 fg[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) fg[i] = frag_blk(gsl, k0 + i, lane);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) wa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fg[i], xt[k0 + i], wa, 0, 0, 0);
+      }
     // dX[32 samples x 128 columns of this wave] += G W_tile (weights as stored before the update)
     if (DX) {
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
         const bf16x8 a = frag_tr_blk(gsl, 16 * kk, 32 * bt, lane);
+        typename std::conditional<FMT == FMT_E4M3, i32x2, bf16x8>::type fb[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const bf16x8 b = FMT == FMT_E4M3 ? frag_tr_fp8<WROWB>(wdx, 16 * kk, 128 * jh + 32 * q, lane)
-                                           : frag_tr_bf16<WROWB>(wdx, 16 * kk, 128 * jh + 32 * q, lane);
+          if constexpr (FMT == FMT_E4M3) fb[q] = frag_tr_raw8<WROWB>(wdx, 16 * kk, 128 * jh + 32 * q, lane);
+          else fb[q] = frag_tr_bf16<WROWB>(wdx, 16 * kk, 128 * jh + 32 * q, lane);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          bf16x8 b;
+          if constexpr (FMT == FMT_E4M3) b = widen8(fb[q]);
+          else b = fb[q];
           dxa[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, dxa[q], 0, 0, 0);
         }
       }
@@ -1233,24 +1283,32 @@ k_dx_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __re
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same for padded batches of 129 to 256 rows, in tiles of 32 labels x 128 columns.  With twice the samples the X operand of the
+// The same in tiles of 32 labels x 128 columns, for padded batches of up to 256 rows (which of the two: elmo_head.hip).  With twice the samples the X operand of the
 // gradient product (64 registers a lane) and the slice of dX (128) no longer fit into one wave, so the waves have a role each: waves
 // 0-3 form the gradient of 32 columns over all samples, waves 4-7 the dX of 64 samples x 128 columns, 16 MFMAs a tile either way, and a
 // SIMD holds one of each.  The update of a tile, by all eight, comes one tile late: while the upper waves update tile t - 1 the
 // lower ones multiply tile t, then they change places, so the matrix cores work behind the vector ALU (a tile's update is some
 // 1.5 k clocks of it on a SIMD, its products 1 k) and a tile costs one barrier.  The new weights are read
-// from the tile into registers an iteration before they are updated, which is what lets three stages do.
+// from the tile into registers an iteration before they are updated, so that the ring gets their stage back.
 // 131072 BF16 labels with compensation, B = 256, d = 768, per pass of 43520 labels: input gradient 36 us and update 71 us as separate
-// kernels, 83 us here, and a launch and a third of the partial sums less; all waves in the same role, products and update in
+// kernels, 81 us here, and a launch and a third of the partial sums less; all waves in the same role, products and update in
 // turn (two waves to a gradient sum, 128 samples each): 95 us; the sums of earlier passes added at the end, not loaded at the start: 88 us.
 // ---------------------------------------------------------------------------------------------
 template <int FMT, bool KAHAN> constexpr int dxw_stage_bytes() {
   return 32 * 128 * (FMT == FMT_E4M3 ? 1 : 2) + 32 * 512 + (KAHAN ? 32 * 256 : 0);
 }
-constexpr int kDxwGsPitch = 132;
-// three stages, two gradient tiles, and with dropout the masked copy of the W tile that the input gradient reads and its keep bits
+// Ring depth: what 160 KiB hold, from 3 to 6 (300000 E4M3 labels, d = 640, B = 128: 3 stages 315 us a step, 6 stages 283).
+constexpr int one_pass_stages(int other, int stage) {
+  const int fit = (160 * 1024 - other) / stage;
+  return fit < 3 ? 3 : fit > 6 ? 6 : fit;
+}
+constexpr int kDxwGsBytes = 32 * 128 * 4;                        // a gradient tile; rows 4 .. 7 of eight have their column halves exchanged, for the banks
+__device__ inline int dxw_gs(int row, int col) { return row * 128 + (col ^ ((row & 4) << 3)); }
+// two gradient tiles, and with dropout the masked copy of the W tile that the input gradient reads and its keep bits
+template <int FMT, bool DROP> constexpr int dxw_other_bytes() { return 2 * kDxwGsBytes + (DROP ? 32 * 128 * (FMT == FMT_E4M3 ? 1 : 2) + 512 : 0); }
+template <int FMT, bool KAHAN, bool DROP> constexpr int dxw_stages() { return one_pass_stages(dxw_other_bytes<FMT, DROP>(), dxw_stage_bytes<FMT, KAHAN>()); }
 template <int FMT, bool KAHAN, bool DROP> constexpr int dxw_smem_bytes() {
-  return kStages * dxw_stage_bytes<FMT, KAHAN>() + 2 * 32 * kDxwGsPitch * 4 + (DROP ? 32 * 128 * (FMT == FMT_E4M3 ? 1 : 2) + 512 : 0);
+  return dxw_stages<FMT, KAHAN, DROP>() * dxw_stage_bytes<FMT, KAHAN>() + dxw_other_bytes<FMT, DROP>();
 }
 template <int FMT, bool SR, bool KAHAN, bool WD, bool DROP, bool LOWER>
 __device__ __forceinline__ void dx_update_wide_role(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restrict__ Wc,
@@ -1262,9 +1320,10 @@ __device__ __forceinline__ void dx_update_wide_role(const char* __restrict__ Gt,
   constexpr bool LOADS_W = ESZ == 2 || LOWER;                // 4 KiB of E4M3 weights: by the lower waves alone
   constexpr int LPS = (LOADS_W ? 1 : 0) + 2 + (KAHAN ? 1 : 0), NSTORE = 1 + (KAHAN ? 1 : 0);   // loads and stores per wave and tile
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), rw = wave & 3;
+  constexpr int NST = dxw_stages<FMT, KAHAN, DROP>();
   const size_t strip = blk_strip(Bp);
-  char* gs0 = smem + kStages * SBYTES;
-  char* wmk = gs0 + 2 * 32 * kDxwGsPitch * 4;
+  char* gs0 = smem + NST * SBYTES;
+  char* wmk = gs0 + 2 * kDxwGsBytes;
   uint16_t* keep = reinterpret_cast<uint16_t*>(wmk + WBYTES);
 
   const int xoct = (Bp >> 3) - 1, KS = Bp >> 4;              // last octet of the samples; k16 steps over them: 12 or 16
@@ -1283,13 +1342,12 @@ __device__ __forceinline__ void dx_update_wide_role(const char* __restrict__ Gt,
         if (64 * rw + 32 * s < Bp) load_acc_blocks<4>(dx_block(plane, d, 64 * rw + 32 * s, j0), lane, dxa[s]);
   }
   auto issue = [&](int t) {
-    char* st = smem + (t % kStages) * SBYTES;
+    char* st = smem + (t % NST) * SBYTES;
     const int l0 = t << 5, valid = n - l0;
     if constexpr (LOADS_W) dma_tile<32, WROWB, ESZ == 2 ? 8 : 4>(Wc + ((size_t)l0 * d + j0) * ESZ, (size_t)d * ESZ, valid, st, wave, lane);
     // rows of G^T past n exist and hold zeros (written by the logits kernel): no clamping, so they add nothing to dX
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      dma_kib(Gt + (size_t)t * strip + (size_t)min(2 * wave + i, KS - 1) * 1024, st + WBYTES + (2 * wave + i) * 1024, lane);
+    for (int i = 0; i < 2; ++i) dma_kib_of(Gt + (size_t)t * strip, 2 * wave + i, KS, st + WBYTES + (2 * wave + i) * 1024, lane);
     if constexpr (KAHAN)
       dma_tile<32, 256, kGemmWaves>(reinterpret_cast<const char*>(Cc) + ((size_t)l0 * d + j0) * 2, (size_t)d * 2, valid, st + WBYTES + GBYTES, wave, lane);
   };
@@ -1321,7 +1379,7 @@ __device__ __forceinline__ void dx_update_wide_role(const char* __restrict__ Gt,
   };
   if constexpr (DROP && LOWER) draw(t0);
   auto update = [&](int t, int rows) {                       // rows: n, or 0 where there is nothing to store
-    const float* gs = reinterpret_cast<const float*>(gs0) + (t & 1) * 32 * kDxwGsPitch + l * kDxwGsPitch + seg * 8;
+    const float* gs = reinterpret_cast<const float*>(gs0 + (t & 1) * kDxwGsBytes) + dxw_gs(l, seg * 8);
     const f32x4 ga = *reinterpret_cast<const f32x4*>(gs), gb = *reinterpret_cast<const f32x4*>(gs + 4);
     float g[8] = {ga[0], ga[1], ga[2], ga[3], gb[0], gb[1], gb[2], gb[3]};
     if (DROP) {
@@ -1340,18 +1398,17 @@ __device__ __forceinline__ void dx_update_wide_role(const char* __restrict__ Gt,
       if constexpr (KAHAN) *reinterpret_cast<u32x4*>(Cc + eoff) = u32x4{cc[0], cc[1], cc[2], cc[3]};
     }
   };
-  if (t0 < t1) issue(t0);
-  if (t0 + 1 < t1) issue(t0 + 1);
+  for (int s = 0; s < NST - 1; ++s)
+    if (t0 + s < t1) issue(t0 + s);
   for (int t = t0; t < t1; ++t) {
-    // Tile t's loads were issued two iterations ago; younger are the loads of tile t + 1 and the stores of the two updates since, of
-    // which one may be waited for (loads and stores retire in issue order and share vmcnt).  Every wave issues its
+    // Younger than tile t's loads are those of the tiles after it and, from the third tile on, at least the stores of the last update
+    // (loads and stores retire in issue order and share vmcnt).  Every wave issues its
     // stores in every tile but a ragged last one, after which nothing is waited for.
-    if (t + 1 >= t1) wait_vmcnt<0>();
-    else if (t < t0 + 2) wait_vmcnt<LPS>();
-    else wait_vmcnt<LPS + NSTORE>();
+    if (t < t0 + 2 || t + NST - 1 > t1) wait_slabs<LPS, NST - 2>(t1 - 1 - t);
+    else wait_vmcnt<(NST - 2) * LPS + NSTORE>();
     barrier_lds();                                           // tile t, and the gradient of tile t - 1
-    if (t + 2 < t1) issue(t + 2);
-    const char* st = smem + (t % kStages) * SBYTES;
+    if (t + NST - 1 < t1) issue(t + NST - 1);
+    const char* st = smem + (t % NST) * SBYTES;
     const char* gsl = st + WBYTES;
     if constexpr (LOWER) {
       if constexpr (DROP) {
@@ -1377,31 +1434,47 @@ __device__ __forceinline__ void dx_update_wide_role(const char* __restrict__ Gt,
 #pragma unroll
       for (int v = 0; v < 16; ++v) wa[v] = 0.0f;
 #pragma unroll
-      for (int ks = 0; ks < 16; ++ks)
-        if (ks < KS) wa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_blk(gsl, ks, lane), xt[ks], wa, 0, 0, 0);
+      for (int k0 = 0; k0 < 16; k0 += 4)                      // (four reads in flight; KS is a multiple of four)
+        if (k0 < KS) {
+          bf16x8 fg[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) fg[i] = frag_blk(gsl, k0 + i, lane);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) wa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fg[i], xt[k0 + i], wa, 0, 0, 0);
+        }
       if constexpr (DROP) draw(t + 1);
       update(t - 1, t > t0 ? n : 0);
-      float* gs = reinterpret_cast<float*>(gs0) + (t & 1) * 32 * kDxwGsPitch;
+      float* gs = reinterpret_cast<float*>(gs0 + (t & 1) * kDxwGsBytes);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) gs[acc_row(v, lane) * kDxwGsPitch + 32 * rw + (lane & 31)] = wa[v];
+      for (int v = 0; v < 16; ++v) gs[dxw_gs(acc_row(v, lane), 32 * rw + (lane & 31))] = wa[v];
     } else {
       if constexpr (DROP) barrier_lds();
       update(t - 1, t > t0 ? n : 0);
       const char* wdx = DROP ? wmk : st;
+      bf16x8 fa[2][2];                                       // dX += G W_tile (weights as stored before the update), all fragments read first
+      typename std::conditional<ESZ == 1, i32x2, bf16x8>::type fb[2][4];
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {                       // dX += G W_tile (weights as stored before the update)
-        bf16x8 a[2];
+      for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) a[s] = frag_tr_blk(gsl, 16 * kk, 64 * rw + 32 * s, lane);
+        for (int s = 0; s < 2; ++s) fa[kk][s] = frag_tr_blk(gsl, 16 * kk, 64 * rw + 32 * s, lane);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if constexpr (ESZ == 1) fb[kk][q] = frag_tr_raw8<WROWB>(wdx, 16 * kk, 32 * q, lane);
+          else fb[kk][q] = frag_tr_bf16<WROWB>(wdx, 16 * kk, 32 * q, lane);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           bf16x8 b;
-          if constexpr (ESZ == 1) b = frag_tr_fp8<WROWB>(wdx, 16 * kk, 32 * q, lane);
-          else b = frag_tr_bf16<WROWB>(wdx, 16 * kk, 32 * q, lane);
+          if constexpr (ESZ == 1) b = widen8(fb[kk][q]);
+          else b = fb[kk][q];
 #pragma unroll
-          for (int s = 0; s < 2; ++s) dxa[s][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], b, dxa[s][q], 0, 0, 0);
+          for (int s = 0; s < 2; ++s) dxa[s][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][s], b, dxa[s][q], 0, 0, 0);
         }
-      }
     }
     fetch(st);
     if constexpr (DROP) kept = keep[l * 8 + (seg >> 1)] >> (8 * (seg & 1));

@@ -322,6 +322,12 @@ __device__ __forceinline__ void ring_alternate(int nk, char* __restrict__ smem, 
 __device__ inline int blk_off(int o, int r) { return (o << 9) + ((r ^ ((o & 3) << 2)) << 4); }
 // Bytes of a block's strip for Bp samples.
 __device__ inline size_t blk_strip(int Bp) { return (size_t)Bp * 64; }
+// KiB `i` of `n` of a strip by one wave, one KiB of LDS; beyond the last, its first 16 bytes 64 times over (a read of one line: whole
+// KiBs again cost the one-pass kernel 4 % at B <= 64, where half of its waves have no samples).
+__device__ inline void dma_kib(const char* __restrict__ g, char* lds, int lane);
+__device__ inline void dma_kib_of(const char* __restrict__ g, int i, int n, char* lds, int lane) {
+  dma_kib(g + (size_t)min(i, n - 1) * 1024, lds, i < n ? lane : 0);
+}
 // One KiB (consecutive in memory and in LDS) by one wave.
 __device__ inline void dma_kib(const char* __restrict__ g, char* lds, int lane) {
   uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)g), hi = __builtin_amdgcn_readfirstlane((uint32_t)((uintptr_t)g >> 32));

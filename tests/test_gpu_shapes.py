@@ -388,10 +388,14 @@ def test_short_rings_and_cut_blocks(b, fmt, flags, T, B, d, L):  # noqa: F811
     (192, 640, 97, 0),      # the second half of the samples half empty
     (193, 384, 4133, 128),  # one row beyond 192; compensation for the first tiles, a launch each
     (256, 768, 3000, 0),    # the most rows; groups of three label tiles, the last with fewer
+    (1, 384, 33, 0),        # one row, where 256 does not divide the width
+    (128, 640, 4100, 128),  # three groups of samples for the lower waves' steps, none for half of the upper waves
+    (64, 256, 32768, 0),    # the most tiles of a small batch that still takes this kernel, and (65) one more row
+    (65, 256, 32769, 0),
 ])
 @pytest.mark.parametrize("fmt,flags,T,wd", [(o.E4M3, o.FLAG_SR | o.FLAG_KAHAN, 0, 0.0), (o.E4M3, o.FLAG_SR, 64, 0.01), (o.BF16, o.FLAG_KAHAN, 64, 0.0), (o.BF16, o.FLAG_SR, 0, 0.0)])
-def test_one_pass_kernel_of_129_to_256_rows(b, fmt, flags, T, wd, B, d, L, kahan_rows):  # noqa: F811
-    """Input gradient and update in one pass over 128-column tiles, two waves to a gradient sum."""
+def test_one_pass_kernel_of_128_columns(b, fmt, flags, T, wd, B, d, L, kahan_rows):  # noqa: F811
+    """Input gradient and update in one pass over 128-column tiles, the update a tile late."""
     kr = kahan_rows if flags & o.FLAG_KAHAN else 0
     case = Case(b, L, d, fmt, L, flags, B, w_std=0.05, comp_std=2e-4 if flags & o.FLAG_KAHAN else 0.0, seed=12, kahan_rows=kr, weight_decay=wd, dropout_p=T / 256)
     case.head.workspace.fill_(0x7F)
@@ -412,3 +416,22 @@ def test_one_pass_kernel_of_129_to_256_rows(b, fmt, flags, T, wd, B, d, L, kahan
         same = dist[:n] == 0
         err = np.abs(o.decode_bf16(case.C()[:n]) - o.decode_bf16(ref["comp_new"][:n]))[same] / np.maximum(np.abs(o.decode(ref["W_new"][:n], fmt)), 2.0**-9)[same]
         assert np.quantile(err, 0.999) <= 2.0**-8
+
+
+@pytest.mark.parametrize("B,L,d,per_row", [(1, 100, 128, 1), (3, 129, 256, 40), (64, 8192, 256, 5), (128, 1000, 384, 16), (127, 70000, 256, 2), (128, 300, 256, 17)])
+def test_small_bf16_steps_find_their_positives(b, B, L, d, per_row):  # noqa: F811
+    """A BF16 step of at most 128 rows and 2048 positives has no label index and transposes X beside its logits; one positive list
+    beyond (128 x 17) and the validating head go the other way, and all give the same bits."""
+    rng = np.random.default_rng(3)
+    X = synth.make_x(rng, B, d)
+    indices = np.concatenate([np.sort(rng.choice(L, size=per_row, replace=False)) for _ in range(B)]).astype(np.int32)
+    indptr = (np.arange(B + 1) * per_row).astype(np.int32)
+    case = Case(b, L, d, o.BF16, L, SR, B, max_nnz=B * per_row, w_std=0.05, seed=4)
+    case.head.workspace.fill_(0x7F)
+    check_step(case, X, indptr, indices, 0.05, 0, 0, 2e-2)
+    other = Case(b, L, d, o.BF16, L, SR | b.ELMO_VALIDATE, B, max_nnz=B * per_row, w_std=0.05, seed=4, like=case)
+    other.head.workspace.fill_(0x7F)
+    dX, loss = other.step(X, indptr, indices, 0.05, 0, 0)
+    again = Case(b, L, d, o.BF16, L, SR, B, max_nnz=B * per_row, w_std=0.05, seed=4, like=case)
+    dX2, loss2 = again.step(X, indptr, indices, 0.05, 0, 0)
+    assert np.array_equal(other.W(), again.W()) and np.array_equal(dX, dX2) and loss == loss2
