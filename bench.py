@@ -2,7 +2,7 @@
 """Benchmark of the ELMO head training step on one MI355X.
 
 A step = one pass of the whole hot path (step set-up, then per label chunk: logits + BCE epilogue,
-input gradient, fused update -- the last two in one kernel when the batch is at most 128 rows --;
+input gradient, fused update -- the last two in one kernel when the batch is at most 256 rows --;
 then the finalise kernel) over one fresh synthetic batch that is already resident in HBM.
 Default workload: the 3M-label FP8 head, the headline configuration (L = 3,000,000, d = 768, B = 1024, E4M3
 weights + BF16 Kahan buffer + stochastic rounding, about 8 Zipf(1.05) positives per sample,
@@ -157,7 +157,7 @@ def measure(b, synth, torch, np, cfg, args, n_warm, n_steps, dev, profile_name, 
     n_chunks = max(1, round(prof["logits"][1] / n_steps))
     n_avg = L / n_chunks                                   # labels per launch, averaged
     Bp = -(-B // 64) * 64
-    # padded batches of at most 128 rows take the single-pass kernel: input gradient and update share
+    # padded batches of at most 256 rows take a single-pass kernel: input gradient and update share
     # one launch (timed under "update") and one read of W
     fused = (not args.no_dx) and prof["dx"][1] == 0
     regime = "hbm" if Bp <= 128 else "mfma"
