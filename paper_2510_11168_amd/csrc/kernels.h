@@ -371,7 +371,6 @@ constexpr int kWideRingBytes = 2 * (256 + 256) * 128;            // K-contiguous
 
 // Register fragments of one step of a product: FM x FN blocks of 32 x 32 outputs.
 template <int FM, int FN> struct FragBF16 { bf16x8 a[FM], b[FN]; };
-template <int FM, int FN> struct FragFP8 { i32x8 a[FM], b[FN]; };
 
 template <int FN> __device__ inline void zero_acc(f32x16 (&acc)[2][FN]) {
 #pragma unroll

@@ -408,9 +408,6 @@ __device__ inline bf16x8 widen8(i32x2 w) {
   u.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((unsigned)w[1], 1.0f, true);
   return u.v;
 }
-template <int ROWB> __device__ inline bf16x8 frag_tr_fp8(const char* lds, int k0, int col0, int lane) {
-  return widen8(frag_tr_raw8<ROWB>(lds, k0, col0, lane));
-}
 
 // Accumulator element v (0..15) of a 32x32 MFMA tile sits at row 8*(v/4) + 4*(lane/32) + v%4,
 // column lane%32.
