@@ -562,7 +562,7 @@ k_logits(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wc, i
       const int r = tid >> 2;
       const int p0 = r < B ? da.indptr[r] : 0, p1 = r < B ? da.indptr[r + 1] : 0;
       barrier_lds();
-      if (p0 >= 0 && p1 <= da.nnz)
+      if (p0 >= 0 && p0 <= p1 && p1 <= da.nnz)                           // (also keeps p0 + 3 from wrapping to a place before the list)
         for (int p = p0 + (tid & 3); p < p1; p += 4) {
           const int lr_ = da.indices[p] - (gt0 << 7);
           if (lr_ >= 0 && lr_ < TB && l0 + lr_ < n) atomicOr(&ym[lr_ * MW + (r >> 5)], 1u << (r & 31));

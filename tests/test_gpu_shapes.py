@@ -435,3 +435,20 @@ def test_small_bf16_steps_find_their_positives(b, B, L, d, per_row):  # noqa: F8
     again = Case(b, L, d, o.BF16, L, SR, B, max_nnz=B * per_row, w_std=0.05, seed=4, like=case)
     dX2, loss2 = again.step(X, indptr, indices, 0.05, 0, 0)
     assert np.array_equal(other.W(), again.W()) and np.array_equal(dX, dX2) and loss == loss2
+
+
+def test_small_bf16_steps_skip_malformed_rows(b):  # noqa: F811
+    """Row pointers that fall, leave the list or stand at the ends of their type: those rows are skipped, the others count."""
+    L, d, top = 1000, 128, 2**31 - 1
+    for indptr in ([0, 2, 1, 2, 3, 4, 5], [0, 1, 2, 3, 4, 5, 9], [-1, 1, 2, 3, -2**31, 4, 6], [0, top, top, 1, 2, top - 1, 3], [top, 0, 6, 6, top - 2, 5, 6]):
+        indices = [1, 2, 300, 4, 999, 6]
+        B = len(indptr) - 1
+        X = torch.from_numpy(o.round_bf16(np.full((B, d), 0.125, np.float32)).view(np.int16)).to("cuda:0")
+        head = b.Head(L, d, o.BF16, L, 0, B, 6)
+        head.workspace.fill_(0x7F)
+        head.step(X, torch.tensor(indptr, dtype=torch.int32, device="cuda:0"), torch.tensor(indices, dtype=torch.int32, device="cuda:0"), 0.5, 0, 0)
+        G = np.full((B, L), 0.5)
+        for r in range(B):
+            if 0 <= indptr[r] <= indptr[r + 1] <= len(indices):
+                G[r, indices[indptr[r]:indptr[r + 1]]] = -0.5
+        assert np.array_equal(head.weights().view(torch.bfloat16).float().cpu().numpy(), np.repeat(-0.5 * 0.125 * G.sum(0).astype(np.float32)[:, None], d, 1))
