@@ -466,7 +466,8 @@ __device__ __forceinline__ void drop_own_rows(char* tile, int wave, int lane, ui
 // 256-row tile would be padding and the kernel is bound by the stream of W: 128 x 128 tiles need
 // 66 KiB of LDS, so two workgroups share a CU and one's epilogue overlaps the other's loads.
 template <int TB> constexpr int logits_mask_offset() { return 2 * (TB + TB) * 128; }   // positives mask: behind the ring
-template <int TB> constexpr int logits_smem() { return logits_mask_offset<TB>() + TB * (TB / 32) * 4 + 32; }
+template <int TB> constexpr int logits_rows_offset() { return logits_mask_offset<TB>() + TB * (TB / 32) * 4 + 32; }
+template <int TB> constexpr int logits_smem() { return logits_rows_offset<TB>() + (TB == 128 ? 132 * 4 : 0); }   // row pointers of a direct step
 
 // One half (0 or 1) of the product of a 128-byte K slab of the logits tile: A = TB sample rows,
 // B = TB label rows, K-contiguous in LDS.  Wave (wm, wn) owns samples 64 wm .. +63 and labels
@@ -520,12 +521,57 @@ __device__ __forceinline__ void logits_tile_product(const char* __restrict__ Xa,
 }
 
 // A small BF16 step needs neither an E4M3 cast of X nor, with this few positives, an index of them: every workgroup finds
-// its tile's in the CSR rows themselves (two dependent loads, as through the index), and the transposed copy of X, which only the
+// its tile's in the CSR lists themselves, and the transposed copy of X, which only the
 // next kernel reads, is made by workgroups of the same launch behind the `tiles` that have logits to compute.  That takes the set-up launch out of the
 // chain of a step that is all launches (8192 labels, d = 256, B = 64: 25.6 -> 21.0 us).
 struct DirectArgs { const int* indptr; const int* indices; int nnz; int tiles; uint16_t* XT; };
-// Positives that every tile walks: at 128 rows of 16, four threads to a row, four round trips, hidden behind the first slab's.
-constexpr int kDirectMaxNnz = 2048;
+// Positives that every tile looks at: four per thread, however they are spread over the rows.
+constexpr int kDirectMaxNnz = 4 * kGemmThreads;
+constexpr int kDirectWalk = 16;
+// mark(row, label - lo) for the positives of a direct step among the `count` labels from lo on, by all threads of a workgroup (B <= 128; `ptr`: 129
+// ints of LDS).  The first kDirectWalk of a row are read by four threads, four loads each in flight together, which is all there is where rows
+// are short.  Where one is longer the whole list is read by place, four loads a thread, and a place that
+// holds one of the tile's labels looks for its row.  (Long rows walked to their end by their four threads: 1 M labels, d = 256, B = 64,
+// one row of 1800: 1421 us a step, now 540, 559 with an
+// index; every list read by place only: 8192 labels, d = 256, B = 64 18.3 -> 18.6 us.)  Malformed rows are
+// skipped; beside one the others may overlap, and are walked by their own threads.  Contains a barrier, which also orders what
+// the caller wrote to LDS before it.
+template <class F> __device__ __forceinline__ void mark_direct_positives(const DirectArgs& da, int B, int tid, int lo, int count, int* ptr, F&& mark) {
+  constexpr int WALK = kDirectWalk / 4, PER = kDirectMaxNnz / kGemmThreads;
+  const int r = tid >> 2, sub = tid & 3, lane = tid & 63;
+  const int begin = r < B ? da.indptr[r] : INT32_MAX, end = r < B ? da.indptr[r + 1] : INT32_MAX;
+  if (sub == 0) ptr[r + 1] = end;
+  if (tid == 0) ptr[0] = begin;
+  const bool sound = r < B && begin >= 0 && begin <= end && end <= da.nnz;    // (also keeps begin + 15 from wrapping to a place before the list)
+  const auto mark_label = [&](int row, int label) {
+    const uint32_t at = (uint32_t)label - (uint32_t)lo;
+    if (label >= 0 && at < (uint32_t)count) mark(row, (int)at);
+  };
+  int l[WALK > PER ? WALK : PER];
+#pragma unroll
+  for (int i = 0; i < WALK; ++i) l[i] = sound && sub + 4 * i < end - begin ? da.indices[begin + sub + 4 * i] : -1;
+  barrier_lds();
+  const int p0 = ptr[2 * lane], p1 = ptr[2 * lane + 1], p2 = ptr[2 * lane + 2];
+#pragma unroll
+  for (int i = 0; i < WALK; ++i) mark_label(r, l[i]);
+  if (__builtin_amdgcn_ballot_w64((2 * lane < B && p1 - p0 > kDirectWalk) || (2 * lane + 1 < B && p2 - p1 > kDirectWalk)) == 0ull) return;
+  if (__builtin_amdgcn_ballot_w64(p0 > p1 || p1 > p2) != 0ull || ptr[0] < 0 || ptr[B] > da.nnz) {
+    if (sound)
+      for (int p = begin + kDirectWalk + sub; p < end; p += 4) mark_label(r, da.indices[p]);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) l[i] = tid + i * kGemmThreads < da.nnz ? da.indices[tid + i * kGemmThreads] : -1;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int p = tid + i * kGemmThreads;
+    if ((uint32_t)l[i] - (uint32_t)lo >= (uint32_t)count) continue;
+    int row = 0;                                                         // the last row that begins at or before p
+#pragma unroll
+    for (int o = 64; o > 0; o >>= 1) row += ptr[row + o] <= p ? o : 0;
+    if (row < B && ptr[row] <= p && p < ptr[row + 1]) mark_label(row, l[i]);   // (places before the first row or behind the last belong to none)
+  }
+}
 // DROP: the W slabs are masked in LDS as they land (drop_slab) and Z is scaled by 1 / (1 - p);
 // elem0 = flat index of the chunk's first weight element.
 template <bool FP8, bool LOSS, int TB, bool DROP>
@@ -558,15 +604,9 @@ k_logits(const char* __restrict__ Xa, int a_rows, const char* __restrict__ Wc, i
   // loop's first barrier publishes it.
   auto build_mask = [&]() {
     for (int i = tid; i < TB * MW; i += kGemmThreads) ym[i] = 0u;
-    if (MAY_DIRECT && da.indptr) {                                       // four threads to a row of the (one) batch tile
-      const int r = tid >> 2;
-      const int p0 = r < B ? da.indptr[r] : 0, p1 = r < B ? da.indptr[r + 1] : 0;
-      barrier_lds();
-      if (p0 >= 0 && p0 <= p1 && p1 <= da.nnz)                           // (also keeps p0 + 3 from wrapping to a place before the list)
-        for (int p = p0 + (tid & 3); p < p1; p += 4) {
-          const int lr_ = da.indices[p] - (gt0 << 7);
-          if (lr_ >= 0 && lr_ < TB && l0 + lr_ < n) atomicOr(&ym[lr_ * MW + (r >> 5)], 1u << (r & 31));
-        }
+    if (MAY_DIRECT && da.indptr) {                                       // (the batch is one tile)
+      mark_direct_positives(da, B, tid, gt0 << 7, min(TB, n - l0), reinterpret_cast<int*>(smem + logits_rows_offset<TB>()),
+                            [&](int r, int at) { atomicOr(&ym[at * MW + (r >> 5)], 1u << (r & 31)); });
       __builtin_amdgcn_s_waitcnt(0xC07F);
       return;
     }

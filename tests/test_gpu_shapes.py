@@ -438,9 +438,10 @@ def test_small_bf16_steps_find_their_positives(b, B, L, d, per_row):  # noqa: F8
 
 
 def test_small_bf16_steps_skip_malformed_rows(b):  # noqa: F811
-    """Row pointers that fall, leave the list or stand at the ends of their type: those rows are skipped, the others count."""
+    """Row pointers that fall, leave the list or stand at the ends of their type: those rows are skipped, the others count, and a list that
+    begins before the first row or goes on behind the last."""
     L, d, top = 1000, 128, 2**31 - 1
-    for indptr in ([0, 2, 1, 2, 3, 4, 5], [0, 1, 2, 3, 4, 5, 9], [-1, 1, 2, 3, -2**31, 4, 6], [0, top, top, 1, 2, top - 1, 3], [top, 0, 6, 6, top - 2, 5, 6]):
+    for indptr in ([0, 2, 1, 2, 3, 4, 5], [0, 1, 2, 3, 4, 5, 9], [-1, 1, 2, 3, -2**31, 4, 6], [0, top, top, 1, 2, top - 1, 3], [top, 0, 6, 6, top - 2, 5, 6], [1, 2, 2, 4], [0, 0, 0, 6, 5]):
         indices = [1, 2, 300, 4, 999, 6]
         B = len(indptr) - 1
         X = torch.from_numpy(o.round_bf16(np.full((B, d), 0.125, np.float32)).view(np.int16)).to("cuda:0")
@@ -452,3 +453,44 @@ def test_small_bf16_steps_skip_malformed_rows(b):  # noqa: F811
             if 0 <= indptr[r] <= indptr[r + 1] <= len(indices):
                 G[r, indices[indptr[r]:indptr[r + 1]]] = -0.5
         assert np.array_equal(head.weights().view(torch.bfloat16).float().cpu().numpy(), np.repeat(-0.5 * 0.125 * G.sum(0).astype(np.float32)[:, None], d, 1))
+
+
+@pytest.mark.parametrize("B,what,L", [(1, "all", 300), (1, "all", 70000), (2, "all", 70000), (64, "one long", 8192), (127, "mixed", 5000), (128, "every third", 3000), (128, "last", 9000), (128, "none", 300)])
+def test_small_bf16_steps_with_uneven_rows(b, B, what, L):  # noqa: F811
+    """Up to 2048 positives however they are spread over the rows: exact weights, as in test_every_positive_reaches_its_label."""
+    d, lr = 128, 0.5
+    rng = np.random.default_rng(4)
+    lens = {"all": np.full(B, min(2048 // B, L)), "one long": np.where(np.arange(B) == B // 2, 1900, 2), "mixed": rng.integers(0, 30, B),
+            "every third": np.arange(B) % 3 // 2 * 40, "last": np.where(np.arange(B) == B - 1, 2048, 0), "none": np.zeros(B, int)}[what]
+    indptr, indices = uneven(B, lens, L)
+    assert len(indices) <= 2048
+    X = rng.choice([-0.125, 0.125], (B, d)).astype(np.float32)
+    X[1::2] = -X[:B // 2 * 2:2]
+    head = b.Head(L, d, o.BF16, 131072, 0, B, max(len(indices), 1))
+    head.workspace.fill_(0x7F)
+    Xd, ip, ix = (torch.from_numpy(v).to("cuda:0") for v in (o.round_bf16(X).view(np.int16), indptr, indices))
+    head.step(Xd, ip, ix, lr, 0, 0)
+    Xf = torch.from_numpy(X).to("cuda:0")
+    want = (-lr / 2 * Xf.double().sum(0)).float().expand(L, d).clone()
+    want.index_add_(0, ix.long(), lr * Xf[torch.repeat_interleave(torch.arange(B, device="cuda:0"), ip.diff().long())])
+    assert torch.equal(head.weights().view(torch.bfloat16).float(), want.bfloat16().float())
+
+
+def test_small_bf16_steps_do_not_wait_for_uneven_rows(b):  # noqa: F811
+    """One row with most of 2000 positives: the logits of many label tiles take about what they take with even rows (four times that
+    where a row's positives are walked by a few threads in every tile)."""
+    B, L, d = 64, 500000, 256
+    us = []
+    for lens in (np.where(np.arange(B) == 5, 1800, 2), np.full(B, 30)):
+        indptr, indices = uneven(B, lens, L)
+        head = b.Head(L, d, o.BF16, L, 0, B, len(indices))
+        args = [torch.from_numpy(v).to("cuda:0") for v in (synth.make_x(np.random.default_rng(1), B, d).view(np.int16), indptr, indices)]
+        b.elmo_head_profile(head.h, True)
+        for _ in range(3):
+            head.step(*args, 0.0, 0, 0)
+        b.elmo_head_profile_read(head.h)
+        for _ in range(10):
+            head.step(*args, 0.0, 0, 0)
+        us.append(100 * b.elmo_head_profile_read(head.h)["logits"][0])
+    say(f"   logits: uneven rows {us[0]:.1f} us, even rows {us[1]:.1f} us")
+    assert us[0] <= 1.5 * us[1]
