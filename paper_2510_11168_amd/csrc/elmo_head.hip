@@ -23,7 +23,6 @@ using elmo::Pass;
 using elmo::align256;
 using elmo::round_up;
 using elmo::lay_out;
-using elmo::choose_pass;
 
 thread_local char g_err[512] = "";
 
@@ -439,46 +438,12 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   int2* pos = (int2*)(h->ws + p.off_pos);
   int* flag = (p.flags & ELMO_VALIDATE) ? (int*)(h->ws + p.off_flag) : nullptr;
 
-  // Small batches are bound by memory traffic: input gradient and update share one pass over W
-  // With dropout that kernel keeps a masked copy of the W tile in LDS, which does not fit next to
-  // BF16 weights with compensation: that one mode takes the separate kernels.
-  const bool small_batch = Bp <= 128 && d % 256 == 0 && !(p.drop_thresh && !fp8 && (p.flags & ELMO_KAHAN));
-  const Pass ps = choose_pass(p, Bp, small_batch, dX_out != nullptr);
+  const elmo::StepPlan sp = elmo::plan_step(p, Bp, dX_out != nullptr);
+  const Pass& ps = sp.ps;
+  const bool wide_batch = sp.kernels == elmo::kOnePass128;
+  const int S = sp.slices;
   uint16_t* Gt = (uint16_t*)(h->ws + ps.off_g);
-  // In tiles of 128 columns (k_dx_update_wide) up to 256 rows, as far as the planes of partial sums have room for groups that
-  // fill the chip (d = 384: 64 groups of 3 workgroups; d = 128, 64 workgroups, takes the separate kernels), and where an input
-  // gradient is asked for: the update alone has no second read of W to save (21293 E4M3 labels, B = 134: 39 us, 45 us there).
-  // At most 128 rows take it where 256 does not divide d (300000 E4M3 labels, d = 640, B = 128: separate kernels 409 us, 283 us there) and where
-  // a workgroup has no more than four of its tiles (16384 E4M3 labels, d = 256, B = 64: 256 columns 29.5, 128 columns 25.7 us;
-  // 16384 x 768, twelve tiles: 35.7 and 36.1; 1 M labels, B = 128, with compensation: 1406 and 1472).
-  const int wide_groups = std::max(1, std::min(256 / (d / 128), p.dx_rows / 256));
-  const int64_t wide_tiles = (std::min<int64_t>(ps.labels, p.L) + 31) / 32 * (d / 128);
-  const bool wide_batch = dX_out && Bp <= 256 && (!small_batch || wide_tiles <= 4 * 256) && wide_groups * (d / 128) >= 192;
-  const bool fused = small_batch || wide_batch;
-  const int col_blocks = wide_batch ? d / 128 : d / 256, label_groups = wide_batch ? wide_groups : small_batch ? std::max(1, 256 / col_blocks) : 0;   // widths above 65536: one group
-  // label slices of the input-gradient product: at most one 512-thread workgroup per CU, so the
-  // whole grid is resident at once (256 CUs) and no second, nearly empty round of workgroups runs
-  int S = std::max(1, 256 / (tiles_b * tiles_j));
-  S = std::min(S, p.dx_rows / Bp256);
-  S = std::max(1, std::min({S, 64, (int)((std::min<int64_t>(ps.labels, p.L) + 63) / 64)}));
-  // Label tiles per group.  Not one: a group's plane is as much work as a tile, here and in the final sum (8192 labels, d = 256, 256
-  // groups of one tile / 128 of two / 64 of four: B = 64 28.9 / 25.6 / 26.9 us, B = 128 35.7 / 31.3 / 30.6); below 129 tiles there are CUs to spare.
-  auto tiles_per_group = [&](int64_t tiles) { return std::max<int64_t>((tiles + label_groups - 1) / label_groups, !wide_batch && tiles > 128 ? 2 : 1); };
-  // planes of partial sums; the fused kernel uses as many as its largest launch has label groups
-  int dx_slices = S;
-  if (fused) {
-    dx_slices = 1;
-    auto groups = [&](int64_t n) {
-      const int64_t t = (n + 31) / 32, per = tiles_per_group(t);
-      return n > 0 ? (int)((t + per - 1) / per) : 0;
-    };
-    for (int64_t c0 = 0; c0 < p.L; c0 += ps.take(p.L - c0)) {
-      const int64_t n = ps.take(p.L - c0), head = std::max<int64_t>(0, std::min(n, p.kahan_rows - c0));
-      dx_slices = std::max({dx_slices, groups(head), groups(n - head)});
-    }
-  }
   bool dx_first = true;                                        // no launch has written the planes yet
-  const int dx_plane_rows = fused && !wide_batch ? 128 : Bp256;
 
   Profiler& prof = h->prof;
   prof.mark(st, CLS_SETUP);
@@ -535,20 +500,20 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
     // (Kahan summation for head labels), the others are updated without it.
     const bool sr = p.flags & ELMO_SR;
     const int n_head = (int)std::max<int64_t>(0, std::min<int64_t>(n, p.kahan_rows - c0));
-    if (fused) {
+    if (sp.one_pass()) {
       prof.mark(st, CLS_UPDATE);
       for (int part = 0; part < 2; ++part) {
         const int l_off = part ? n_head : 0, n_part = part ? n - n_head : n_head;   // n_head is a multiple of 32 or all of n
         if (n_part == 0) continue;
         const bool kahan = part == 0;
-        const int ntiles32 = (n_part + 31) / 32, tpg = (int)tiles_per_group(ntiles32);
+        const int ntiles32 = (n_part + 31) / 32, tpg = (int)sp.tiles_per_group(ntiles32);
         const bool first = dx_first;                         // the step's first launch writes every plane that is summed at the end
-        const int groups_used = first ? dx_slices : (ntiles32 + tpg - 1) / tpg;
+        const int groups_used = first ? sp.planes : sp.groups(n_part);
         const uint64_t elem0 = (uint64_t)(c0 + l_off) * (uint64_t)d;
         const char* Gp = (const char*)(Gt + (size_t)l_off * Bp);
         char* Wp = Wc + (size_t)l_off * d * esz;
         uint16_t* Cp = kahan ? Cc + (size_t)l_off * d : nullptr;
-        const int grid = groups_used * col_blocks;
+        const int grid = groups_used * sp.col_blocks;
         int rc;
 #define ELMO_WIDE(F, SR_, KA_) rc = launch_dx_update_wide<F, SR_, KA_>(st, grid, Gp, (const char*)XT, Wp, Cp, dXacc, n_part, d, Bp, lr, p.weight_decay, seed, step, elem0, tpg, first, dr)
 #define ELMO_WIDE_F(F)                                                                          \
@@ -599,7 +564,7 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
   if (dX_out || loss_out) {
     const int groups = dX_out ? (B + 31) / 32 * (d / 32) * 4 : 0;
     elmo::k_finalize<<<groups + (loss_out ? 1 : 0), 64 * elmo::kFinalWaves, 0, st>>>(
-        dXacc, dx_slices, dx_plane_rows, B, d, groups, wide_batch ? dr.scale : 1.0f, (uint16_t*)dX_out, loss_slots, p.ntiles * loss_tiles, loss_out);
+        dXacc, sp.planes, sp.plane_rows, B, d, groups, wide_batch ? dr.scale : 1.0f, (uint16_t*)dX_out, loss_slots, p.ntiles * loss_tiles, loss_out);
     if (int rc = check_launch("k_finalize")) return rc;
   }
   prof.mark(st, CLS_END);

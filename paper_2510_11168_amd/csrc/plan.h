@@ -117,4 +117,61 @@ inline Pass choose_pass(const Plan& p, int Bp, bool small_batch, bool want_dx) {
   return best;
 }
 
+// What a step launches for a batch padded to Bp rows: its passes, the kernels of their backward half and how those split the labels.
+//   kOnePass256: input gradient and update in one pass over the weights, tiles of 32 labels x 256 columns (k_dx_update), at most 128 rows.
+//     With dropout that kernel keeps a masked copy of the W tile in LDS, which does not fit next to BF16 weights with
+//     compensation: without an input gradient that one mode takes the separate kernels.
+//   kOnePass128: the same in tiles of 128 columns (k_dx_update_wide), at most 256 rows, as far as the planes of partial sums have room for groups that
+//     fill the chip (d = 384: 64 groups of 3 workgroups; d = 128, 64 workgroups, takes the separate kernels), and where an input
+//     gradient is asked for: the update alone has no second read of W to save (21293 E4M3 labels, B = 134: 39 us, 45 us there).
+//     At most 128 rows take it where 256 does not divide d (300000 E4M3 labels, d = 640, B = 128: separate kernels 409 us, 283 us there) and where
+//     a workgroup has no more than four of its tiles (16384 E4M3 labels, d = 256, B = 64: 256 columns 29.5, 128 columns 25.7 us;
+//     16384 x 768, twelve tiles: 35.7 and 36.1; 1 M labels, B = 128, with compensation: 1406 and 1472).
+//   kSeparate: input-gradient product, then update (k_dx, k_update).
+enum Backward { kSeparate, kOnePass256, kOnePass128 };
+struct StepPlan {
+  Pass ps;
+  Backward kernels;
+  int slices;                     // kSeparate: label slices of the input-gradient product
+  int col_blocks, label_groups;   // one pass: workgroups side by side over the columns, and the most over the labels
+  int planes, plane_rows;         // of partial sums of dX: what the step's first launch writes and the end adds up
+  bool one_pass() const { return kernels != kSeparate; }
+  // Label tiles per group.  Not one: a group's plane is as much work as a tile, here and in the final sum (8192 labels, d = 256, 256
+  // groups of one tile / 128 of two / 64 of four: B = 64 28.9 / 25.6 / 26.9 us, B = 128 35.7 / 31.3 / 30.6); below 129 tiles there are CUs to spare.
+  int64_t tiles_per_group(int64_t tiles) const {
+    return std::max<int64_t>((tiles + label_groups - 1) / label_groups, kernels == kOnePass256 && tiles > 128 ? 2 : 1);
+  }
+  int groups(int64_t labels) const {
+    const int64_t t = (labels + 31) / 32, per = tiles_per_group(t);
+    return labels > 0 ? (int)((t + per - 1) / per) : 0;
+  }
+};
+inline StepPlan plan_step(const Plan& p, int Bp, bool want_dx) {
+  StepPlan s;
+  const int d = p.d, Bp256 = round_up(Bp, 256), tiles_b = Bp256 / 256, tiles_j = (d + 255) / 256;
+  const bool no_room = p.drop_thresh && p.fmt != ELMO_FP8_E4M3 && (p.flags & ELMO_KAHAN);
+  const bool narrow = Bp <= 128 && d % 256 == 0 && !no_room;
+  s.ps = choose_pass(p, Bp, narrow, want_dx);
+  const int64_t most = std::min<int64_t>(s.ps.labels, p.L);
+  const int wide_groups = std::max(1, std::min(256 / (d / 128), p.dx_rows / 256));
+  const int64_t wide_tiles = (most + 31) / 32 * (d / 128);
+  const bool wide = want_dx && Bp <= 256 && (!narrow || wide_tiles <= 4 * 256) && wide_groups * (d / 128) >= 192;
+  s.kernels = wide ? kOnePass128 : narrow ? kOnePass256 : kSeparate;
+  s.col_blocks = wide ? d / 128 : d / 256;
+  s.label_groups = wide ? wide_groups : narrow ? std::max(1, 256 / s.col_blocks) : 0;    // widths above 65536: one group
+  // slices: at most one 512-thread workgroup per CU, so the
+  // whole grid is resident at once (256 CUs) and no second, nearly empty round of workgroups runs
+  s.slices = std::min(std::max(1, 256 / (tiles_b * tiles_j)), p.dx_rows / Bp256);
+  s.slices = std::max(1, std::min({s.slices, 64, (int)((most + 63) / 64)}));
+  // a one-pass kernel uses as many planes as its largest launch has label groups
+  s.planes = s.one_pass() ? 1 : s.slices;
+  if (s.one_pass())
+    for (int64_t c0 = 0; c0 < p.L; c0 += s.ps.take(p.L - c0)) {
+      const int64_t n = s.ps.take(p.L - c0), head = std::max<int64_t>(0, std::min(n, p.kahan_rows - c0));
+      s.planes = std::max({s.planes, s.groups(head), s.groups(n - head)});
+    }
+  s.plane_rows = s.kernels == kOnePass256 ? 128 : Bp256;
+  return s;
+}
+
 }  // namespace elmo

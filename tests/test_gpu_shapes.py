@@ -18,17 +18,22 @@ def batch(L, d, B, seed=5, rule="lognormal5"):
     return X, indptr, indices
 
 
-# (B, d, L, chunk, kahan_rows, passes of the step, planes of its first pass, of its last): test_step_passes.py holds the library to the last three
+# (kernels of the backward half, B, d, L, chunk, kahan_rows, passes of the step, planes that its first pass has labels for, its last):
+# test_step_passes.py holds the library to the first and the last three.  "256" / "128": one pass over 256- or 128-column tiles.
 PLANES = [
-    (40, 256, 246016, 9600, 0, 3, 234, 256),        # small batch: a later pass has more label groups than the first
-    (40, 512, 128 * 3 + 5, 128, 0, 1, 13, 13),      # fewer label tiles than groups; a ragged last tile
-    (100, 256, 1024, 1024, 128, 1, 28, 28),         # one pass in two parts, the first with fewer groups than the second
-    (300, 128, 65624, 6400, 0, 2, 58, 64),          # more label slices in the second pass
-    (130, 384, 70, 1000, 0, 1, 2, 2),               # fewer label slabs than slices, half a column tile
+    ("256", 40, 256, 246016, 9600, 0, 3, 234, 256),         # a later pass has more label groups than the first
+    ("256", 40, 512, 8193, 8193, 0, 1, 86, 86),             # the fewest labels; groups of three tiles, the last of two, one label in its last
+    ("256", 100, 256, 20000, 20000, 128, 1, 207, 207),      # one pass in two parts, the first with four groups for 207 planes
+    ("128", 40, 512, 128 * 3 + 5, 128, 0, 1, 13, 13),       # fewer label tiles than groups; a ragged last tile
+    ("128", 100, 256, 1024, 1024, 128, 1, 28, 28),          # one pass in two parts, the first with fewer groups than the second
+    ("128", 130, 384, 70, 1000, 0, 1, 3, 3),
+    ("separate", 300, 128, 65624, 6400, 0, 2, 61, 64),      # 64 label slices, three of them without labels in the first pass
+    ("separate", 300, 384, 70, 1000, 0, 1, 2, 2),           # three label slabs on two slices, half a column tile
+    ("separate", 130, 128, 70, 1000, 0, 1, 2, 2),
 ]
 
 
-@pytest.mark.parametrize("B,d,L,chunk,kahan_rows,passes", [row[:6] for row in PLANES])
+@pytest.mark.parametrize("B,d,L,chunk,kahan_rows,passes", [row[1:7] for row in PLANES])
 def test_input_gradient_planes(b, B, d, L, chunk, kahan_rows, passes):  # noqa: F811
     """The first launch of a step writes every plane of partial sums that the end adds up, whether it has labels
     for it or not; later launches add to them."""
@@ -183,24 +188,25 @@ def test_quantize_sizes_and_alignment(b, fmt, n, first, shift):  # noqa: F811
 
 
 SR, KA = o.FLAG_SR, o.FLAG_KAHAN
-# (fmt, flags, B, d, L, chunk, kahan_rows, dropout threshold, weight decay, passes)
+# (kernels, fmt, flags, B, d, L, chunk, kahan_rows, dropout threshold, weight decay, passes)
 SEVERAL = [
-    (o.E4M3, SR, 40, 256, 250000, 9600, 0, 0, 0.0, 3),              # the small-batch kernel
-    (o.E4M3, SR | KA, 40, 256, 250000, 9600, 128 * 800, 0, 0.0, 3), # compensation ends inside a pass
-    (o.E4M3, SR | KA, 70, 256, 100000, 512, 0, 77, 0.01, 2),        # masked tile copy
-    (o.BF16, SR, 100, 256, 100000, 512, 0, 128, 0.0, 2),
-    (o.BF16, KA, 70, 256, 100000, 512, 128 * 500, 0, 0.01, 2),
-    (o.BF16, KA, 70, 256, 100000, 512, 0, 26, 0.0, 2),              # no room for the masked copy: the separate kernels at a small batch
-    (o.E4M3, SR, 300, 384, 150000, 20000, 0, 0, 0.0, 4),            # the separate kernels, passes in the top-k scratch
-    (o.E4M3, SR | KA, 130, 640, 100003, 30000, 128 * 300, 0, 0.0, 2),   # the last pass ragged
-    (o.E4M3, SR | KA, 300, 128, 100000, 512, 128 * 500, 64, 0.01, 2),
-    (o.BF16, SR, 300, 128, 60000, 512, 0, 128, 0.0, 2),
-    (o.BF16, KA, 600, 256, 60000, 512, 0, 26, 0.01, 2),             # the last pass larger than the first
-    (o.E4M3, SR, 5, 256, 5000, 128, 0, 0, 0.0, 1),                  # everything in one pass
+    ("256", o.E4M3, SR, 40, 256, 250000, 9600, 0, 0, 0.0, 3),
+    ("256", o.E4M3, SR | KA, 40, 256, 250000, 9600, 128 * 800, 0, 0.0, 3),      # compensation ends inside a pass
+    ("256", o.E4M3, SR | KA, 70, 256, 100000, 512, 0, 77, 0.01, 2),             # masked tile copy
+    ("256", o.BF16, SR, 100, 256, 100000, 512, 0, 128, 0.0, 2),
+    ("256", o.BF16, KA, 70, 256, 100000, 512, 128 * 500, 0, 0.01, 2),
+    ("128", o.BF16, KA, 70, 256, 100000, 512, 0, 26, 0.0, 2),                   # no room for the masked copy of 256 columns
+    ("128", o.E4M3, SR | KA, 130, 640, 100003, 30000, 128 * 300, 0, 0.0, 2),    # the last pass ragged
+    ("separate", o.E4M3, SR, 300, 384, 150000, 20000, 0, 0, 0.0, 4),            # passes in the top-k scratch
+    ("separate", o.E4M3, SR | KA, 300, 128, 100000, 512, 128 * 500, 64, 0.01, 2),
+    ("separate", o.E4M3, SR | KA, 70, 128, 100000, 512, 128 * 500, 64, 0.01, 2),    # a small batch
+    ("separate", o.BF16, SR, 300, 128, 60000, 512, 0, 128, 0.0, 2),
+    ("separate", o.BF16, KA, 600, 256, 60000, 512, 0, 26, 0.01, 2),             # the last pass larger than the first
+    ("128", o.E4M3, SR, 5, 256, 5000, 128, 0, 0, 0.0, 1),                       # everything in one pass
 ]
 
 
-@pytest.mark.parametrize("fmt,flags,B,d,L,chunk,kahan_rows,T,wd,passes", SEVERAL)
+@pytest.mark.parametrize("fmt,flags,B,d,L,chunk,kahan_rows,T,wd,passes", [row[1:] for row in SEVERAL])
 def test_passes_larger_than_the_chunk(b, fmt, flags, B, d, L, chunk, kahan_rows, T, wd, passes):  # noqa: F811
     """A head whose passes are made of several chunks computes what one with a single chunk does: the same weights and
     compensation bit by bit, dX and loss to the order of FP32 sums (BF16 rounding of dX: one spacing, 2^-8 in norm), and
@@ -383,19 +389,26 @@ def test_short_rings_and_cut_blocks(b, fmt, flags, T, B, d, L):  # noqa: F811
     assert_dx_close(dX, ref["dX_partial"], tol)
 
 
-@pytest.mark.parametrize("B,d,L,kahan_rows", [
-    (129, 256, 31, 0),      # the fewest rows, less than a label tile
-    (192, 640, 97, 0),      # the second half of the samples half empty
-    (193, 384, 4133, 128),  # one row beyond 192; compensation for the first tiles, a launch each
-    (256, 768, 3000, 0),    # the most rows; groups of three label tiles, the last with fewer
-    (1, 384, 33, 0),        # one row, where 256 does not divide the width
-    (128, 640, 4100, 128),  # three groups of samples for the lower waves' steps, none for half of the upper waves
-    (64, 256, 32768, 0),    # the most tiles of a small batch that still takes this kernel, and (65) one more row
-    (65, 256, 32769, 0),
-])
-@pytest.mark.parametrize("fmt,flags,T,wd", [(o.E4M3, o.FLAG_SR | o.FLAG_KAHAN, 0, 0.0), (o.E4M3, o.FLAG_SR, 64, 0.01), (o.BF16, o.FLAG_KAHAN, 64, 0.0), (o.BF16, o.FLAG_SR, 0, 0.0)])
-def test_one_pass_kernel_of_128_columns(b, fmt, flags, T, wd, B, d, L, kahan_rows):  # noqa: F811
-    """Input gradient and update in one pass over 128-column tiles, the update a tile late."""
+# (kernel, B, d, L, kahan_rows)
+ONE_PASS = [
+    ("128", 129, 256, 31, 0),       # the fewest rows, less than a label tile
+    ("128", 192, 640, 97, 0),       # the second half of the samples half empty
+    ("128", 193, 384, 4133, 128),   # one row beyond 192; compensation for the first tiles, a launch each
+    ("128", 256, 768, 3000, 0),     # the most rows; groups of three label tiles, the last with fewer
+    ("128", 1, 384, 33, 0),         # one row, where 256 does not divide the width
+    ("128", 128, 640, 4100, 128),   # three groups of samples for the lower waves' steps, none for half of the upper waves
+    ("128", 64, 256, 16384, 0),     # the most tiles of a small batch that still takes 128 columns,
+    ("256", 64, 256, 16385, 0),     # one label more: the last of three to a group holds one label,
+    ("256", 65, 256, 16385, 8192),  # and one more row; compensation for half of the labels
+]
+ONE_PASS_MODES = [(o.E4M3, SR | KA, 0, 0.0), (o.E4M3, SR, 64, 0.01), (o.BF16, KA, 64, 0.0), (o.BF16, SR, 0, 0.0)]
+
+
+@pytest.mark.parametrize("B,d,L,kahan_rows", [row[1:] for row in ONE_PASS])
+@pytest.mark.parametrize("fmt,flags,T,wd", ONE_PASS_MODES)
+def test_one_pass_kernels(b, fmt, flags, T, wd, B, d, L, kahan_rows):  # noqa: F811
+    """Input gradient and update in one pass over the weights, over 128-column tiles (the update a tile late) and 256-column ones; the
+    update alone, which other kernels do beyond 128 rows and at other widths, gives the same bits."""
     kr = kahan_rows if flags & o.FLAG_KAHAN else 0
     case = Case(b, L, d, fmt, L, flags, B, w_std=0.05, comp_std=2e-4 if flags & o.FLAG_KAHAN else 0.0, seed=12, kahan_rows=kr, weight_decay=wd, dropout_p=T / 256)
     case.head.workspace.fill_(0x7F)
@@ -416,6 +429,10 @@ def test_one_pass_kernel_of_128_columns(b, fmt, flags, T, wd, B, d, L, kahan_row
         same = dist[:n] == 0
         err = np.abs(o.decode_bf16(case.C()[:n]) - o.decode_bf16(ref["comp_new"][:n]))[same] / np.maximum(np.abs(o.decode(ref["W_new"][:n], fmt)), 2.0**-9)[same]
         assert np.quantile(err, 0.999) <= 2.0**-8
+    alone = Case(b, L, d, fmt, L, flags, B, w_std=0.05, comp_std=2e-4 if flags & o.FLAG_KAHAN else 0.0, seed=12, kahan_rows=kr, weight_decay=wd, dropout_p=T / 256, like=case)
+    alone.head.workspace.fill_(0x7F)
+    alone.step(X, indptr, indices, 0.05, 3, 1, want_dx=False)
+    assert np.array_equal(alone.W(), case.W()) and (not flags & o.FLAG_KAHAN or np.array_equal(alone.C(), case.C()))
 
 
 @pytest.mark.parametrize("B,L,d,per_row", [(1, 100, 128, 1), (3, 129, 256, 40), (64, 8192, 256, 5), (128, 1000, 384, 16), (127, 70000, 256, 2), (128, 300, 256, 17)])

@@ -10,23 +10,31 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = r"""
 #include "plan.h"
-// out: off_g, end of its region, slots, off_topk, total, number of passes, then the passes' labels (at most 4096)
-extern "C" int step_passes(int64_t L, int d, int fmt, int64_t chunk, int max_B, int B, int kahan_bf16_drop, int want_dx, int64_t* out) {
+// out: off_g, end of its region, slots, off_topk, total, kernels of the backward half, planes, rows of a plane, rows of all planes that there is
+// room for, number of passes, then for each (at most 2000) its labels and the planes that it has labels for
+extern "C" int step_plan(int64_t L, int d, int fmt, int64_t chunk, int max_B, int B, int64_t kahan_rows, int flags, int drop_thresh, int want_dx, int64_t* out) {
   elmo::Plan p{};
   p.L = L; p.d = d; p.fmt = fmt; p.chunk = (chunk + 127) / 128 * 128; p.maxB = max_B; p.max_nnz = 64 * max_B;
+  p.flags = flags; p.kahan_rows = flags & ELMO_KAHAN ? (kahan_rows ? kahan_rows : L) : 0; p.drop_thresh = drop_thresh;
   elmo::lay_out(p);
-  const int Bp = elmo::round_up(B, 64);
-  const bool small = Bp <= 128 && d % 256 == 0 && !kahan_bf16_drop;
-  const elmo::Pass ps = elmo::choose_pass(p, Bp, small, want_dx != 0);
+  const elmo::StepPlan s = elmo::plan_step(p, elmo::round_up(B, 64), want_dx != 0);
+  const elmo::Pass& ps = s.ps;
   out[0] = ps.off_g; out[1] = ps.off_g == p.off_g ? p.off_dx : ps.slots; out[2] = ps.slots; out[3] = p.off_topk; out[4] = p.total;
-  int64_t n = 0, c0 = 0;
-  for (; c0 < L && n < 4096; c0 += ps.take(L - c0)) out[6 + n++] = ps.take(L - c0);
-  out[5] = n;
-  int64_t largest = 0;
-  for (int i = 0; i < n; ++i) largest = out[6 + i] > largest ? out[6 + i] : largest;
+  out[5] = s.kernels; out[6] = s.planes; out[7] = s.plane_rows; out[8] = p.dx_rows;
+  int64_t n = 0, c0 = 0, largest = 0;
+  for (; c0 < L && n < 2000; c0 += ps.take(L - c0), ++n) {
+    const int64_t labels = ps.take(L - c0), head = std::max<int64_t>(0, std::min(labels, p.kahan_rows - c0));
+    const int64_t slabs = (labels + 31) / 32, per = (slabs + s.slices - 1) / s.slices;    // as k_dx cuts them
+    out[10 + 2 * n] = labels;
+    out[11 + 2 * n] = s.one_pass() ? std::max(s.groups(head), s.groups(labels - head)) : (slabs + per - 1) / per;
+    largest = std::max(largest, labels);
+  }
+  out[9] = n;
   return c0 == L && largest == ps.largest(L) ? 0 : -1;
 }
 """
+SEPARATE, ONE_PASS_256, ONE_PASS_128 = 0, 1, 2
+SR, KAHAN = 1, 2
 
 
 def load(tmp):
@@ -34,13 +42,16 @@ def load(tmp):
     lib = str(tmp / "shim.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
                     os.path.join(ROOT, "paper_2510_11168_amd", "csrc"), "-o", lib, str(tmp / "shim.cpp")], check=True)
-    f = ctypes.CDLL(lib).step_passes
-    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64] + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int64)]
+    f = ctypes.CDLL(lib).step_plan
+    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_int,
+                  ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
 
-    def passes(L, d, fmt, chunk, B, max_B=None, separate=False, want_dx=True):
+    def passes(L, d, fmt, chunk, B, max_B=None, kahan_rows=0, flags=SR, drop=0, want_dx=True):
         out = (ctypes.c_int64 * 4200)()
-        assert f(L, d, fmt, chunk, max_B or B, B, int(separate), int(want_dx), out) == 0
-        return dict(off=out[0], end=out[1], slots=out[2], off_topk=out[3], total=out[4], labels=list(out[6:6 + out[5]]))
+        assert f(L, d, fmt, chunk, max_B or B, B, kahan_rows, flags, drop, int(want_dx), out) == 0
+        n = out[9]
+        return dict(off=out[0], end=out[1], slots=out[2], off_topk=out[3], total=out[4], kernels=out[5], planes=out[6], plane_rows=out[7],
+                    dx_rows=out[8], labels=list(out[10:10 + 2 * n:2]), filled=list(out[11:11 + 2 * n:2]))
     return passes
 
 
@@ -59,13 +70,17 @@ def test_passes_cover_the_labels_and_their_gradients_fit(passes):
         max_B = log_int(1, 8192)
         B = rng.choice([max_B, log_int(1, max_B)])
         chunk = rng.choice([1, 128, log_int(1, L), L, 2 * L])
-        if L > 2000 * max(chunk, 1):
-            chunk = L // 2000 + 1
-        r = passes(L, d, fmt, chunk, B, max_B, rng.random() < 0.2, rng.random() < 0.8)
+        if L > 1900 * max(chunk, 1):
+            chunk = L // 1900 + 1
+        kahan = rng.random() < 0.5
+        r = passes(L, d, fmt, chunk, B, max_B, L // 3 // 128 * 128 if kahan and rng.random() < 0.5 else 0, SR | KAHAN if kahan else SR,
+                   64 if rng.random() < 0.2 else 0, rng.random() < 0.8)
         n, chunk128, Bp = r["labels"], (chunk + 127) // 128 * 128, (B + 63) // 64 * 64
         assert sum(n) == L and all(x % 128 == 0 for x in n[:-1]) and all(x >= min(chunk128, L) for x in n[:-1])
         # whole tiles of 128 labels, and the last rows are read 512 bytes wide
         assert r["off"] + (max(n) + 127) // 128 * 128 * Bp * 2 + 4096 <= r["end"]
+        # every plane of partial sums has its room, and is written by some pass
+        assert r["planes"] * r["plane_rows"] <= r["dx_rows"] and max(r["filled"]) <= r["planes"]
         # tile losses of 128 x 128 tiles, behind everything else
         assert r["slots"] == 0 or (r["off_topk"] <= r["slots"] and r["slots"] + (L + 127) // 128 * ((Bp + 127) // 128) * 4 <= r["total"])
 
@@ -79,28 +94,19 @@ def test_an_input_gradient_that_is_not_asked_for_is_not_priced(passes, B, fmt):
     assert passes(60000, 768, fmt, 16384, B, want_dx=False)["labels"] == [20096, 20096, 19808]
 
 
-def planes(labels, B, d, kahan_rows=0):
-    """Planes of input-gradient partials that a pass over `labels` labels fills: label groups of 32-label tiles for a small
-    batch, slices of 64-label slabs otherwise."""
-    Bp = (B + 63) // 64 * 64
-    if Bp <= 128 and d % 256 == 0:
-        def groups(n):
-            t = -(-n // 32)
-            return -(-t // -(-t // max(1, 256 // (d // 256))))
-        parts = [n for n in (min(kahan_rows, labels), labels - min(kahan_rows, labels)) if n]
-        return max(groups(n) for n in parts)
-    slabs = -(-labels // 64)
-    S = min(max(1, 256 // (-(-Bp // 256) * -(-d // 256))), 64, slabs)
-    return -(-slabs // -(-slabs // S))
-
-
 def test_heads_of_the_gpu_tests_split_as_they_say(passes):
-    """The GPU tests of later passes are worth something only while their heads really go in several."""
+    """The GPU tests of later passes and of single kernels are worth something only while their heads really go that way."""
     gpu = pytest.importorskip("test_gpu_shapes")
-    for B, d, L, chunk, kahan_rows, n, first, last in gpu.PLANES:
-        labels = passes(L, d, gpu.o.E4M3, chunk, B)["labels"]
-        assert len(labels) == n and planes(labels[0], B, d, kahan_rows) == first and planes(labels[-1], B, d, kahan_rows) == last, (labels, B, d, L)
-    for fmt, flags, B, d, L, chunk, kahan_rows, T, wd, n in gpu.SEVERAL:
-        separate = T and fmt == gpu.o.BF16 and flags & gpu.KA
-        assert len(passes(L, d, fmt, chunk, B, separate=bool(separate))["labels"]) == n, (fmt, flags, B, d, L)
-        assert len(passes(L, d, fmt, L, B, separate=bool(separate))["labels"]) == 1
+    kernels = {"separate": SEPARATE, "256": ONE_PASS_256, "128": ONE_PASS_128}
+    for kernel, B, d, L, chunk, kahan_rows, n, first, last in gpu.PLANES:
+        r = passes(L, d, gpu.o.E4M3, chunk, B, kahan_rows=kahan_rows, flags=gpu.SR | (gpu.KA if kahan_rows else 0))
+        assert (r["kernels"], len(r["labels"]), r["filled"][0], r["filled"][-1]) == (kernels[kernel], n, first, last), (r, B, d, L)
+    for kernel, fmt, flags, B, d, L, chunk, kahan_rows, T, wd, n in gpu.SEVERAL:
+        for ch, several in ((chunk, n), (L, 1)):
+            r = passes(L, d, fmt, ch, B, kahan_rows=kahan_rows, flags=flags, drop=T)
+            assert (r["kernels"], len(r["labels"])) == (kernels[kernel], several), (r["kernels"], len(r["labels"]), fmt, flags, B, d, L)
+    for kernel, B, d, L, kahan_rows in gpu.ONE_PASS:
+        for fmt, flags, T, wd in gpu.ONE_PASS_MODES:
+            r = passes(L, d, fmt, L, B, kahan_rows=kahan_rows if flags & gpu.KA else 0, flags=flags, drop=T)
+            no_room = T and fmt == gpu.o.BF16 and flags & gpu.KA
+            assert r["kernels"] == (ONE_PASS_128 if no_room else kernels[kernel]), (r, fmt, flags, B, d, L)
