@@ -136,11 +136,7 @@ struct StepPlan {
   int col_blocks, label_groups;   // one pass: workgroups side by side over the columns, and the most over the labels
   int planes, plane_rows;         // of partial sums of dX: what the step's first launch writes and the end adds up
   bool one_pass() const { return kernels != kSeparate; }
-  // Label tiles per group.  Not one: a group's plane is as much work as a tile, here and in the final sum (8192 labels, d = 256, 256
-  // groups of one tile / 128 of two / 64 of four: B = 64 28.9 / 25.6 / 26.9 us, B = 128 35.7 / 31.3 / 30.6); below 129 tiles there are CUs to spare.
-  int64_t tiles_per_group(int64_t tiles) const {
-    return std::max<int64_t>((tiles + label_groups - 1) / label_groups, kernels == kOnePass256 && tiles > 128 ? 2 : 1);
-  }
+  int64_t tiles_per_group(int64_t tiles) const { return (tiles + label_groups - 1) / label_groups; }
   int groups(int64_t labels) const {
     const int64_t t = (labels + 31) / 32, per = tiles_per_group(t);
     return labels > 0 ? (int)((t + per - 1) / per) : 0;

@@ -94,6 +94,14 @@ def test_an_input_gradient_that_is_not_asked_for_is_not_priced(passes, B, fmt):
     assert passes(60000, 768, fmt, 16384, B, want_dx=False)["labels"] == [20096, 20096, 19808]
 
 
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("L,B", [(4097, 16), (5000, 128), (8192, 64)])
+def test_one_label_tile_per_workgroup_where_there_are_cus(passes, L, B, fmt):
+    """An update without an input gradient has no planes to write: up to 256 tiles of 32 labels each has a workgroup of its own at d = 256."""
+    r = passes(L, 256, fmt, L, B, want_dx=False)
+    assert (r["kernels"], r["labels"], r["filled"]) == (ONE_PASS_256, [L], [-(-L // 32)])
+
+
 def test_heads_of_the_gpu_tests_split_as_they_say(passes):
     """The GPU tests of later passes and of single kernels are worth something only while their heads really go that way."""
     gpu = pytest.importorskip("test_gpu_shapes")
