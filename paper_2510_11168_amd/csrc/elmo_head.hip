@@ -406,7 +406,6 @@ int raise_lds_limits() {
 // would have no tile, and four times the tiles, two on a CU at once, are one wave up to here.  32768 BF16 labels,
 // B = 256, d = 768: 30.4 -> 24.8 us; 60000 E4M3 labels, d = 512, B = 160, whole step: 134 -> 120 us; with a second wave
 // of the small tiles the large ones win (43776 labels: 34 us against 43 us).
-constexpr int kLogitsSmallGrid = 128;
 
 }  // namespace
 
@@ -469,7 +468,7 @@ extern "C" int elmo_head_step(elmo_head_t* h, const void* X, int32_t B, const in
 
   // the logits kernel's tile is tb samples x tb labels
   const int64_t pass_tiles = (ps.largest(p.L) + 255) / 256 * tiles_b;
-  const int tb = Bp <= 128 || (pass_tiles <= kLogitsSmallGrid && ps.slots) ? 128 : 256;
+  const int tb = Bp <= 128 || (pass_tiles <= elmo::kLogitsSmallGrid && ps.slots) ? 128 : 256;
   const int loss_tiles = (Bp + tb - 1) / tb;
   if (tb == 128 && Bp > 128) loss_slots = (float*)(h->ws + ps.slots);
   // ---- chunk schedule (Section 4.2): forward, backward and update of one label chunk at a time

@@ -58,18 +58,26 @@ inline void lay_out(Plan& p) {
 // their gradients anyway -- the chunk's own region when the batch is smaller than max_B, or the top-k
 // scratch, which is idle during a step.  Short launches cost most: L = 8192, B = 64 in chunks of 2048 spent
 // 54 of 61 us in eight kernels of 6-7 us each that leave most of the chip idle, one pass takes 26 us.
-// A larger batch has whole waves of 256 x 256 tiles to think of (one workgroup per CU): 677016 labels at
-// B = 2733 in passes of 16384 (192 update tiles) take 10.06 ms and in passes of 22656 (267, a second
-// wave of 11) 10.85 ms.  So every number of passes that the room allows is priced with the waves of
-// its launches (microseconds per tile and K slab as measured at d = 768: a tile's epilogue and its slabs,
-// and what the launches cost before and after their tiles, 15 us, 13 without the input gradient where dX is not asked
-// for: 60000 E4M3 labels at B = 3000 506 us in the passes that are cheapest with it, 480 without) and the cheapest is
-// taken, the chunk itself included.  The prices only rank the splits of one head, and coarsely: they give
-// 258 us for the step of 131072 BF16 labels with compensation at B = 256 that takes 424, whose update is bound by
-// memory.  Offered are passes of equal size, and passes of whole waves of update tiles, the last of which takes what is
-// left if that fits (L = 131072, B = 256: 171 + 171 + 170 label tiles 442 us, 170 + 170 + 172 420 us).  No pass but the
-// last is smaller than the chunk.  Results do not depend on the split: every label's quantities depend on its own
-// weight row only, and dX is summed in FP32.
+// So every number of passes that the room allows is priced by what the backward kernels of the step (below) have to do and the cheapest is
+// taken, the chunk itself included; at one price the larger passes.
+//   kSeparate has whole waves of 256 x 256 tiles to think of (one workgroup per CU): 677016 labels at
+//     B = 2733 in passes of 16384 (192 update tiles) take 10.06 ms and in passes of 22656 (267, a second
+//     wave of 11) 10.85 ms.  Its prices are the waves of the launches (microseconds per tile and K slab as measured at d = 768: a tile's epilogue
+//     and its slabs, and what the launches cost before and after their tiles, 15 us, 13 without the input gradient where dX is not asked
+//     for: 60000 E4M3 labels at B = 3000 506 us in the passes that are cheapest with it, 480 without).
+//   kOnePass128 is a pass over the weights whatever the split; a pass costs its launches and the planes of partial sums that it reads and
+//     writes (20 us), the waves of its logits tiles (half a tile each, the rest hides behind other work; up to 128 tiles of 256 labels take the small
+//     ones, two to a CU), and the label tiles of its longest group.  1031 heads, 129 to 256 rows and 384 or 640 columns at fewer, each at up to 12 splits:
+//     the split with this price is 0.4 % slower than the best on average (worst 13 %), priced as kSeparate 1.5 % (15 %), the fewest passes
+//     1.3 % (19 %).  1202307 E4M3 labels, d = 768, B = 129: 28 passes 2567 us, 23 passes 2323.  (What it cannot see: for some numbers of label tiles to a
+//     group the groups' strides meet in memory, 58 or 59 tiles of 640 columns with compensation 15 % slower than 57 or 60.)
+//   kOnePass256 (at most 128 rows) takes the fewest passes, of equal size.
+// Offered are passes of equal size, and for kSeparate passes of whole waves of update tiles (L = 131072, B = 256: 171 + 171 + 170 label tiles
+// 442 us, 170 + 170 + 172 420 us), for kOnePass128 of whole waves of small logits tiles, the last of which takes what is
+// left if that fits.  No pass but the last is smaller than the chunk.  The prices only rank the splits of one head.  Results do
+// not depend on the split: every label's quantities depend on its own weight row only, and dX is summed in FP32.
+constexpr int kLogitsSmallGrid = 128;     // 256 x 256 logits tiles of a launch up to which 128 x 128 tiles take their place
+enum Backward { kSeparate, kOnePass256, kOnePass128 };
 struct Pass {
   int64_t labels, most;      // labels of a pass; what is left at the end is one pass if it is no more than `most`
   size_t off_g, slots;
@@ -79,23 +87,31 @@ struct Pass {
     return std::max(before ? labels : 0, L - before * labels);
   }
 };
-inline Pass choose_pass(const Plan& p, int Bp, bool small_batch, bool want_dx) {
+inline int label_groups_128(const Plan& p) { return std::max(1, std::min(256 / (p.d / 128), p.dx_rows / 256)); }
+inline Pass choose_pass(const Plan& p, int Bp, Backward kernels, bool want_dx) {
   // tile losses of 128 x 128 logits tiles at a batch above 128 go to the end of the top-k scratch (0: no room)
   const size_t slots = align256((size_t)p.ntiles * ((Bp + 127) / 128) * 4);
   Pass best{p.chunk, p.chunk, p.off_g, p.total - p.off_topk >= slots ? p.total - slots : 0};
   if (p.chunk >= p.L) return best;
   const int esz = p.fmt == ELMO_FP8_E4M3 ? 1 : 2;
   const int64_t tiles_b = (Bp + 255) / 256, tiles_j = (p.d + 255) / 256, slices = std::max<int64_t>(1, 256 / (tiles_b * tiles_j));
-  auto launches = [&](int64_t n) {
+  const int groups = label_groups_128(p);
+  auto launches = [&](int64_t n, bool small_logits) {
     const int64_t lt = (n + 255) / 256;
+    if (kernels == kOnePass128) {
+      const int64_t tiles = (n + 31) / 32;
+      const double waves = Bp <= 128 ? (double)(((n + 127) / 128 + 511) / 512) : small_logits ? 0.8 : (double)((lt + 255) / 256);
+      return 20.0 + waves * (3.0 + 0.7 * (p.d * esz / 128)) + (double)((tiles + groups - 1) / groups);
+    }
     return (double)((lt * tiles_j + 255) / 256) * (10.0 + 1.4 * (Bp / 64)) + (double)((lt * tiles_b + 255) / 256) * (6.0 + 1.4 * (p.d * esz / 128)) +
            (want_dx ? 1.4 * (double)((lt * 4 + slices - 1) / slices) + 15.0 : 13.0);
   };
   auto price = [&](int64_t n, int64_t most) {
-    const int64_t before = (p.L - most + n - 1) / n;           // (most < L, or one pass)
-    return p.L <= most ? launches(p.L) : (double)before * launches(n) + launches(p.L - before * n);
+    const int64_t before = p.L <= most ? 0 : (p.L - most + n - 1) / n, last = p.L - before * n;
+    const bool small_logits = best.slots && (std::max(before ? n : 0, last) + 255) / 256 * tiles_b <= kLogitsSmallGrid;
+    return (double)before * launches(n, small_logits) + launches(last, small_logits);
   };
-  double cheapest = small_batch ? 0.0 : price(p.chunk, p.chunk);
+  double cheapest = kernels == kOnePass256 ? 0.0 : price(p.chunk, p.chunk);
   for (auto [off, end] : {std::pair<size_t, size_t>{p.off_g, p.off_dx}, {p.off_topk, best.slots}}) {
     if (end < off) continue;
     if (end - off <= 4096) continue;
@@ -104,15 +120,18 @@ inline Pass choose_pass(const Plan& p, int Bp, bool small_batch, bool want_dx) {
     const int64_t least = (p.L + room - 1) / room;
     auto consider = [&](int64_t labels) {
       if (labels <= p.chunk || labels > room) return;
-      if (const double t = price(labels, room); t < cheapest) { cheapest = t; best = {labels, room, off, best.slots}; }
+      const double t = price(labels, room);
+      if (t > cheapest + 1e-6 || (t > cheapest - 1e-6 && (kernels == kSeparate || labels <= best.labels))) return;
+      cheapest = t;
+      best = {labels, room, off, best.slots};
     };
-    if (small_batch) {                         // no tiles to fill: the fewer launches the better
+    if (kernels == kOnePass256) {              // no tiles to fill: the fewer launches the better
       const int64_t labels = ((p.L + least - 1) / least + 127) / 128 * 128;
       if (labels > best.labels) best = {labels, labels, off, best.slots};
       continue;
     }
     for (int64_t passes = least; passes < least + 64; ++passes) consider(((p.L + passes - 1) / passes + 127) / 128 * 128);
-    for (int64_t waves = 1; waves <= 64; ++waves) consider(256 * waves / tiles_j * 256);
+    for (int64_t waves = 1; waves <= 64; ++waves) consider(kernels == kSeparate ? 256 * waves / tiles_j * 256 : 32768 * waves);
   }
   return best;
 }
@@ -128,7 +147,6 @@ inline Pass choose_pass(const Plan& p, int Bp, bool small_batch, bool want_dx) {
 //     a workgroup has no more than four of its tiles (16384 E4M3 labels, d = 256, B = 64: 256 columns 29.5, 128 columns 25.7 us;
 //     16384 x 768, twelve tiles: 35.7 and 36.1; 1 M labels, B = 128, with compensation: 1406 and 1472).
 //   kSeparate: input-gradient product, then update (k_dx, k_update).
-enum Backward { kSeparate, kOnePass256, kOnePass128 };
 struct StepPlan {
   Pass ps;
   Backward kernels;
@@ -147,11 +165,11 @@ inline StepPlan plan_step(const Plan& p, int Bp, bool want_dx) {
   const int d = p.d, Bp256 = round_up(Bp, 256), tiles_b = Bp256 / 256, tiles_j = (d + 255) / 256;
   const bool no_room = p.drop_thresh && p.fmt != ELMO_FP8_E4M3 && (p.flags & ELMO_KAHAN);
   const bool narrow = Bp <= 128 && d % 256 == 0 && !no_room;
-  s.ps = choose_pass(p, Bp, narrow, want_dx);
-  const int64_t most = std::min<int64_t>(s.ps.labels, p.L);
-  const int wide_groups = std::max(1, std::min(256 / (d / 128), p.dx_rows / 256));
-  const int64_t wide_tiles = (most + 31) / 32 * (d / 128);
-  const bool wide = want_dx && Bp <= 256 && (!narrow || wide_tiles <= 4 * 256) && wide_groups * (d / 128) >= 192;
+  const int wide_groups = label_groups_128(p);
+  const bool may_wide = want_dx && Bp <= 256 && wide_groups * (d / 128) >= 192;
+  s.ps = choose_pass(p, Bp, narrow ? kOnePass256 : may_wide ? kOnePass128 : kSeparate, want_dx);
+  const int64_t most = std::min<int64_t>(s.ps.labels, p.L), wide_tiles = (most + 31) / 32 * (d / 128);
+  const bool wide = may_wide && (!narrow || wide_tiles <= 4 * 256);
   s.kernels = wide ? kOnePass128 : narrow ? kOnePass256 : kSeparate;
   s.col_blocks = wide ? d / 128 : d / 256;
   s.label_groups = wide ? wide_groups : narrow ? std::max(1, 256 / s.col_blocks) : 0;    // widths above 65536: one group

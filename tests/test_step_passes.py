@@ -94,6 +94,14 @@ def test_an_input_gradient_that_is_not_asked_for_is_not_priced(passes, B, fmt):
     assert passes(60000, 768, fmt, 16384, B, want_dx=False)["labels"] == [20096, 20096, 19808]
 
 
+@pytest.mark.parametrize("L,d,fmt,chunk,B,n", [(1500000, 640, 0, 16384, 32, 16), (562459, 640, 1, 16384, 25, 6), (1000000, 768, 1, 30000, 160, 19),
+                                             (1202307, 768, 1, 16384, 129, 23)])
+def test_one_pass_heads_are_not_cut_for_update_tiles(passes, L, d, fmt, chunk, B, n):
+    """A pass of a one-pass kernel has no waves of update tiles to fill; what it costs besides its labels is its launches and planes."""
+    r = passes(L, d, fmt, chunk, B)
+    assert (r["kernels"], len(r["labels"])) == (ONE_PASS_128, n)
+
+
 @pytest.mark.parametrize("fmt", [0, 1])
 @pytest.mark.parametrize("L,B", [(4097, 16), (5000, 128), (8192, 64)])
 def test_one_label_tile_per_workgroup_where_there_are_cus(passes, L, B, fmt):
