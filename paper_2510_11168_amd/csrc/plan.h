@@ -39,7 +39,7 @@ inline void lay_out(Plan& p) {
   size_t o = 0;
   p.off_xq = o;  o += align256(p.fmt == ELMO_FP8_E4M3 ? (size_t)p.Bp_max * p.d : 0);
   p.off_xt = o;  o += align256((size_t)p.d * p.Bp_max * 2);
-  p.off_g = o;   o += align256((size_t)chunk_eff * p.Bp_max * 2 + 4096);   // + slack: the last rows are read 512 bytes wide
+  p.off_g = o;   o += align256((size_t)chunk_eff * p.Bp_max * 2);   // whole blocks of 32 labels, read and written as such
   p.off_dx = o;  o += align256((size_t)p.dx_rows * p.d * 4);
   p.off_loss = o; o += align256((size_t)p.ntiles * p.tiles_b_max * 4);
   p.off_cnt = o; o += align256((size_t)(p.ntiles + 1) * 4);
@@ -114,8 +114,7 @@ inline Pass choose_pass(const Plan& p, int Bp, Backward kernels, bool want_dx) {
   double cheapest = kernels == kOnePass256 ? 0.0 : price(p.chunk, p.chunk);
   for (auto [off, end] : {std::pair<size_t, size_t>{p.off_g, p.off_dx}, {p.off_topk, best.slots}}) {
     if (end < off) continue;
-    if (end - off <= 4096) continue;
-    const int64_t room = (int64_t)((end - off - 4096) / ((size_t)Bp * 2)) / 128 * 128;   // the last rows are read 512 bytes wide
+    const int64_t room = (int64_t)((end - off) / ((size_t)Bp * 2)) / 128 * 128;
     if (room <= p.chunk) continue;
     const int64_t least = (p.L + room - 1) / room;
     auto consider = [&](int64_t labels) {

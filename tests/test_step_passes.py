@@ -77,8 +77,8 @@ def test_passes_cover_the_labels_and_their_gradients_fit(passes):
                    64 if rng.random() < 0.2 else 0, rng.random() < 0.8)
         n, chunk128, Bp = r["labels"], (chunk + 127) // 128 * 128, (B + 63) // 64 * 64
         assert sum(n) == L and all(x % 128 == 0 for x in n[:-1]) and all(x >= min(chunk128, L) for x in n[:-1])
-        # whole tiles of 128 labels, and the last rows are read 512 bytes wide
-        assert r["off"] + (max(n) + 127) // 128 * 128 * Bp * 2 + 4096 <= r["end"]
+        # whole tiles of 128 labels
+        assert r["off"] + (max(n) + 127) // 128 * 128 * Bp * 2 <= r["end"]
         # every plane of partial sums has its room, and is written by some pass
         assert r["planes"] * r["plane_rows"] <= r["dx_rows"] and max(r["filled"]) <= r["planes"]
         # tile losses of 128 x 128 tiles, behind everything else
