@@ -516,7 +516,7 @@ __device__ __forceinline__ void logits_tile_product(const char* __restrict__ Xa,
   zero_acc(acc);
   ring_pipeline_pp<TB, 128, TB, 128, 2, kGemmWaves, true>(
       Xa, rowb, a_valid, 0, 128, 8, Wc, rowb, w_valid, 0, 128, 8, (int)(rowb >> 7), smem, wave, lane,
-      [&](const char* sa, const char* sb, int q0, int) { logits_slab_product<FP8, FN>(sa, sb, q0 >> 1, wm, wn, lane, acc); },
+      [&](const char* sa, const char* sb, int h) { logits_slab_product<FP8, FN>(sa, sb, h, wm, wn, lane, acc); },
       static_cast<Prep&&>(prep), static_cast<Extra&&>(extra));
 }
 

@@ -167,15 +167,6 @@ __device__ inline uint32_t e4m3_sr(float t, uint32_t r16) {
   return (t != t) ? (((f2u(t) >> 24) & 0x80u) | 0x7Fu) : q;
 }
 
-__device__ inline float e4m3_decode_byte(uint32_t packed, int byte) {
-  switch (byte) {
-    case 0: return __builtin_amdgcn_cvt_f32_fp8((int)packed, 0);
-    case 1: return __builtin_amdgcn_cvt_f32_fp8((int)packed, 1);
-    case 2: return __builtin_amdgcn_cvt_f32_fp8((int)packed, 2);
-    default: return __builtin_amdgcn_cvt_f32_fp8((int)packed, 3);
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // FP32 -> a simulated format with E exponent and M mantissa bits, result as FP32 (the bit-width
 // study of Section 4.3).  IEEE pattern: bias 2^(E-1)-1, top exponent code reserved, gradual

@@ -1,6 +1,6 @@
 // LDS tile staging and MFMA fragment access shared by the head's three matrix products
 // (Algorithm 1: logits, input gradient, weight gradient).  gfx950 only, 64-wide wavefronts,
-// matrix-product workgroups of 512 threads arranged as 4 x 2 waves, each wave owning 64 x 128 outputs.
+// matrix-product workgroups of 512 threads: 4 x 2 waves of 64 x 128 outputs each (logits, update) or 2 x 4 of 128 x 64 (input gradient).
 //
 // LDS tile layout: ROWS rows of ROWB bytes (ROWB = 64, 128, 256 or 512), cut into 16-byte chunks whose
 // index is XORed with a key derived from the row.  gfx950's LDS has 64 banks of 4 bytes (256 bytes
@@ -73,8 +73,7 @@ __device__ inline void barrier_lds() {
 // whole tile rows; each lane fetches the global chunk that belongs at its swizzled position.
 // Rows at or beyond rows_valid (>= 1) re-read the last valid row.  Issues ROWS*ROWB/4096 loads per
 // wave; completion is tracked by vmcnt in issue order.
-// I0, I1: only loads I0 .. I1-1 of the wave's NI loads (default: all), for callers that pace them.
-template <int ROWS, int ROWB, int NW, int I0 = 0, int I1 = 1 << 20>
+template <int ROWS, int ROWB, int NW>
 __device__ inline void dma_tile(const char* __restrict__ g, size_t stride, int rows_valid, char* lds_tile, int wave, int lane,
                                 int chunks_valid = 1 << 20) {
   constexpr int RPI = 1024 / ROWB, CPR = ROWB / 16, NI = ROWS / RPI / NW;
@@ -88,7 +87,7 @@ __device__ inline void dma_tile(const char* __restrict__ g, size_t stride, int r
     g = reinterpret_cast<const char*>(((uintptr_t)hi << 32) | lo);
   }
 #pragma unroll
-  for (int i = (I0 > 0 ? I0 : 0); i < (I1 < NI ? I1 : NI); ++i) {
+  for (int i = 0; i < NI; ++i) {
     const int rbase = (wave * NI + i) * RPI;
     const int r = rbase + lane / CPR;
     const int c = min((lane % CPR) ^ swz_key<ROWB>(r), chunks_valid - 1);   // chunks past a short row re-read its last one
@@ -135,16 +134,6 @@ template <int ROWS, int ROWB> struct TileLoader {
       else v[it] = u32x4{0u, 0u, 0u, 0u};
     }
   }
-  // Branch-free variant: rows at or beyond rows_valid (>= 1) re-read the last valid row.  For
-  // operands whose out-of-range rows only feed outputs that are masked later.
-  __device__ inline void load_clamped(const char* __restrict__ g, size_t stride, int rows_valid, int tid) {
-#pragma unroll
-    for (int it = 0; it < N; ++it) {
-      const int id = it * kThreads + tid;
-      const int r = min(id / CPR, rows_valid - 1), c = id % CPR;
-      v[it] = *reinterpret_cast<const u32x4*>(g + (size_t)r * stride + c * 16);
-    }
-  }
   __device__ inline void store(char* lds, int tid) const {
 #pragma unroll
     for (int it = 0; it < N; ++it) {
@@ -160,13 +149,11 @@ template <int ROWS, int ROWB> struct TileLoader {
 // wait until at most the younger slabs' loads are outstanding (vmcnt counts in issue order), one
 // barrier, refill the stage that was consumed one step earlier, then the slab's products.
 //
-// Ping-pong issue order.  The product of one slab is split in two parts (by default its two
-// halves), mma(stageA, stageB, 0, LATE_AFTER) and mma(stageA, stageB, LATE_AFTER, 4), in units of
-// quarters of the slab.  A wave that issues an asynchronous
+// Ping-pong issue order.  The product of one slab is split in two halves, mma(stageA, stageB, h, ks).  A wave that issues an asynchronous
 // load is held until the memory pipeline accepts it, i.e. roughly for as long as the data takes
 // to move; with every wave issuing at the same point the load and MFMA phases add up instead of
 // overlapping.  Here waves 0..NW/2-1 issue right after the barrier (the whole A slab and the first
-// half of the B slab), waves NW/2..NW-1 between the two parts (the second half of the B slab);
+// half of the B slab), waves NW/2..NW-1 between the two halves (the second half of the B slab);
 // with UNEVEN = false both groups issue an equal share of both slabs.
 // Waves w and w + 4 share a SIMD, so one wave of each SIMD computes while its partner is held.
 // Measured on the BF16 main loop alone: all waves issuing together 1.33 PFLOP/s, equal shares
@@ -175,17 +162,15 @@ template <int ROWS, int ROWB> struct TileLoader {
 //
 // ring_stream_pp is the general form: src(ks, off_a, va, off_b, vb) names slab ks of each operand
 // (byte offset from ga / gb and number of valid rows), so a workgroup can run the ring across the
-// output tiles it owns without draining it; mma(stageA, stageB, q0, q1, ks).  The base pointers are
+// output tiles it owns without draining it.  The base pointers are
 // restrict-qualified parameters on purpose: inlining then tags every LDS access inside with alias
 // information, without which the compiler puts a vmcnt(0) in front of LDS reads it cannot tell
 // from the asynchronous loads still in flight.
 // prep(stageB, ks), if given, is run by every wave on the landed B slab before the product (it may
 // rewrite the slab in LDS); a barrier follows it.
-struct NoPrep {};
-// LATE_AFTER (1..3): the product of a slab is four quarters, mma(stageA, stageB, q0, q1, ks) runs
-// quarters [q0, q1); the late waves issue after LATE_AFTER of them (2 = between the two halves).
 // extra(), if given, runs once, behind the loads of the first slabs.
-template <int AROWS, int AROWB, int BROWS, int BROWB, int NST, int NW, bool UNEVEN, int LATE_AFTER = 2, class Src, class Mma,
+struct NoPrep {};
+template <int AROWS, int AROWB, int BROWS, int BROWB, int NST, int NW, bool UNEVEN, class Src, class Mma,
           class Prep = NoPrep, class Extra = NoPrep>
 __device__ inline void ring_stream_pp(const char* __restrict__ ga, size_t stride_a, int chunks_a, const char* __restrict__ gb,
                                       size_t stride_b, int chunks_b, int nk, char* smem, int wave, int lane, Src&& src, Mma&& mma,
@@ -231,28 +216,28 @@ __device__ inline void ring_stream_pp(const char* __restrict__ ga, size_t stride
       barrier_lds();
     }
     __builtin_amdgcn_sched_barrier(0);
-    mma(st, st + ABYTES, 0, LATE_AFTER, ks);
+    mma(st, st + ABYTES, 0, ks);
     __builtin_amdgcn_sched_barrier(0);
     if (more && late) issue(ks + NST - 1);
     __builtin_amdgcn_sched_barrier(0);
-    mma(st, st + ABYTES, LATE_AFTER, 4, ks);
+    mma(st, st + ABYTES, 1, ks);
   }
   barrier_nofence();   // every wave is done with the ring: the caller may reuse the memory
 }
 
 // One output tile: slab ks of an operand starts at g + ks*adv and has v0 - ks*dv valid rows.
-template <int AROWS, int AROWB, int BROWS, int BROWB, int NST, int NW, bool UNEVEN, int LATE_AFTER = 2, class Mma, class Prep = NoPrep,
+template <int AROWS, int AROWB, int BROWS, int BROWB, int NST, int NW, bool UNEVEN, class Mma, class Prep = NoPrep,
           class Extra = NoPrep>
 __device__ inline void ring_pipeline_pp(const char* __restrict__ ga, size_t stride_a, int va0, int dva, size_t adv_a, int chunks_a,
                                         const char* __restrict__ gb, size_t stride_b, int vb0, int dvb, size_t adv_b, int chunks_b,
                                         int nk, char* smem, int wave, int lane, Mma&& mma, Prep&& prep = Prep{}, Extra&& extra = Extra{}) {
-  ring_stream_pp<AROWS, AROWB, BROWS, BROWB, NST, NW, UNEVEN, LATE_AFTER>(
+  ring_stream_pp<AROWS, AROWB, BROWS, BROWB, NST, NW, UNEVEN>(
       ga, stride_a, chunks_a, gb, stride_b, chunks_b, nk, smem, wave, lane,
       [&](int ks, size_t& off_a, int& va, size_t& off_b, int& vb) {
         off_a = (size_t)ks * adv_a; va = va0 - ks * dva;
         off_b = (size_t)ks * adv_b; vb = vb0 - ks * dvb;
       },
-      [&](const char* sa, const char* sb, int q0, int q1, int) { mma(sa, sb, q0, q1); }, static_cast<Prep&&>(prep), static_cast<Extra&&>(extra));
+      [&](const char* sa, const char* sb, int h, int) { mma(sa, sb, h); }, static_cast<Prep&&>(prep), static_cast<Extra&&>(extra));
 }
 
 // Alternating ring: the K loop of one output tile in slabs of two fragment steps.  Waves w and w + NW / 2 share a SIMD; the

@@ -474,14 +474,14 @@ k_topk_filter_run(const char* __restrict__ Xa, int a_rows, const char* __restric
         off_a = (size_t)b0 * rowb + (size_t)sl * 128; va = a_rows - b0;
         off_b = (size_t)l0 * rowb + (size_t)sl * 128; vb = n - l0;
       },
-      [&](const char* sa, const char* sb, int q0, int q1, int ks) {
+      [&](const char* sa, const char* sb, int h, int ks) {
         const int t = ks / nk, sl = ks - t * nk;
-        if (q0 == 0 && sl == 0) {
+        if (h == 0 && sl == 0) {
           zero_acc(acc);
           fetch_side(t + 1);
         }
-        logits_slab_product<FP8, 4>(sa, sb, q0 >> 1, wm, wn, lane, acc);
-        if (q1 == 4 && sl == nk - 1) { if constexpr (DENSE) filter_dense(t); else filter(t); }
+        logits_slab_product<FP8, 4>(sa, sb, h, wm, wn, lane, acc);
+        if (h == 1 && sl == nk - 1) { if constexpr (DENSE) filter_dense(t); else filter(t); }
       });
   if (agg) {
     barrier_lds();                                                     // every wave's LDS appends are in
@@ -589,11 +589,11 @@ k_topk_small(const char* __restrict__ Xa, int a_rows, const char* __restrict__ W
         off_a = (size_t)b0 * rowb + (size_t)sl * 128; va = a_rows - b0;
         off_b = (size_t)l0 * rowb + (size_t)sl * 128; vb = n - l0;
       },
-      [&](const char* sa, const char* sb, int q0, int q1, int ks) {
+      [&](const char* sa, const char* sb, int h, int ks) {
         const int t = ks / nk, sl = ks - t * nk;
-        if (q0 == 0 && sl == 0) zero_acc(acc);
-        logits_slab_product<FP8, FN>(sa, sb, q0 >> 1, wm, wn, lane, acc);
-        if (q1 == 4 && sl == nk - 1) filter((w0 + t * G) << 8);
+        if (h == 0 && sl == 0) zero_acc(acc);
+        logits_slab_product<FP8, FN>(sa, sb, h, wm, wn, lane, acc);
+        if (h == 1 && sl == nk - 1) filter((w0 + t * G) << 8);
       });
   if (FIRST) return;
   barrier_lds();                                                       // every wave's LDS appends are in
