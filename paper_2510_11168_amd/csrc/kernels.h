@@ -360,7 +360,7 @@ __global__ void __launch_bounds__(kSetupThreads) k_step_setup(const uint16_t* __
 }
 
 // ---------------------------------------------------------------------------------------------
-// The three matrix products share one shape: 512-thread workgroups (8 waves) computing a 256 x 256 output tile,
+// The three matrix products share one shape: 512-thread workgroups (8 waves) computing a 256 x 256 output tile (logits also 128 x 128),
 // operands streamed by asynchronous global->LDS loads through a ring of LDS stages (tiles.h: ring_pipeline_pp for
 // the logits, ring_alternate for the other two).  One workgroup per CU.  On this part the matrix cores and the L2->LDS
 // fill do not overlap for free: a tile of this size halves the fill traffic per flop of a 256 x 128 tile.
@@ -456,8 +456,8 @@ __device__ __forceinline__ void drop_own_rows(char* tile, int wave, int lane, ui
 // accumulation over the full embedding width, then G = sigmoid(Z) - Y, and stores G^T as
 // BF16 in blocks of 32 labels (tiles.h, blk_off), the order in which the other two products take it.  Z never reaches memory.
 // FP8: both operands E4M3, v_mfma_f32_32x32x64_f8f6f4.  BF16: v_mfma_f32_32x32x16_bf16.
-// The positives of the tile's two 128-label bins are turned into a bit mask in LDS before the K
-// loop; afterwards every wave finishes its accumulators in registers (sigmoid, minus the mask
+// The positives of the tile's two 128-label bins are turned into a bit mask in LDS behind the loads of the first
+// slab; after the K loop every wave finishes its accumulators in registers (sigmoid, minus the mask
 // bit, BF16) and stores them a KiB at a time, without LDS and without a workgroup barrier.
 // Rows of G^T between n and the next multiple of 128 are written as zeros (the input-gradient
 // product reads whole 32-label blocks).
@@ -966,8 +966,7 @@ k_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restr
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr int ESZ = FMT == FMT_E4M3 ? 1 : 2;
   constexpr int WQ = FMT == FMT_E4M3 ? 1 : 2;       // 16-byte loads per 16 weights
-  // (the wave index is left a vector value here: with a scalar one, as in the other two products,
-  // this kernel's K loop measured 9 % slower, 66.4 k against 60.4 k clocks per tile)
+  // (the epilogue's wave index is a vector value, the K loop's a scalar one; scalar in both measures the same within 1 %)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
   const int tiles_j = (d + 255) >> 8;
   const int wg = xcd_logical_id(blockIdx.x, gridDim.x);
@@ -977,8 +976,8 @@ k_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __restr
   // halves of 32 labels: per half the lane handles 4 passes x 16 consecutive columns of one row
   // (row = 8 pass + lane / 8; eight lanes cover the 128 columns of a row, i.e. whole 128-byte
   // lines of E4M3 weights -- halves of 64 columns measured 3.5 % slower for E4M3 with
-  // compensation and 7 % faster for BF16).  The first half's weights (and compensation) are fetched before
-  // the product, the second half's pass by pass while the first is being updated, so the
+  // compensation and 7 % faster for BF16).  The first half's weights (and compensation) are fetched behind the loads of
+  // the first slabs (two passes) and right after the product (two), the second half's pass by pass while the first is being updated, so the
   // read-modify-write does not wait on memory.  A wave whose columns lie beyond d (the last
   // column tile of a d = 128 (mod 256) head) has nothing to update.
   const int wl0 = l0 + wm * 64, wj0 = j0 + wn * 128;
@@ -1322,7 +1321,7 @@ k_dx_update(const char* __restrict__ Gt, const char* __restrict__ XT, char* __re
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same in tiles of 32 labels x 128 columns, for padded batches of up to 256 rows (which of the two: elmo_head.hip).  With twice the samples the X operand of the
+// The same in tiles of 32 labels x 128 columns, for padded batches of up to 256 rows (which of the two: plan.h).  With twice the samples the X operand of the
 // gradient product (64 registers a lane) and the slice of dX (128) no longer fit into one wave, so the waves have a role each: waves
 // 0-3 form the gradient of 32 columns over all samples, waves 4-7 the dX of 64 samples x 128 columns, 16 MFMAs a tile either way, and a
 // SIMD holds one of each.  The update of a tile, by all eight, comes one tile late: while the upper waves update tile t - 1 the
@@ -1365,7 +1364,7 @@ __device__ __forceinline__ void dx_update_wide_role(const char* __restrict__ Gt,
   char* wmk = gs0 + 2 * kDxwGsBytes;
   uint16_t* keep = reinterpret_cast<uint16_t*>(wmk + WBYTES);
 
-  const int xoct = (Bp >> 3) - 1, KS = Bp >> 4;              // last octet of the samples; k16 steps over them: 12 or 16
+  const int xoct = (Bp >> 3) - 1, KS = Bp >> 4;              // last octet of the samples; k16 steps over them: 4, 8, 12 or 16
   bf16x8 xt[LOWER ? 16 : 1];                                 // lower: X^T fragments of columns 32 rw ..
   f32x16 dxa[LOWER ? 1 : 2][4];                              // upper: dX of samples 64 rw .., all columns
   if constexpr (LOWER) {

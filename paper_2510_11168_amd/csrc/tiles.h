@@ -250,8 +250,9 @@ __device__ inline void ring_pipeline_pp(const char* __restrict__ ga, size_t stri
 // waves had in registers (lgkmcnt(0)) one barrier earlier; the younger slabs stay in flight over a wait (vmcnt counts in issue order).
 // The update's K loop alone (131072 x 768 outputs, 1024 samples, values as in training, random): 1381 TFLOP/s, 1168 clocks a
 // slab of 32 samples (1024 are MFMAs).  Free-running waves with the same loads and two fragment sets ahead: 1266 TFLOP/s, 1450
-// clocks, with 3 stages or with 5 (so it is not the latency of the loads).  The rest is power: on zeros the same loop
-// runs 1774 TFLOP/s at 2.2 GHz, on random values the clock falls to 1.6 GHz.
+// clocks, with 3 stages or with 5 (so it is not the latency of the loads).  What this loop alone lacks is clock: on zeros it
+// runs 1774 TFLOP/s at 2.2 GHz, on random values at 1.6 GHz.  (Within the kernels, whose epilogues leave the matrix cores idle, the clock stays
+// near 2 GHz: there the epilogues are what is left.)
 template <int LPS, int N> __device__ inline void wait_slabs(int left) {   // at most min(left, N) slabs of LPS loads outstanding
   if constexpr (N == 0) wait_vmcnt<0>();
   else if (left >= N) wait_vmcnt<N * LPS>();
