@@ -59,7 +59,7 @@ inline void lay_out(Plan& p) {
 // scratch, which is idle during a step.  Short launches cost most: L = 8192, B = 64 in chunks of 2048 spent
 // 54 of 61 us in eight kernels of 6-7 us each that leave most of the chip idle, one pass takes 26 us.
 // So every number of passes that the room allows is priced by what the backward kernels of the step (below) have to do and the cheapest is
-// taken, the chunk itself included; at one price the larger passes.
+// taken, the chunk itself included.
 //   kSeparate has whole waves of 256 x 256 tiles to think of (one workgroup per CU): 677016 labels at
 //     B = 2733 in passes of 16384 (192 update tiles) take 10.06 ms and in passes of 22656 (267, a second
 //     wave of 11) 10.85 ms.  Its prices are the waves of the launches (microseconds per tile and K slab as measured at d = 768: a tile's epilogue
